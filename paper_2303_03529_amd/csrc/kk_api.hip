@@ -123,6 +123,14 @@ using MTinyCfg = kk::MixedDlCfg<64, 64, 2, 2, 3, 8>;
 using MTinyBf6 = kk::MixedDlCfg<64, 64, 2, 2, 3, 8, true, kk::PROD_ALL6>;
 static_assert(SPLIT_PAD_SMALL % MTinyCfg::BM == 0, "tiny split tiles must divide the padding");
 static_assert(kk::PAD % SmallF64::BM == 0 && SPLIT_PAD_LARGE % SmallMx::BM == 0, "small tiles must divide the padding");
+// Tile class of the setup products C = Z Q and G = S C and of the reverse pass's C E' C^T (two
+// items, never split along K): the rules of the response transforms, which are the same product
+// shape. At Nb = 144 the 128 x 128 tiles are 8 workgroups in all (26 us a product, 10.8 us on
+// 64 x 64 tiles), at 1152 they are 162 (157 us, 128 us on 64 x 64 tiles).
+int store_class(int np, int cus) {
+  return np <= TINY_NP_F64 ? 2 : np <= SMALL_NP_F64 && !f64_large_tiles_fill(np, cus) ? 1 : 0;
+}
+static_assert(kk::StoreCfg::BM == kk::StoreCfg::BN && SmallF64::BM == SmallF64::BN, "square setup tiles");
 // Rows nb..np-1 of every operand a response transform or a setup product
 // contracts over are zero (the padded copies of S, Z, Q and the potentials are
 // zero there, hence C, G and Y too), so those contractions stop at nb rounded up
@@ -160,8 +168,10 @@ struct kk_handle_s {
          *w[2] = {nullptr, nullptr};
   double *t = nullptr, *mu = nullptr, *wsum = nullptr;
   int* offsets = nullptr;
+  std::vector<int> h_offsets;  // what offsets holds
   int2 *tiles_upper = nullptr, *tiles_full = nullptr, *tiles_store = nullptr;
   int n_upper = 0, n_full = 0, n_store = 0;
+  int store_cls = 0;  // tile class of the setup products (launch_gemm's cls)
   // small systems: 64 x 64 tiles for the FP64 response transforms
   bool small_f64 = false;
   bool tiny_f64 = false;  // small_f64 with np <= TINY_NP_F64: TinyF64 kernels
@@ -185,7 +195,7 @@ struct kk_handle_s {
   float* x32 = nullptr;  // split forward: the product C^T U~ G per direction, FP32
   _Float16 *yh = nullptr, *yl = nullptr, *yr = nullptr;
   double* msc = nullptr;
-  double* mscratch = nullptr;  // 4 np doubles: row statistics for the split scales
+  double* mscratch = nullptr;  // 8 np doubles: row statistics for the split scales
   double* cvec = nullptr;      // 2N: centring vector of the fused small-system step (kk_fused.hpp)
   double* pmax = nullptr;      // 2 per block of the fused step: largest centred potentials
 
@@ -537,7 +547,12 @@ kk_status launch_gemm(kk_handle h, int epi, kk::GemmArgs& a, int cls = 0) {
   if (a.nitems > kk::MAX_GEMM_BATCH) return fail(KK_EINVAL, "internal: too many GEMM items");
   const bool small = cls != 0;
   if (epi == kk::EPI_STORE) {
-    kk::gemm_f64<kk::EPI_STORE, kk::StoreCfg><<<grid, kk::StoreCfg::THREADS, 0, h->stream>>>(a);
+    if (cls == 2)
+      kk::gemm_f64<kk::EPI_STORE, TinyF64><<<grid, TinyF64::THREADS, 0, h->stream>>>(a);
+    else if (cls == 1)
+      kk::gemm_f64<kk::EPI_STORE, SmallF64><<<grid, SmallF64::THREADS, 0, h->stream>>>(a);
+    else
+      kk::gemm_f64<kk::EPI_STORE, kk::StoreCfg><<<grid, kk::StoreCfg::THREADS, 0, h->stream>>>(a);
   } else if (epi == kk::EPI_FERMI) {
     ProfileScope ps(h, 0);
     if (cls == 2)
@@ -987,7 +1002,9 @@ kk_status allocate_prepared(kk_handle h) {
   if ((st = dalloc_t(h, &h->offsets, (size_t)n_atoms + 1))) return st;
   std::vector<int2> up = tile_order(np, kk::FwdCfg::BM, kk::FwdCfg::BN, true);
   std::vector<int2> full = tile_order(np, kk::BackCfg::BM, kk::BackCfg::BN, false);
-  std::vector<int2> stt = tile_order(np, kk::StoreCfg::BM, kk::StoreCfg::BN, false);
+  h->store_cls = store_class(np, cu_count());
+  const int sb = h->store_cls ? SmallF64::BM : kk::StoreCfg::BM;
+  std::vector<int2> stt = tile_order(np, sb, sb, false);
   std::vector<int2> sup, sfull, mfull;
   if (h->small_f64) {
     sup = tile_order(np, SmallF64::BM, SmallF64::BN, true);
@@ -1023,7 +1040,7 @@ kk_status allocate_prepared(kk_handle h) {
                              h->stream));
   if (h->precision != KK_FP64) {
     if ((st = dalloc_t(h, &h->mconst, 8))) return st;
-    if ((st = dalloc_t(h, &h->mscratch, (size_t)4 * np))) return st;
+    if ((st = dalloc_t(h, &h->mscratch, (size_t)8 * np))) return st;
     if ((st = dalloc_t(h, &h->cvec, (size_t)2 * n_atoms))) return st;
     if ((st = dalloc_t(h, &h->pmax, (size_t)2 * kk::FUSED_MAX_BLOCKS))) return st;
     for (int s = 0; s < 2; ++s) {
@@ -1057,36 +1074,34 @@ kk_status allocate_prepared(kk_handle h) {
 // the FP16 splits of C, C^T, G^T with their power-of-two scales.
 kk_status prepare_mixed(kk_handle h) {
   const int np = h->np;
-  double* rmax = h->mscratch;
-  double* rn2 = rmax + 2 * np;
+  double *rmax = h->mscratch, *rn2 = rmax + 4 * (size_t)np;
+  // rows of C^T are columns of C; rows of G^T columns of G
+  kk::RowStatsArgs ra{};
+  kk::SplitMatrices sm{};
   for (int s = 0; s < 2; ++s) {
-    dim3 pg(np / 32, np / 32), pb(256);
-    kk::transpose_sq<<<pg, pb, 0, h->stream>>>(h->G[s], h->GT[s], np);
-    LAUNCH_CHECK("transpose G");
-    // rows of C^T are columns of C; rows of G^T columns of G
-    kk::row_stats<<<np, 1024, 0, h->stream>>>(h->CT[s], np, rmax, rn2);
-    LAUNCH_CHECK("row_stats");
-    kk::row_stats<<<np, 1024, 0, h->stream>>>(h->GT[s], np, rmax + np, rn2 + np);
-    LAUNCH_CHECK("row_stats");
-    kk::const_scales<<<1, 1024, 0, h->stream>>>(rmax, rn2, rmax + np, rn2 + np, np, h->mconst + 4 * s);
-    LAUNCH_CHECK("const_scales");
-    if (s == 0 && 2 * h->natoms <= kk::FUSED_MAX_N2) {
-      kk::centre_vector<<<h->natoms + 1, 256, 0, h->stream>>>(h->gamma, h->natoms, h->W, h->offsets, h->w[0], h->w[1],
-                                                               h->wsum, h->cvec);
-      LAUNCH_CHECK("centre_vector");
-    }
-    if (h->bf16) {
-      kk::split_matrix<true, 3><<<pg, pb, 0, h->stream>>>(h->C[s], np, 0, h->mconst + 4 * s, h->Ch[s], h->Cl[s],
-                                                          h->Cr[s]);
-      kk::split_matrix<true, 3><<<pg, pb, 0, h->stream>>>(h->GT[s], np, 0, h->mconst + 4 * s + 1, h->GTh[s],
-                                                          h->GTl[s], h->GTr[s]);
-    } else {
-      kk::split_matrix<<<pg, pb, 0, h->stream>>>(h->C[s], np, 0, h->mconst + 4 * s, h->Ch[s], h->Cl[s], nullptr);
-      kk::split_matrix<<<pg, pb, 0, h->stream>>>(h->GT[s], np, 0, h->mconst + 4 * s + 1, h->GTh[s], h->GTl[s],
-                                                 nullptr);
-    }
-    LAUNCH_CHECK("split_matrix");
+    ra.m[2 * s] = h->CT[s];
+    ra.m[2 * s + 1] = h->GT[s];
+    const int c = 2 * s, g = 2 * s + 1;
+    sm.src[c] = h->C[s]; sm.scale[c] = h->mconst + 4 * s;
+    sm.hi[c] = h->Ch[s]; sm.lo[c] = h->Cl[s]; sm.res[c] = h->Cr[s];
+    sm.src[g] = h->GT[s]; sm.scale[g] = h->mconst + 4 * s + 1;
+    sm.hi[g] = h->GTh[s]; sm.lo[g] = h->GTl[s]; sm.res[g] = h->GTr[s];
   }
+  kk::row_stats<<<dim3(np, 4), kk::ROW_STATS_THREADS, 0, h->stream>>>(ra, np, rmax, rn2);
+  LAUNCH_CHECK("row_stats");
+  kk::const_scales<<<2, 1024, 0, h->stream>>>(rmax, rn2, np, h->mconst);
+  LAUNCH_CHECK("const_scales");
+  if (2 * h->natoms <= kk::FUSED_MAX_N2) {
+    kk::centre_vector<<<h->natoms + 1, 256, 0, h->stream>>>(h->gamma, h->natoms, h->W, h->offsets, h->w[0], h->w[1],
+                                                             h->wsum, h->cvec);
+    LAUNCH_CHECK("centre_vector");
+  }
+  const int blocks = (int)std::min<size_t>(((size_t)np * np / 8 + 255) / 256, 4096);
+  if (h->bf16)
+    kk::split_matrix<true, 3><<<dim3(blocks, 4), 256, 0, h->stream>>>(sm, np);
+  else
+    kk::split_matrix<false, 2><<<dim3(blocks, 4), 256, 0, h->stream>>>(sm, np);
+  LAUNCH_CHECK("split_matrix");
   return KK_OK;
 }
 
@@ -1225,53 +1240,53 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
     if ((st = allocate_prepared(h))) return st;
   }
   h->W = W; h->kT = kT; h->beta = 1.0 / kT; h->n_e = n_electrons;
-  HIP_OR_FAIL(hipMemcpyAsync(h->offsets, atom_offsets, sizeof(int) * (n_atoms + 1), hipMemcpyHostToDevice,
-                             h->stream));
-  HIP_OR_FAIL(hipMemcpyAsync(h->gamma, gamma, sizeof(double) * n_atoms * n_atoms, hipMemcpyDeviceToDevice,
-                             h->stream));
-
-  // Padded copies: S, Z^T (into CT[0]) and Q_s (into CT[1] as scratch), then
-  // C_s = Z Q_s, G_s = S C_s, CT_s = C_s^T.
-  dim3 pg(np / 32, np / 32), pb(256);
-  kk::pad_copy<<<pg, pb, 0, h->stream>>>(S, nb, h->S, np, 0);
-  LAUNCH_CHECK("pad_copy S");
-  kk::pad_copy<<<pg, pb, 0, h->stream>>>(Z, nb, h->G[0], np, 1);  // G[0] holds Z^T for now
-  LAUNCH_CHECK("pad_copy Z");
-  const double* Qs[2] = {Q_up, Q_dn};
-  for (int s = 0; s < 2; ++s) {
-    kk::pad_copy<<<pg, pb, 0, h->stream>>>(Qs[s], nb, h->CT[s], np, 0);
-    LAUNCH_CHECK("pad_copy Q");
+  // the offsets on the device stay unless they change (a copy from pageable host memory waits)
+  if (!reuse || !std::equal(h->h_offsets.begin(), h->h_offsets.end(), atom_offsets)) {
+    h->h_offsets.assign(atom_offsets, atom_offsets + n_atoms + 1);
+    HIP_OR_FAIL(hipMemcpyAsync(h->offsets, h->h_offsets.data(), sizeof(int) * (n_atoms + 1), hipMemcpyHostToDevice,
+                               h->stream));
   }
+
+  // Padded copies: S, Z^T (into G[0]) and Q_s (into CT[s] as scratch), and gamma; then
+  // C_s = Z Q_s, G_s = S C_s, CT_s = C_s^T (split forms: GT_s = G_s^T).
+  const dim3 pg(np / 32, np / 32), pb(256);
+  kk::SetupCopies sc{};
+  sc.src[0] = S; sc.src[1] = Z; sc.src[2] = Q_up; sc.src[3] = Q_dn;
+  sc.dst[0] = h->S; sc.dst[1] = h->G[0]; sc.dst[2] = h->CT[0]; sc.dst[3] = h->CT[1];
+  sc.gamma = gamma; sc.gamma_dst = h->gamma; sc.gamma_n = (size_t)n_atoms * n_atoms;
+  sc.nb = nb; sc.np = np;
+  kk::setup_copies<<<dim3(pg.x, pg.y, kk::SETUP_COPIES_Z), pb, 0, h->stream>>>(sc);
+  LAUNCH_CHECK("setup_copies");
+  // chemical potential, occupations and their weights, with the levels in padded arrays
+  kk::SpectrumArgs sp{};
+  sp.e[0] = eps_up; sp.e[1] = eps_dn;
+  for (int s = 0; s < 2; ++s) { sp.eps[s] = h->eps[s]; sp.f[s] = h->f[s]; sp.fc[s] = h->fc[s]; sp.w[s] = h->w[s]; }
+  sp.mu = h->mu; sp.wsum = h->wsum; sp.nb = nb; sp.np = np; sp.n_e = n_electrons; sp.beta = h->beta;
+  kk::spectrum<<<1, kk::SPECTRUM_THREADS, 0, h->stream>>>(sp);
+  LAUNCH_CHECK("spectrum");
   kk::GemmArgs a{};
   a.n = np; a.k_half = h->kc; a.two_halves = 0; a.ntiles = h->n_store; a.tiles = h->tiles_store;
   a.stop = nullptr; a.nitems = 2;
+  const int cls = h->store_cls;
   for (int s = 0; s < 2; ++s) {  // C_s[m][n] = sum_k Z^T[k][m] Q_s[k][n]
     a.item[s] = kk::GemmItem{};
     a.item[s].a0 = h->G[0]; a.item[s].b0 = h->CT[s]; a.item[s].out = h->C[s];
   }
-  if ((st = launch_gemm(h, kk::EPI_STORE, a))) return st;
+  if ((st = launch_gemm(h, kk::EPI_STORE, a, cls))) return st;
   for (int s = 0; s < 2; ++s) {  // G_s[m][n] = sum_k S[k][m] C_s[k][n] (S symmetric)
     a.item[s] = kk::GemmItem{};
     a.item[s].a0 = h->S; a.item[s].b0 = h->C[s]; a.item[s].out = h->G[s];
   }
-  if ((st = launch_gemm(h, kk::EPI_STORE, a))) return st;
+  if ((st = launch_gemm(h, kk::EPI_STORE, a, cls))) return st;
+  kk::TransposeArgs ta{};
   for (int s = 0; s < 2; ++s) {
-    kk::transpose_sq<<<pg, pb, 0, h->stream>>>(h->C[s], h->CT[s], np);
-    LAUNCH_CHECK("transpose C");
+    ta.src[s] = h->C[s]; ta.dst[s] = h->CT[s];
+    ta.src[2 + s] = h->G[s]; ta.dst[2 + s] = h->GT[s];
   }
-  // chemical potential and occupations (eps copied into padded arrays)
-  kk::solve_mu<<<1, 1024, 0, h->stream>>>(eps_up, eps_dn, nb, n_electrons, h->beta, h->mu);
-  LAUNCH_CHECK("solve_mu");
-  const double* es[2] = {eps_up, eps_dn};
-  for (int s = 0; s < 2; ++s) {
-    kk::occupations<<<(np + 255) / 256, 256, 0, h->stream>>>(es[s], nb, np, h->mu, h->beta, h->eps[s],
-                                                              h->f[s], h->fc[s], h->w[s]);
-    LAUNCH_CHECK("occupations");
-  }
-  kk::sum_two<<<1, 1024, 0, h->stream>>>(h->w[0], h->w[1], np, h->wsum);
-  LAUNCH_CHECK("sum_two");
-  kk::atom_row_dots<<<n_atoms, 256, 0, h->stream>>>(h->C[0], h->C[1], np, h->G[0], h->G[1], np, h->w[0],
-                                                     h->w[1], np, h->offsets, n_atoms, h->t);
+  kk::transpose_sq<<<dim3(pg.x, pg.y, mixed ? 4 : 2), pb, 0, h->stream>>>(ta, np);
+  LAUNCH_CHECK("transpose");
+  kk::atom_row_dots<<<dim3(n_atoms, 2), kk::ROW_DOTS_THREADS, 0, h->stream>>>(
+      h->C[0], h->C[1], np, h->G[0], h->G[1], np, h->w[0], h->w[1], np, h->offsets, n_atoms, h->t);
   LAUNCH_CHECK("atom_row_dots");
   if (mixed && (st = prepare_mixed(h))) return st;
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
@@ -1572,8 +1587,8 @@ kk_status kk_ground_state_charges(kk_handle h, const double* reference, double* 
   if ((st = ensure_workspace(h, 1))) return st;
   const int N = h->natoms;
   // populations per spin into the first 2N doubles of the response scratch
-  kk::atom_row_dots<<<N, 256, 0, h->stream>>>(h->C[0], h->C[1], h->np, h->G[0], h->G[1], h->np, h->f[0],
-                                               h->f[1], h->np, h->offsets, N, h->q1);
+  kk::atom_row_dots<<<dim3(N, 2), kk::ROW_DOTS_THREADS, 0, h->stream>>>(
+      h->C[0], h->C[1], h->np, h->G[0], h->G[1], h->np, h->f[0], h->f[1], h->np, h->offsets, N, h->q1);
   LAUNCH_CHECK("atom_row_dots");
   kk::mix_spins<<<(N + 255) / 256, 256, 0, h->stream>>>(h->q1, reference, N, qm);
   LAUNCH_CHECK("mix_spins");
@@ -2059,12 +2074,12 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
     a.item[s] = kk::GemmItem{};
     a.item[s].a0 = Ep[s]; a.item[s].b0 = h->CT[s]; a.item[s].out = h->aY + (size_t)s * np2;
   }
-  if ((st = launch_gemm(h, kk::EPI_STORE, a))) return st;
+  if ((st = launch_gemm(h, kk::EPI_STORE, a, h->store_cls))) return st;
   for (int s = 0; s < 2; ++s) {  // C U1
     a.item[s] = kk::GemmItem{};
     a.item[s].a0 = h->CT[s]; a.item[s].b0 = h->aY + (size_t)s * np2; a.item[s].out = h->aY + (size_t)(2 + s) * np2;
   }
-  if ((st = launch_gemm(h, kk::EPI_STORE, a))) return st;
+  if ((st = launch_gemm(h, kk::EPI_STORE, a, h->store_cls))) return st;
   double* Hb[2] = {H_bar_up, H_bar_dn};
   for (int s = 0; s < 2; ++s) {
     const int blocks = (int)std::min<size_t>(((size_t)nb * nb + 255) / 256, 65536);

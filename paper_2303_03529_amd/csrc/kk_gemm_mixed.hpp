@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include "kk_gemm.hpp"
+#include "kk_kernels.hpp"
 
 namespace kk {
 
@@ -821,31 +822,35 @@ static_assert(MIXED_PAD_LARGE % MLargeCfg::BM == 0 && MIXED_PAD_LARGE % MLargeCf
 // ---------------------------------------------------------------------------
 // Split helpers
 
-// dst_hi/lo[r][c] = split(scale * src[r][c] (or src[c][r] if transpose)), all np x np;
-// NP = 3 also writes the third piece to res (BF16 form).
-template <bool BF16 = false, int NP = 2>
-__global__ void split_matrix(const double* __restrict__ src, int np, int transpose, const double* __restrict__ scale_p,
-                             _Float16* __restrict__ hi, _Float16* __restrict__ lo, _Float16* __restrict__ res) {
-  __shared__ double t[32][33];
-  const double s = *scale_p;
-  const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  auto put = [&](size_t o, double v) {
-    _Float16 pc[NP];
-    split_pieces<BF16, NP>(v, pc);
-    hi[o] = pc[0];
-    lo[o] = pc[1];
-    if constexpr (NP == 3) res[o] = pc[2];
-  };
-  if (transpose) {
-    for (int k = ty; k < 32; k += 8) t[k][tx] = src[(size_t)(bx + k) * np + by + tx];
-    __syncthreads();
-    for (int k = ty; k < 32; k += 8) put((size_t)(by + k) * np + bx + tx, s * t[tx][k]);
-  } else {
-    for (int k = ty; k < 32; k += 8) {
-      const size_t o = (size_t)(by + k) * np + bx + tx;
-      put(o, s * src[o]);
+// hi/lo[r][c] = split(scale * src[r][c]) of up to four np x np matrices, one per blockIdx.y;
+// NP = 3 also writes the third piece to res (BF16 form). Eight consecutive elements per thread
+// and step (16-byte loads and stores).
+struct SplitMatrices {
+  const double* src[4];
+  const double* scale[4];
+  _Float16 *hi[4], *lo[4], *res[4];
+};
+template <bool BF16, int NP>
+__global__ void split_matrix(const SplitMatrices a, int np) {
+  const int z = blockIdx.y;
+  const double s = *a.scale[z];
+  const size_t total = (size_t)np * np / 8, gs = (size_t)gridDim.x * blockDim.x;
+  for (size_t g = (size_t)blockIdx.x * blockDim.x + threadIdx.x; g < total; g += gs) {
+    const d2* sv = reinterpret_cast<const d2*>(a.src[z]) + 4 * g;
+    d2 v[4];
+    h8 vp[NP];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = sv[q];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      _Float16 pc[NP];
+      split_pieces<BF16, NP>(s * v[q >> 1][q & 1], pc);
+#pragma unroll
+      for (int k = 0; k < NP; ++k) vp[k][q] = pc[k];
     }
+    reinterpret_cast<h8*>(a.hi[z])[g] = vp[0];
+    reinterpret_cast<h8*>(a.lo[z])[g] = vp[1];
+    if constexpr (NP == 3) reinterpret_cast<h8*>(a.res[z])[g] = vp[2];
   }
 }
 
@@ -885,28 +890,29 @@ __device__ __forceinline__ void split_scaled_columns_dev(const double* __restric
   }
 }
 
-// Per-row max |x| and sum x^2 of an np x np FP64 matrix (one block per row).
-__global__ void row_stats(const double* __restrict__ m, int np, double* __restrict__ rmax,
-                          double* __restrict__ rnorm2) {
-  __shared__ double sh[17];
-  __shared__ double shm[1024];
-  const double* row = m + (size_t)blockIdx.x * np;
+// Per-row max |x| and sum x^2 of four np x np FP64 matrices (blockIdx.y), one block per row;
+// matrix q's statistics at rmax + q np and rnorm2 + q np.
+constexpr int ROW_STATS_THREADS = 256;
+struct RowStatsArgs {
+  const double* m[4];
+};
+__global__ void __launch_bounds__(ROW_STATS_THREADS)
+    row_stats(const RowStatsArgs a, int np, double* __restrict__ rmax, double* __restrict__ rnorm2) {
+  __shared__ double sh[17], shm[ROW_STATS_THREADS / WAVE];
+  const double* row = a.m[blockIdx.y] + (size_t)blockIdx.x * np;
   double mx = 0.0, s2 = 0.0;
-  for (int c = threadIdx.x; c < np; c += blockDim.x) {
-    const double v = row[c];
-    mx = fmax(mx, fabs(v));
-    s2 += v * v;
+  for (int c = 2 * threadIdx.x; c < np; c += 2 * ROW_STATS_THREADS) {
+    const d2 v = *reinterpret_cast<const d2*>(row + c);
+    mx = fmax(mx, fmax(fabs(v[0]), fabs(v[1])));
+    s2 += v[0] * v[0] + v[1] * v[1];
   }
-  s2 = block_sum(s2, sh);
-  shm[threadIdx.x] = mx;
-  __syncthreads();
-  for (int st = blockDim.x / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) shm[threadIdx.x] = fmax(shm[threadIdx.x], shm[threadIdx.x + st]);
-    __syncthreads();
-  }
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+  if ((threadIdx.x & (WAVE - 1)) == 0) shm[threadIdx.x / WAVE] = mx;
+  s2 = block_sum(s2, sh);  // its barriers also publish shm
   if (threadIdx.x == 0) {
-    rmax[blockIdx.x] = shm[0];
-    rnorm2[blockIdx.x] = s2;
+    for (int q = 1; q < ROW_STATS_THREADS / WAVE; ++q) mx = fmax(mx, shm[q]);
+    rmax[(size_t)blockIdx.y * np + blockIdx.x] = mx;
+    rnorm2[(size_t)blockIdx.y * np + blockIdx.x] = s2;
   }
 }
 
@@ -916,11 +922,14 @@ __device__ __forceinline__ double pow2_scale(double bound, int top) {
   return ldexp(1.0, top - (int)ceil(log2(bound)));
 }
 
-// Reduce row statistics of C^T and G^T (rows = columns of C and G) into the
-// per-spin constants: [0] s_C, [1] s_G, [2] max column norm of C, [3] of G.
-__global__ void const_scales(const double* __restrict__ cmax, const double* __restrict__ cn2,
-                             const double* __restrict__ gmax, const double* __restrict__ gn2, int np,
+// Reduce the row statistics of C^T and G^T (rows = columns of C and G; matrices 2 s and 2 s + 1
+// of row_stats) into the constants of spin s = blockIdx.x, at out + 4 s: [0] s_C, [1] s_G,
+// [2] max column norm of C, [3] of G.
+__global__ void const_scales(const double* __restrict__ rmax, const double* __restrict__ rn2, int np,
                              double* __restrict__ out) {
+  const double *cmax = rmax + (size_t)2 * blockIdx.x * np, *gmax = cmax + np;
+  const double *cn2 = rn2 + (size_t)2 * blockIdx.x * np, *gn2 = cn2 + np;
+  out += 4 * blockIdx.x;
   __shared__ double sm[4][1024];
   double a = 0, b = 0, c = 0, d = 0;
   for (int i = threadIdx.x; i < np; i += blockDim.x) {

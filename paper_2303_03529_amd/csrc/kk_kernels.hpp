@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "kk_gemm.hpp"
+
 namespace kk {
 
 constexpr int WAVE = 64;
@@ -64,133 +66,268 @@ __device__ double block_sum(double v, double* sh) {
   return r;
 }
 
-// dst (np x np, zero padded) = src (nb x nb) or its transpose. 32 x 32 tiles.
-__global__ void pad_copy(const double* __restrict__ src, int nb, double* __restrict__ dst, int np,
-                         int transpose) {
+// The padded copies of a prepare in one launch, blockIdx.z choosing the matrix: 0 S, 1 Z
+// (transposed), 2 and 3 Q of each spin, each dst (np x np, zero padded) = src (nb x nb) in
+// 32 x 32 tiles; 4 gamma (contiguous). As launches of their own they cost a small prepare about
+// 4 us each; together 3.4 us at 16 atoms.
+struct SetupCopies {
+  const double* src[4];
+  double* dst[4];
+  const double* gamma;
+  double* gamma_dst;
+  size_t gamma_n;
+  int nb, np;
+};
+constexpr int SETUP_COPIES_Z = 5, SETUP_TRANSPOSED = 1;
+__global__ void setup_copies(const SetupCopies c) {
+  if (blockIdx.z == 4) {
+    const size_t step = (size_t)gridDim.x * gridDim.y * blockDim.x;
+    for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < c.gamma_n; i += step)
+      c.gamma_dst[i] = c.gamma[i];
+    return;
+  }
   __shared__ double t[32][33];
+  const bool transpose = blockIdx.z == SETUP_TRANSPOSED;
+  const double* __restrict__ src = c.src[blockIdx.z];
+  double* __restrict__ dst = c.dst[blockIdx.z];
+  const int nb = c.nb, np = c.np;
   const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
-  for (int k = ty; k < 32; k += 8) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
     // read source rows coalesced: source tile origin is (by, bx) if plain, (bx, by) if transposed
+    const int k = ty + 8 * q;
     const int sr = (transpose ? bx : by) + k, sc = (transpose ? by : bx) + tx;
     t[k][tx] = (sr < nb && sc < nb) ? src[(size_t)sr * nb + sc] : 0.0;
   }
   __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int dr = by + k, dc = bx + tx;
-    if (dr < np && dc < np) dst[(size_t)dr * np + dc] = transpose ? t[tx][k] : t[k][tx];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int k = ty + 8 * q;
+    dst[(size_t)(by + k) * np + bx + tx] = transpose ? t[tx][k] : t[k][tx];
   }
 }
 
-// dst (np x np) = src^T (both np x np).
-__global__ void transpose_sq(const double* __restrict__ src, double* __restrict__ dst, int np) {
+// dst = src^T of up to four np x np matrices, one per blockIdx.z (32 x 32 tiles).
+struct TransposeArgs {
+  const double* src[4];
+  double* dst[4];
+};
+__global__ void transpose_sq(const TransposeArgs a, int np) {
   __shared__ double t[32][33];
+  const double* __restrict__ src = a.src[blockIdx.z];
+  double* __restrict__ dst = a.dst[blockIdx.z];
   const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int k = ty; k < 32; k += 8) t[k][tx] = src[(size_t)(bx + k) * np + by + tx];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[ty + 8 * q][tx] = src[(size_t)(bx + ty + 8 * q) * np + by + tx];
   __syncthreads();
-  for (int k = ty; k < 32; k += 8) dst[(size_t)(by + k) * np + bx + tx] = t[tx][k];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) dst[(size_t)(by + ty + 8 * q) * np + bx + tx] = t[tx][ty + 8 * q];
 }
 
 __device__ __forceinline__ double occ(double e, double mu, double beta) {
   return 1.0 / (1.0 + exp(beta * (e - mu)));
 }
 
-// Sec. II.C: one chemical potential for both spins with sum_sigma sum_k
-// f(eps_k) = N_e. Bisection on [min eps - 40 kT, max eps + 40 kT], then Newton
-// steps with dN/dmu = sum beta f (1 - f). One block of 1024 threads.
-__global__ void __launch_bounds__(1024) solve_mu(const double* __restrict__ e_up,
-                                                 const double* __restrict__ e_dn, int nb,
-                                                 double n_e, double beta, double* mu_out) {
-  __shared__ double sh[17];
-  const double kT = 1.0 / beta;
+// Sec. II.C: the spectrum of a prepared expansion point in one launch of one block. One
+// chemical potential for both spins with sum_sigma sum_k f(eps_k) = N_e, then per level (padded
+// to np with zeros) eps, f = 1/(1+exp(beta(e-mu))), fc = 1 - f (computed as f of the mirrored
+// argument) and w = beta f fc, and wsum = the sum of both spins' w.
+// mu is where the bisection of [min eps - 40 kT, max eps + 40 kT] down to 1e-15 ends, polished by
+// Newton steps where its count is still off. What the kernel costs is its number of counts, all of
+// it reduction latency, so the halvings whose outcome is known are not counted: Newton's
+// iteration (with its own sums, ordered for speed) first finds the root to the count's rounding,
+// and the bisection then counts only at midpoints within SPECTRUM_NOISE N_e / (dN/dmu) of it,
+// where rounding could decide. A count too flat there to tell (that distance reaches
+// 0.1 kT: a gap many kT wide at N_e) leaves every halving to a count of its own, as does a
+// Newton iteration that does not settle. The count is monotone and its slope changes by at most a
+// factor e per kT, so farther out its sign is that of the midpoint's side: mu has the same bits
+// either way. Against 57 counts, and with the occupations and the sum as launches of their own:
+// 16 atoms 65 + 14 -> 30 us, 128 atoms 89 + 14 -> 37 us, 1024 atoms 393 + 20 -> 123 us.
+struct SpectrumArgs {
+  const double* e[2];                    // levels of each spin, nb
+  double *eps[2], *f[2], *fc[2], *w[2];  // np each
+  double *mu, *wsum;
+  int nb, np;
+  double n_e, beta;
+};
+constexpr double SPECTRUM_NOISE = 2e-14;
+constexpr int SPECTRUM_THREADS = 1024, SPECTRUM_PER = 9;  // levels per thread and spin kept in registers
+
+// Sums of a pair over the block, the same bits in every thread, with one barrier: buf alternates
+// between calls, so a wave still reading one call's partial sums never sees the next call's.
+__device__ __forceinline__ d2 block_sum_pair(double a, double b, double (*sh)[SPECTRUM_THREADS / WAVE][2], int& buf) {
+  constexpr int NW = SPECTRUM_THREADS / WAVE;
+  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+  a = wave_sum_dpp(a);
+  b = wave_sum_dpp(b);
+  if (lane == 0) {
+    sh[buf][wave][0] = a;
+    sh[buf][wave][1] = b;
+  }
+  __syncthreads();
+  const double x = lane < NW ? sh[buf][lane][0] : 0.0, y = lane < NW ? sh[buf][lane][1] : 0.0;
+  buf ^= 1;
+  return d2{wave_sum_dpp(x), wave_sum_dpp(y)};
+}
+
+__global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs a) {
+  constexpr int T = SPECTRUM_THREADS, PER = SPECTRUM_PER, NW = T / WAVE;
+  __shared__ double sh[17], pair[2][NW][2];
+  __shared__ double smin[NW], smax[NW];
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE, nb = a.nb;
+  const double beta = a.beta, n_e = a.n_e, kT = 1.0 / beta;
+  int buf = 0;
+  double e0[PER], e1[PER];
   double lo = 1e300, hi = -1e300;
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) {
-    lo = fmin(lo, fmin(e_up[i], e_dn[i]));
-    hi = fmax(hi, fmax(e_up[i], e_dn[i]));
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = tid + k * T;
+    e0[k] = i < nb ? a.e[0][i] : 0.0;
+    e1[k] = i < nb ? a.e[1][i] : 0.0;
   }
-  // min/max via sums of one-hot is awkward; use LDS reductions directly.
-  __shared__ double smin[1024], smax[1024];
-  smin[threadIdx.x] = lo;
-  smax[threadIdx.x] = hi;
+  // fn(i, up, dn) for this thread's levels in ascending order
+  auto levels = [&](int n, auto&& fn) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (tid + k * T < n) fn(tid + k * T, e0[k], e1[k]);
+    for (int i = tid + PER * T; i < n; i += T) fn(i, i < nb ? a.e[0][i] : 0.0, i < nb ? a.e[1][i] : 0.0);
+  };
+  levels(nb, [&](int, double u, double d) {
+    lo = fmin(lo, fmin(u, d));
+    hi = fmax(hi, fmax(u, d));
+  });
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o));
+    hi = fmax(hi, __shfl_xor(hi, o));
+  }
+  if (lane == 0) {
+    smin[wave] = lo;
+    smax[wave] = hi;
+  }
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      smin[threadIdx.x] = fmin(smin[threadIdx.x], smin[threadIdx.x + s]);
-      smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + s]);
+  for (int q = 0; q < NW; ++q) {
+    lo = fmin(lo, smin[q]);
+    hi = fmax(hi, smax[q]);
+  }
+  lo -= 40.0 * kT;
+  hi += 40.0 * kT;
+
+  // the root to the count's rounding, and how far from it a midpoint's side is certain
+  double root = 0.5 * (lo + hi), margin = 1e300;
+  {
+    double l = lo, h = hi, step = hi - lo;
+    for (int it = 0; it < 24; ++it) {
+      double c = 0.0, d = 0.0;
+      levels(nb, [&](int, double u, double v) {
+        const double fu = occ(u, root, beta), fv = occ(v, root, beta);
+        c += fu + fv;
+        d += fu * (1.0 - fu) + fv * (1.0 - fv);
+      });
+      const d2 s = block_sum_pair(c, d, pair, buf);
+      const double resid = s[0] - n_e, slope = beta * s[1];
+      const double near = SPECTRUM_NOISE * n_e / slope + 1e-14 * fabs(root);
+      if (fabs(resid) <= 0.05 * SPECTRUM_NOISE * n_e) {
+        if (near < 0.1 * kT) margin = near;
+        break;
+      }
+      if (resid < 0.0) l = root; else h = root;
+      double next = root - resid / slope;
+      // the bracket halved where Newton leaves it or has not halved its last step
+      if (!(next > l && next < h) || fabs(next - root) > 0.5 * step) next = 0.5 * (l + h);
+      step = fabs(next - root);
+      root = next;
     }
-    __syncthreads();
   }
-  lo = smin[0] - 40.0 * kT;
-  hi = smax[0] + 40.0 * kT;
-  __syncthreads();
   for (int iter = 0; iter < 400; ++iter) {
     const double mid = 0.5 * (lo + hi);
-    double c = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) c += occ(e_up[i], mid, beta) + occ(e_dn[i], mid, beta);
-    c = block_sum(c, sh);
-    if (c < n_e) lo = mid; else hi = mid;
+    bool below = mid < root;
+    if (!(fabs(mid - root) > margin)) {
+      double c = 0.0;
+      levels(nb, [&](int, double u, double v) { c += occ(u, mid, beta) + occ(v, mid, beta); });
+      c = block_sum(c, sh);
+      below = c < n_e;
+    }
+    if (below) lo = mid; else hi = mid;
     if (hi - lo <= 1e-15 * fmax(1.0, fabs(mid))) break;
   }
   double mu = 0.5 * (lo + hi);
   for (int it = 0; it < 3; ++it) {
     double c = 0.0, d = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) {
-      const double fu = occ(e_up[i], mu, beta), fd = occ(e_dn[i], mu, beta);
+    levels(nb, [&](int, double u, double v) {
+      const double fu = occ(u, mu, beta), fd = occ(v, mu, beta);
       c += fu + fd;
-      d += fu * occ(-e_up[i], -mu, beta) + fd * occ(-e_dn[i], -mu, beta);
-    }
+      d += fu * occ(-u, -mu, beta) + fd * occ(-v, -mu, beta);
+    });
     c = block_sum(c, sh);
     d = block_sum(d, sh) * beta;
     const double resid = c - n_e;
     if (d <= 0.0 || fabs(resid) <= 1e-13 * n_e) break;
     mu -= resid / d;
   }
-  if (threadIdx.x == 0) *mu_out = mu;
+  if (tid == 0) *a.mu = mu;
+  double ws = 0.0;
+  levels(a.np, [&](int i, double u, double v) {
+    double w[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const bool in = i < nb;
+      const double e = s ? v : u, f = in ? occ(e, mu, beta) : 0.0, fc = in ? occ(-e, -mu, beta) : 0.0;
+      w[s] = in ? beta * f * fc : 0.0;
+      a.eps[s][i] = in ? e : 0.0;
+      a.f[s][i] = f;
+      a.fc[s][i] = fc;
+      a.w[s][i] = w[s];
+    }
+    ws += w[0] + w[1];
+  });
+  ws = block_sum(ws, sh);
+  if (tid == 0) *a.wsum = ws;
 }
 
-// Occupations of one spin: f = 1/(1+exp(beta(e-mu))), fc = 1 - f (computed as
-// f of the mirrored argument), w = beta f fc; padded entries (i >= nb) are 0.
-__global__ void occupations(const double* __restrict__ eps_in, int nb, int np,
-                            const double* __restrict__ mu_p, double beta, double* __restrict__ eps,
-                            double* __restrict__ f, double* __restrict__ fc, double* __restrict__ w) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= np) return;
-  if (i < nb) {
-    const double mu = *mu_p, e = eps_in[i];
-    const double a = occ(e, mu, beta), b = occ(-e, -mu, beta);
-    eps[i] = e; f[i] = a; fc[i] = b; w[i] = beta * a * b;
-  } else {
-    eps[i] = 0.0; f[i] = 0.0; fc[i] = 0.0; w[i] = 0.0;
-  }
-}
-
-// out[s*natoms + I] = sum_{i in I} sum_k X_s[i][k] * Y_s[i][k] * (wk ? wk_s[k] : 1)
-// for s = 0, 1 (two spins). One block per atom.
-__global__ void atom_row_dots(const double* __restrict__ x0, const double* __restrict__ x1, int ldx,
-                              const double* __restrict__ y0, const double* __restrict__ y1, int ldy,
-                              const double* __restrict__ wk0, const double* __restrict__ wk1,
-                              int ncols, const int* __restrict__ offsets, int natoms,
-                              double* __restrict__ out) {
+// out[s*natoms + I] = sum_{i in I} sum_k X_s[i][k] * Y_s[i][k] * wk_s[k], one block of
+// ROW_DOTS_THREADS threads per atom (blockIdx.x) and spin (blockIdx.y). A thread takes the columns
+// k = tid, tid + T, ... of one row after another; ROW_DOTS_BATCH of these are loaded before the
+// first is used, so that the block keeps enough loads in flight (it is bound by HBM, and by
+// latency in small systems: 16 atoms 9.8 -> 4.0 us, 128 atoms 40 -> 10 us, 1024 atoms 645 -> 501 us
+// against one block per atom for both spins, a load at a time); the sum's order and roundings do not depend on the batch. ncols >= 1.
+constexpr int ROW_DOTS_THREADS = 256, ROW_DOTS_BATCH = 9;
+__global__ void __launch_bounds__(ROW_DOTS_THREADS)
+    atom_row_dots(const double* __restrict__ x0, const double* __restrict__ x1, int ldx,
+                  const double* __restrict__ y0, const double* __restrict__ y1, int ldy,
+                  const double* __restrict__ wk0, const double* __restrict__ wk1, int ncols,
+                  const int* __restrict__ offsets, int natoms, double* __restrict__ out) {
   __shared__ double sh[17];
-  const int a = blockIdx.x;
+  const int a = blockIdx.x, s = blockIdx.y;
   const int r0 = offsets[a], r1 = offsets[a + 1];
-  for (int s = 0; s < 2; ++s) {
-    const double* x = s ? x1 : x0;
-    const double* y = s ? y1 : y0;
-    const double* wk = s ? wk1 : wk0;
-    double acc = 0.0;
-    for (int i = r0; i < r1; ++i) {
-      const double* xr = x + (size_t)i * ldx;
-      const double* yr = y + (size_t)i * ldy;
-      for (int k = threadIdx.x; k < ncols; k += blockDim.x) {
-        const double p = xr[k] * yr[k];
-        acc += wk ? p * wk[k] : p;
+  const double *x = s ? x1 : x0, *y = s ? y1 : y0, *wk = s ? wk1 : wk0;
+  double acc = 0.0;
+  int i = r0, k = threadIdx.x;
+  if (k >= ncols) i = r1;
+  while (i < r1) {
+    double xv[ROW_DOTS_BATCH], yv[ROW_DOTS_BATCH], wv[ROW_DOTS_BATCH];
+#pragma unroll
+    for (int q = 0; q < ROW_DOTS_BATCH; ++q) {
+      const bool in = i < r1;
+      xv[q] = in ? x[(size_t)i * ldx + k] : 0.0;
+      yv[q] = in ? y[(size_t)i * ldy + k] : 0.0;
+      wv[q] = in ? wk[k] : 0.0;
+      k += ROW_DOTS_THREADS;
+      if (k >= ncols) {
+        k = threadIdx.x;
+        ++i;
       }
     }
-    acc = block_sum(acc, sh);
-    if (threadIdx.x == 0) out[s * natoms + a] = acc;
+#pragma unroll
+    for (int q = 0; q < ROW_DOTS_BATCH; ++q) {
+#pragma clang fp contract(off)
+      const double p = xv[q] * yv[q];
+      acc += p * wv[q];
+    }
   }
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) out[s * natoms + a] = acc;
 }
 
 // Mulliken projection of caller density-matrix changes (Sec. III.A):
