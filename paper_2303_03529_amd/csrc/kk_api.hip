@@ -179,6 +179,8 @@ struct kk_handle_s {
   bool mx_tiny = false;   // split products on MTinyCfg / MTinyBf6 (64 x 64 tiles)
   bool full_fwd = false;  // FP64 forward as full tiles + fermi_symmetrize_f64 (K-splits, 64 x 64 tiles, full_forward_pairs)
   int2 *stiles_upper = nullptr, *stiles_full = nullptr;
+  kk::Window win{};       // window tables of the prepared spectrum (kk_gemm.hpp)
+  bool windowed = false;  // the response transforms use them (use_window)
   int n_supper = 0, n_sfull = 0;
 
   // split-precision state (precision KK_MIXED_F16 or KK_MIXED_BF16; the BF16 form keeps a
@@ -663,6 +665,7 @@ kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
   fa.n = np; fa.k_half = ck; fa.two_halves = 0; fa.ntiles = tiny ? h->n_sfull : h->n_full;
   fa.nitems = 2 * batch * kch;
   fa.tiles = tiny ? h->stiles_full : h->tiles_full; fa.stop = stop; fa.beta = h->beta;
+  if (h->windowed) fa.win = h->win;
   sa = fa;
   sa.nitems = 2 * batch;
   ba = fa;
@@ -720,7 +723,9 @@ kk_status transforms_f64(kk_handle h, int batch, const int* stop) {
   fa.ntiles = small ? (full ? h->n_sfull : h->n_supper) : (full ? h->n_full : h->n_upper);
   fa.nitems = 2 * batch; fa.tiles = small ? (full ? h->stiles_full : h->stiles_upper) : (full ? h->tiles_full : h->tiles_upper);
   fa.stop = stop; fa.beta = h->beta;
+  if (h->windowed) fa.win = h->win;
   kk::GemmArgs ba{};
+  ba.win = fa.win;
   ba.n = np; ba.k_half = h->kc; ba.two_halves = 0; ba.ntiles = small ? h->n_sfull : h->n_full;
   ba.nitems = 2 * batch; ba.tiles = small ? h->stiles_full : h->tiles_full; ba.stop = stop; ba.beta = h->beta;
   for (int b = 0; b < batch; ++b)
@@ -902,6 +907,7 @@ kk_status response_chunk_mixed(kk_handle h, int batch, const double* v, double* 
   kk::MixedArgs fa{};
   fa.n = np; fa.k = kch > 1 ? h->kck : h->kc; fa.ntiles = h->n_mfull; fa.nitems = 2 * batch * kch;
   fa.tiles = h->mtiles_full; fa.stop = stop; fa.beta = h->beta;
+  if (h->windowed) fa.win = h->win;
   if (h->sk) {
     fa.sk_grid = h->sk_grid;
     fa.sk_slots = h->kch;
@@ -978,6 +984,34 @@ kk_status check_handle(kk_handle h) {
   if (!h->prepared) return fail(KK_ENOTPREPARED, "kk_prepare has not succeeded on this handle");
   return KK_OK;
 }
+
+// The forward transform's tile list and tile sides, whose active part the window tables hold.
+struct ForwardTiles {
+  const int2* tiles;
+  int n, bm, bn;
+};
+ForwardTiles forward_tiles(kk_handle h) {
+  if (h->precision != KK_FP64) {
+    if (h->mx_large) return {h->mtiles_full, h->n_mfull, kk::MLargeCfg::BM, kk::MLargeCfg::BN};
+    if (h->mx_tiny) return {h->mtiles_full, h->n_mfull, MTinyCfg::BM, MTinyCfg::BN};
+    return {h->mtiles_full, h->n_mfull, kk::MSmallCfg::BM, kk::MSmallCfg::BN};
+  }
+  if (h->small_f64)
+    return {h->full_fwd ? h->stiles_full : h->stiles_upper, h->full_fwd ? h->n_sfull : h->n_supper, SmallF64::BM,
+            SmallF64::BN};
+  return {h->full_fwd ? h->tiles_full : h->tiles_upper, h->full_fwd ? h->n_full : h->n_upper, kk::FwdCfg::BM,
+          kk::FwdCfg::BN};
+}
+static_assert(kk::FwdCfg::BM == kk::BackCfg::BM && kk::FwdCfg::BN == kk::BackCfg::BN, "one tile side for both forms");
+
+// Whether the response transforms of a handle go by its window tables. Not below WIN_MIN_NP,
+// where no launch gets shorter by the tiles left out and the tables are a dependent load more
+// (128 atoms, one round of workgroups, is already level: 1.939 and 1.948 ms at m = 8); nor with
+// stream-K products, whose schedule counts every tile.
+#ifndef KK_WIN_MIN_NP
+#define KK_WIN_MIN_NP 640
+#endif
+bool use_window(kk_handle h) { return h->np >= KK_WIN_MIN_NP && !h->sk; }
 
 // Every device buffer of a prepared handle for its (natoms, np, precision),
 // plus the tile tables (which depend only on np).
@@ -1064,6 +1098,22 @@ kk_status allocate_prepared(kk_handle h) {
     if ((st = dalloc_t(h, &h->mtiles_full, mfull.size()))) return st;
     HIP_OR_FAIL(hipMemcpyAsync(h->mtiles_full, mfull.data(), sizeof(int2) * mfull.size(),
                                hipMemcpyHostToDevice, h->stream));
+  }
+  h->windowed = use_window(h);
+  h->win = kk::Window{};
+  h->win.nblk = np / kk::WIN;
+  h->win.chunks = h->sk ? 1 : h->kch;
+  const size_t nblk = h->win.nblk;
+  int* count = nullptr;
+  if ((st = dalloc_t(h, &count, 2))) return st;
+  h->win.count = count;
+  for (int s = 0; s < 2; ++s) {
+    unsigned char* act = nullptr;
+    int2 *range = nullptr, *tiles = nullptr;
+    if ((st = dalloc_t(h, &act, nblk * nblk))) return st;
+    if ((st = dalloc_t(h, &range, nblk))) return st;
+    if ((st = dalloc_t(h, &tiles, (size_t)forward_tiles(h).n))) return st;
+    h->win.act[s] = act; h->win.range[s] = range; h->win.tiles[s] = tiles;
   }
   // the host tile vectors must outlive the copies
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
@@ -1262,6 +1312,17 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
   sp.e[0] = eps_up; sp.e[1] = eps_dn;
   for (int s = 0; s < 2; ++s) { sp.eps[s] = h->eps[s]; sp.f[s] = h->f[s]; sp.fc[s] = h->fc[s]; sp.w[s] = h->w[s]; }
   sp.mu = h->mu; sp.wsum = h->wsum; sp.nb = nb; sp.np = np; sp.n_e = n_electrons; sp.beta = h->beta;
+  const ForwardTiles ft = forward_tiles(h);
+  for (int s = 0; s < 2; ++s) {
+    sp.act[s] = const_cast<unsigned char*>(h->win.act[s]);
+    sp.range[s] = const_cast<int2*>(h->win.range[s]);
+    sp.tiles[s] = const_cast<int2*>(h->win.tiles[s]);
+  }
+  sp.count = const_cast<int*>(h->win.count);
+  sp.tiles_in = ft.tiles; sp.ntiles = split_large ? 0 : ft.n;  // a batch has tile lists of its own
+  sp.bm = ft.bm / kk::WIN; sp.bn = ft.bn / kk::WIN;
+  sp.exact_cut = precision == KK_MIXED_F16;
+  sp.cut = sp.exact_cut ? kk::WIN_CUT_F16 : kk::WIN_CUT;
   kk::spectrum<<<1, kk::SPECTRUM_THREADS, 0, h->stream>>>(sp);
   LAUNCH_CHECK("spectrum");
   kk::GemmArgs a{};
@@ -2456,6 +2517,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
       if (mixed) {
         kk::BatchItemMixed fi{}, bi{};
         fi.n = bi.n = h->np; fi.k = bi.k = h->kc; fi.beta = bi.beta = h->beta; fi.stop = bi.stop = &h->kst->stop;
+        fi.act = bi.act = h->win.act[s]; fi.range = bi.range = h->win.range[s]; fi.nblk = bi.nblk = h->win.nblk;
         kk::MixedItem& F = fi.g;
         F.a0h = h->uct_h + s * np2; F.a0l = h->uct_l + s * np2; F.b0h = h->GTh[s]; F.b0l = h->GTl[s];
         F.yh = h->yh + s * np2; F.yl = h->yl + s * np2; F.x32 = h->x32 + s * np2;
@@ -2469,6 +2531,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
       } else {
         kk::BatchItemF64 fi{}, bi{};
         fi.n = bi.n = h->np; fi.k = bi.k = h->kc; fi.beta = bi.beta = h->beta; fi.stop = bi.stop = &h->kst->stop;
+        fi.act = bi.act = h->win.act[s]; fi.range = bi.range = h->win.range[s]; fi.nblk = bi.nblk = h->win.nblk;
         kk::GemmItem& F = fi.g;
         F.a0 = h->C[s]; F.b0 = h->G[s]; F.a1 = h->G[s]; F.b1 = h->C[s];
         F.scale = h->u + s * np; F.out = h->Y + s * np2;

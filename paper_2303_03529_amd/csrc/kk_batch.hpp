@@ -40,6 +40,9 @@ struct BatchItemF64 {
   int n, k;  // padded size; contraction length (rows past the system's nb are zero)
   const int* stop;
   double beta;
+  const unsigned char* act;  // the item's spin of its system's Window
+  const int2* range;
+  int nblk;
 };
 
 struct BatchItemMixed {
@@ -47,6 +50,9 @@ struct BatchItemMixed {
   int n, k;
   const int* stop;
   double beta;
+  const unsigned char* act;  // the item's spin of its system's Window
+  const int2* range;
+  int nblk;
 };
 
 __global__ void b_reset(SysDesc* d) {
@@ -123,7 +129,7 @@ __global__ __launch_bounds__(BATCH_SYM_T_MIXED) void b_symmetrize(const BatchIte
   const int z = pair_item(pair_off, nitems, blockIdx.x);
   const BatchItemMixed& it = items[z];
   if (*it.stop) return;
-  fermi_symmetrize_v8_dev<false, 2>(it.g, it.n, it.beta, blockIdx.x - pair_off[z]);
+  fermi_symmetrize_v8_dev<false, 2>(it.g, it.n, it.beta, blockIdx.x - pair_off[z], it.act, it.nblk);
 }
 
 __global__ __launch_bounds__(BATCH_SYM_T_F64) void b_symmetrize_f64(const BatchItemF64* __restrict__ items,
@@ -131,7 +137,8 @@ __global__ __launch_bounds__(BATCH_SYM_T_F64) void b_symmetrize_f64(const BatchI
   const int z = pair_item(pair_off, nitems, blockIdx.x);
   const BatchItemF64& it = items[z];
   if (*it.stop) return;
-  fermi_symmetrize_f64_dev<BATCH_SYM_B_F64, BATCH_SYM_T_F64>(it.g, it.n, it.beta, blockIdx.x - pair_off[z]);
+  fermi_symmetrize_f64_dev<BATCH_SYM_B_F64, BATCH_SYM_T_F64>(it.g, it.n, it.beta, blockIdx.x - pair_off[z], it.act,
+                                                             it.nblk);
 }
 
 __global__ void b_combine(const SysDesc* __restrict__ d) {
@@ -162,6 +169,16 @@ __global__ void b_info(const SysDesc* __restrict__ d, int ns, KrylovState* __res
   if (i < ns) out[i] = *d[i].kst;
 }
 
+// Whether a BM x BN forward tile holds a block in which Y may be non-zero.
+template <class Cfg, class Item>
+__device__ __forceinline__ bool window_tile_active(const Item& it, int tm, int tn) {
+  bool any = false;
+  for (int i = 0; i < Cfg::BM / WIN; ++i)
+    for (int j = 0; j < Cfg::BN / WIN; ++j)
+      any |= window_active(it.act, it.nblk, tm * (Cfg::BM / WIN) + i, tn * (Cfg::BN / WIN) + j);
+  return any;
+}
+
 // Persistent transforms: each workgroup takes tiles t = blockIdx.x, + gridDim.x, ...
 // from a list sorted by decreasing cost; a tile of a system whose Krylov
 // expansion has stopped is skipped (uniformly for the workgroup).
@@ -177,7 +194,12 @@ __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(Cf
     const int4 tl = tiles[t];
     const BatchItemF64& it = items[tl.x];
     if (*it.stop) continue;
-    f64_tile<EPI, Cfg>(it.g, it.n, it.k, two_halves != 0, make_int2(tl.y, tl.z), it.beta);
+    int2 rows = make_int2(0, it.k);
+    if constexpr (EPI == EPI_MULLIKEN)
+      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, 0, it.k, Cfg::BK, 0);
+    else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
+      continue;
+    f64_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, two_halves != 0, make_int2(tl.y, tl.z), it.beta);
   }
 }
 
@@ -193,7 +215,12 @@ void b_gemm_mixed(const BatchItemMixed* __restrict__ items, const int4* __restri
     const int4 tl = tiles[t];
     const BatchItemMixed& it = items[tl.x];
     if (*it.stop) continue;
-    mixed_tile<EPI, Cfg>(it.g, it.n, it.k, make_int2(tl.y, tl.z));
+    int2 rows = make_int2(0, it.k);
+    if constexpr (EPI == EPI_MULLIKEN)
+      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, 0, it.k, WIN_ROWS_MIXED<Cfg>, Cfg::BK);
+    else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
+      continue;
+    mixed_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, make_int2(tl.y, tl.z));
   }
 }
 

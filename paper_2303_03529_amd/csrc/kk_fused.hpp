@@ -435,6 +435,14 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
   double* const Y = it.out;
   const int m = I * B + r, cb = J * B + c4;
   const size_t oo = (size_t)m * n + cb, om = (size_t)(J * B + r) * n + I * B + c4;
+  if (!window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
+    if (stopped) return;
+    for (int h = 0; h < 2; ++h) {
+      reinterpret_cast<d2*>(Y + oo)[h] = d2{0.0, 0.0};
+      reinterpret_cast<d2*>(Y + om)[h] = d2{0.0, 0.0};
+    }
+    return;
+  }
   d2 own[NCH][2], mir[NCH][2];
 #pragma unroll
   for (int j = 0; j < NCH; ++j)
@@ -511,6 +519,16 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_chunks(const MixedArgs arg
   const int r = threadIdx.x / (B / 4), c4 = (threadIdx.x % (B / 4)) * 4;
   const int m = I * B + r, cb = J * B + c4;
   const size_t oo = (size_t)m * n + cb, om = (size_t)(J * B + r) * n + I * B + c4;
+  if (!window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
+    if (stopped) return;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      _Float16* dst = p == 0 ? it.yh : (p == 1 ? it.yl : it.yr);
+      *reinterpret_cast<h4v*>(dst + oo) = h4v{};
+      *reinterpret_cast<h4v*>(dst + om) = h4v{};
+    }
+    return;
+  }
   int nown = NCH, nmir = NCH;
   if (args.sk_grid > 0) {
     const int nk = args.k / 32, nt = n / args.sk_side, ti = I * B / args.sk_side, tj = J * B / args.sk_side;
@@ -590,7 +608,7 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_chunks(const MixedArgs arg
 // batches (b_symmetrize).
 template <bool BF16, int NP>
 __device__ __forceinline__ void fermi_symmetrize_v8_dev(const MixedItem& it, const int n, const double beta,
-                                                        const int pair) {
+                                                        const int pair, const unsigned char* act, const int nblk64) {
   static_assert(NP == 2 || NP == 3, "two or three pieces");
   constexpr int B = 64;
   const int2 ij = upper_pair(pair, n / B);
@@ -600,6 +618,16 @@ __device__ __forceinline__ void fermi_symmetrize_v8_dev(const MixedItem& it, con
   const int r = threadIdx.x >> 3, c8 = (threadIdx.x & 7) * 8;
   const int m = I * B + r, cb = J * B + c8;
   const size_t oo = (size_t)m * n + cb, om = (size_t)(J * B + r) * n + I * B + c8;
+  if (!window_active(act, nblk64, I, J)) {
+    static_assert(B == WIN, "block pairs are window blocks");
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      _Float16* dst = p == 0 ? it.yh : (p == 1 ? it.yl : it.yr);
+      *reinterpret_cast<h8*>(dst + oo) = h8{};
+      *reinterpret_cast<h8*>(dst + om) = h8{};
+    }
+    return;
+  }
   const f4v own0 = *reinterpret_cast<const f4v*>(it.x32 + oo);
   const f4v own1 = *reinterpret_cast<const f4v*>(it.x32 + oo + 4);
   const f4v mir0 = *reinterpret_cast<const f4v*>(it.x32 + om);
@@ -659,7 +687,8 @@ __device__ __forceinline__ void fermi_symmetrize_v8_dev(const MixedItem& it, con
 template <bool BF16, int NP>
 __global__ __launch_bounds__(512) void fermi_symmetrize_v8(const MixedArgs args) {
   if (args.stop != nullptr && *args.stop != 0) return;
-  fermi_symmetrize_v8_dev<BF16, NP>(args.item[blockIdx.y], args.n, args.beta, blockIdx.x);
+  fermi_symmetrize_v8_dev<BF16, NP>(args.item[blockIdx.y], args.n, args.beta, blockIdx.x, args.win.act[blockIdx.y & 1],
+                                    args.win.nblk);
 }
 
 }  // namespace kk

@@ -88,6 +88,7 @@ struct MixedArgs {
   // each sk_side x sk_side tile from its table position, tile_table_pos).
   int sk_grid, sk_slots, sk_side;
   size_t sk_stride;
+  Window win;  // all null: every tile, every row
   MixedItem item[MAX_GEMM_BATCH];
 };
 
@@ -178,8 +179,8 @@ __device__ __forceinline__ void split_pieces(double v, _Float16 (&p)[NP]) {
 // Main loop with register staging: global -> registers -> LDS (double buffer).
 // Leaves the FP32 sums in acc; ends with a barrier.
 template <class Cfg>
-__device__ __forceinline__ void mixed_mainloop_lds(const MixedItem& it, const int n, const int kc, const int m0,
-                                                   const int n0, f16x (&acc)[Cfg::WTM][Cfg::WTN]) {
+__device__ __forceinline__ void mixed_mainloop_lds(const MixedItem& it, const int n, const int k_lo, const int kc,
+                                                   const int m0, const int n0, f16x (&acc)[Cfg::WTM][Cfg::WTN]) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, KP = Cfg::KP;
   constexpr int WTM = Cfg::WTM, WTN = Cfg::WTN;
   constexpr int CPR = BK / 8;  // 16-byte chunks per row per matrix
@@ -243,7 +244,7 @@ __device__ __forceinline__ void mixed_mainloop_lds(const MixedItem& it, const in
 
 #define KK_MLOAD(kt)                                                                         \
   {                                                                                          \
-    const int k0 = (kt) * BK;                                                                \
+    const int k0 = k_lo + (kt) * BK;                                                         \
     const _Float16 *ah = it.a0h + k0, *al = it.a0l + k0, *bh = it.b0h + k0, *bl = it.b0l + k0; \
     _Pragma("unroll") for (int p = 0; p < APM; ++p) {                                        \
       sah[p] = *reinterpret_cast<const h8*>(ah + aoff[p]);                                   \
@@ -463,8 +464,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 // this wave's reads of the previous stage (lgkmcnt 0), so its slot can be refilled.
 // Leaves the FP32 sums in acc; ends with a barrier.
 template <class Cfg>
-__device__ __forceinline__ void mixed_mainloop_dl(const MixedItem& it, const int n, const int kc, const int m0,
-                                                  const int n0, f16x (&acc)[Cfg::WTM][Cfg::WTN]) {
+__device__ __forceinline__ void mixed_mainloop_dl(const MixedItem& it, const int n, const int k_lo, const int kc,
+                                                  const int m0, const int n0, f16x (&acc)[Cfg::WTM][Cfg::WTN]) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = 32, NS = Cfg::NS, PW = Cfg::PER_WAVE;
   constexpr int WTM = Cfg::WTM, WTN = Cfg::WTN;
   constexpr int A_BLK = Cfg::A_BLK, B_BLK = Cfg::B_BLK, SB = Cfg::STAGE_BYTES, NPC = Cfg::NPC;
@@ -518,7 +519,7 @@ __device__ __forceinline__ void mixed_mainloop_dl(const MixedItem& it, const int
   const _Float16 *const pa0[3] = {it.a0h, it.a0l, NPC == 3 ? it.a0r : nullptr};
   const _Float16 *const pb0[3] = {it.b0h, it.b0l, NPC == 3 ? it.b0r : nullptr};
   auto issue = [&](int kt) __attribute__((always_inline)) {
-    const int k0 = kt * BK;
+    const int k0 = k_lo + kt * BK;
     unsigned char* slot = ring + (kt % NS) * SB;
 #pragma unroll
     for (int j = 0; j < PW; ++j) {
@@ -653,26 +654,45 @@ __device__ __forceinline__ void mixed_mainloop_dl(const MixedItem& it, const int
   }
 }
 
-// One output tile over a contraction of length kc (see f64_tile); ends with a barrier.
+// Rows that a contraction may begin at without changing its FP32 sums: whole flush groups, so that
+// leaving out groups that are zero leaves the others as they are.
+template <class Cfg>
+constexpr int WIN_ROWS_MIXED = (Cfg::FLUSH > 0 ? Cfg::FLUSH : 1) * Cfg::BK;
+
+// One output tile over the kc (>= 1 stage) columns of the operands from k_lo (see f64_tile); ends
+// with a barrier.
 template <int EPI, class Cfg>
-__device__ __forceinline__ void mixed_tile(const MixedItem& it, const int n, const int kc, const int2 tile) {
+__device__ __forceinline__ void mixed_tile(const MixedItem& it, const int n, const int k_lo, const int kc,
+                                           const int2 tile) {
   static_assert(EPI == EPI_STORE || EPI == EPI_MULLIKEN, "split-precision epilogues");
   const int m0 = tile.x * Cfg::BM, n0 = tile.y * Cfg::BN;
   f16x acc[Cfg::WTM][Cfg::WTN];
   if constexpr (Cfg::DL)
-    mixed_mainloop_dl<Cfg>(it, n, kc, m0, n0, acc);
+    mixed_mainloop_dl<Cfg>(it, n, k_lo, kc, m0, n0, acc);
   else
-    mixed_mainloop_lds<Cfg>(it, n, kc, m0, n0, acc);
+    mixed_mainloop_lds<Cfg>(it, n, k_lo, kc, m0, n0, acc);
   mixed_epilogue<EPI, Cfg>(it, n, tile, acc);
 }
 
 template <int EPI, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_mixed(const MixedArgs args) {
   if (args.stop != nullptr && *args.stop != 0) return;
-  const int total = args.ntiles * args.nitems;
-  const int logical = xcd_remap(blockIdx.x, total);
-  const int z = logical / args.ntiles;
-  mixed_tile<EPI, Cfg>(args.item[z], args.n, args.k, args.tiles[logical - z * args.ntiles]);
+  int z;
+  int2 tile, rows = make_int2(0, args.k);
+  if (EPI == EPI_STORE && args.win.count != nullptr) {
+    if (!window_tile(args.win, args.nitems, z, tile)) return;  // the symmetrizing pass writes the zeros
+  } else {
+    const int total = args.ntiles * args.nitems;
+    const int logical = xcd_remap(blockIdx.x, total);
+    z = logical / args.ntiles;
+    tile = args.tiles[logical - z * args.ntiles];
+    if (EPI == EPI_MULLIKEN && args.win.count != nullptr) {
+      const int j = z % args.win.chunks, s = (z / args.win.chunks) & 1;
+      rows = window_rows(args.win.range[s], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, j * args.k, args.k,
+                         WIN_ROWS_MIXED<Cfg>, Cfg::BK);
+    }
+  }
+  mixed_tile<EPI, Cfg>(args.item[z], args.n, rows.x, rows.y - rows.x, tile);
 }
 
 // Stream-K form of gemm_mixed for launches with fewer tiles than CUs, or a last round of
@@ -706,7 +726,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_mixed_sk(c
       it.x32 += j * args.sk_stride;
     else
       it.part += j * args.sk_stride;
-    mixed_tile<EPI, Cfg>(it, args.n, (k1 - k0) * Cfg::BK, tile);
+    mixed_tile<EPI, Cfg>(it, args.n, 0, (k1 - k0) * Cfg::BK, tile);
     if constexpr (EPI == EPI_MULLIKEN) {
       if (j == 0) {
         const int nseg = sk_segments(t, nk, grid, total);

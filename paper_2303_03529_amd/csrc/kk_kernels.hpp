@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <climits>
+
 #include "kk_gemm.hpp"
 
 namespace kk {
@@ -151,8 +153,28 @@ struct SpectrumArgs {
   double *mu, *wsum;
   int nb, np;
   double n_e, beta;
+  // Window tables (kk_gemm.hpp): act, range and tiles of each spin, count of both. tiles_in: the
+  // forward tile list in launch order, ntiles of bm x bn blocks. cut: with ref the largest of
+  // the w and |F| between the outermost levels, blocks are active from |F| >= cut ref (exact_cut
+  // 0) or from beta cut (exact_cut 1).
+  unsigned char* act[2];
+  int2* range[2];
+  int2* tiles[2];
+  int* count;
+  const int2* tiles_in;
+  int ntiles, bm, bn, exact_cut;
+  double cut;
 };
 constexpr double SPECTRUM_NOISE = 2e-14;
+// Which blocks of Y are left out (Window). Within a block pair |F_ij| = beta f_lo (1 - f_hi)
+// phi <= beta max f max(1 - f) min(1, 1 / (beta gap)) over the pair's levels, the lower factor
+// from the block that can hold the lower level.
+//   FP64, BF16: below 2^-60 of ref, a lower bound of the largest |F|, 2^7 below FP64's rounding
+//   of the products' sums.
+//   FP16 x 3: below 2^-42 beta, where s_Y |Y| <= 2^14 |F| / (beta / 4) < 2^-25 rounds to zero in
+//   both pieces of Y, so leaving the block out changes no bit of the products.
+constexpr double WIN_CUT = 0x1p-60, WIN_CUT_F16 = 0x1p-42;
+constexpr int WIN_MAX_BLOCKS = 1024;  // Nb <= 65536
 constexpr int SPECTRUM_THREADS = 1024, SPECTRUM_PER = 9;  // levels per thread and spin kept in registers
 
 // Sums of a pair over the block, the same bits in every thread, with one barrier: buf alternates
@@ -176,6 +198,9 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
   constexpr int T = SPECTRUM_THREADS, PER = SPECTRUM_PER, NW = T / WAVE;
   __shared__ double sh[17], pair[2][NW][2];
   __shared__ double smin[NW], smax[NW];
+  __shared__ double bmin[2][WIN_MAX_BLOCKS], bmax[2][WIN_MAX_BLOCKS];  // levels of each window block
+  __shared__ double bf[WIN_MAX_BLOCKS], bfc[WIN_MAX_BLOCKS];           // largest f and 1 - f of one spin's
+  __shared__ int blo[WIN_MAX_BLOCKS], bhi[WIN_MAX_BLOCKS], wcount[NW];
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE, nb = a.nb;
   const double beta = a.beta, n_e = a.n_e, kT = 1.0 / beta;
   int buf = 0;
@@ -211,6 +236,7 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
     lo = fmin(lo, smin[q]);
     hi = fmax(hi, smax[q]);
   }
+  const double e_min = lo, e_max = hi;
   lo -= 40.0 * kT;
   hi += 40.0 * kT;
 
@@ -267,8 +293,8 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
     mu -= resid / d;
   }
   if (tid == 0) *a.mu = mu;
-  double ws = 0.0;
-  levels(a.np, [&](int i, double u, double v) {
+  double ws = 0.0, ref = 0.0;
+  levels(a.np, [&](int i, double u, double v) {  // whole waves: np and the strides are multiples of 64
     double w[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -279,11 +305,88 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
       a.f[s][i] = f;
       a.fc[s][i] = fc;
       a.w[s][i] = w[s];
+      ref = fmax(ref, f * fc);
+      // the block's lowest and highest level; a NaN makes them unbounded, an all-padding block
+      // keeps them reversed
+      const bool nan = __any(in && !(e == e && mu == mu));
+      double bl = in ? e : INFINITY, bh = in ? e : -INFINITY;
+      for (int o = 32; o > 0; o >>= 1) {
+        bl = fmin(bl, __shfl_xor(bl, o));
+        bh = fmax(bh, __shfl_xor(bh, o));
+      }
+      if (lane == 0) {
+        bmin[s][i / WIN] = nan ? -INFINITY : bl;
+        bmax[s][i / WIN] = nan ? INFINITY : bh;
+      }
     }
     ws += w[0] + w[1];
   });
   ws = block_sum(ws, sh);
   if (tid == 0) *a.wsum = ws;
+
+  // Window tables
+  static_assert(WIN == WAVE, "a wave's levels are a window block");
+  const int nblk = a.np / WIN;
+  for (int o = 32; o > 0; o >>= 1) ref = fmax(ref, __shfl_xor(ref, o));
+  if (lane == 0) smax[wave] = ref;
+  __syncthreads();
+  for (int q = 0; q < NW; ++q) ref = fmax(ref, smax[q]);
+  const double wide = beta * (e_max - e_min);
+  ref = fmax(ref, occ(e_min, mu, beta) * occ(-e_max, -mu, beta) * (wide > 0.0 ? -expm1(-wide) / wide : 1.0));
+  const double cut = a.exact_cut ? a.cut : a.cut * ref;
+  for (int s = 0; s < 2; ++s) {
+    for (int b = tid; b < nblk; b += T) {  // f falls with the level, so the block's ends bound it
+      const bool any = bmin[s][b] <= bmax[s][b];
+      bf[b] = any ? (isinf(bmin[s][b]) ? 1.0 : occ(bmin[s][b], mu, beta)) : 0.0;
+      bfc[b] = any ? (isinf(bmax[s][b]) ? 1.0 : occ(-bmax[s][b], -mu, beta)) : 0.0;
+      blo[b] = INT_MAX;
+      bhi[b] = 0;
+    }
+    __syncthreads();
+    for (int p = tid; p < nblk * nblk; p += T) {
+      const int I = p / nblk, J = p - I * nblk;
+      const double imin = bmin[s][I], imax = bmax[s][I], jmin = bmin[s][J], jmax = bmax[s][J];
+      double bound = 0.0;
+      if (!(imin > jmax)) bound = bf[I] * bfc[J];
+      if (!(jmin > imax)) bound = fmax(bound, bf[J] * bfc[I]);
+      const double z = beta * fmax(jmin - imax, imin - jmax);
+      if (z > 1.0) bound /= z;
+      const bool on = imin <= imax && jmin <= jmax && !(bound < cut);
+      if (on) {
+        atomicMin(&blo[J], I);
+        atomicMax(&bhi[J], I + 1);
+      }
+      a.act[s][p] = on || I == J;
+    }
+    __syncthreads();
+    for (int b = tid; b < nblk; b += T) a.range[s][b] = bhi[b] > 0 ? make_int2(blo[b] * WIN, bhi[b] * WIN) : make_int2(0, 0);
+    int on_before = 0, off_before = 0;
+    for (int base = 0; base < a.ntiles; base += T) {
+      const int t = base + tid;
+      bool on = false;
+      int2 tile = make_int2(0, 0);
+      if (t < a.ntiles) {
+        tile = a.tiles_in[t];
+        for (int i = 0; i < a.bm; ++i)
+          for (int j = 0; j < a.bn; ++j) on |= a.act[s][(size_t)(tile.x * a.bm + i) * nblk + tile.y * a.bn + j] != 0;
+      }
+      const unsigned long long ball = __ballot(on);
+      if (lane == 0) wcount[wave] = __popcll(ball);
+      __syncthreads();
+      int before = 0, total = 0;
+      for (int q = 0; q < NW; ++q) {
+        if (q < wave) before += wcount[q];
+        total += wcount[q];
+      }
+      before += __popcll(ball & ((1ull << lane) - 1));
+      if (t < a.ntiles)
+        a.tiles[s][on ? on_before + before : a.ntiles - 1 - (off_before + tid - before)] = tile;
+      on_before += total;
+      off_before += min(T, a.ntiles - base) - total;
+      __syncthreads();
+    }
+    if (tid == 0) a.count[s] = on_before;
+  }
 }
 
 // out[s*natoms + I] = sum_{i in I} sum_k X_s[i][k] * Y_s[i][k] * wk_s[k], one block of
