@@ -2172,7 +2172,8 @@ namespace {
 // transforms, systems with np <= small_np_max use 64 x 64 tiles.
 
 struct TileClass {  // full-tile list of one tile class, shared by both transforms
-  int4* tiles = nullptr;
+  int4* tiles = nullptr;  // kk::TileQueues: the XCDs' queues one after another
+  int* off = nullptr;     // XCDS + 1 queue starts
   int n = 0;
 };
 
@@ -2192,6 +2193,8 @@ struct kk_batch_s {
   int* d_pair_off = nullptr;     // first symmetrizing block pair of each forward item
   int sym_pairs = 0;             // block pairs over all forward items
   TileClass cls[2];              // 0: large tiles, 1: small tiles
+  int* d_queue = nullptr;        // queue counters: XCDS for each of an update's transform launches
+  int queues_used = 0;           // launches enqueued so far for the update at hand
   const double** d_delta = nullptr;
   double** d_out = nullptr;
   kk::KrylovState* d_info = nullptr;
@@ -2226,6 +2229,7 @@ struct kk_batch_s {
     for (auto& c : cls) c = TileClass{};
     d_sys = nullptr; d_items_fwd = d_items_back = nullptr; d_delta = nullptr; d_out = nullptr; d_info = nullptr;
     d_pair_off = nullptr;
+    d_queue = nullptr;
     sym_pairs = 0;
     prepared = false;
     tuned = false;
@@ -2242,15 +2246,17 @@ kk_status balloc(kk_batch b, T** p, size_t count) {
   return st;
 }
 
-// Build the tile lists of both classes for a threshold: items (2 per system)
-// sorted by decreasing np so the persistent workgroups start with the costly tiles.
+// Build the tile queues of both classes for a threshold: the systems (2 items each) by decreasing
+// np, so that the costly tiles start first, each item cut into row groups of TILE_GROUP tile rows
+// walked column by column (tile_order), and every group given to the queue with the least work so far.
 // Both transforms walk the full tiles (the forward as the product A = C^T U~ G).
 kk_status build_tile_lists(kk_batch b, int small_np_max) {
   const bool mixed = b->precision == KK_MIXED_F16;
   std::vector<int> order(b->ns);
   for (int i = 0; i < b->ns; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->np_of[x] > b->np_of[y]; });
-  std::vector<int4> lists[2];
+  std::vector<int4> queues[2][kk::XCDS];
+  double load[2][kk::XCDS] = {};
   for (int i : order) {
     const int np = b->np_of[i];
     const int c = np <= small_np_max ? 1 : 0;
@@ -2260,7 +2266,24 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
     const int tbm = c ? sbm : bm, tbn = c ? sbn : bn;
     for (int s = 0; s < 2; ++s) {
       const int item = 2 * i + s;
-      for (const int2& t : tile_order(np, tbm, tbn, false)) lists[c].push_back(make_int4(item, t.x, t.y, 0));
+      int group = -1, q = 0;
+      for (const int2& t : tile_order(np, tbm, tbn, false)) {
+        if (t.x / kk::TILE_GROUP != group) {
+          group = t.x / kk::TILE_GROUP;
+          q = (int)(std::min_element(load[c], load[c] + kk::XCDS) - load[c]);
+        }
+        queues[c][q].push_back(make_int4(item, t.x, t.y, 0));
+        load[c][q] += b->sys[i]->kc;
+      }
+    }
+  }
+  std::vector<int4> lists[2];
+  std::vector<int> offs[2];
+  for (int c = 0; c < 2; ++c) {
+    offs[c].push_back(0);
+    for (const std::vector<int4>& q : queues[c]) {
+      lists[c].insert(lists[c].end(), q.begin(), q.end());
+      offs[c].push_back((int)lists[c].size());
     }
   }
   for (int i = 0; i < b->ns; ++i)
@@ -2279,7 +2302,9 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
       }
       kk_status st;
       if ((st = balloc(b, &tc.tiles, cap + 1))) return st;
+      if ((st = balloc(b, &tc.off, kk::XCDS + 1))) return st;
     }
+    HIP_OR_FAIL(hipMemcpyAsync(tc.off, offs[c].data(), sizeof(int) * offs[c].size(), hipMemcpyHostToDevice, b->stream));
     if (tc.n)
       HIP_OR_FAIL(hipMemcpyAsync(tc.tiles, lists[c].data(), sizeof(int4) * tc.n, hipMemcpyHostToDevice, b->stream));
   }
@@ -2287,14 +2312,15 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
   return KK_OK;
 }
 
+constexpr int BATCH_QUEUE_LAUNCHES = 4 * kk::MAX_RANK;  // per direction two transforms of two tile classes
+
 template <int EPI, class Cfg, class Item>
-kk_status launch_persistent(kk_batch b, const Item* items, const int4* tiles, int ntiles, int two_halves) {
-  if (ntiles == 0) return KK_OK;
-  const int grid = std::min(ntiles, cu_count() * b->grid_mult);
-  if constexpr (std::is_same<Item, kk::BatchItemF64>::value)
-    kk::b_gemm_f64<EPI, Cfg><<<grid, Cfg::THREADS, 0, b->stream>>>(items, tiles, ntiles, two_halves);
-  else
-    kk::b_gemm_mixed<EPI, Cfg><<<grid, Cfg::THREADS, 0, b->stream>>>(items, tiles, ntiles, two_halves);
+kk_status launch_persistent(kk_batch b, const Item* items, const TileClass& c) {
+  if (c.n == 0) return KK_OK;
+  if (b->queues_used >= BATCH_QUEUE_LAUNCHES) return fail(KK_EINVAL, "internal: too many transform launches");
+  const int grid = std::min(c.n, cu_count() * b->grid_mult);
+  const kk::TileQueues q{c.tiles, c.off, b->d_queue + kk::XCDS * b->queues_used++};
+  kk::b_gemm<EPI, Cfg><<<grid, Cfg::THREADS, 0, b->stream>>>(items, q);
   LAUNCH_CHECK("b_gemm");
   return KK_OK;
 }
@@ -2303,7 +2329,8 @@ kk_status launch_persistent(kk_batch b, const Item* items, const int4* tiles, in
 kk_status enqueue_update(kk_batch b, int m) {
   const int ns = b->ns;
   const int bx_vec = (2 * b->maxN + 255) / 256;
-  kk::b_reset<<<ns, 64, 0, b->stream>>>(b->d_sys);
+  b->queues_used = 0;
+  kk::b_reset<<<ns, 64, 0, b->stream>>>(b->d_sys, b->d_queue, kk::XCDS * BATCH_QUEUE_LAUNCHES);
   LAUNCH_CHECK("b_reset");
   kk::b_init<<<dim3(bx_vec, ns), 256, 0, b->stream>>>(b->d_sys, b->d_delta);
   LAUNCH_CHECK("b_init");
@@ -2334,27 +2361,27 @@ kk_status enqueue_update(kk_batch b, int m) {
       auto* bi = static_cast<const kk::BatchItemMixed*>(b->d_items_back);
       // forward: full-tile products A = C^T U~ G (the back-transform's tile lists), then
       // one symmetrizing pass over all items
-      if ((st = launch_persistent<kk::EPI_STORE, kk::MLargeCfg>(b, fi, b->cls[0].tiles, b->cls[0].n, 0)))
+      if ((st = launch_persistent<kk::EPI_STORE, kk::MLargeCfg>(b, fi, b->cls[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_STORE, SmallMx>(b, fi, b->cls[1].tiles, b->cls[1].n, 0))) return st;
+      if ((st = launch_persistent<kk::EPI_STORE, SmallMx>(b, fi, b->cls[1]))) return st;
       kk::b_symmetrize<<<b->sym_pairs, kk::BATCH_SYM_T_MIXED, 0, b->stream>>>(fi, b->d_pair_off, 2 * ns);
       LAUNCH_CHECK("b_symmetrize");
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, kk::MLargeCfg>(b, bi, b->cls[0].tiles, b->cls[0].n, 0)))
+      if ((st = launch_persistent<kk::EPI_MULLIKEN, kk::MLargeCfg>(b, bi, b->cls[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, SmallMx>(b, bi, b->cls[1].tiles, b->cls[1].n, 0)))
+      if ((st = launch_persistent<kk::EPI_MULLIKEN, SmallMx>(b, bi, b->cls[1])))
         return st;
     } else {
       auto* fi = static_cast<const kk::BatchItemF64*>(b->d_items_fwd);
       auto* bi = static_cast<const kk::BatchItemF64*>(b->d_items_back);
       // forward: full-tile products A = C^T U~ G into Y, then one in-place symmetrizing pass
-      if ((st = launch_persistent<kk::EPI_XSTORE, kk::BackCfg>(b, fi, b->cls[0].tiles, b->cls[0].n, 0)))
+      if ((st = launch_persistent<kk::EPI_XSTORE, kk::BackCfg>(b, fi, b->cls[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_XSTORE, SmallF64>(b, fi, b->cls[1].tiles, b->cls[1].n, 0))) return st;
+      if ((st = launch_persistent<kk::EPI_XSTORE, SmallF64>(b, fi, b->cls[1]))) return st;
       kk::b_symmetrize_f64<<<b->sym_pairs, kk::BATCH_SYM_T_F64, 0, b->stream>>>(fi, b->d_pair_off, 2 * ns);
       LAUNCH_CHECK("b_symmetrize_f64");
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, kk::BackCfg>(b, bi, b->cls[0].tiles, b->cls[0].n, 0)))
+      if ((st = launch_persistent<kk::EPI_MULLIKEN, kk::BackCfg>(b, bi, b->cls[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, SmallF64>(b, bi, b->cls[1].tiles, b->cls[1].n, 0)))
+      if ((st = launch_persistent<kk::EPI_MULLIKEN, SmallF64>(b, bi, b->cls[1])))
         return st;
     }
     kk::b_combine<<<dim3((b->maxN + kk::COMBINE_ATOMS - 1) / kk::COMBINE_ATOMS, ns), kk::COMBINE_THREADS, 0,
@@ -2582,6 +2609,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
   if ((st = balloc(b, &b->d_delta, n_systems))) return st;
   if ((st = balloc(b, &b->d_out, n_systems))) return st;
   if ((st = balloc(b, &b->d_info, n_systems))) return st;
+  if ((st = balloc(b, &b->d_queue, (size_t)kk::XCDS * BATCH_QUEUE_LAUNCHES))) return st;
   b->h_delta.assign(n_systems, nullptr);
   b->h_out.assign(n_systems, nullptr);
   if ((st = build_tile_lists(b, 0))) return st;

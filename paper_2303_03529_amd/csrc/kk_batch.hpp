@@ -3,8 +3,8 @@
 // Every system keeps its own prepared state (a full single-system handle);
 // the batch adds device descriptor tables so that each step of the Krylov
 // loop is ONE launch for all systems: small kernels take the system from
-// blockIdx.y, and the two dense transforms are persistent kernels that walk a
-// global tile list (system, spin, tile row, tile column) sorted by cost.
+// blockIdx.y, and the two dense transforms are persistent kernels that take
+// tiles (system, spin, tile row, tile column) from queues, dearest first.
 // The whole update is captured once into a hipGraph and replayed.
 #pragma once
 
@@ -55,7 +55,9 @@ struct BatchItemMixed {
   int nblk;
 };
 
-__global__ void b_reset(SysDesc* d) {
+// Also clears the update's tile queue counters.
+__global__ void b_reset(SysDesc* d, int* queue, int nqueue) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nqueue; i += gridDim.x * blockDim.x) queue[i] = 0;
   if (threadIdx.x == 0) {
     KrylovState* st = d[blockIdx.x].kst;
     st->rank = 0; st->stop = 0; st->status = 0; st->pad = 0;
@@ -179,19 +181,58 @@ __device__ __forceinline__ bool window_tile_active(const Item& it, int tm, int t
   return any;
 }
 
-// Persistent transforms: each workgroup takes tiles t = blockIdx.x, + gridDim.x, ...
-// from a list sorted by decreasing cost; a tile of a system whose Krylov
-// expansion has stopped is skipped (uniformly for the workgroup).
+// Tile queues of a persistent transform: one per XCD, so that the workgroups of an XCD (blockIdx
+// mod 8) work on the same systems' panels in its L2. tiles[off[x]..off[x + 1]) is queue x, filled
+// by the host with whole row groups of systems, dearest first, to equal cost; next[x] counts
+// what has been taken. A workgroup takes tiles from its own queue until that is empty, then from
+// the others', so the launch ends level whatever the systems' stop flags and windows leave out,
+// and a workgroup that starts late finds all queues empty and ends. Against a fixed stride over one
+// list (tile t to workgroup t mod grid): 24 clusters of 16-250 atoms, FP64, m = 6, 54.6 -> 49.8 ms
+// an update; 64 clusters FP16 x 3 49.8 -> 45.3 ms, FP64 5.33 -> 5.94 updates/s (the windows alone,
+// whose gaps a stride cannot close, gave the 24 clusters 0.8 %).
+constexpr int XCDS = 8;
+struct TileQueues {
+  const int4* tiles;
+  const int* off;  // XCDS + 1
+  int* next;       // XCDS counters, zero at the launch
+};
+
+// Takes the workgroup's next tile; false once every queue is empty. ahead: the position thread 0
+// has reserved in queue (blockIdx + turn) mod 8, taken while the previous tile ran.
+__device__ __forceinline__ bool queue_take(const TileQueues& q, int& turn, int& ahead, int4& tile) {
+  __shared__ int4 taken;
+  if (threadIdx.x == 0) {
+    int4 got = make_int4(-1, 0, 0, 0);
+    while (turn < XCDS) {
+      const int x = (blockIdx.x + turn) % XCDS, at = q.off[x] + ahead;
+      if (at < q.off[x + 1]) {
+        got = q.tiles[at];
+        ahead = atomicAdd(&q.next[x], 1);
+        break;
+      }
+      if (++turn < XCDS) ahead = atomicAdd(&q.next[(blockIdx.x + turn) % XCDS], 1);
+    }
+    taken = got;
+  }
+  __syncthreads();
+  tile = taken;
+  __syncthreads();  // taken is free for the next call
+  return tile.x >= 0;
+}
+
+// Persistent transforms over the tile queues; a tile of a system whose Krylov expansion has
+// stopped, or that its window leaves out, is skipped (uniformly for the workgroup).
 // Held to MIN_BLOCKS workgroups per CU: the two-half forward form with the Fermi
 // epilogue, which this kernel ran before the full-tile forward, took ~164 registers per
 // lane and one workgroup per CU when left to itself (13 % slower); the full-tile
 // product and the back-transform fit without spilling.
 template <int EPI, class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(Cfg::WAVES_PER_EU))) void b_gemm_f64(const BatchItemF64* __restrict__ items,
-                                                                          const int4* __restrict__ tiles,
-                                                                          int ntiles, int two_halves) {
-  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int4 tl = tiles[t];
+__global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(Cfg::WAVES_PER_EU)))
+void b_gemm(const BatchItemF64* __restrict__ items, const TileQueues q) {
+  int turn = 0, ahead = 0;
+  int4 tl;
+  if (threadIdx.x == 0) ahead = atomicAdd(&q.next[blockIdx.x % XCDS], 1);
+  while (queue_take(q, turn, ahead, tl)) {
     const BatchItemF64& it = items[tl.x];
     if (*it.stop) continue;
     int2 rows = make_int2(0, it.k);
@@ -199,20 +240,20 @@ __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(Cf
       rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, 0, it.k, Cfg::BK, 0);
     else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
       continue;
-    f64_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, two_halves != 0, make_int2(tl.y, tl.z), it.beta);
+    f64_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, false, make_int2(tl.y, tl.z), it.beta);
   }
 }
 
 // Held to MIN_BLOCKS workgroups per CU as well (the two-half forward form with a staged
 // mirror epilogue, which this kernel ran before the full-tile forward, took ~190 registers
-// and one workgroup per CU when left to itself, 4 % slower). The split products have one K
-// half, so the last argument (kept for one launcher of both precisions) must be 0.
+// and one workgroup per CU when left to itself, 4 % slower).
 template <int EPI, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu((Cfg::MIN_BLOCKS * Cfg::THREADS / 64 + 3) / 4)))
-void b_gemm_mixed(const BatchItemMixed* __restrict__ items, const int4* __restrict__ tiles, int ntiles,
-                  int /*two_halves*/) {
-  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int4 tl = tiles[t];
+void b_gemm(const BatchItemMixed* __restrict__ items, const TileQueues q) {
+  int turn = 0, ahead = 0;
+  int4 tl;
+  if (threadIdx.x == 0) ahead = atomicAdd(&q.next[blockIdx.x % XCDS], 1);
+  while (queue_take(q, turn, ahead, tl)) {
     const BatchItemMixed& it = items[tl.x];
     if (*it.stop) continue;
     int2 rows = make_int2(0, it.k);
