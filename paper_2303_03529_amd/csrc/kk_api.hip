@@ -23,6 +23,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -249,6 +250,11 @@ struct kk_handle_s {
   double g_W = 0.0, g_beta = 0.0;
   bool no_graph = false;  // set if a capture failed: the eager path from then on
 
+  // adaptive updates that the host waits for (krylov_adaptive_sync)
+  kk::SolveReport* report = nullptr;  // pinned host memory
+  unsigned long long report_seq = 0;
+  int rank_hint = 1;
+
   void drop_graph() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -326,14 +332,30 @@ kk_status dalloc(std::vector<void*>& owner, void** p, size_t bytes) {
   return KK_OK;
 }
 
-template <typename T>
-kk_status dalloc_t(kk_handle h, T** p, size_t count, bool workspace = false) {
-  void* q = nullptr;
-  kk_status st = dalloc(workspace ? h->ws_owned : h->owned, &q, count * sizeof(T));
-  *p = static_cast<T*>(q);
-  ++h->alloc_gen;
-  return st;
-}
+// Buffers carved out of one device allocation (256-byte aligned): add each, then commit. One
+// hipMalloc for a handle's two dozen buffers instead of one each, which is most of what a
+// small system's first prepare and first call cost.
+class Slab {
+ public:
+  template <typename T>
+  void add(T** p, size_t count) {
+    parts_.push_back({static_cast<void*>(p), bytes_});
+    bytes_ += (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
+  }
+  kk_status commit(std::vector<void*>& owner) {
+    void* base = nullptr;
+    kk_status st = dalloc(owner, &base, bytes_);
+    for (const auto& p : parts_) {
+      void* at = st ? nullptr : static_cast<char*>(base) + p.second;
+      std::memcpy(p.first, &at, sizeof at);  // a T* of the caller's, whatever T
+    }
+    return st;
+  }
+
+ private:
+  std::vector<std::pair<void*, size_t>> parts_;
+  size_t bytes_ = 0;
+};
 
 // Zero device memory with a plain kernel (no memset nodes if a caller captures).
 __global__ void zero_fill(double* p, size_t n) {
@@ -505,8 +527,11 @@ struct ProfileScope {
 template <int NCH>
 void sym_f64_launch(kk_handle h, const kk::GemmArgs& sa, size_t cstride) {
   const int nblk = sa.n / kk::SYM64_B;
-  kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, NCH>
-      <<<dim3(nblk * (nblk + 1) / 2, sa.nitems), 256, 0, h->stream>>>(sa, cstride);
+  const dim3 grid(nblk * (nblk + 1) / 2, sa.nitems);
+  if (NCH == 1 && sa.win.count != nullptr)
+    kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, 1, true><<<grid, 256, 0, h->stream>>>(sa, cstride);
+  else
+    kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, NCH, false><<<grid, 256, 0, h->stream>>>(sa, cstride);
 }
 kk_status launch_sym_f64(kk_handle h, const kk::GemmArgs& sa, int nch, size_t cstride) {
   switch (nch) {
@@ -522,8 +547,11 @@ kk_status launch_sym_f64(kk_handle h, const kk::GemmArgs& sa, int nch, size_t cs
 template <bool BF16, int NP, int NCH>
 void sym_mixed_launch(kk_handle h, const kk::MixedArgs& sa, size_t cstride) {
   const int nblk = sa.n / kk::SYM_B;
-  kk::fermi_symmetrize_chunks<kk::SYM_B, 256, BF16, NP, NCH>
-      <<<dim3(nblk * (nblk + 1) / 2, sa.nitems), 256, 0, h->stream>>>(sa, cstride);
+  const dim3 grid(nblk * (nblk + 1) / 2, sa.nitems);
+  if (NCH == 1 && sa.win.count != nullptr)
+    kk::fermi_symmetrize_chunks<kk::SYM_B, 256, BF16, NP, 1, true><<<grid, 256, 0, h->stream>>>(sa, cstride);
+  else
+    kk::fermi_symmetrize_chunks<kk::SYM_B, 256, BF16, NP, NCH, false><<<grid, 256, 0, h->stream>>>(sa, cstride);
 }
 template <bool BF16, int NP>
 kk_status launch_sym_mixed_t(kk_handle h, const kk::MixedArgs& sa, int nch, size_t cstride) {
@@ -542,6 +570,29 @@ kk_status launch_sym_mixed(kk_handle h, const kk::MixedArgs& sa, int nch, size_t
                  : launch_sym_mixed_t<false, 2>(h, sa, nch, cstride);
 }
 
+// One product launch, by its window tables where it has them (gemm_f64's and gemm_mixed's
+// WINDOWED; the tiny classes have too few tiles to, use_window).
+template <int EPI, class Cfg>
+void run_gemm_f64(kk_handle h, const kk::GemmArgs& a) {
+  const int grid = a.ntiles * a.nitems;
+  if constexpr (!std::is_same<Cfg, TinyF64>::value)
+    if (a.win.count != nullptr) {
+      kk::gemm_f64<EPI, Cfg, true><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+      return;
+    }
+  kk::gemm_f64<EPI, Cfg><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+}
+template <int EPI, class Cfg>
+void run_gemm_mixed(kk_handle h, const kk::MixedArgs& a) {
+  const int grid = a.ntiles * a.nitems;
+  if constexpr (!std::is_same<Cfg, MTinyCfg>::value && !std::is_same<Cfg, MTinyBf6>::value)
+    if (a.win.count != nullptr) {
+      kk::gemm_mixed<EPI, Cfg, true><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+      return;
+    }
+  kk::gemm_mixed<EPI, Cfg><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+}
+
 // cls: 0 the large tiles (FwdCfg / BackCfg), 1 SmallF64, 2 TinyF64.
 kk_status launch_gemm(kk_handle h, int epi, kk::GemmArgs& a, int cls = 0) {
   const int grid = a.ntiles * a.nitems;
@@ -558,19 +609,19 @@ kk_status launch_gemm(kk_handle h, int epi, kk::GemmArgs& a, int cls = 0) {
   } else if (epi == kk::EPI_FERMI) {
     ProfileScope ps(h, 0);
     if (cls == 2)
-      kk::gemm_f64<kk::EPI_FERMI, TinyF64><<<grid, TinyF64::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_FERMI, TinyF64>(h, a);
     else if (cls == 1)
-      kk::gemm_f64<kk::EPI_FERMI, SmallF64><<<grid, SmallF64::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_FERMI, SmallF64>(h, a);
     else
-      kk::gemm_f64<kk::EPI_FERMI, kk::FwdCfg><<<grid, kk::FwdCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_FERMI, kk::FwdCfg>(h, a);
   } else if (epi == kk::EPI_XSTORE) {  // forward: full-tile product into Y, then Y = F o X in place
     ProfileScope ps(h, 0);
     if (cls == 2)
-      kk::gemm_f64<kk::EPI_XSTORE, TinyF64><<<grid, TinyF64::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_XSTORE, TinyF64>(h, a);
     else if (cls == 1)
-      kk::gemm_f64<kk::EPI_XSTORE, SmallF64><<<grid, SmallF64::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_XSTORE, SmallF64>(h, a);
     else
-      kk::gemm_f64<kk::EPI_XSTORE, kk::BackCfg><<<grid, kk::BackCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_XSTORE, kk::BackCfg>(h, a);
     LAUNCH_CHECK("gemm_f64");
     if (small) {
       kk_status st = launch_sym_f64(h, a, 1, 0);
@@ -589,11 +640,11 @@ kk_status launch_gemm(kk_handle h, int epi, kk::GemmArgs& a, int cls = 0) {
   } else {
     ProfileScope ps(h, 1);
     if (cls == 2)
-      kk::gemm_f64<kk::EPI_MULLIKEN, TinyF64><<<grid, TinyF64::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_MULLIKEN, TinyF64>(h, a);
     else if (cls == 1)
-      kk::gemm_f64<kk::EPI_MULLIKEN, SmallF64><<<grid, SmallF64::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_MULLIKEN, SmallF64>(h, a);
     else
-      kk::gemm_f64<kk::EPI_MULLIKEN, kk::BackCfg><<<grid, kk::BackCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_f64<kk::EPI_MULLIKEN, kk::BackCfg>(h, a);
   }
   LAUNCH_CHECK("gemm_f64");
   return KK_OK;
@@ -604,22 +655,26 @@ kk_status ensure_workspace(kk_handle h, int chunk) {
   const size_t np = h->np, items = (size_t)2 * chunk;
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   h->free_workspace();
-  kk_status st;
-  if ((st = dalloc_t(h, &h->u, items * np, true))) return st;
   const size_t kch = h->kch;  // K-split: one partial product per chunk
+  Slab slab;
+  slab.add(&h->u, items * np);
   if (h->precision == KK_FP64) {
-    if ((st = dalloc_t(h, &h->Y, items * kch * np * np, true))) return st;
+    slab.add(&h->Y, items * kch * np * np);
   } else {
-    for (_Float16** q : {&h->uct_h, &h->uct_l, &h->yh, &h->yl})
-      if ((st = dalloc_t(h, q, items * np * np, true))) return st;
+    for (_Float16** q : {&h->uct_h, &h->uct_l, &h->yh, &h->yl}) slab.add(q, items * np * np);
     if (h->bf16)
-      for (_Float16** q : {&h->uct_r, &h->yr})
-        if ((st = dalloc_t(h, q, items * np * np, true))) return st;
-    if ((st = dalloc_t(h, &h->x32, items * kch * np * np, true))) return st;
-    if ((st = dalloc_t(h, &h->msc, items * 8, true))) return st;
+      for (_Float16** q : {&h->uct_r, &h->yr}) slab.add(q, items * np * np);
+    slab.add(&h->x32, items * kch * np * np);
+    slab.add(&h->msc, items * 8);
   }
-  if ((st = dalloc_t(h, &h->xdiag, items * np, true))) return st;
-  if ((st = dalloc_t(h, &h->part, items * h->nparts * np, true))) return st;
+  slab.add(&h->xdiag, items * np);
+  slab.add(&h->part, items * h->nparts * np);
+  kk_status st = slab.commit(h->ws_owned);
+  ++h->alloc_gen;
+  if (st) {
+    h->free_workspace();
+    return st;
+  }
   if ((st = zero(h, h->u, items * np))) return st;
   h->chunk_cap = chunk;
   return KK_OK;
@@ -665,7 +720,6 @@ kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
   fa.n = np; fa.k_half = ck; fa.two_halves = 0; fa.ntiles = tiny ? h->n_sfull : h->n_full;
   fa.nitems = 2 * batch * kch;
   fa.tiles = tiny ? h->stiles_full : h->tiles_full; fa.stop = stop; fa.beta = h->beta;
-  if (h->windowed) fa.win = h->win;
   sa = fa;
   sa.nitems = 2 * batch;
   ba = fa;
@@ -692,9 +746,9 @@ kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
   {
     ProfileScope ps(h, 0);
     if (tiny)
-      kk::gemm_f64<kk::EPI_XSTORE, TinyF64><<<fa.ntiles * fa.nitems, TinyF64::THREADS, 0, h->stream>>>(fa);
+      run_gemm_f64<kk::EPI_XSTORE, TinyF64>(h, fa);
     else
-      kk::gemm_f64<kk::EPI_XSTORE, kk::BackCfg><<<fa.ntiles * fa.nitems, kk::BackCfg::THREADS, 0, h->stream>>>(fa);
+      run_gemm_f64<kk::EPI_XSTORE, kk::BackCfg>(h, fa);
     LAUNCH_CHECK("gemm_f64 k-split");
     kk_status st = launch_sym_f64(h, sa, kch, np2);
     if (st) return st;
@@ -702,9 +756,9 @@ kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
   {
     ProfileScope ps(h, 1);
     if (tiny)
-      kk::gemm_f64<kk::EPI_MULLIKEN, TinyF64><<<ba.ntiles * ba.nitems, TinyF64::THREADS, 0, h->stream>>>(ba);
+      run_gemm_f64<kk::EPI_MULLIKEN, TinyF64>(h, ba);
     else
-      kk::gemm_f64<kk::EPI_MULLIKEN, kk::BackCfg><<<ba.ntiles * ba.nitems, kk::BackCfg::THREADS, 0, h->stream>>>(ba);
+      run_gemm_f64<kk::EPI_MULLIKEN, kk::BackCfg>(h, ba);
     LAUNCH_CHECK("gemm_f64 k-split");
   }
   return KK_OK;
@@ -790,7 +844,7 @@ kk_status launch_bf16_single(kk_handle h, bool forward, kk::MixedArgs& a, const 
     if (a.sk_grid > 0)
       kk::gemm_mixed_sk<kk::EPI_STORE, Cfg><<<a.sk_grid, Cfg::THREADS, 0, h->stream>>>(a);
     else
-      kk::gemm_mixed<kk::EPI_STORE, Cfg><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_STORE, Cfg>(h, a);
     LAUNCH_CHECK("gemm_mixed bf16 one pass");
     if (h->mx_large) {
       const int nblk = a.n / kk::SYM_B_LARGE;
@@ -803,7 +857,7 @@ kk_status launch_bf16_single(kk_handle h, bool forward, kk::MixedArgs& a, const 
   if (a.sk_grid > 0)
     kk::gemm_mixed_sk<kk::EPI_MULLIKEN, Cfg><<<a.sk_grid, Cfg::THREADS, 0, h->stream>>>(a);
   else
-    kk::gemm_mixed<kk::EPI_MULLIKEN, Cfg><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+    run_gemm_mixed<kk::EPI_MULLIKEN, Cfg>(h, a);
   LAUNCH_CHECK("gemm_mixed bf16 one pass");
   return KK_OK;
 }
@@ -824,13 +878,13 @@ kk_status launch_mixed(kk_handle h, bool forward, kk::MixedArgs& a, const _Float
   if (forward) {
     ProfileScope ps(h, 0);
     if (h->mx_large)
-      kk::gemm_mixed<kk::EPI_STORE, kk::MLargeCfg><<<grid, kk::MLargeCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_STORE, kk::MLargeCfg>(h, a);
     else if (h->mx_tiny)
-      kk::gemm_mixed<kk::EPI_STORE, MTinyCfg><<<grid, MTinyCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_STORE, MTinyCfg>(h, a);
     else if (a.sk_grid > 0)
       kk::gemm_mixed_sk<kk::EPI_STORE, kk::MSmallCfg><<<a.sk_grid, kk::MSmallCfg::THREADS, 0, h->stream>>>(a);
     else
-      kk::gemm_mixed<kk::EPI_STORE, kk::MSmallCfg><<<grid, kk::MSmallCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_STORE, kk::MSmallCfg>(h, a);
     LAUNCH_CHECK("gemm_mixed");
     if (!h->mx_large) {
       kk_status st = launch_sym_mixed(h, sym != nullptr ? *sym : a, kch, (size_t)a.n * a.n);
@@ -843,13 +897,13 @@ kk_status launch_mixed(kk_handle h, bool forward, kk::MixedArgs& a, const _Float
   } else {
     ProfileScope ps(h, 1);
     if (h->mx_large)
-      kk::gemm_mixed<kk::EPI_MULLIKEN, kk::MLargeCfg><<<grid, kk::MLargeCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_MULLIKEN, kk::MLargeCfg>(h, a);
     else if (h->mx_tiny)
-      kk::gemm_mixed<kk::EPI_MULLIKEN, MTinyCfg><<<grid, MTinyCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_MULLIKEN, MTinyCfg>(h, a);
     else if (a.sk_grid > 0)
       kk::gemm_mixed_sk<kk::EPI_MULLIKEN, kk::MSmallCfg><<<a.sk_grid, kk::MSmallCfg::THREADS, 0, h->stream>>>(a);
     else
-      kk::gemm_mixed<kk::EPI_MULLIKEN, kk::MSmallCfg><<<grid, kk::MSmallCfg::THREADS, 0, h->stream>>>(a);
+      run_gemm_mixed<kk::EPI_MULLIKEN, kk::MSmallCfg>(h, a);
   }
   LAUNCH_CHECK("gemm_mixed");
   return KK_OK;
@@ -1004,118 +1058,104 @@ ForwardTiles forward_tiles(kk_handle h) {
 }
 static_assert(kk::FwdCfg::BM == kk::BackCfg::BM && kk::FwdCfg::BN == kk::BackCfg::BN, "one tile side for both forms");
 
-// Whether the response transforms of a handle go by its window tables. Not below WIN_MIN_NP,
-// where no launch gets shorter by the tiles left out and the tables are a dependent load more
-// (128 atoms, one round of workgroups, is already level: 1.939 and 1.948 ms at m = 8); nor with
-// stream-K products, whose schedule counts every tile.
-#ifndef KK_WIN_MIN_NP
-#define KK_WIN_MIN_NP 640
-#endif
-bool use_window(kk_handle h) { return h->np >= KK_WIN_MIN_NP && !h->sk; }
+// Whether the response transforms of a handle go by its window tables: only where a launch has more
+// tiles than the chip has CUs. One round of workgroups does not end sooner by the tiles left out,
+// and the tables are a dependent load more in each (FP64 at 128 atoms, split three ways along K,
+// 1.939 and 1.948 ms; FP16 x 3 at 90 atoms 409 and 418 us; but FP64 at 170 atoms, 1152 tiles, 3.54
+// -> 3.01 ms, BF16 at 220 atoms, 512 tiles, 2.69 -> 2.49 ms, each without and with them). K-split and stream-K
+// handles are of the first kind.
+bool use_window(kk_handle h, const ForwardTiles& ft, int cus) {
+  return h->kch == 1 && 2 * (h->np / ft.bm) * (h->np / ft.bn) > cus;
+}
 
 // Every device buffer of a prepared handle for its (natoms, np, precision),
 // plus the tile tables (which depend only on np).
 kk_status allocate_prepared(kk_handle h) {
-  const int np = h->np, n_atoms = h->natoms;
+  const int np = h->np, n_atoms = h->natoms, n2 = 2 * n_atoms;
   const size_t np2 = (size_t)np * np;
-  kk_status st;
-  if ((st = dalloc_t(h, &h->S, np2))) return st;
+  Slab slab;
+  slab.add(&h->S, np2);
   for (int s = 0; s < 2; ++s) {
-    if ((st = dalloc_t(h, &h->C[s], np2))) return st;
-    if ((st = dalloc_t(h, &h->CT[s], np2))) return st;
-    if ((st = dalloc_t(h, &h->G[s], np2))) return st;
-    if ((st = dalloc_t(h, &h->eps[s], np))) return st;
-    if ((st = dalloc_t(h, &h->f[s], np))) return st;
-    if ((st = dalloc_t(h, &h->fc[s], np))) return st;
-    if ((st = dalloc_t(h, &h->w[s], np))) return st;
+    for (double** q : {&h->C[s], &h->CT[s], &h->G[s]}) slab.add(q, np2);
+    for (double** q : {&h->eps[s], &h->f[s], &h->fc[s], &h->w[s]}) slab.add(q, np);
   }
-  if ((st = dalloc_t(h, &h->gamma, (size_t)n_atoms * n_atoms))) return st;
-  if ((st = dalloc_t(h, &h->t, (size_t)2 * n_atoms))) return st;
-  if ((st = dalloc_t(h, &h->mu, 1))) return st;
-  if ((st = dalloc_t(h, &h->wsum, 1))) return st;
-  if ((st = dalloc_t(h, &h->offsets, (size_t)n_atoms + 1))) return st;
-  std::vector<int2> up = tile_order(np, kk::FwdCfg::BM, kk::FwdCfg::BN, true);
-  std::vector<int2> full = tile_order(np, kk::BackCfg::BM, kk::BackCfg::BN, false);
+  slab.add(&h->gamma, (size_t)n_atoms * n_atoms);
+  slab.add(&h->t, n2);
+  slab.add(&h->mu, 1);
+  slab.add(&h->wsum, 1);
+  slab.add(&h->offsets, (size_t)n_atoms + 1);
+  slab.add(&h->V, (size_t)kk::MAX_RANK * n2);
+  slab.add(&h->Ft, (size_t)kk::MAX_RANK * n2);
+  slab.add(&h->ftilde, n2);
+  slab.add(&h->q1, n2);
+  slab.add(&h->kst, 1);
+  // tile tables, uploaded together below
+  std::vector<std::pair<int2**, std::vector<int2>>> tables;
+  auto table = [&](int2** p, int* count, int bm, int bn, bool upper) {
+    tables.push_back({p, tile_order(np, bm, bn, upper)});
+    *count = (int)tables.back().second.size();
+    slab.add(p, tables.back().second.size());
+  };
+  table(&h->tiles_upper, &h->n_upper, kk::FwdCfg::BM, kk::FwdCfg::BN, true);
+  table(&h->tiles_full, &h->n_full, kk::BackCfg::BM, kk::BackCfg::BN, false);
   h->store_cls = store_class(np, cu_count());
   const int sb = h->store_cls ? SmallF64::BM : kk::StoreCfg::BM;
-  std::vector<int2> stt = tile_order(np, sb, sb, false);
-  std::vector<int2> sup, sfull, mfull;
+  table(&h->tiles_store, &h->n_store, sb, sb, false);
   if (h->small_f64) {
-    sup = tile_order(np, SmallF64::BM, SmallF64::BN, true);
-    sfull = tile_order(np, SmallF64::BM, SmallF64::BN, false);
-    h->n_supper = (int)sup.size();
-    h->n_sfull = (int)sfull.size();
-    if ((st = dalloc_t(h, &h->stiles_upper, sup.size()))) return st;
-    if ((st = dalloc_t(h, &h->stiles_full, sfull.size()))) return st;
-    HIP_OR_FAIL(hipMemcpyAsync(h->stiles_upper, sup.data(), sizeof(int2) * sup.size(), hipMemcpyHostToDevice,
-                               h->stream));
-    HIP_OR_FAIL(hipMemcpyAsync(h->stiles_full, sfull.data(), sizeof(int2) * sfull.size(), hipMemcpyHostToDevice,
-                               h->stream));
+    table(&h->stiles_upper, &h->n_supper, SmallF64::BM, SmallF64::BN, true);
+    table(&h->stiles_full, &h->n_sfull, SmallF64::BM, SmallF64::BN, false);
   }
-  h->n_upper = (int)up.size();
-  h->n_full = (int)full.size();
-  h->n_store = (int)stt.size();
   static_assert(kk::FwdCfg::MIN_BLOCKS == kk::BackCfg::MIN_BLOCKS, "one slot count for both forward forms");
   h->full_fwd = h->kch > 1 || h->small_f64 || full_forward_pairs(h->n_upper, h->n_full, cu_count());
-  if ((st = dalloc_t(h, &h->tiles_upper, up.size()))) return st;
-  if ((st = dalloc_t(h, &h->tiles_full, full.size()))) return st;
-  if ((st = dalloc_t(h, &h->tiles_store, stt.size()))) return st;
-  const int n2 = 2 * n_atoms;
-  if ((st = dalloc_t(h, &h->V, (size_t)kk::MAX_RANK * n2))) return st;
-  if ((st = dalloc_t(h, &h->Ft, (size_t)kk::MAX_RANK * n2))) return st;
-  if ((st = dalloc_t(h, &h->ftilde, (size_t)n2))) return st;
-  if ((st = dalloc_t(h, &h->q1, (size_t)n2))) return st;
-  if ((st = dalloc_t(h, &h->kst, 1))) return st;
-  HIP_OR_FAIL(hipMemcpyAsync(h->tiles_upper, up.data(), sizeof(int2) * up.size(), hipMemcpyHostToDevice,
-                             h->stream));
-  HIP_OR_FAIL(hipMemcpyAsync(h->tiles_full, full.data(), sizeof(int2) * full.size(), hipMemcpyHostToDevice,
-                             h->stream));
-  HIP_OR_FAIL(hipMemcpyAsync(h->tiles_store, stt.data(), sizeof(int2) * stt.size(), hipMemcpyHostToDevice,
-                             h->stream));
   if (h->precision != KK_FP64) {
-    if ((st = dalloc_t(h, &h->mconst, 8))) return st;
-    if ((st = dalloc_t(h, &h->mscratch, (size_t)8 * np))) return st;
-    if ((st = dalloc_t(h, &h->cvec, (size_t)2 * n_atoms))) return st;
-    if ((st = dalloc_t(h, &h->pmax, (size_t)2 * kk::FUSED_MAX_BLOCKS))) return st;
+    slab.add(&h->mconst, 8);
+    slab.add(&h->mscratch, (size_t)8 * np);
+    slab.add(&h->cvec, n2);
+    slab.add(&h->pmax, (size_t)2 * kk::FUSED_MAX_BLOCKS);
     for (int s = 0; s < 2; ++s) {
-      if ((st = dalloc_t(h, &h->GT[s], np2))) return st;
-      for (_Float16** q : {&h->Ch[s], &h->Cl[s], &h->GTh[s], &h->GTl[s]})
-        if ((st = dalloc_t(h, q, np2))) return st;
+      slab.add(&h->GT[s], np2);
+      for (_Float16** q : {&h->Ch[s], &h->Cl[s], &h->GTh[s], &h->GTl[s]}) slab.add(q, np2);
       if (h->bf16)
-        for (_Float16** q : {&h->Cr[s], &h->GTr[s]})
-          if ((st = dalloc_t(h, q, np2))) return st;
+        for (_Float16** q : {&h->Cr[s], &h->GTr[s]}) slab.add(q, np2);
     }
-    mfull = h->mx_large  ? tile_order(np, kk::MLargeCfg::BM, kk::MLargeCfg::BN, false)
-            : h->mx_tiny ? tile_order(np, MTinyCfg::BM, MTinyCfg::BN, false)
-                         : tile_order(np, kk::MSmallCfg::BM, kk::MSmallCfg::BN, false);
-    h->n_mfull = (int)mfull.size();
+    if (h->mx_large)
+      table(&h->mtiles_full, &h->n_mfull, kk::MLargeCfg::BM, kk::MLargeCfg::BN, false);
+    else if (h->mx_tiny)
+      table(&h->mtiles_full, &h->n_mfull, MTinyCfg::BM, MTinyCfg::BN, false);
+    else
+      table(&h->mtiles_full, &h->n_mfull, kk::MSmallCfg::BM, kk::MSmallCfg::BN, false);
     if (h->sk) {  // the symmetrizing pass of a stream-K product finds tiles by kk::tile_table_pos
       const int T = np / kk::MSmallCfg::BM;
+      const std::vector<int2>& v = tables.back().second;
       for (int i = 0; i < h->n_mfull; ++i)
-        if (kk::tile_table_pos(mfull[i].x, mfull[i].y, T, T) != i)
+        if (kk::tile_table_pos(v[i].x, v[i].y, T, T) != i)
           return fail(KK_EINVAL, "internal: tile table order differs from tile_table_pos");
     }
-    if ((st = dalloc_t(h, &h->mtiles_full, mfull.size()))) return st;
-    HIP_OR_FAIL(hipMemcpyAsync(h->mtiles_full, mfull.data(), sizeof(int2) * mfull.size(),
-                               hipMemcpyHostToDevice, h->stream));
   }
-  h->windowed = use_window(h);
+  const ForwardTiles ft = forward_tiles(h);
+  h->windowed = use_window(h, ft, cu_count());
   h->win = kk::Window{};
   h->win.nblk = np / kk::WIN;
-  h->win.chunks = h->sk ? 1 : h->kch;
-  const size_t nblk = h->win.nblk;
   int* count = nullptr;
-  if ((st = dalloc_t(h, &count, 2))) return st;
+  unsigned char* act[2];
+  int2 *range[2], *tiles[2];
+  slab.add(&count, 2);
+  for (int s = 0; s < 2; ++s) {
+    slab.add(&act[s], (size_t)h->win.nblk * h->win.nblk);
+    slab.add(&range[s], h->win.nblk);
+    slab.add(&tiles[s], ft.n);
+  }
+  kk_status st = slab.commit(h->owned);
+  ++h->alloc_gen;
+  if (st) return st;
   h->win.count = count;
   for (int s = 0; s < 2; ++s) {
-    unsigned char* act = nullptr;
-    int2 *range = nullptr, *tiles = nullptr;
-    if ((st = dalloc_t(h, &act, nblk * nblk))) return st;
-    if ((st = dalloc_t(h, &range, nblk))) return st;
-    if ((st = dalloc_t(h, &tiles, (size_t)forward_tiles(h).n))) return st;
-    h->win.act[s] = act; h->win.range[s] = range; h->win.tiles[s] = tiles;
+    h->win.act[s] = act[s]; h->win.range[s] = range[s]; h->win.tiles[s] = tiles[s];
   }
-  // the host tile vectors must outlive the copies
+  for (const auto& t : tables)
+    HIP_OR_FAIL(hipMemcpyAsync(*t.first, t.second.data(), sizeof(int2) * t.second.size(), hipMemcpyHostToDevice,
+                               h->stream));
+  // the host tables must outlive the copies
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   return KK_OK;
 }
@@ -1178,6 +1218,7 @@ kk_status kk_destroy(kk_handle h) {
   if (h->gstream) (void)hipStreamSynchronize(h->gstream);
   h->drop_graph();
   if (h->gstream) (void)hipStreamDestroy(h->gstream);
+  if (h->report) (void)hipHostFree(h->report);
   delete h;
   return KK_OK;
 }
@@ -1412,6 +1453,7 @@ kk_status mulliken_project(kk_handle h, int batch, const double* dD_up, const do
 namespace {
 
 kk_status enqueue_krylov(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta);
+kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta);
 kk_status krylov_graph(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta);
 
 kk_status krylov_run(kk_handle h, const char* who, const double* delta, int m, double tol, const double* K0,
@@ -1424,7 +1466,10 @@ kk_status krylov_run(kk_handle h, const char* who, const double* delta, int m, d
     return fail(KK_EINVAL, "%s: need 1 <= m <= min(2N, %d), got %d", who, kk::MAX_RANK, m);
   if (!(tol >= 0.0)) return fail(KK_EINVAL, "%s: tolerance must be >= 0", who);
   if ((st = ensure_workspace(h, 1))) return st;
-  if (!h->profiling && !h->no_graph) {
+  const bool waited = tol > 0.0 && info != nullptr && !h->profiling;
+  if (waited) {
+    st = krylov_adaptive_sync(h, delta, m, tol, K0, Kdelta);
+  } else if (!h->profiling && !h->no_graph) {
     st = krylov_graph(h, delta, m, tol, K0, Kdelta);
     if (st == KK_EHIP && h->no_graph) st = enqueue_krylov(h, delta, m, tol, K0, Kdelta);  // capture refused
   } else {
@@ -1436,8 +1481,12 @@ kk_status krylov_run(kk_handle h, const char* who, const double* delta, int m, d
   h->fwd_K0 = K0;
   if (info) {
     kk::KrylovState hs;
-    HIP_OR_FAIL(hipMemcpyAsync(&hs, h->kst, sizeof hs, hipMemcpyDeviceToHost, h->stream));
-    HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+    if (waited) {
+      hs = h->report->st;
+    } else {
+      HIP_OR_FAIL(hipMemcpyAsync(&hs, h->kst, sizeof hs, hipMemcpyDeviceToHost, h->stream));
+      HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+    }
     info->rank_used = hs.rank;
     info->status = hs.status;
     info->min_pivot = hs.min_pivot;
@@ -1452,49 +1501,101 @@ kk_status krylov_run(kk_handle h, const char* who, const double* delta, int m, d
 }
 
 // The launches of one update (Algorithm of Sec. II.E: precondition, m Krylov steps of
-// orthonormalize / response / precondition, least-squares solve) on h->stream.
-kk_status enqueue_krylov(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta) {
+// orthonormalize / response / precondition, least-squares solve) on h->stream, in parts.
+
+// f~ = K0 delta (or -delta), and the Krylov state cleared, in one launch
+kk_status enqueue_start(kk_handle h, const double* delta, const double* K0) {
+  const int n2 = 2 * h->natoms, threads = 256, blocks = (n2 * kk::WAVE + threads - 1) / threads;
+  kk::precondition<<<blocks, threads, 0, h->stream>>>(K0, delta, nullptr, h->ftilde, n2, nullptr, h->kst);
+  LAUNCH_CHECK("precondition");
+  return KK_OK;
+}
+
+// Direction k: v_k and f~_k.
+kk_status enqueue_direction(kk_handle h, int k, const double* K0) {
   kk_status st;
   const int n2 = 2 * h->natoms;
   const int* stop = &h->kst->stop;
   const int gv_threads = 256, gv_blocks = (n2 * kk::WAVE + gv_threads - 1) / gv_threads;
-  // orthonormalization: one block just large enough for 8 entries per thread
-  const int orth_threads = std::max(64, std::min(1024, ((n2 + 7) / 8 + 63) / 64 * 64));
-
-  // f~ = K0 delta (or -delta), and the Krylov state cleared, in one launch
-  kk::precondition<<<gv_blocks, gv_threads, 0, h->stream>>>(K0, delta, nullptr, h->ftilde, n2, nullptr, h->kst);
-  LAUNCH_CHECK("precondition");
   // Small systems: one launch orthonormalizes and builds the potentials (kk_fused.hpp), and
   // with K0 = -I the combine also preconditions.
   const bool fused = n2 <= kk::FUSED_MAX_N2;
-  for (int k = 0; k < m; ++k) {
-    const double* src = (k == 0) ? h->ftilde : h->Ft + (size_t)(k - 1) * n2;
-    const double* vk = h->V + (size_t)k * n2;
-    double* ftk = h->Ft + (size_t)k * n2;
-    if (fused) {
-      const bool split = h->precision != KK_FP64;
-      kk::orth_potentials<<<(h->natoms + kk::FUSED_ATOMS - 1) / kk::FUSED_ATOMS, kk::FUSED_THREADS, 0,
-                            h->stream>>>(src, h->V, n2, h->kst, k, h->gamma, h->natoms, h->W, h->offsets, h->np,
-                                         h->u, split ? h->cvec : nullptr, split ? h->pmax : nullptr);
-      LAUNCH_CHECK("orth_potentials");
-      if ((st = response_any(h, 1, vk, h->q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk)))
-        return st;
-    } else {
-      kk::krylov_orthonormalize<<<1, orth_threads, 0, h->stream>>>(src, h->V, n2, h->kst);
-      LAUNCH_CHECK("krylov_orthonormalize");
-      if ((st = response_any(h, 1, vk, h->q1, stop))) return st;
-    }
-    if (!fused || K0 != nullptr) {
-      kk::precondition<<<gv_blocks, gv_threads, 0, h->stream>>>(K0, h->q1, vk, ftk, n2, stop);
-      LAUNCH_CHECK("precondition");
-    }
-    if (tol > 0.0 && k + 1 < m) {  // residual of the rank-(k+1) solve; may end the expansion
-      kk::krylov_solve<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, h->ftilde, n2, h->kst, Kdelta, tol);
-      LAUNCH_CHECK("krylov_solve");
-    }
+  const double* src = (k == 0) ? h->ftilde : h->Ft + (size_t)(k - 1) * n2;
+  const double* vk = h->V + (size_t)k * n2;
+  double* ftk = h->Ft + (size_t)k * n2;
+  if (fused) {
+    const bool split = h->precision != KK_FP64;
+    kk::orth_potentials<<<(h->natoms + kk::FUSED_ATOMS - 1) / kk::FUSED_ATOMS, kk::FUSED_THREADS, 0,
+                          h->stream>>>(src, h->V, n2, h->kst, k, h->gamma, h->natoms, h->W, h->offsets, h->np,
+                                       h->u, split ? h->cvec : nullptr, split ? h->pmax : nullptr);
+    LAUNCH_CHECK("orth_potentials");
+    if ((st = response_any(h, 1, vk, h->q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk)))
+      return st;
+  } else {
+    // one block just large enough for 8 entries per thread
+    const int orth_threads = std::max(64, std::min(1024, ((n2 + 7) / 8 + 63) / 64 * 64));
+    kk::krylov_orthonormalize<<<1, orth_threads, 0, h->stream>>>(src, h->V, n2, h->kst);
+    LAUNCH_CHECK("krylov_orthonormalize");
+    if ((st = response_any(h, 1, vk, h->q1, stop))) return st;
   }
-  kk::krylov_solve<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, h->ftilde, n2, h->kst, Kdelta, 0.0);
+  if (!fused || K0 != nullptr) {
+    kk::precondition<<<gv_blocks, gv_threads, 0, h->stream>>>(K0, h->q1, vk, ftk, n2, stop);
+    LAUNCH_CHECK("precondition");
+  }
+  return KK_OK;
+}
+
+// The solve on the directions so far; a residual <= tol (> 0) ends the expansion.
+kk_status enqueue_solve(kk_handle h, double* Kdelta, double tol, kk::SolveReport* report = nullptr,
+                        unsigned long long seq = 0) {
+  kk::krylov_solve<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, h->ftilde, 2 * h->natoms, h->kst, Kdelta, tol, report, seq);
   LAUNCH_CHECK("krylov_solve");
+  return KK_OK;
+}
+
+kk_status enqueue_krylov(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta) {
+  kk_status st;
+  if ((st = enqueue_start(h, delta, K0))) return st;
+  for (int k = 0; k < m; ++k) {
+    if ((st = enqueue_direction(h, k, K0))) return st;
+    if (tol > 0.0 && k + 1 < m && (st = enqueue_solve(h, Kdelta, tol))) return st;
+  }
+  return enqueue_solve(h, Kdelta, 0.0);
+}
+
+// An adaptive update whose caller waits for it anyway (info given): directions are enqueued only
+// as far as the expansion goes, where a graph of all m_max pays 2-4 us for every launch
+// after its end (six a direction). The first rank_hint directions, the rank of the last such
+// update, go out at once; after that the host waits for each solve's word before the next
+// direction, about as long as a direction enqueued in vain takes. Same launches up to the end, same
+// results. Synchronizes the stream; the final state is in h->report.
+kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta) {
+  if (!h->report) {
+    void* p = nullptr;
+    hipError_t e = hipHostMalloc(&p, sizeof(kk::SolveReport), hipHostMallocDefault);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(KK_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
+    }
+    h->report = new (p) kk::SolveReport{};
+  }
+  kk_status st;
+  if ((st = enqueue_start(h, delta, K0))) return st;
+  for (int k = 0; k < m; ++k) {
+    if ((st = enqueue_direction(h, k, K0))) return st;
+    const unsigned long long seq = ++h->report_seq;
+    if ((st = enqueue_solve(h, Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
+    if (k + 1 == m || k + 1 < h->rank_hint) continue;
+    // the word of this solve, or the stream's end (an error included, which the sync reports)
+    for (int spin = 1;; ++spin) {
+      if (__atomic_load_n(&h->report->word, __ATOMIC_RELAXED) >= 2 * seq) break;
+      if (spin % 4096 == 0 && hipStreamQuery(h->stream) != hipErrorNotReady) break;
+    }
+    const unsigned long long word = __atomic_load_n(&h->report->word, __ATOMIC_RELAXED);
+    if (word < 2 * seq || (word & 1)) break;
+  }
+  HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+  h->rank_hint = h->report->st.rank;
   return KK_OK;
 }
 

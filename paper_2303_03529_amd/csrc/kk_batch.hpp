@@ -237,7 +237,7 @@ void b_gemm(const BatchItemF64* __restrict__ items, const TileQueues q) {
     if (*it.stop) continue;
     int2 rows = make_int2(0, it.k);
     if constexpr (EPI == EPI_MULLIKEN)
-      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, 0, it.k, Cfg::BK, 0);
+      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, Cfg::BK, 0);
     else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
       continue;
     f64_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, false, make_int2(tl.y, tl.z), it.beta);
@@ -258,7 +258,7 @@ void b_gemm(const BatchItemMixed* __restrict__ items, const TileQueues q) {
     if (*it.stop) continue;
     int2 rows = make_int2(0, it.k);
     if constexpr (EPI == EPI_MULLIKEN)
-      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, 0, it.k, WIN_ROWS_MIXED<Cfg>, Cfg::BK);
+      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, WIN_ROWS_MIXED<Cfg>, Cfg::BK);
     else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
       continue;
     mixed_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, make_int2(tl.y, tl.z));

@@ -422,7 +422,7 @@ __device__ __forceinline__ int2 upper_pair(int pair, int nblk) {
 // elsewhere, written over A_0 (block (I, J) by the thread that read it, block (J, I)
 // through LDS after the whole pair was read). B x B blocks of T = B * B / 4 threads: thread
 // (r, q) takes columns 4q..4q+3 of row r of both blocks (16-byte loads and stores).
-template <int B, int T, int NCH>
+template <int B, int T, int NCH, bool WINDOWED>
 __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs args, size_t cstride) {
   static_assert(T * 4 == B * B, "4 elements per thread");
   const int stopped = args.stop != nullptr ? *args.stop : 0;  // tested once the loads are issued
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
   double* const Y = it.out;
   const int m = I * B + r, cb = J * B + c4;
   const size_t oo = (size_t)m * n + cb, om = (size_t)(J * B + r) * n + I * B + c4;
-  if (!window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
+  if (WINDOWED && !window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
     if (stopped) return;
     for (int h = 0; h < 2; ++h) {
       reinterpret_cast<d2*>(Y + oo)[h] = d2{0.0, 0.0};
@@ -505,7 +505,7 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
 // (NCH = the most segments of any tile).
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
-template <int B, int T, bool BF16, int NP, int NCH>
+template <int B, int T, bool BF16, int NP, int NCH, bool WINDOWED>
 __global__ __launch_bounds__(T) void fermi_symmetrize_chunks(const MixedArgs args, size_t cstride) {
   static_assert(T * 4 == B * B, "4 elements per thread");
   static_assert(NP == 2 || NP == 3, "two or three pieces");
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_chunks(const MixedArgs arg
   const int r = threadIdx.x / (B / 4), c4 = (threadIdx.x % (B / 4)) * 4;
   const int m = I * B + r, cb = J * B + c4;
   const size_t oo = (size_t)m * n + cb, om = (size_t)(J * B + r) * n + I * B + c4;
-  if (!window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
+  if (WINDOWED && !window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
     if (stopped) return;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {

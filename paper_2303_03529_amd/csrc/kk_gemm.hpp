@@ -77,7 +77,6 @@ struct Window {
   const int2* tiles[2];         // forward tile list: the active tiles in launch order, then the others
   const int* count;             // active tiles of each spin
   int nblk;                     // n / WIN
-  int chunks;                   // contraction chunks per item (K-split), 1 otherwise
 };
 
 // Hardware hands workgroup ids to the 8 XCDs round-robin; give each XCD a
@@ -89,14 +88,13 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
 }
 
 // Forward launch: the tile and item of block b, or false past the active tiles, whose XCD ranges
-// are taken over the active ones alone. Items are ((direction, spin), chunk).
+// are taken over the active ones alone. Items are (direction, spin).
 __device__ __forceinline__ bool window_tile(const Window& w, int nitems, int& z, int2& tile) {
   const int n0 = w.count[0], per = n0 + w.count[1], total = per * (nitems / 2);
   if ((int)blockIdx.x >= total) return false;
   const int logical = xcd_remap(blockIdx.x, total);
   const int set = logical / per, r = logical - set * per, s = r >= n0;
-  const int dir = set / w.chunks;
-  z = (2 * dir + s) * w.chunks + (set - dir * w.chunks);
+  z = 2 * set + s;
   tile = w.tiles[s][s ? r - n0 : r];
   return true;
 }
@@ -104,14 +102,14 @@ __device__ __forceinline__ bool window_tile(const Window& w, int nitems, int& z,
 __device__ __forceinline__ void window_rest(const Window& w, int ntiles, int nitems, int& z, int2& tile) {
   const int n0 = w.count[0], n1 = w.count[1];
   const int idx = (int)blockIdx.x - (n0 + n1) * (nitems / 2), r0 = ntiles - n0, per = r0 + ntiles - n1;
-  const int set = idx / per, r = idx - set * per, s = r >= r0, dir = set / w.chunks;
-  z = (2 * dir + s) * w.chunks + (set - dir * w.chunks);
+  const int set = idx / per, r = idx - set * per, s = r >= r0;
+  z = 2 * set + s;
   tile = w.tiles[s][s ? n1 + r - r0 : n0 + r];
 }
-// Back-transform: the rows [lo, hi) of a contraction over [0, k_len), chunk k0 rows in, that the
-// columns of `blocks` blocks from block c need, lo rounded down to a multiple of `align`; the
-// first `least` rows where none or fewer remain.
-__device__ __forceinline__ int2 window_rows(const int2* range, int c, int blocks, int k0, int k_len, int align, int least) {
+// Back-transform: the rows [lo, hi) of a contraction over [0, k_len) that the columns of `blocks`
+// blocks from block c need, lo rounded down to a multiple of `align`; the first `least` rows where
+// none or fewer remain.
+__device__ __forceinline__ int2 window_rows(const int2* range, int c, int blocks, int k_len, int align, int least) {
   int lo = 1 << 30, hi = 0;
   for (int q = 0; q < blocks; ++q) {
     const int2 r = range[c + q];
@@ -120,8 +118,8 @@ __device__ __forceinline__ int2 window_rows(const int2* range, int c, int blocks
       hi = max(hi, r.y);
     }
   }
-  lo = max(0, lo - k0) / align * align;
-  hi = min(k_len, hi - k0);
+  lo = lo / align * align;
+  hi = min(k_len, hi);
   return hi > lo && hi - lo >= least ? make_int2(lo, hi) : make_int2(0, least);
 }
 __device__ __forceinline__ bool window_active(const unsigned char* act, int nblk, int I, int J) {
@@ -368,13 +366,15 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
   }
 }
 
-template <int EPI, class Cfg>
+// WINDOWED: the launch goes by args.win. (A choice at run time cost the smallest systems, whose
+// launches are all latency, 0.2 us a kernel.)
+template <int EPI, class Cfg, bool WINDOWED = false>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const GemmArgs args) {
   static_assert(Cfg::BN % WIN == 0 && Cfg::BM % WIN == 0, "tiles are whole window blocks");
   if (args.stop != nullptr && *args.stop != 0) return;
   int z;
   int2 tile, rows = make_int2(0, args.k_half);
-  if ((EPI == EPI_FERMI || EPI == EPI_XSTORE) && args.win.count != nullptr) {
+  if constexpr (WINDOWED && (EPI == EPI_FERMI || EPI == EPI_XSTORE)) {
     if (!window_tile(args.win, args.nitems, z, tile)) {
       if constexpr (EPI == EPI_FERMI) {  // no pass follows that would write the inactive tiles' zeros
         window_rest(args.win, args.ntiles, args.nitems, z, tile);
@@ -393,10 +393,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const 
     const int logical = xcd_remap(blockIdx.x, total);
     z = logical / args.ntiles;
     tile = args.tiles[logical - z * args.ntiles];
-    if (EPI == EPI_MULLIKEN && args.win.count != nullptr) {
-      const int j = z % args.win.chunks, s = (z / args.win.chunks) & 1;
-      rows = window_rows(args.win.range[s], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, j * args.k_half, args.k_half,
-                         Cfg::BK, 0);
+    if constexpr (WINDOWED && EPI == EPI_MULLIKEN) {
+      rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k_half, Cfg::BK, 0);
     }
   }
   f64_tile<EPI, Cfg>(args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0, tile, args.beta);

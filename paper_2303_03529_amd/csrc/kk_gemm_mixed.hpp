@@ -674,22 +674,21 @@ __device__ __forceinline__ void mixed_tile(const MixedItem& it, const int n, con
   mixed_epilogue<EPI, Cfg>(it, n, tile, acc);
 }
 
-template <int EPI, class Cfg>
+template <int EPI, class Cfg, bool WINDOWED = false>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_mixed(const MixedArgs args) {
   if (args.stop != nullptr && *args.stop != 0) return;
   int z;
   int2 tile, rows = make_int2(0, args.k);
-  if (EPI == EPI_STORE && args.win.count != nullptr) {
+  if constexpr (WINDOWED && EPI == EPI_STORE) {
     if (!window_tile(args.win, args.nitems, z, tile)) return;  // the symmetrizing pass writes the zeros
   } else {
     const int total = args.ntiles * args.nitems;
     const int logical = xcd_remap(blockIdx.x, total);
     z = logical / args.ntiles;
     tile = args.tiles[logical - z * args.ntiles];
-    if (EPI == EPI_MULLIKEN && args.win.count != nullptr) {
-      const int j = z % args.win.chunks, s = (z / args.win.chunks) & 1;
-      rows = window_rows(args.win.range[s], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, j * args.k, args.k,
-                         WIN_ROWS_MIXED<Cfg>, Cfg::BK);
+    if constexpr (WINDOWED && EPI == EPI_MULLIKEN) {
+      rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k, WIN_ROWS_MIXED<Cfg>,
+                         Cfg::BK);
     }
   }
   mixed_tile<EPI, Cfg>(args.item[z], args.n, rows.x, rows.y - rows.x, tile);

@@ -583,6 +583,14 @@ struct KrylovState {
   double ls_residual;  // ||F~ c - f~|| / ||f~|| of the last solve
 };
 
+// What a solve tells a host that waits for it, in pinned host memory. word = 2 seq + stop is one
+// store, so the host may act on it while the kernel still runs; st is whole once the stream
+// has passed the kernel.
+struct SolveReport {
+  unsigned long long word;
+  KrylovState st;
+};
+
 // y = K0 (x - sub) (sub may be null), or -(x - sub) when K0 is null.
 // One wave per row. Skipped after a breakdown when stop is given. With reset given (the
 // first launch of an update, stop null) thread 0 also clears that Krylov state.
@@ -686,7 +694,8 @@ __global__ void __launch_bounds__(1024) krylov_orthonormalize(const double* __re
 // expansion (used by the adaptive-rank call after each direction). One block.
 __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const double* __restrict__ Ft,
                                           const double* __restrict__ ftilde, int n2, KrylovState* st,
-                                          double* __restrict__ x, double stop_tol) {
+                                          double* __restrict__ x, double stop_tol, SolveReport* report = nullptr,
+                                          unsigned long long seq = 0) {
   __shared__ double sr[2][16];
   __shared__ double O[MAX_RANK][MAX_RANK + 1];
   __shared__ double c[MAX_RANK];
@@ -821,7 +830,12 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
     }
     const double res = ff > 0.0 ? sqrt(rr / ff) : 0.0;
     st->ls_residual = res;
-    if (stop_tol > 0.0 && okv && res <= stop_tol) st->stop = 1;
+    int stop = st->stop;
+    if (stop_tol > 0.0 && okv && res <= stop_tol) st->stop = stop = 1;
+    if (report != nullptr) {
+      __hip_atomic_store(&report->word, 2 * seq + (stop != 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      report->st = *st;
+    }
   }
 }
 
@@ -829,8 +843,8 @@ __global__ void __launch_bounds__(1024) krylov_solve(const double* __restrict__ 
                                                      const double* __restrict__ Ft,
                                                      const double* __restrict__ ftilde, int n2,
                                                      KrylovState* st, double* __restrict__ x,
-                                                     double stop_tol) {
-  solve_dev(V, Ft, ftilde, n2, st, x, stop_tol);
+                                                     double stop_tol, SolveReport* report, unsigned long long seq) {
+  solve_dev(V, Ft, ftilde, n2, st, x, stop_tol, report, seq);
 }
 
 // Host-side copies of the argument lists of precondition and krylov_solve (declaration
@@ -861,19 +875,22 @@ struct PreconditionArgs {
 };
 
 struct SolveArgs {
-  static constexpr int COUNT = 7;
+  static constexpr int COUNT = 9;
   const double *V, *Ft, *ftilde;
   int n2;
   KrylovState* st;
   double* out;
   double tol;
+  SolveReport* report;
+  unsigned long long seq;
   static SolveArgs from(void** kp) {
     return {kernel_arg<const double*>(kp, 0), kernel_arg<const double*>(kp, 1), kernel_arg<const double*>(kp, 2),
             kernel_arg<int>(kp, 3),           kernel_arg<KrylovState*>(kp, 4),  kernel_arg<double*>(kp, 5),
-            kernel_arg<double>(kp, 6)};
+            kernel_arg<double>(kp, 6),        kernel_arg<SolveReport*>(kp, 7),  kernel_arg<unsigned long long>(kp, 8)};
   }
   void pointers(void** o) {
     o[0] = &V; o[1] = &Ft; o[2] = &ftilde; o[3] = &n2; o[4] = &st; o[5] = &out; o[6] = &tol;
+    o[7] = &report; o[8] = &seq;
   }
 };
 
