@@ -246,11 +246,13 @@ def bench_grad(args):
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
     names = {0: "forward_fermi", 1: "back_mulliken", 2: "reverse_forward_xy", 3: "reverse_accumulate"}
-    flops_launch = {0: 4.0 * nb ** 3, 1: 4.0 * nb ** 3, 2: 8.0 * nb ** 3, 3: 8.0 * nb ** 3}
+    # the reverse pass's launches cover several directions each: 8 Nb^3 a direction for X of its four
+    # items, and for the accumulation
+    flops = {0: 4.0 * nb ** 3, 1: 4.0 * nb ** 3, 2: 8.0 * m * args.steps * nb ** 3, 3: 8.0 * m * args.steps * nb ** 3}
     kern = {}
     for kid, name in names.items():
         ms, n = h.profile_read(kid)
-        kern[name] = (ms / max(n, 1), n, flops_launch[kid])
+        kern[name] = (ms / max(n, 1), n, flops[kid] / max(n, 1) if kid >= 2 else flops[kid])
     h.profile_enable(False)
     h.close()
     err = None

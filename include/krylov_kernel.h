@@ -242,8 +242,8 @@ kk_status kk_xlbomd_update(kk_handle h, const double *n_hist, int k_max, const d
  *                  other parameters (U, W, H0, n) chains through its own
  *                  construction; the expansion-point dependence on gamma and W
  *                  (through H^sigma) is left to that chain.
- * The per-direction response matrices are recomputed in the reverse sweep,
- * never stored. Levels closer than 1e-3 kT (exact degeneracies included) are
+ * The per-direction response matrices are recomputed in the reverse sweep, a
+ * group of directions at a time, never kept from the forward. Levels closer than 1e-3 kT (exact degeneracies included) are
  * handled through second divided differences of the Fermi function. With a
  * breakdown (rank r < m) the rank-r expansion is differentiated and
  * KK_BREAKDOWN is returned.
@@ -332,8 +332,9 @@ const char *kk_last_error(void);
  * (kernel_id 0: the forward eigenbasis transform with the Fermi Hadamard
  * product, one kernel or the full-tile product followed by its symmetrizing
  * pass; 1: back-transform with the Mulliken projection; 2: the forward
- * transform of the reverse pass, which also writes X; 3: the reverse pass's
- * accumulation of Y0_b Xa + Y0_a Xb). kk_profile_read synchronizes and returns
+ * transforms of the reverse pass, which also write X, one or more directions a
+ * step; 3: the reverse pass's accumulation of Y0_b Xa + Y0_a Xb over a group
+ * of directions). kk_profile_read synchronizes and returns
  * the summed milliseconds and step count since the last reset. At most 8192
  * steps are recorded between resets.
  */

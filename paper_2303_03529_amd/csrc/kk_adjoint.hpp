@@ -87,14 +87,17 @@ __device__ __forceinline__ double w_dd_close(double ei, double ej, double mu, do
   return -(d2 + d4 * h * h / 6.0);
 }
 
+// One spin of a group of directions: X of their items (a up, a dn, b up, b dn), np2 apart.
 struct AdjSpin {
-  const double *Xa, *Xb;          // np x np
+  const double *Xa, *Xb;           // np x np, direction 0; the next direction's stride apart
   const double *eps, *f, *fc, *w;  // np
   double* D;                       // np x np accumulator
   double* gdiag;                   // np accumulator
 };
 struct AdjSpins {
   AdjSpin s[2];
+  size_t stride;
+  int directions;
 };
 
 // Reverse-pass state of the Krylov loop on the device.
@@ -105,27 +108,35 @@ __global__ void __launch_bounds__(1024) adj_init(const double* __restrict__ V, c
                                                  const KrylovState* __restrict__ st,
                                                  const double* __restrict__ xbar, double* __restrict__ Vbar,
                                                  double* __restrict__ Fbar, double* __restrict__ bbar) {
-  __shared__ double sh[17];
   __shared__ double O[MAX_RANK][MAX_RANK + 1];
   __shared__ double c[MAX_RANK], z[MAX_RANK];
   __shared__ int ok;
   const int r = st->rank;
-  for (int a = 0; a < r; ++a) {
-    for (int b = 0; b <= a; ++b) {
-      double d = 0.0;
-      for (int i = threadIdx.x; i < n2; i += blockDim.x) d += Ft[(size_t)a * n2 + i] * Ft[(size_t)b * n2 + i];
-      d = block_sum(d, sh);
-      if (threadIdx.x == 0) O[a][b] = d;
+  // O = F~^T F~ (lower triangle), F~^T f~ and V^T x_bar, one wave each
+  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, npairs = r * (r + 1) / 2;
+  for (int p = wave; p < npairs + 2 * r; p += blockDim.x / WAVE) {
+    int a, b = 0;
+    const double *x, *y;
+    if (p < npairs) {
+      a = 0;
+      while ((a + 1) * (a + 2) / 2 <= p) ++a;
+      b = p - a * (a + 1) / 2;
+      x = Ft + (size_t)a * n2;
+      y = Ft + (size_t)b * n2;
+    } else {
+      a = (p - npairs) >> 1;
+      x = ((p - npairs) & 1 ? V : Ft) + (size_t)a * n2;
+      y = (p - npairs) & 1 ? xbar : ftilde;
     }
-    double d = 0.0, e = 0.0;
-    for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-      d += Ft[(size_t)a * n2 + i] * ftilde[i];
-      e += V[(size_t)a * n2 + i] * xbar[i];
+    double d = 0.0;
+    for (int i = lane; i < n2; i += WAVE) d += x[i] * y[i];
+    d = wave_sum_dpp(d);
+    if (lane == 0) {
+      if (p < npairs) O[a][b] = d;
+      else ((p - npairs) & 1 ? z : c)[a] = d;
     }
-    d = block_sum(d, sh);
-    e = block_sum(e, sh);
-    if (threadIdx.x == 0) { c[a] = d; z[a] = e; }
   }
+  __syncthreads();
   if (threadIdx.x == 0) {
     ok = 1;
     for (int j = 0; j < r && ok; ++j) {
@@ -175,45 +186,68 @@ __global__ void __launch_bounds__(1024) adj_init(const double* __restrict__ V, c
 
 // Reverse of the orthonormalization that produced v_{k+1} from f~_k (skipped
 // for the last direction), then y = -lambda_k (K0 = -I) or lambda_k (the host
-// applies K0^T). One block.
+// applies K0^T). With u given (K0 = -I) the potentials of a = M y follow, on every orbital. One
+// block of 1024 threads, PER >= n2 / 1024 entries each; the 2 (k + 1) dot products run NJ rows of V
+// at a time, so that a reduction (all of this kernel's time) serves as many rows.
+template <int PER, int NJ>
 __global__ void __launch_bounds__(1024) adj_gs(const double* __restrict__ V, const double* __restrict__ Ft, int n2,
                                                int k, int last, double* __restrict__ Vbar,
-                                               double* __restrict__ Fbar, double* __restrict__ y, int negate) {
-  __shared__ double sh[17];
+                                               double* __restrict__ Fbar, double* __restrict__ y, int negate,
+                                               const int* __restrict__ offsets, int np, double* __restrict__ u) {
+  constexpr int NW = 16;
+  __shared__ double part[2][NW][2 * NJ];
   __shared__ double hh[MAX_RANK], pp[MAX_RANK];
-  constexpr int PER = 8;
+  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+  int buf = 0;
+  // sums of N values over the block into sum[], the same bits in every thread; one barrier
+  auto reduce = [&](auto& v, auto& sum) __attribute__((always_inline)) {
+    constexpr int N = sizeof(v) / sizeof(double);
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const double t = wave_sum_dpp(v[q]);
+      if (lane == 0) part[buf][wave][q] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < N; ++q) sum[q] = wave_sum_dpp(lane < nw ? part[buf][lane][q] : 0.0);
+    buf ^= 1;
+  };
   double* fb = Fbar + (size_t)k * n2;
   if (!last) {
     const double* vn = V + (size_t)(k + 1) * n2;
     const double* fk = Ft + (size_t)k * n2;
     const double* vb = Vbar + (size_t)(k + 1) * n2;
-    double rho = 0.0, t = 0.0;
+    double first[2] = {}, rt[2], wb[PER];
     for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-      rho += vn[i] * fk[i];
-      t += vn[i] * vb[i];
+      first[0] += vn[i] * fk[i];
+      first[1] += vn[i] * vb[i];
     }
-    rho = block_sum(rho, sh);
-    t = block_sum(t, sh);
-    double wb[PER];
+    reduce(first, rt);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       const int i = threadIdx.x + e * blockDim.x;
-      wb[e] = i < n2 ? (vb[i] - vn[i] * t) / rho : 0.0;
+      wb[e] = i < n2 ? (vb[i] - vn[i] * rt[1]) / rt[0] : 0.0;
     }
-    for (int j = 0; j <= k; ++j) {
-      const double* vj = V + (size_t)j * n2;
-      double h = 0.0, p = 0.0;
+    for (int j0 = 0; j0 <= k; j0 += NJ) {
+      double d[2 * NJ] = {}, sum[2 * NJ];
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const int i = threadIdx.x + e * blockDim.x;
-        if (i < n2) {
-          h += vj[i] * fk[i];
-          p += vj[i] * wb[e];
+      for (int q = 0; q < NJ; ++q) {
+        if (j0 + q > k) break;
+        const double* vj = V + (size_t)(j0 + q) * n2;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+          const int i = threadIdx.x + e * blockDim.x;
+          const double v = i < n2 ? vj[i] : 0.0;
+          d[2 * q] += v * (i < n2 ? fk[i] : 0.0);
+          d[2 * q + 1] += v * wb[e];
         }
       }
-      h = block_sum(h, sh);
-      p = block_sum(p, sh);
-      if (threadIdx.x == 0) { hh[j] = h; pp[j] = p; }
+      reduce(d, sum);
+      if (threadIdx.x == 0)
+        for (int q = 0; q < NJ && j0 + q <= k; ++q) {
+          hh[j0 + q] = sum[2 * q];
+          pp[j0 + q] = sum[2 * q + 1];
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -231,6 +265,16 @@ __global__ void __launch_bounds__(1024) adj_gs(const double* __restrict__ V, con
     __syncthreads();
   }
   for (int i = threadIdx.x; i < n2; i += blockDim.x) y[i] = negate ? -fb[i] : fb[i];
+  if (u == nullptr) return;
+  __syncthreads();
+  const int N = n2 / 2;
+  for (int a = threadIdx.x; a < N; a += blockDim.x) {
+    const double up = y[a] + y[N + a], dn = y[a] - y[N + a];
+    for (int i = offsets[a]; i < offsets[a + 1]; ++i) {
+      u[i] = up;
+      u[np + i] = dn;
+    }
+  }
 }
 
 // y = A^T x for a row-major n x n A (one thread per output; coalesced over columns).
@@ -242,8 +286,7 @@ __global__ void gemv_t(const double* __restrict__ A, const double* __restrict__ 
   y[i] = s;
 }
 
-// Chemical-potential shifts of the two directions of a reverse step: items
-// 0,1 = (a, up/dn), 2,3 = (b, up/dn) of xdiag. One block per direction.
+// Chemical-potential shifts of the pairs of items (2 p, 2 p + 1) = (up, dn) of xdiag. One block each.
 __global__ void adj_dmu(const double* __restrict__ xdiag, int nb, int np, const double* __restrict__ w0,
                         const double* __restrict__ w1, const double* __restrict__ wsum_p, double* __restrict__ dmu) {
   __shared__ double sh[17];
@@ -257,33 +300,46 @@ __global__ void adj_dmu(const double* __restrict__ xdiag, int nb, int np, const 
   if (threadIdx.x == 0) dmu[p] = wsum > 0.0 ? s / wsum : 0.0;
 }
 
-// Row i of spin blockIdx.y: D_ij += dmu_b Xa_ij + dmu_a Xb_ij and
-// g_i += sum_j 2 f[e_i, e_i, e_j] Xa_ij Xb_ij + w'_i (Xa_ii dmu_b + Xb_ii dmu_a - dmu_a dmu_b).
+// Row i of spin blockIdx.y over all directions k of the group (dmu[2 k] of a, dmu[2 k + 1] of b):
+// D_ij += sum_k dmu_b Xa_ij + dmu_a Xb_ij and
+// g_i += sum_k (sum_j 2 f[e_i, e_i, e_j] Xa_ij Xb_ij + w'_i (Xa_ii dmu_b + Xb_ii dmu_a - dmu_a dmu_b)).
+// The divided difference is formed once per element and D is updated once, whatever the directions
+// (128 atoms, 8 directions: 8 x 21 us -> 78 us).
 __global__ void adj_rows(AdjSpins sp, int nb, int np, const double* __restrict__ dmu, const double* __restrict__ mu_p,
                          double beta, double tau) {
   __shared__ double sh[17];
   const AdjSpin& s = sp.s[blockIdx.y];
-  const int i = blockIdx.x;
-  const double da = dmu[0], db = dmu[1], mu = *mu_p;
+  const int i = blockIdx.x, nd = sp.directions;
+  const double mu = *mu_p;
   const double ei = s.eps[i], fi = s.f[i], fci = s.fc[i];
   const double* xa = s.Xa + (size_t)i * np;
   const double* xb = s.Xb + (size_t)i * np;
   double* d = s.D + (size_t)i * np;
   double acc = 0.0;
   for (int j = threadIdx.x; j < nb; j += blockDim.x) {
-    const double a = xa[j], b = xb[j];
-    d[j] += db * a + da * b;
-    acc += 2.0 * fermi_dd2(ei, fi, fci, ei, fi, fci, s.eps[j], s.f[j], s.fc[j], mu, beta, tau) * a * b;
+    double dj = d[j], ab = 0.0;
+    for (int k = 0; k < nd; ++k) {
+      const double a = xa[k * sp.stride + j], b = xb[k * sp.stride + j];
+      dj += dmu[2 * k + 1] * a + dmu[2 * k] * b;
+      ab += a * b;
+    }
+    d[j] = dj;
+    acc += 2.0 * fermi_dd2(ei, fi, fci, ei, fi, fci, s.eps[j], s.f[j], s.fc[j], mu, beta, tau) * ab;
   }
   acc = block_sum(acc, sh);
   if (threadIdx.x == 0) {
     double d2, d4;
     fermi_d2_d4(ei, mu, beta, &d2, &d4);
-    s.gdiag[i] += acc - d2 * (xa[i] * db + xb[i] * da - da * db);
+    double t = 0.0;
+    for (int k = 0; k < nd; ++k) {
+      const double da = dmu[2 * k], db = dmu[2 * k + 1];
+      t += xa[k * sp.stride + i] * db + xb[k * sp.stride + i] * da - da * db;
+    }
+    s.gdiag[i] += acc - d2 * t;
   }
 }
 
-// Near-degenerate pairs: pk[p] += sum_l f[e_i, e_j, e_l] (Xb_il Xa_jl + Xa_il Xb_jl)
+// Near-degenerate pairs: pk[p] += sum_k sum_l f[e_i, e_j, e_l] (Xb_il Xa_jl + Xa_il Xb_jl)
 // (X symmetric). pairs[p] = (i, j) for p < n0 in spin 0, then spin 1. One block per pair.
 __global__ void adj_pairs(AdjSpins sp, const int2* __restrict__ pairs, int n0, int nb, int np,
                           const double* __restrict__ mu_p, double beta, double tau, double* __restrict__ pk) {
@@ -296,23 +352,40 @@ __global__ void adj_pairs(AdjSpins sp, const int2* __restrict__ pairs, int n0, i
   const double *xai = s.Xa + (size_t)i * np, *xbi = s.Xb + (size_t)i * np;
   const double *xaj = s.Xa + (size_t)j * np, *xbj = s.Xb + (size_t)j * np;
   double acc = 0.0;
-  for (int l = threadIdx.x; l < nb; l += blockDim.x)
-    acc += fermi_dd2(ei, fi, fci, ej, fj, fcj, s.eps[l], s.f[l], s.fc[l], mu, beta, tau) *
-           (xbi[l] * xaj[l] + xai[l] * xbj[l]);
+  for (int l = threadIdx.x; l < nb; l += blockDim.x) {
+    double x = 0.0;
+    for (int k = 0; k < sp.directions; ++k) {
+      const size_t o = k * sp.stride + l;
+      x += xbi[o] * xaj[o] + xai[o] * xbj[o];
+    }
+    acc += fermi_dd2(ei, fi, fci, ej, fj, fcj, s.eps[l], s.f[l], s.fc[l], mu, beta, tau) * x;
+  }
   acc = block_sum(acc, sh);
   if (threadIdx.x == 0) pk[p] += acc;
 }
 
-// E'_bar of one spin in the eigenbasis (see the header), 32 x 32 tiles; pairs
-// closer than tau are left at 0 for adj_pair_final.
-__global__ void adj_final(const double* __restrict__ K, const double* __restrict__ D, const double* __restrict__ eps,
-                          const double* __restrict__ w, const double* __restrict__ gdiag,
-                          const double* __restrict__ gtot_p, const double* __restrict__ wsum_p, int nb, int np,
-                          double tau, double* __restrict__ Ep) {
+// E'_bar in the eigenbasis (see the header), spin blockIdx.z, 32 x 32 tiles; pairs closer than tau
+// are left at 0 for adj_pair_final. K of a spin is the sum of `chunks` partial sums, 2 np^2 apart.
+struct AdjFinal {
+  const double *K, *D;  // [chunks][2][np][np], [2][np][np]
+  const double *eps[2], *w[2], *gdiag[2];
+  double* Ep;           // [2][np][np]
+};
+__global__ void adj_final(const AdjFinal a, int chunks, const double* __restrict__ gtot_p,
+                          const double* __restrict__ wsum_p, int nb, int np, double tau) {
+  const int z = blockIdx.z;
+  const size_t np2 = (size_t)np * np;
+  const double *K = a.K + z * np2, *D = a.D + z * np2, *eps = a.eps[z], *w = a.w[z], *gdiag = a.gdiag[z];
+  double* Ep = a.Ep + z * np2;
+  auto k_at = [&](size_t o) {
+    double v = K[o];
+    for (int c = 1; c < chunks; ++c) v += K[o + 2 * c * np2];
+    return v;
+  };
   __shared__ double kt[32][33];
   const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
-  for (int r = ty; r < 32; r += 8) kt[r][tx] = K[(size_t)(bx + r) * np + by + tx];  // K^T tile
+  for (int r = ty; r < 32; r += 8) kt[r][tx] = k_at((size_t)(bx + r) * np + by + tx);  // K^T tile
   __syncthreads();
   const double wsum = *wsum_p, gtot = *gtot_p;
   for (int r = ty; r < 32; r += 8) {
@@ -325,7 +398,7 @@ __global__ void adj_final(const double* __restrict__ K, const double* __restrict
         const double gap = eps[i] - eps[j];
         if (fabs(gap) >= tau) {
           const size_t ij = (size_t)i * np + j;
-          v = ((K[ij] - kt[tx][r]) + (w[i] - w[j]) * D[ij]) / gap;
+          v = ((k_at(ij) - kt[tx][r]) + (w[i] - w[j]) * D[ij]) / gap;
         }
       }
     }
@@ -350,21 +423,15 @@ __global__ void adj_pair_final(const int2* __restrict__ pairs, int n0, int npair
   Ep[(size_t)j * np + i] = v;
 }
 
-// v_bar_k += Gamma g - y and gamma_bar += g_q v_q^T; one wave per atom row.
+// v_bar_k += Gamma g - y; one wave per atom row.
 __global__ void adj_apply(const double* __restrict__ gamma, int N, double W, const double* __restrict__ g,
-                          const double* __restrict__ y, const double* __restrict__ vk, double* __restrict__ vbar,
-                          double* __restrict__ gamma_bar) {
+                          const double* __restrict__ y, double* __restrict__ vbar) {
   const int a = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int lane = threadIdx.x & (WAVE - 1);
   if (a >= N) return;
   const double* gr = gamma + (size_t)a * N;
-  double* gb = gamma_bar + (size_t)a * N;
-  const double ga = g[a];
   double s = 0.0;
-  for (int j = lane; j < N; j += WAVE) {
-    s += gr[j] * g[j];
-    gb[j] += ga * vk[j];
-  }
+  for (int j = lane; j < N; j += WAVE) s += gr[j] * g[j];
   s = wave_sum(s);
   if (lane == 0) {
     vbar[a] += s - y[a];
@@ -372,13 +439,29 @@ __global__ void adj_apply(const double* __restrict__ gamma, int N, double W, con
   }
 }
 
-// W_bar += g_m . v_m (one block, fixed order).
-__global__ void adj_wbar(const double* __restrict__ g, const double* __restrict__ vk, int N, double* __restrict__ wbar) {
+// The parameter gradients of all directions at once (g and V: rank x 2N), directions in the
+// sweep's order: gamma_bar_ij = sum_k g_q,i v_q,j, one block per row i, and W_bar = sum_k g_m . v_m
+// in block N.
+__global__ void adj_params(const double* __restrict__ g, const double* __restrict__ V, int N, int rank,
+                           double* __restrict__ gamma_bar, double* __restrict__ wbar) {
   __shared__ double sh[17];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) s += g[N + i] * vk[N + i];
-  s = block_sum(s, sh);
-  if (threadIdx.x == 0) *wbar += s;
+  const int i = blockIdx.x;
+  const size_t n2 = 2 * (size_t)N;
+  if (i < N) {
+    for (int j = threadIdx.x; j < N; j += blockDim.x) {
+      double s = 0.0;
+      for (int k = rank - 1; k >= 0; --k) s += g[k * n2 + i] * V[k * n2 + j];
+      gamma_bar[(size_t)i * N + j] = s;
+    }
+    return;
+  }
+  double w = 0.0;
+  for (int k = rank - 1; k >= 0; --k) {
+    double s = 0.0;
+    for (int j = threadIdx.x; j < N; j += blockDim.x) s += g[k * n2 + N + j] * V[k * n2 + N + j];
+    w += block_sum(s, sh);
+  }
+  if (threadIdx.x == 0) *wbar = w;
 }
 
 // f~_bar += reverse of v_1 = f~ / |f~|; out = -f~_bar (K0 = -I) or f~_bar. One block.
@@ -400,8 +483,11 @@ __global__ void __launch_bounds__(1024) adj_finish(const double* __restrict__ V,
   }
 }
 
-// dst (nb x nb) = src (np x np) without the padding.
-__global__ void unpad_copy(const double* __restrict__ src, int np, double* __restrict__ dst, int nb) {
+// dst (nb x nb) = src (np x np) without the padding, for both spins (blockIdx.y; src np^2 apart).
+__global__ void unpad_copy(const double* __restrict__ src2, int np, double* __restrict__ dst0,
+                           double* __restrict__ dst1, int nb) {
+  const double* src = src2 + (size_t)blockIdx.y * np * np;
+  double* dst = blockIdx.y ? dst1 : dst0;
   const size_t n = (size_t)nb * nb;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
     const size_t i = e / nb, j = e - i * nb;

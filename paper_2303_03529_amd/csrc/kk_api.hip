@@ -265,25 +265,35 @@ struct kk_handle_s {
     g_solve_args.clear();
   }
 
-  // reverse-pass workspace (krylov_kernel_adjoint), allocated on first use
-  std::vector<void*> adj_owned;
-  double *aX = nullptr, *aY = nullptr, *aK = nullptr, *aD = nullptr;  // 4, 4, 2, 2 padded matrices
+  // reverse-pass workspace (krylov_kernel_adjoint), allocated on first use: the Krylov vectors, and
+  // for dL/dH the X and Y of a group of adj_group directions
+  std::vector<void*> adj_owned, adjh_owned;
+  double *aX = nullptr, *aY = nullptr, *aK = nullptr, *aD = nullptr, *aP = nullptr;
   double *au = nullptr, *axdiag = nullptr, *apart = nullptr, *agdiag = nullptr;
   double *admu = nullptr, *agtot = nullptr, *ag = nullptr, *ay = nullptr, *alam = nullptr;
   double *aVbar = nullptr, *aFbar = nullptr, *abbar = nullptr, *aKd = nullptr;
+  int2* atiles = nullptr;
+  int adj_group = 0, adj_chunks = 1;
   std::vector<void*> pair_owned;
   int2* apairs = nullptr;
   double* apk = nullptr;
   int pair_cap = 0, an0 = 0, an1 = 0;
   long pairs_gen = -1;
 
+  void free_adjoint_h() {
+    for (void* p : adjh_owned) (void)hipFree(p);
+    adjh_owned.clear();
+    aX = aY = aK = aD = aP = au = axdiag = apart = agdiag = admu = agtot = nullptr;
+    atiles = nullptr;
+    adj_group = 0;
+  }
   void free_adjoint() {
+    free_adjoint_h();
     for (void* p : adj_owned) (void)hipFree(p);
     for (void* p : pair_owned) (void)hipFree(p);
     adj_owned.clear();
     pair_owned.clear();
-    aX = aY = aK = aD = au = axdiag = apart = agdiag = nullptr;
-    admu = agtot = ag = ay = alam = aVbar = aFbar = abbar = aKd = nullptr;
+    ag = ay = alam = aVbar = aFbar = abbar = aKd = nullptr;
     apairs = nullptr;
     apk = nullptr;
     pair_cap = an0 = an1 = 0;
@@ -432,6 +442,43 @@ int choose_ksplit(int np, int kc, int tiles, int cus, bool one_per_cu, int* chun
   if (!one_per_cu && load(best) > 0.75 * load(1)) return 1;
   *chunk_rows = best_ck;
   return best;
+}
+
+// How the FP64 products of one system's two spins run: their tile class (launch_gemm's cls) and
+// the chunks of their contraction, ck rows each.
+struct F64Plan {
+  int cls = 0, chunks = 1, ck = 0;
+  int side() const { return cls ? SmallF64::BM : kk::BackCfg::BM; }
+  int tiles(int np) const { return (np / side()) * (np / side()); }
+  // Mulliken partial rows per chunk
+  int nbase(int np) const { return cls ? (np / SmallF64::BN) * SmallF64::WAVES_N : (np / kk::BackCfg::BN) * kk::BackCfg::WAVES_N; }
+};
+// Largest padded size whose K-split runs on 64 x 64 tiles (TinyF64, K stage 32), in chunks down to
+// two K stages, whenever the FP64 rule splits them at all (16 atoms, kc = 160: four chunks of 64
+// rows, 128 workgroups instead of 32; 37 atoms: three chunks of 128 rows, 216 workgroups
+// instead of the 128 x 128 split's 54). Updates/s against the 128 x 128 split or the
+// unsplit 64 x 64 tiles, one process: 16 atoms m = 4 6048 -> 7082, 8 atoms 7187 -> 7795, 29 atoms m = 8
+// 1680 -> 2977, 37 atoms 1816 -> 2747, 56 atoms 1734 -> 2100; from a padded size of 640
+// the rule stops splitting these tiles (70 and 85 atoms: level).
+constexpr int KTINY_MAX_NP = 512;
+F64Plan plan_f64(int np, int kc, int cus, bool may_split) {
+  F64Plan p;
+  p.ck = kc;
+  if (may_split) {
+    p.chunks = choose_ksplit(np, kc, (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN), cus, false, &p.ck);
+    if (np <= KTINY_MAX_NP) {
+      int ck = kc;
+      const int c = choose_ksplit(np, kc, (np / TinyF64::BM) * (np / TinyF64::BN), cus, false, &ck, 2 * TinyF64::BK);
+      if (c > 1) {
+        p.cls = 2;
+        p.chunks = c;
+        p.ck = ck;
+        return p;
+      }
+    }
+  }
+  if (p.chunks == 1 && np <= SMALL_NP_F64 && !f64_large_tiles_fill(np, cus)) p.cls = np <= TINY_NP_F64 ? 2 : 1;
+  return p;
 }
 
 // Stream-K products for the split forms' small shape (gemm_mixed_sk), taken where no
@@ -631,12 +678,6 @@ kk_status launch_gemm(kk_handle h, int epi, kk::GemmArgs& a, int cls = 0) {
       kk::fermi_symmetrize_f64<kk::SYM64_B_LARGE, kk::SYM64_T_LARGE>
           <<<dim3(nblk * (nblk + 1) / 2, a.nitems), kk::SYM64_T_LARGE, 0, h->stream>>>(a);
     }
-  } else if (epi == kk::EPI_FERMI_XY) {
-    ProfileScope ps(h, 2);
-    kk::gemm_f64<kk::EPI_FERMI_XY, kk::FwdCfg><<<grid, kk::FwdCfg::THREADS, 0, h->stream>>>(a);
-  } else if (epi == kk::EPI_ACCUM) {
-    ProfileScope ps(h, 3);
-    kk::gemm_f64<kk::EPI_ACCUM, kk::BackCfg><<<grid, kk::BackCfg::THREADS, 0, h->stream>>>(a);
   } else {
     ProfileScope ps(h, 1);
     if (cls == 2)
@@ -838,7 +879,6 @@ static_assert(kk::SYM_B_LARGE == 64, "the large handles' symmetrizing pass runs 
 template <class Cfg>
 kk_status launch_bf16_single(kk_handle h, bool forward, kk::MixedArgs& a, const _Float16* const* a2,
                              const _Float16* const* b2, const kk::MixedArgs* sym, int kch) {
-  const int grid = a.ntiles * a.nitems;
   for (int z = 0; z < a.nitems; ++z) { a.item[z].a0r = a2[z]; a.item[z].b0r = b2[z]; }
   if (forward) {
     if (a.sk_grid > 0)
@@ -865,8 +905,7 @@ kk_status launch_bf16_single(kk_handle h, bool forward, kk::MixedArgs& a, const 
 // sym, kch: the K-split form, as for launch_bf16_single (small product configuration only).
 kk_status launch_mixed(kk_handle h, bool forward, kk::MixedArgs& a, const _Float16* const* a2 = nullptr,
                        const _Float16* const* b2 = nullptr, const kk::MixedArgs* sym = nullptr, int kch = 1) {
-  const int grid = a.ntiles * a.nitems;
-  if (grid <= 0) return KK_OK;
+  if (a.ntiles * a.nitems <= 0) return KK_OK;
   if (a.nitems > kk::MAX_GEMM_BATCH) return fail(KK_EINVAL, "internal: too many GEMM items");
   if ((kch > 1 || a.sk_grid > 0) && h->mx_large) return fail(KK_EINVAL, "internal: K-split on the large split tiles");
   if (h->bf16) {
@@ -1266,20 +1305,25 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
     h->bf16 = precision == KK_MIXED_BF16;
     h->natoms = n_atoms; h->nb = nb; h->np = np;
     h->kc = (nb + KSTEP - 1) / KSTEP * KSTEP;
-    // the K-split runs on the 128 x 128 tiles of either form, for FP64 systems up to a padded
-    // size of 512 on 64 x 64 tiles (a batch's systems never split)
+    // (a batch's systems never split)
     h->kch = 1;
     h->kck = h->kc;
     h->sk = false;
     h->sk_grid = 0;
-    h->ktiny = false;
+    h->ktiny = h->small_f64 = h->tiny_f64 = false;
     h->mx_tiny = mixed && !mx_large && !split_large && np <= MTINY_MAX_NP;
-    if (!split_large && !mx_large) {
+    if (!mixed) {
+      const F64Plan p = plan_f64(np, h->kc, cu_count(), !split_large);
+      h->kch = p.chunks;
+      h->kck = p.ck;
+      h->small_f64 = p.cls != 0;
+      h->tiny_f64 = p.cls == 2;
+      h->ktiny = h->tiny_f64 && p.chunks > 1;
+    } else if (!split_large && !mx_large) {
       const int tiles = h->mx_tiny ? (np / MTinyCfg::BM) * (np / MTinyCfg::BN)
-                        : mixed    ? (np / kk::MSmallCfg::BM) * (np / kk::MSmallCfg::BN)
-                                   : (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN);
-      h->kch = choose_ksplit(np, h->kc, tiles, cu_count(), mixed, &h->kck);
-      if (mixed && !h->mx_tiny && h->kch == 1) {
+                                   : (np / kk::MSmallCfg::BM) * (np / kk::MSmallCfg::BN);
+      h->kch = choose_ksplit(np, h->kc, tiles, cu_count(), true, &h->kck);
+      if (!h->mx_tiny && h->kch == 1) {
         const int slots = choose_stream_k(tiles, h->kc / kk::MSmallCfg::BK, cu_count());
         if (slots > 1) {
           h->sk = true;
@@ -1294,33 +1338,6 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
     // round the split forms' rule allows it is faster: 113 atoms, m = 8, FP16 x 3 1480 ->
     // 1627 updates/s, BF16 1169 -> 1320; 56 atoms 2241 -> 2575 and 1916 -> 2370.)
     h->kchb = h->kch;
-    h->small_f64 = !mixed && np <= SMALL_NP_F64 && h->kch == 1 && !f64_large_tiles_fill(np, cu_count());
-    h->tiny_f64 = h->small_f64 && np <= TINY_NP_F64;
-#ifndef KK_TINY_KSPLIT
-#define KK_TINY_KSPLIT 1
-#endif
-#ifndef KK_KTINY_MAX_NP
-#define KK_KTINY_MAX_NP 512
-#endif
-    if (KK_TINY_KSPLIT && !mixed && np <= KK_KTINY_MAX_NP && !split_large) {
-      // FP64 systems up to a padded size of 512 split the contraction of 64 x 64 tiles
-      // (TinyF64, K stage 32) instead, in chunks down to two K stages, whenever the FP64 rule
-      // splits them at all (16 atoms, kc = 160: four chunks of 64 rows, 128 workgroups
-      // instead of 32; 37 atoms: three chunks of 128 rows, 216 workgroups instead of the
-      // 128 x 128 split's 54). Updates/s against the 128 x 128 split or the unsplit 64 x 64
-      // tiles, one process: 16 atoms m = 4 6048 -> 7082, 8 atoms 7187 -> 7795, 29 atoms m = 8
-      // 1680 -> 2977, 37 atoms 1816 -> 2747, 56 atoms 1734 -> 2100; from a padded size of 640
-      // the rule stops splitting these tiles (70 and 85 atoms: level).
-      const int t64 = (np / TinyF64::BM) * (np / TinyF64::BN);
-      int ck = h->kc;
-      const int c = choose_ksplit(np, h->kc, t64, cu_count(), false, &ck, 2 * TinyF64::BK);
-      if (c > 1) {
-        h->kch = h->kchb = c;
-        h->kck = ck;
-        h->ktiny = true;
-        h->small_f64 = h->tiny_f64 = true;
-      }
-    }
     h->mx_large = mx_large;
     h->nbase = mixed ? (mx_large    ? (np / kk::MLargeCfg::BN) * kk::MLargeCfg::WAVES_N
                         : h->mx_tiny ? (np / MTinyCfg::BN) * MTinyCfg::WAVES_N
@@ -1956,40 +1973,192 @@ kk_status krylov_kernel_apply_noalloc(kk_handle h, const double* delta, int m, c
 
 namespace {
 
-// Mulliken partial rows per spin written by the FP64 back-transform of the reverse pass.
-int adj_nparts(kk_handle h) { return (h->np / kk::BackCfg::BN) * kk::BackCfg::WAVES_N; }
+// The reverse pass's FP64 products run by the plan of an FP64 handle of the same size, whatever
+// the handle's own precision.
+F64Plan adjoint_plan(kk_handle h) { return plan_f64(h->np, h->kc, cu_count(), true); }
 
-// Reverse-pass workspace: the Krylov vectors always; the 12 padded matrices of the
-// expansion-point part only once a call asks for dL/dH.
-kk_status ensure_adjoint(kk_handle h, bool want_H) {
+// Directions whose X and Y the reverse pass holds at a time: 8 padded matrices each, within the
+// workspace budget.
+int adjoint_group(kk_handle h, int m) {
+  const size_t per = (size_t)8 * h->np * h->np * sizeof(double);
+  return (int)std::max<size_t>(1, std::min<size_t>(m, WORKSPACE_BUDGET / per));
+}
+
+// Chunks of the commutator sums' contraction (gemm_pairs): the fewest of the candidates whose
+// workgroups, two co-resident per CU, end within 5 % of the soonest (launch_time).
+int adjoint_chunks(int tiles, int cus) {
+  const int candidates[] = {1, 2, 3, 4, 6, 8};
+  double best = 1e300;
+  for (int c : candidates) best = std::min(best, launch_time(2 * tiles * c, cus, 1.0 / c));
+  for (int c : candidates)
+    if (launch_time(2 * tiles * c, cus, 1.0 / c) <= 1.05 * best) return c;
+  return 1;
+}
+
+// Reverse-pass workspace: the Krylov vectors always; the padded matrices of the expansion-point
+// part only once a call asks for dL/dH (for a rank m, and again when a later rank wants larger
+// groups).
+kk_status ensure_adjoint(kk_handle h, bool want_H, int m) {
   const size_t np = h->np, np2 = np * np, n2 = 2 * (size_t)h->natoms;
   kk_status st;
-  auto get = [&](double** p, size_t count) -> kk_status {
-    void* q = nullptr;
-    kk_status e = dalloc(h->adj_owned, &q, count * sizeof(double));
-    *p = static_cast<double*>(q);
-    return e;
-  };
-  if (want_H && !h->aX) {
-    if ((st = get(&h->aX, 4 * np2))) return st;
-    if ((st = get(&h->aY, 4 * np2))) return st;
-    if ((st = get(&h->aK, 2 * np2))) return st;
-    if ((st = get(&h->aD, 2 * np2))) return st;
+  if (!h->ag) {
+    Slab slab;
+    for (double** q : {&h->alam, &h->abbar, &h->aKd, &h->ay}) slab.add(q, n2);
+    for (double** q : {&h->ag, &h->aVbar, &h->aFbar}) slab.add(q, kk::MAX_RANK * n2);
+    if ((st = slab.commit(h->adj_owned))) return st;
   }
-  if (h->ag) return KK_OK;
-  if ((st = get(&h->au, 4 * np))) return st;
-  if ((st = get(&h->axdiag, 4 * np))) return st;
-  if ((st = get(&h->apart, 2 * (size_t)adj_nparts(h) * np))) return st;
-  if ((st = get(&h->agdiag, 2 * np))) return st;
-  if ((st = get(&h->admu, 2))) return st;
-  if ((st = get(&h->agtot, 1))) return st;
-  if ((st = get(&h->ag, n2))) return st;
-  if ((st = get(&h->ay, n2))) return st;
-  if ((st = get(&h->alam, n2))) return st;
-  if ((st = get(&h->abbar, n2))) return st;
-  if ((st = get(&h->aKd, n2))) return st;
-  if ((st = get(&h->aVbar, kk::MAX_RANK * n2))) return st;
-  if ((st = get(&h->aFbar, kk::MAX_RANK * n2))) return st;
+  const size_t group = adjoint_group(h, m);
+  if (!want_H || (int)group <= h->adj_group) return KK_OK;
+  HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+  h->free_adjoint_h();
+  const F64Plan plan = adjoint_plan(h);
+  const std::vector<int2> tiles = tile_order((int)np, plan.side(), plan.side(), false);
+  h->adj_chunks = adjoint_chunks((int)tiles.size(), cu_count());
+  Slab slab;
+  slab.add(&h->aX, group * 4 * np2);
+  slab.add(&h->aY, group * 4 * np2);
+  slab.add(&h->aK, (size_t)h->adj_chunks * 2 * np2);
+  slab.add(&h->aD, 2 * np2);
+  if (plan.chunks > 1) slab.add(&h->aP, (size_t)kk::MAX_GEMM_BATCH * np2);
+  slab.add(&h->au, (group + 1) * 2 * np);  // a's potentials, then b's of the group
+  slab.add(&h->axdiag, group * 4 * np);
+  slab.add(&h->apart, (size_t)2 * plan.chunks * plan.nbase((int)np) * np);
+  slab.add(&h->agdiag, 2 * np);
+  slab.add(&h->admu, group * 2);
+  slab.add(&h->agtot, 1);
+  slab.add(&h->atiles, tiles.size());
+  if ((st = slab.commit(h->adjh_owned))) return st;
+  h->adj_group = (int)group;
+  HIP_OR_FAIL(hipMemcpyAsync(h->atiles, tiles.data(), sizeof(int2) * tiles.size(), hipMemcpyHostToDevice, h->stream));
+  // rows of the potentials past nb are never written; they scale zero rows and must be finite
+  if ((st = zero(h, h->au, (group + 1) * 2 * np))) return st;
+  HIP_OR_FAIL(hipStreamSynchronize(h->stream));  // the host table must outlive its copy
+  return KK_OK;
+}
+
+// (The reverse pass of 128 atoms, m = 8, with the transforms of two spins cut along K like the
+// forward's, the v_k's batched, and the sums over directions in single launches: gradient 9.35 -> 6.90 ms.
+// Before, each direction ran its four items on 128 x 128 upper tiles over two K halves, 336 us, and
+// its own accumulation.)
+// X and Y of `count` directions whose potentials are in u (2 np doubles each), directions slot,
+// slot + 1, ... of the group, items first and first + 1 (0: a, 2: b).
+kk_status adjoint_forward(kk_handle h, const F64Plan& plan, int slot, int count, int first, const double* u) {
+  const size_t np = h->np, np2 = np * np;
+  // a launch with a workgroup for every slot of the chip needs no K-split
+  const int whole = 2 * count * plan.tiles((int)np) >= 2 * cu_count() ? 1 : plan.chunks;
+  const int step = kk::MAX_GEMM_BATCH / (2 * whole);
+  for (int d0 = 0; d0 < count; d0 += step) {
+    const int nd = std::min(step, count - d0);
+    kk::GemmArgs fa{}, sa{};
+    fa.n = (int)np; fa.k_half = whole > 1 ? plan.ck : h->kc; fa.ntiles = plan.tiles((int)np);
+    fa.tiles = h->atiles; fa.beta = h->beta;
+    fa.nitems = 2 * nd * whole;
+    sa = fa;
+    sa.nitems = 2 * nd;
+    for (int z = 0; z < 2 * nd; ++z) {
+      const int s = z & 1, d = slot + d0 + z / 2, item = first + s;
+      kk::GemmItem& si = sa.item[z];
+      si.xout = h->aX + ((size_t)d * 4 + item) * np2;
+      si.out = h->aY + ((size_t)d * 4 + item) * np2;
+      si.eps = h->eps[s]; si.f = h->f[s]; si.fc = h->fc[s]; si.w = h->w[s];
+      si.xdiag = h->axdiag + ((size_t)d * 4 + item) * np;
+      double* partial = whole > 1 ? h->aP + (size_t)z * whole * np2 : si.xout;
+      si.a0 = partial;
+      for (int j = 0; j < whole; ++j) {
+        const size_t k0 = (size_t)j * plan.ck;
+        kk::GemmItem& fi = fa.item[z * whole + j];
+        fi.a0 = h->C[s] + k0 * np; fi.b0 = h->G[s] + k0 * np;
+        fi.scale = u + ((size_t)(d0 + z / 2) * 2 + s) * np + k0;
+        fi.out = partial + j * np2;
+      }
+    }
+    ProfileScope ps(h, 2);
+    if (plan.cls == 2)
+      run_gemm_f64<kk::EPI_XSTORE, TinyF64>(h, fa);
+    else if (plan.cls == 1)
+      run_gemm_f64<kk::EPI_XSTORE, SmallF64>(h, fa);
+    else
+      run_gemm_f64<kk::EPI_XSTORE, kk::BackCfg>(h, fa);
+    LAUNCH_CHECK("gemm_f64 reverse forward");
+    const int nblk = (int)np / kk::SYM64_B;
+    const dim3 grid(nblk * (nblk + 1) / 2, sa.nitems);
+    switch (whole) {
+      case 1: kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, 1, false, true><<<grid, 256, 0, h->stream>>>(sa, np2); break;
+      case 2: kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, 2, false, true><<<grid, 256, 0, h->stream>>>(sa, np2); break;
+      case 3: kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, 3, false, true><<<grid, 256, 0, h->stream>>>(sa, np2); break;
+      case 4: kk::fermi_symmetrize_f64_chunks<kk::SYM64_B, 256, 4, false, true><<<grid, 256, 0, h->stream>>>(sa, np2); break;
+      default: return fail(KK_EINVAL, "internal: K-split into %d chunks", whole);
+    }
+    LAUNCH_CHECK("fermi_symmetrize_f64_chunks xy");
+  }
+  return KK_OK;
+}
+
+// The window tables whose cut is FP64's (an FP16 x 3 handle's are coarser), or none.
+kk::Window adjoint_window(kk_handle h) { return h->precision == KK_MIXED_F16 ? kk::Window{} : h->win; }
+
+// g = M chi M y of direction `slot`: back-transform and Mulliken sums of its a items.
+kk_status adjoint_back(kk_handle h, const F64Plan& plan, int slot, double* g) {
+  const size_t np = h->np, np2 = np * np;
+  const int nparts = plan.chunks * plan.nbase((int)np), N = h->natoms;
+  const double* xdiag = h->axdiag + (size_t)slot * 4 * np;
+  kk::GemmArgs ba{};
+  ba.n = (int)np; ba.k_half = plan.chunks > 1 ? plan.ck : h->kc; ba.ntiles = plan.tiles((int)np);
+  ba.nitems = 2 * plan.chunks; ba.tiles = h->atiles; ba.beta = h->beta;
+  if (plan.chunks == 1) ba.win = adjoint_window(h);
+  for (int s = 0; s < 2; ++s)
+    for (int j = 0; j < plan.chunks; ++j) {
+      const size_t k0 = (size_t)j * plan.ck;
+      kk::GemmItem& it = ba.item[s * plan.chunks + j];
+      it.a0 = h->CT[s] + k0 * np; it.b0 = h->aY + ((size_t)slot * 4 + s) * np2 + k0 * np; it.g = h->G[s];
+      it.part = h->apart + ((size_t)s * nparts + (size_t)j * plan.nbase((int)np)) * np;
+    }
+  {
+    ProfileScope ps(h, 1);
+    if (plan.cls == 2)
+      run_gemm_f64<kk::EPI_MULLIKEN, TinyF64>(h, ba);
+    else if (plan.cls == 1)
+      run_gemm_f64<kk::EPI_MULLIKEN, SmallF64>(h, ba);
+    else
+      run_gemm_f64<kk::EPI_MULLIKEN, kk::BackCfg>(h, ba);
+    LAUNCH_CHECK("gemm_f64 reverse back");
+  }
+  const dim3 grid((N + kk::COMBINE_ATOMS - 1) / kk::COMBINE_ATOMS, 1);
+  if (2 * N <= kk::FUSED_MAX_N2)
+    kk::combine_small<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(xdiag, h->apart, nparts, h->w[0], h->w[1], h->wsum,
+                                                                  h->t, h->nb, (int)np, h->offsets, N, g, nullptr,
+                                                                  nullptr, nullptr);
+  else
+    kk::combine<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(xdiag, h->apart, nparts, h->w[0], h->w[1], h->wsum, h->t,
+                                                             h->nb, (int)np, h->offsets, N, g, nullptr);
+  LAUNCH_CHECK("combine");
+  return KK_OK;
+}
+
+template <class Cfg>
+void run_gemm_pairs(kk_handle h, const kk::PairArgs& a, bool accumulate) {
+  const int grid = a.ntiles * 2 * a.chunks;
+  if (accumulate)
+    kk::gemm_pairs<Cfg, true><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+  else
+    kk::gemm_pairs<Cfg, false><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+}
+
+// K (+)= sum over the group's directions of Y_b Xa + Y_a Xb, both spins.
+kk_status adjoint_commutators(kk_handle h, const F64Plan& plan, int directions, bool accumulate) {
+  const kk::Window win = adjoint_window(h);
+  kk::PairArgs pa{};
+  pa.X = h->aX; pa.Y = h->aY; pa.out = h->aK; pa.tiles = h->atiles;
+  pa.range[0] = win.range[0]; pa.range[1] = win.range[1];
+  pa.n = h->np; pa.k = h->kc; pa.directions = directions; pa.ntiles = plan.tiles(h->np); pa.chunks = h->adj_chunks;
+  ProfileScope ps(h, 3);
+  if (plan.cls == 2)
+    run_gemm_pairs<TinyF64>(h, pa, accumulate);
+  else if (plan.cls == 1)
+    run_gemm_pairs<SmallF64>(h, pa, accumulate);
+  else
+    run_gemm_pairs<kk::BackCfg>(h, pa, accumulate);
+  LAUNCH_CHECK("gemm_pairs");
   return KK_OK;
 }
 
@@ -2065,7 +2234,7 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
     return fail(KK_EINVAL, "%s: need 1 <= m <= min(2N, %d), got %d", who, kk::MAX_RANK, m);
   const double tau = 1e-3 * h->kT;
 
-  if ((st = ensure_adjoint(h, want_H))) return st;
+  if ((st = ensure_adjoint(h, want_H, m))) return st;
   if ((st = ensure_workspace(h, 1))) return st;
   // forward expansion: recomputed, or the one the last kernel call left
   if (reuse_forward) {
@@ -2085,110 +2254,84 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
   const int npairs = want_H ? h->an0 + h->an1 : 0;
 
   if (want_H) {
-    if ((st = zero(h, h->aK, 2 * np2))) return st;
     if ((st = zero(h, h->aD, 2 * np2))) return st;
     if ((st = zero(h, h->agdiag, 2 * (size_t)np))) return st;
     if (npairs > 0 && (st = zero(h, h->apk, npairs))) return st;
+    if (r == 0 && (st = zero(h, h->aK, (size_t)h->adj_chunks * 2 * np2))) return st;
   }
-  if ((st = zero(h, gamma_bar, (size_t)N * N))) return st;
-  if ((st = zero(h, W_bar, 1))) return st;
 
   kk::adj_init<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, h->ftilde, n2, h->kst, Kdelta_bar, h->aVbar, h->aFbar,
                                           h->abbar);
   LAUNCH_CHECK("adj_init");
 
-  kk::AdjSpins sp{};
-  for (int s = 0; s < 2; ++s) {
-    sp.s[s].Xa = h->aX + (size_t)s * np2;
-    sp.s[s].Xb = h->aX + (size_t)(2 + s) * np2;
-    sp.s[s].eps = h->eps[s]; sp.s[s].f = h->f[s]; sp.s[s].fc = h->fc[s]; sp.s[s].w = h->w[s];
-    sp.s[s].D = h->aD + (size_t)s * np2;
-    sp.s[s].gdiag = h->agdiag + (size_t)s * np;
-  }
+  // Directions from the last to the first: y_k, its transposed response g_k and the adjoint of v_k.
+  // For dL/dH they are taken in groups: X and Y of every v_k of the group (b) first, in batched
+  // launches, then the sweep, which leaves those of y_k (a), then what sums over both.
+  const F64Plan plan = adjoint_plan(h);
   const int wave_blocks = (N * kk::WAVE + 255) / 256;
-  for (int k = r - 1; k >= 0; --k) {
-    const double* vk = h->V + (size_t)k * n2;
-    // lambda_k and y_k = K0^T lambda_k
-    kk::adj_gs<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, n2, k, k == r - 1, h->aVbar, h->aFbar,
-                                          K0 ? h->alam : h->ay, K0 ? 0 : 1);
-    LAUNCH_CHECK("adj_gs");
-    if (K0) {
-      kk::gemv_t<<<(n2 + 255) / 256, 256, 0, h->stream>>>(K0, h->alam, n2, h->ay);
-      LAUNCH_CHECK("gemv_t");
+  for (int k1 = r; k1 > 0;) {
+    const int nd = want_H ? std::min(k1, h->adj_group) : k1, k0 = k1 - nd;
+    double* const ub = h->au + 2 * (size_t)np;
+    if (want_H) {
+      kk::potentials<<<(N * nd * kk::WAVE + 255) / 256, 256, 0, h->stream>>>(
+          h->gamma, N, h->W, h->V + (size_t)k0 * n2, nd, h->offsets, np, ub, nullptr);
+      LAUNCH_CHECK("potentials");
+      if ((st = adjoint_forward(h, plan, 0, nd, 2, ub))) return st;
     }
-    if (!want_H) {
-      // only g = M chi M y is needed: one response with identity coupling, in the handle's precision
-      if ((st = response_any(h, 1, h->ay, h->ag, nullptr, true))) return st;
-      kk::adj_apply<<<wave_blocks, 256, 0, h->stream>>>(h->gamma, N, h->W, h->ag, h->ay, vk,
-                                                         h->aVbar + (size_t)k * n2, gamma_bar);
+    for (int k = k1 - 1; k >= k0; --k) {
+      // lambda_k and y_k = K0^T lambda_k; with H the potentials of a = M y_k (identity coupling)
+      const bool pot = want_H && !K0;
+      double* gk = h->ag + (size_t)k * n2;
+      void (*const gs)(const double*, const double*, int, int, int, double*, double*, double*, int, const int*, int,
+                       double*) = n2 <= 1024   ? &kk::adj_gs<1, 4>
+                                  : n2 <= 2048 ? &kk::adj_gs<2, 4>
+                                               : &kk::adj_gs<8, 1>;
+      gs<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, n2, k, k == r - 1, h->aVbar, h->aFbar, K0 ? h->alam : h->ay,
+                                    K0 ? 0 : 1, h->offsets, np, pot ? h->au : nullptr);
+      LAUNCH_CHECK("adj_gs");
+      if (K0) {
+        kk::gemv_t<<<(n2 + 255) / 256, 256, 0, h->stream>>>(K0, h->alam, n2, h->ay);
+        LAUNCH_CHECK("gemv_t");
+      }
+      if (want_H) {
+        if (!pot) {
+          kk::potentials<<<wave_blocks, 256, 0, h->stream>>>(nullptr, N, 1.0, h->ay, 1, h->offsets, np, h->au, nullptr);
+          LAUNCH_CHECK("potentials");
+        }
+        if ((st = adjoint_forward(h, plan, k - k0, 1, 0, h->au))) return st;
+        if ((st = adjoint_back(h, plan, k - k0, gk))) return st;
+      } else {
+        // only g = M chi M y is needed: one response with identity coupling, in the handle's precision
+        if ((st = response_any(h, 1, h->ay, gk, nullptr, true))) return st;
+      }
+      kk::adj_apply<<<wave_blocks, 256, 0, h->stream>>>(h->gamma, N, h->W, gk, h->ay, h->aVbar + (size_t)k * n2);
       LAUNCH_CHECK("adj_apply");
-      kk::adj_wbar<<<1, 256, 0, h->stream>>>(h->ag, vk, N, W_bar);
-      LAUNCH_CHECK("adj_wbar");
-      continue;
     }
-    // potentials: a = M y (identity coupling), b = M Gamma v_k
-    kk::potentials<<<wave_blocks, 256, 0, h->stream>>>(nullptr, N, 1.0, h->ay, 1, h->offsets, np, h->au, nullptr);
-    kk::potentials<<<wave_blocks, 256, 0, h->stream>>>(h->gamma, N, h->W, vk, 1, h->offsets, np, h->au + 2 * np,
-                                                        nullptr);
-    LAUNCH_CHECK("potentials");
-    // X and Y0 of the four items (a up, a dn, b up, b dn)
-    kk::GemmArgs fa{};
-    fa.n = np; fa.k_half = np; fa.two_halves = 1; fa.ntiles = h->n_upper; fa.nitems = 4;
-    fa.tiles = h->tiles_upper; fa.beta = h->beta;
-    for (int z = 0; z < 4; ++z) {
-      const int s = z & 1;
-      kk::GemmItem& it = fa.item[z];
-      it.a0 = h->C[s]; it.b0 = h->G[s]; it.a1 = h->G[s]; it.b1 = h->C[s];
-      it.scale = h->au + (size_t)z * np; it.out = h->aY + (size_t)z * np2; it.xout = h->aX + (size_t)z * np2;
-      it.eps = h->eps[s]; it.f = h->f[s]; it.fc = h->fc[s]; it.w = h->w[s];
-      it.xdiag = h->axdiag + (size_t)z * np;
-    }
-    if ((st = launch_gemm(h, kk::EPI_FERMI_XY, fa))) return st;
-    // g = M chi M y: back-transform and Mulliken sums of the a items
-    kk::GemmArgs ba{};
-    ba.n = np; ba.k_half = np; ba.two_halves = 0; ba.ntiles = h->n_full; ba.nitems = 2;
-    ba.tiles = h->tiles_full; ba.beta = h->beta;
-    for (int s = 0; s < 2; ++s) {
-      kk::GemmItem& it = ba.item[s];
-      it.a0 = h->CT[s]; it.b0 = h->aY + (size_t)s * np2; it.g = h->G[s];
-      it.part = h->apart + (size_t)s * adj_nparts(h) * np;
-    }
-    if ((st = launch_gemm(h, kk::EPI_MULLIKEN, ba))) return st;
-    {
-      dim3 grid((N + kk::COMBINE_ATOMS - 1) / kk::COMBINE_ATOMS, 1);
-      kk::combine<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(h->axdiag, h->apart, adj_nparts(h), h->w[0], h->w[1],
-                                                              h->wsum, h->t,
-                                                nb, np, h->offsets, N, h->ag, nullptr);
-      LAUNCH_CHECK("combine");
-    }
-    kk::adj_dmu<<<2, 1024, 0, h->stream>>>(h->axdiag, nb, np, h->w[0], h->w[1], h->wsum, h->admu);
-    LAUNCH_CHECK("adj_dmu");
-    // K += Y0_b Xa + Y0_a Xb per spin
-    kk::GemmArgs ka{};
-    ka.n = np; ka.k_half = np; ka.two_halves = 1; ka.ntiles = h->n_full; ka.nitems = 2;
-    ka.tiles = h->tiles_full; ka.beta = h->beta;
-    for (int s = 0; s < 2; ++s) {
-      kk::GemmItem& it = ka.item[s];
-      it.a0 = h->aY + (size_t)(2 + s) * np2; it.b0 = h->aX + (size_t)s * np2;
-      it.a1 = h->aY + (size_t)s * np2; it.b1 = h->aX + (size_t)(2 + s) * np2;
-      it.out = h->aK + (size_t)s * np2;
-    }
-    if ((st = launch_gemm(h, kk::EPI_ACCUM, ka))) return st;
-    {
-      dim3 grid(nb, 2);
-      kk::adj_rows<<<grid, 256, 0, h->stream>>>(sp, nb, np, h->admu, h->mu, h->beta, tau);
+    if (want_H) {
+      kk::AdjSpins sp{};
+      sp.stride = 4 * np2;
+      sp.directions = nd;
+      for (int s = 0; s < 2; ++s) {
+        sp.s[s].Xa = h->aX + (size_t)s * np2;
+        sp.s[s].Xb = h->aX + (size_t)(2 + s) * np2;
+        sp.s[s].eps = h->eps[s]; sp.s[s].f = h->f[s]; sp.s[s].fc = h->fc[s]; sp.s[s].w = h->w[s];
+        sp.s[s].D = h->aD + (size_t)s * np2;
+        sp.s[s].gdiag = h->agdiag + (size_t)s * np;
+      }
+      if ((st = adjoint_commutators(h, plan, nd, k1 != r))) return st;
+      kk::adj_dmu<<<2 * nd, 1024, 0, h->stream>>>(h->axdiag, nb, np, h->w[0], h->w[1], h->wsum, h->admu);
+      LAUNCH_CHECK("adj_dmu");
+      kk::adj_rows<<<dim3(nb, 2), 256, 0, h->stream>>>(sp, nb, np, h->admu, h->mu, h->beta, tau);
       LAUNCH_CHECK("adj_rows");
+      if (npairs > 0) {
+        kk::adj_pairs<<<npairs, 256, 0, h->stream>>>(sp, h->apairs, h->an0, nb, np, h->mu, h->beta, tau, h->apk);
+        LAUNCH_CHECK("adj_pairs");
+      }
     }
-    if (npairs > 0) {
-      kk::adj_pairs<<<npairs, 256, 0, h->stream>>>(sp, h->apairs, h->an0, nb, np, h->mu, h->beta, tau, h->apk);
-      LAUNCH_CHECK("adj_pairs");
-    }
-    kk::adj_apply<<<wave_blocks, 256, 0, h->stream>>>(h->gamma, N, h->W, h->ag, h->ay, vk,
-                                                       h->aVbar + (size_t)k * n2, gamma_bar);
-    LAUNCH_CHECK("adj_apply");
-    kk::adj_wbar<<<1, 256, 0, h->stream>>>(h->ag, vk, N, W_bar);
-    LAUNCH_CHECK("adj_wbar");
+    k1 = k0;
   }
+  kk::adj_params<<<N + 1, 256, 0, h->stream>>>(h->ag, h->V, N, r, gamma_bar, W_bar);
+  LAUNCH_CHECK("adj_params");
   // dL/d delta
   if (r > 0) {
     kk::adj_finish<<<1, 1024, 0, h->stream>>>(h->V, h->aVbar, h->ftilde, n2, h->abbar, K0 ? h->alam : delta_bar,
@@ -2217,13 +2360,11 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
   kk::sum_two<<<1, 1024, 0, h->stream>>>(h->agdiag, h->agdiag + np, np, h->agtot);
   LAUNCH_CHECK("sum_two");
   double* Ep[2] = {h->aX, h->aX + np2};
-  for (int s = 0; s < 2; ++s) {
-    dim3 grid(np / 32, np / 32);
-    kk::adj_final<<<grid, 256, 0, h->stream>>>(h->aK + (size_t)s * np2, h->aD + (size_t)s * np2, h->eps[s],
-                                                h->w[s], h->agdiag + (size_t)s * np, h->agtot, h->wsum, nb, np, tau,
-                                                Ep[s]);
-    LAUNCH_CHECK("adj_final");
-  }
+  kk::AdjFinal fin{};
+  fin.K = h->aK; fin.D = h->aD; fin.Ep = h->aX;
+  for (int s = 0; s < 2; ++s) { fin.eps[s] = h->eps[s]; fin.w[s] = h->w[s]; fin.gdiag[s] = h->agdiag + (size_t)s * np; }
+  kk::adj_final<<<dim3(np / 32, np / 32, 2), 256, 0, h->stream>>>(fin, h->adj_chunks, h->agtot, h->wsum, nb, np, tau);
+  LAUNCH_CHECK("adj_final");
   if (npairs > 0) {
     kk::adj_pair_final<<<(npairs + 255) / 256, 256, 0, h->stream>>>(h->apairs, h->an0, npairs, h->apk, h->aD,
                                                                      h->aD + np2, h->eps[0], h->eps[1], h->mu,
@@ -2231,7 +2372,7 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
     LAUNCH_CHECK("adj_pair_final");
   }
   kk::GemmArgs a{};
-  a.n = np; a.k_half = np; a.two_halves = 0; a.ntiles = h->n_store; a.tiles = h->tiles_store; a.nitems = 2;
+  a.n = np; a.k_half = h->kc; a.two_halves = 0; a.ntiles = h->n_store; a.tiles = h->tiles_store; a.nitems = 2;
   for (int s = 0; s < 2; ++s) {  // U1 = E'_bar C^T
     a.item[s] = kk::GemmItem{};
     a.item[s].a0 = Ep[s]; a.item[s].b0 = h->CT[s]; a.item[s].out = h->aY + (size_t)s * np2;
@@ -2242,12 +2383,9 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
     a.item[s].a0 = h->CT[s]; a.item[s].b0 = h->aY + (size_t)s * np2; a.item[s].out = h->aY + (size_t)(2 + s) * np2;
   }
   if ((st = launch_gemm(h, kk::EPI_STORE, a, h->store_cls))) return st;
-  double* Hb[2] = {H_bar_up, H_bar_dn};
-  for (int s = 0; s < 2; ++s) {
-    const int blocks = (int)std::min<size_t>(((size_t)nb * nb + 255) / 256, 65536);
-    kk::unpad_copy<<<blocks, 256, 0, h->stream>>>(h->aY + (size_t)(2 + s) * np2, np, Hb[s], nb);
-    LAUNCH_CHECK("unpad_copy");
-  }
+  const int blocks = (int)std::min<size_t>(((size_t)nb * nb + 255) / 256, 32768);
+  kk::unpad_copy<<<dim3(blocks, 2), 256, 0, h->stream>>>(h->aY + 2 * np2, np, H_bar_up, H_bar_dn, nb);
+  LAUNCH_CHECK("unpad_copy");
   if (info) {
     HIP_OR_FAIL(hipStreamSynchronize(h->stream));
     info->rank_used = hs.rank;

@@ -240,7 +240,8 @@ void b_gemm(const BatchItemF64* __restrict__ items, const TileQueues q) {
       rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, Cfg::BK, 0);
     else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
       continue;
-    f64_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, false, make_int2(tl.y, tl.z), it.beta);
+    const HalfRows src{it.g, it.n, rows.x, rows.y - rows.x, false};
+    f64_tile<EPI, Cfg>(it.g, src, it.n, make_int2(tl.y, tl.z), it.beta);
   }
 }
 

@@ -422,7 +422,8 @@ __device__ __forceinline__ int2 upper_pair(int pair, int nblk) {
 // elsewhere, written over A_0 (block (I, J) by the thread that read it, block (J, I)
 // through LDS after the whole pair was read). B x B blocks of T = B * B / 4 threads: thread
 // (r, q) takes columns 4q..4q+3 of row r of both blocks (16-byte loads and stores).
-template <int B, int T, int NCH, bool WINDOWED>
+// XY (the reverse pass): A_j at it.a0 + j cstride, X written to it.xout as well, which may be A_0.
+template <int B, int T, int NCH, bool WINDOWED, bool XY = false>
 __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs args, size_t cstride) {
   static_assert(T * 4 == B * B, "4 elements per thread");
   const int stopped = args.stop != nullptr ? *args.stop : 0;  // tested once the loads are issued
@@ -430,9 +431,10 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
   const int n = args.n;
   const int2 ij = upper_pair(blockIdx.x, n / B);
   const int I = ij.x, J = ij.y;
-  __shared__ double At[B][B + 1];
+  __shared__ double At[B][B + 1], Xt[XY ? B : 1][B + 1];
   const int r = threadIdx.x / (B / 4), c4 = (threadIdx.x % (B / 4)) * 4;
   double* const Y = it.out;
+  const double* const A = XY ? it.a0 : it.out;
   const int m = I * B + r, cb = J * B + c4;
   const size_t oo = (size_t)m * n + cb, om = (size_t)(J * B + r) * n + I * B + c4;
   if (WINDOWED && !window_active(args.win.act[blockIdx.y & 1], args.win.nblk, I * B / WIN, J * B / WIN)) {
@@ -448,8 +450,8 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
   for (int j = 0; j < NCH; ++j)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      own[j][h] = reinterpret_cast<const d2*>(Y + oo + j * cstride)[h];
-      mir[j][h] = reinterpret_cast<const d2*>(Y + om + j * cstride)[h];
+      own[j][h] = reinterpret_cast<const d2*>(A + oo + j * cstride)[h];
+      mir[j][h] = reinterpret_cast<const d2*>(A + om + j * cstride)[h];
     }
   const double em = it.eps[m], fm = it.f[m], fcm = it.fc[m], wm = it.w[m];
   d2 en[2], fn[2], fcn[2];
@@ -468,7 +470,7 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
     At[r][c4 + e] = a;
   }
   __syncthreads();
-  double yv[4];
+  double yv[4], xv[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int c = c4 + e;
@@ -485,17 +487,29 @@ __global__ __launch_bounds__(T) void fermi_symmetrize_f64_chunks(const GemmArgs 
                                    args.beta) * x;
     }
     yv[e] = y;
+    xv[e] = x;
   }
   // only this thread read these elements of block (I, J), all chunks of them
   reinterpret_cast<d2*>(Y + oo)[0] = d2{yv[0], yv[1]};
   reinterpret_cast<d2*>(Y + oo)[1] = d2{yv[2], yv[3]};
+  if constexpr (XY) {
+    reinterpret_cast<d2*>(it.xout + oo)[0] = d2{xv[0], xv[1]};
+    reinterpret_cast<d2*>(it.xout + oo)[1] = d2{xv[2], xv[3]};
+  }
   if (I == J) return;  // a diagonal block is symmetric by construction
   __syncthreads();     // every read of At is done
 #pragma unroll
-  for (int e = 0; e < 4; ++e) At[c4 + e][r] = yv[e];
+  for (int e = 0; e < 4; ++e) {
+    At[c4 + e][r] = yv[e];
+    if constexpr (XY) Xt[c4 + e][r] = xv[e];
+  }
   __syncthreads();
   reinterpret_cast<d2*>(Y + om)[0] = d2{At[r][c4], At[r][c4 + 1]};
   reinterpret_cast<d2*>(Y + om)[1] = d2{At[r][c4 + 2], At[r][c4 + 3]};
+  if constexpr (XY) {
+    reinterpret_cast<d2*>(it.xout + om)[0] = d2{Xt[r][c4], Xt[r][c4 + 1]};
+    reinterpret_cast<d2*>(it.xout + om)[1] = d2{Xt[r][c4 + 2], Xt[r][c4 + 3]};
+  }
 }
 
 // Split forms: the FP32 partial products at it.x32 + j cstride, X scaled by 1 / the

@@ -23,8 +23,6 @@
 //               elements below it are skipped.
 //   EPI_MULLIKEN  Sec. III.A Mulliken rows: part[p][m] = sum over the wave's
 //               columns n of acc[m][n] * G[m][n]; the caller sums the parts.
-//   EPI_FERMI_XY  EPI_FERMI that also writes X itself (both triangles) to xout,
-//               for the reverse pass, which needs X and Y of each direction.
 //   EPI_ACCUM   out[m][n] += acc                                (adjoint sums)
 //   EPI_XSTORE  out[m][n] = acc with the row scale applied like EPI_FERMI: the
 //               product A = C^T U~ G over full tiles (one K half), which
@@ -41,7 +39,7 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 constexpr int PAD = 128;    // every padded dimension is a multiple of this
 constexpr int MAX_GEMM_BATCH = 16;
 
-enum { EPI_STORE = 0, EPI_FERMI = 1, EPI_MULLIKEN = 2, EPI_FERMI_XY = 3, EPI_ACCUM = 4, EPI_XSTORE = 5 };
+enum { EPI_STORE = 0, EPI_FERMI = 1, EPI_MULLIKEN = 2, EPI_ACCUM = 4, EPI_XSTORE = 5 };
 
 struct GemmItem {
   const double* a0;   // first K half: A operand, [K][n] row-major
@@ -57,7 +55,7 @@ struct GemmItem {
   const double* w;      // beta f (1 - f)
   double* xdiag;        // EPI_FERMI: diag X
   double* part;         // EPI_MULLIKEN: [parts][n]
-  double* xout;         // EPI_FERMI_XY: X
+  double* xout;         // symmetrizing pass of the reverse pass: X (a0 then holds A, out receives Y)
 };
 
 // Where the divided differences F of a prepared spectrum are negligible (built by the spectrum
@@ -176,11 +174,54 @@ struct TileCfg {
   static constexpr int LDS_BYTES = 2 * BK * (BM + BN) * 8;
 };
 
-// One output tile: both operands n x n (row stride n), contracted over the k_half rows from k_lo of
-// each half. Ends with a barrier, so a workgroup may run several tiles in sequence.
-template <int EPI, class Cfg>
-__device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const int k_lo, const int k_half,
-                                         const bool two_halves, const int2 tile, const double beta_arg) {
+// Where a tile's contraction rows come from: rows(k0) sets A and B to row k0 of the contraction
+// (k0 a multiple of the K stage), scale(k0) gives the row scales from there.
+
+// The k_half rows from k_lo of the item's first operands, then (two_halves) of its second.
+struct HalfRows {
+  const GemmItem& it;
+  int n, k_lo, k_half;
+  bool two_halves;
+  __device__ __forceinline__ int stages(int bk) const { return (two_halves ? 2 * k_half : k_half) / bk; }
+  __device__ __forceinline__ void rows(int k0, const double*& A, const double*& B) const {
+    A = it.a0;
+    B = it.b0;
+    if (two_halves && k0 >= k_half) {
+      A = it.a1; B = it.b1; k0 -= k_half;
+    }
+    A += (size_t)(k_lo + k0) * n;
+    B += (size_t)(k_lo + k0) * n;
+  }
+  __device__ __forceinline__ const double* scale(int k0) const {
+    if (two_halves && k0 >= k_half) k0 -= k_half;
+    return it.scale + k_lo + k0;
+  }
+};
+
+// The reverse pass's sum over directions k of Y_b Xa + Y_a Xb as one contraction: 2 directions
+// operand pairs of `per` K stages (bk rows) each from row k_lo, of which this tile takes the stages
+// from first on. X and Y hold the items (a up, a dn, b up, b dn) of every direction, np2 apart.
+struct PairRows {
+  const double *X, *Y;  // of the tile's spin, direction 0
+  size_t np2;
+  int n, k_lo, per, bk, first, count;
+  unsigned long long magic;  // ceil(2^32 / per): stage / per for stages below 2^32 / per
+  __device__ __forceinline__ int stages(int) const { return count; }
+  __device__ __forceinline__ void rows(int k0, const double*& A, const double*& B) const {
+    const unsigned t = first + k0 / bk;
+    const unsigned q = (unsigned)((t * magic) >> 32), r = t - q * per;
+    const size_t dir = (size_t)(q >> 1) * 4 * np2, row = (size_t)(k_lo + r * bk) * n;
+    A = Y + dir + ((q & 1) ? 0 : 2) * np2 + row;
+    B = X + dir + ((q & 1) ? 2 : 0) * np2 + row;
+  }
+  __device__ __forceinline__ const double* scale(int) const { return nullptr; }
+};
+
+// One output tile: both operands n x n (row stride n), contracted over src's rows. Ends with a
+// barrier, so a workgroup may run several tiles in sequence.
+template <int EPI, class Cfg, class Rows>
+__device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, const int n, const int2 tile,
+                                         const double beta_arg) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
   constexpr int WTM = Cfg::WTM, WTN = Cfg::WTN;
   constexpr int AP = Cfg::A_PIECES, BP = Cfg::B_PIECES;
@@ -192,7 +233,7 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
   __shared__ double Bs[2][BK][BN];
 
   const int tid = threadIdx.x;
-  const int nk = (two_halves ? 2 * k_half : k_half) / BK;
+  const int nk = src.stages(BK);
   const int wave = tid >> 6, lane = tid & 63;
   const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
   const int lr = lane >> 4, lc = lane & 15;
@@ -211,7 +252,7 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
   // The forward transform's row scales go through a 3-slot LDS ring: the BK scales of
   // stage s are loaded by the first BK threads at the start of step s - 2, put in slot
   // s % 3 at its end, and multiplied in when stage s is written to LDS (end of step s - 1).
-  constexpr bool SCALED = EPI == EPI_FERMI || EPI == EPI_FERMI_XY || EPI == EPI_XSTORE;
+  constexpr bool SCALED = EPI == EPI_FERMI || EPI == EPI_XSTORE;
   __shared__ double Ss[SCALED ? 3 : 1][BK];
   d2 ra[AP], rb[BP];
   double sreg = 0.0;
@@ -232,14 +273,10 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
     boff[p] = (unsigned)(row * n + col) * 8u;
   }
   auto gload = [&](const int kt) __attribute__((always_inline)) {
-    int k0 = kt * BK;
-    const double* A = it.a0;
-    const double* B = it.b0;
-    if (two_halves && k0 >= k_half) {
-      A = it.a1; B = it.b1; k0 -= k_half;
-    }
-    const char* Ab = reinterpret_cast<const char*>(A + (size_t)(k_lo + k0) * n + m0);
-    const char* Bb = reinterpret_cast<const char*>(B + (size_t)(k_lo + k0) * n + n0);
+    const double *A, *B;
+    src.rows(kt * BK, A, B);
+    const char* Ab = reinterpret_cast<const char*>(A + m0);
+    const char* Bb = reinterpret_cast<const char*>(B + n0);
 #pragma unroll
     for (int p = 0; p < AP; ++p) ra[p] = *reinterpret_cast<const d2*>(Ab + aoff[p]);
 #pragma unroll
@@ -247,9 +284,7 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
   };
   auto sload = [&](const int kt) __attribute__((always_inline)) {
     if constexpr (SCALED) {
-      int k0 = kt * BK;
-      if (two_halves && k0 >= k_half) k0 -= k_half;
-      if (tid < BK) sreg = it.scale[k_lo + k0 + tid];
+      if (tid < BK) sreg = src.scale(kt * BK)[tid];
     }
   };
   auto sstore = [&](const int kt) __attribute__((always_inline)) {
@@ -317,7 +352,7 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
           if constexpr (EPI == EPI_ACCUM) *o += acc[i][j][r];
           else *o = acc[i][j][r];
         }
-  } else if constexpr (EPI == EPI_FERMI || EPI == EPI_FERMI_XY) {
+  } else if constexpr (EPI == EPI_FERMI) {
     const double beta = beta_arg;
     // Column spectra are re-read per row (cached) rather than held, which keeps the
     // epilogue inside the main loop's register budget.
@@ -333,10 +368,6 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const int n, const 
           if (m > c) continue;
           const double en = it.eps[c], fn = it.f[c], fcn = it.fc[c];
           const double x = 0.5 * acc[i][j][r];
-          if constexpr (EPI == EPI_FERMI_XY) {
-            it.xout[(size_t)m * n + c] = x;
-            it.xout[(size_t)c * n + m] = x;
-          }
           if (m == c) {
             it.xdiag[m] = x;
             it.out[(size_t)m * n + m] = -it.w[m] * x;
@@ -397,7 +428,39 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const 
       rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k_half, Cfg::BK, 0);
     }
   }
-  f64_tile<EPI, Cfg>(args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0, tile, args.beta);
+  const HalfRows src{args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0};
+  f64_tile<EPI, Cfg>(args.item[z], src, args.n, tile, args.beta);
+}
+
+// The commutator sums of the reverse pass: out + (2 c + s) np2 (+)= chunk c of spin s's
+// contraction (PairRows), over all tiles. With `range` (Window) the rows where no Y of the tile's
+// row block lies are left out. One launch for all directions in place of one each: 2 x 81 tiles of
+// 128 atoms fill 256 CUs only when the contraction is cut, and the sums stay in registers between
+// directions (128 atoms, 8 directions: 8 x 314 us -> 1514 us, 65 TFLOP/s).
+struct PairArgs {
+  const double *X, *Y;  // [directions][4][n][n]
+  double* out;          // [chunks][2][n][n]
+  const int2* tiles;
+  const int2* range[2];
+  int n, k, directions, ntiles, chunks;
+};
+template <class Cfg, bool ACCUMULATE>
+__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_pairs(const PairArgs a) {
+  const int logical = xcd_remap(blockIdx.x, a.ntiles * 2 * a.chunks);
+  const int z = logical / a.ntiles, s = z & 1, c = z >> 1;
+  const int2 tile = a.tiles[logical - z * a.ntiles];
+  int2 rows = make_int2(0, a.k);
+  if (a.range[0] != nullptr)
+    rows = window_rows(a.range[s], tile.x * (Cfg::BM / WIN), Cfg::BM / WIN, a.k, Cfg::BK, Cfg::BK);
+  const size_t np2 = (size_t)a.n * a.n;
+  const int per = (rows.y - rows.x) / Cfg::BK;
+  const long total = (long)2 * a.directions * per;
+  const int first = (int)(total * c / a.chunks), last = (int)(total * (c + 1) / a.chunks);
+  const PairRows src{a.X + s * np2, a.Y + s * np2, np2, a.n, rows.x, per, Cfg::BK, first, last - first,
+                     ((1ull << 32) + per - 1) / per};
+  GemmItem it{};
+  it.out = a.out + (2 * (size_t)c + s) * np2;
+  f64_tile<ACCUMULATE ? EPI_ACCUM : EPI_STORE, Cfg>(it, src, a.n, tile, 0.0);
 }
 
 // Second pass of the FP64 forward transform when it runs as a full-tile product

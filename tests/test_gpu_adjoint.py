@@ -95,6 +95,34 @@ def test_adjoint_ragged_cluster_matches_oracle_gradient():
     compare(gpu_gradients(sysd, 6), gradients(sysd, 6))
 
 
+@pytest.mark.parametrize("atoms,m", [(2, 3), (29, 12), (57, 3), (85, 2)])
+def test_adjoint_tile_classes_and_launch_groups(atoms, m):
+    """Sizes and ranks where the reverse pass's products change their tiles, K-split and number of
+    launches: two atoms (one tile), 29 atoms with more directions than a launch takes, 57 and 85 atoms
+    (64 x 64 and 128 x 128 tiles cut along K). dL/dU against the size of its terms, which cancel."""
+    sysd = make_system(n_atoms=atoms, seed=10_000 + atoms)
+    compare(gpu_gradients(sysd, m), gradients(sysd, m), U_scale=U_gradient_scale(sysd, m))
+
+
+def test_adjoint_rank_grows_on_one_handle():
+    """A later call with a larger rank (a larger group of directions held) on the same handle."""
+    sysd = make_system(2, seed=16)
+    ep = expansion_point(sysd)
+    h = handle_from_expansion(sysd, ep)
+    fresh = handle_from_expansion(sysd, ep)
+    try:
+        d = t(sysd["delta"])
+        for m in (2, 9, 4):
+            x, _ = h.krylov_kernel_apply(d, m)
+            a = h.krylov_kernel_adjoint(d, m, 2 * x, reuse_forward=True)
+            b = fresh.krylov_kernel_adjoint(d, m, 2 * x)
+            for k in ("delta", "gamma", "H_up", "H_dn"):
+                assert rel(a[k].cpu().numpy(), b[k].cpu().numpy()) < 1e-14, (m, k)
+    finally:
+        h.close()
+        fresh.close()
+
+
 def test_adjoint_reuse_equals_recompute():
     """reuse_forward=1 after krylov_kernel_apply gives the same gradients as a fresh expansion."""
     sysd = make_system(2, seed=16)

@@ -74,6 +74,28 @@ def test_ascending_and_shuffled_levels_agree(atoms, precision):
     assert max(err) < TOL[precision], err
 
 
+@pytest.mark.parametrize("atoms", [140, 170, 265])
+def test_gradients_agree(atoms):
+    """The reverse pass, whose back-transforms and commutator sums go by the same windows. The
+    gradient with respect to H is a matrix in the orbital basis, the same for both orders; its
+    commutators cancel, which costs digits (bound 1e-9)."""
+    y = make(atoms, 300 + atoms)
+    delta = t(0.01 * np.random.default_rng(atoms).standard_normal(2 * atoms))
+    got = []
+    for shuffled in (False, True):
+        h = krylov.Handle()
+        try:
+            h.prepare(*arguments(y, shuffled), krylov.KK_FP64)
+            x, _ = h.krylov_kernel_apply(delta, 3)
+            g = h.krylov_kernel_adjoint(delta, 3, 2.0 * x, reuse_forward=True)
+            got.append([g[k].cpu().numpy() for k in ("delta", "gamma", "W", "H_up", "H_dn")])
+        finally:
+            h.close()
+    err = [rel(a, b) for a, b in zip(*got)]
+    print(atoms, err, flush=True)
+    assert max(err) < 1e-9, err
+
+
 @pytest.mark.parametrize("gap", [8.0, 40.0])
 def test_insulator(gap):
     """A gap of 32 and 160 kT at N_e: the smallest kept factor is 1 / (width of the spectrum), far
