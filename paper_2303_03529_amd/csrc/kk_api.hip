@@ -159,6 +159,8 @@ struct kk_handle_s {
   // of partial results per item, sk_grid workgroups per product launch
   bool sk = false;
   int sk_grid = 0;
+  // Krylov directions on the kernels of kk_tiny.hpp (their partial rows: kc / TINY_TILE per spin)
+  bool tiny_step = false;
   bool ktiny = false;  // FP64 K-split on 64 x 64 TinyF64 tiles (small_f64 and tiny_f64 then set)
   double W = 0, kT = 0, beta = 0, n_e = 0;
   std::vector<void*> owned;  // every device allocation of the prepared state
@@ -443,6 +445,12 @@ int choose_ksplit(int np, int kc, int tiles, int cus, bool one_per_cu, int* chun
   *chunk_rows = best_ck;
   return best;
 }
+
+// Largest contraction length of the tiny step (kk_tiny.hpp).
+#ifndef KK_TINY_STEP_MAX_KC
+#define KK_TINY_STEP_MAX_KC 576
+#endif
+constexpr int TINY_STEP_MAX_KC = KK_TINY_STEP_MAX_KC;
 
 // How the FP64 products of one system's two spins run: their tile class (launch_gemm's cls) and
 // the chunks of their contraction, ck rows each.
@@ -734,15 +742,17 @@ int max_chunk(kk_handle h) {
 
 // The last step of a response: q1 (and with K0 = -I the preconditioned derivative ft) from
 // the Mulliken partial rows and diag X (combine; combine_small for the fused small step).
-kk_status launch_combine(kk_handle h, int batch, double* q1, const int* stop, const double* vsub, double* ft) {
+kk_status launch_combine(kk_handle h, int batch, double* q1, const int* stop, const double* vsub, double* ft,
+                         int nparts = 0) {
   const int N = h->natoms;
+  if (nparts == 0) nparts = h->nparts;
   dim3 grid((N + kk::COMBINE_ATOMS - 1) / kk::COMBINE_ATOMS, batch);
   if (2 * N <= kk::FUSED_MAX_N2)
-    kk::combine_small<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(h->xdiag, h->part, h->nparts, h->w[0], h->w[1],
+    kk::combine_small<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(h->xdiag, h->part, nparts, h->w[0], h->w[1],
                                                                   h->wsum, h->t, h->nb, h->np, h->offsets, N, q1,
                                                                   stop, vsub, ft);
   else
-    kk::combine<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(h->xdiag, h->part, h->nparts, h->w[0], h->w[1],
+    kk::combine<<<grid, kk::COMBINE_THREADS, 0, h->stream>>>(h->xdiag, h->part, nparts, h->w[0], h->w[1],
                                                              h->wsum, h->t, h->nb, h->np, h->offsets, N, q1, stop,
                                                              vsub, ft);
   LAUNCH_CHECK("combine");
@@ -1345,6 +1355,8 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
                      : h->small_f64 ? (np / SmallF64::BN) * SmallF64::WAVES_N
                                     : (np / kk::BackCfg::BN) * kk::BackCfg::WAVES_N;
     h->nparts = h->kchb * h->nbase;
+    h->tiny_step = !mixed && !split_large && h->kc <= TINY_STEP_MAX_KC && n_atoms <= kk::COMBINE_BLOCK_ATOMS &&
+                   h->nparts >= h->kc / kk::TINY_TILE;
     if ((st = allocate_prepared(h))) return st;
   }
   h->W = W; h->kT = kT; h->beta = 1.0 / kT; h->n_e = n_electrons;
@@ -1528,8 +1540,69 @@ kk_status enqueue_start(kk_handle h, const double* delta, const double* K0) {
   return KK_OK;
 }
 
-// Direction k: v_k and f~_k.
-kk_status enqueue_direction(kk_handle h, int k, const double* K0) {
+// What the next launch needs to form f~_k from the partial rows of direction k (tiny handles).
+kk::CombineArgs combine_args(kk_handle h, int k) {
+  const size_t n2 = 2 * (size_t)h->natoms;
+  kk::CombineArgs c{};
+  c.xdiag = h->xdiag; c.part = h->part; c.w_up = h->w[0]; c.w_dn = h->w[1]; c.wsum = h->wsum; c.t = h->t;
+  c.v = h->V + k * n2; c.offsets = h->offsets; c.q1 = h->q1; c.ft = h->Ft + k * n2;
+  c.nparts = h->kc / kk::TINY_TILE; c.nb = h->nb; c.np = h->np; c.natoms = h->natoms;
+  return c;
+}
+
+// orth_potentials of direction k on the code for the system's size.
+template <int NMAX, bool COMBINE>
+void run_orth_potentials(kk_handle h, int k, const double* src, const kk::CombineArgs& c) {
+  const bool split = h->precision != KK_FP64;
+  kk::orth_potentials<NMAX, COMBINE>
+      <<<(h->natoms + kk::FUSED_ATOMS - 1) / kk::FUSED_ATOMS, COMBINE ? kk::COMBINE_BLOCK : kk::FUSED_THREADS, 0,
+         h->stream>>>(src, h->V, 2 * h->natoms, h->kst, k, h->gamma, h->natoms, h->W, h->offsets, h->np, h->u,
+                      split ? h->cvec : nullptr, split ? h->pmax : nullptr, c);
+}
+kk_status launch_orth_potentials(kk_handle h, int k, const double* src, bool combine) {
+  const int N = h->natoms;
+  if (combine)
+    run_orth_potentials<kk::COMBINE_BLOCK_ATOMS, true>(h, k, src, combine_args(h, k - 1));
+  else if (N <= 64)
+    run_orth_potentials<64, false>(h, k, src, kk::CombineArgs{});
+  else if (N <= 128)
+    run_orth_potentials<128, false>(h, k, src, kk::CombineArgs{});
+  else if (N <= 256)
+    run_orth_potentials<256, false>(h, k, src, kk::CombineArgs{});
+  else
+    run_orth_potentials<512, false>(h, k, src, kk::CombineArgs{});
+  LAUNCH_CHECK("orth_potentials");
+  return KK_OK;
+}
+static_assert(2 * 512 == kk::FUSED_MAX_N2, "the largest unrolling");
+
+// Both transforms of one direction of a tiny handle, whose potentials are in h->u.
+kk_status transforms_tiny(kk_handle h, const int* stop) {
+  const size_t np = h->np, np2 = np * np;
+  kk::TinyArgs a{};
+  a.n = h->np; a.kc = h->kc; a.tiles = h->kc / kk::TINY_TILE; a.beta = h->beta; a.stop = stop;
+  for (int s = 0; s < 2; ++s) {
+    kk::TinyArgs::Item& it = a.item[s];
+    it.C = h->C[s]; it.G = h->G[s]; it.CT = h->CT[s]; it.u = h->u + s * np;
+    it.eps = h->eps[s]; it.f = h->f[s]; it.fc = h->fc[s]; it.w = h->w[s];
+    it.Y = h->Y + s * np2; it.xdiag = h->xdiag + s * np; it.part = h->part + (size_t)s * a.tiles * np;
+  }
+  {
+    ProfileScope ps(h, 0);
+    kk::tiny_forward<<<dim3(a.tiles * (a.tiles + 1) / 2, 2), kk::TINY_THREADS, 0, h->stream>>>(a);
+    LAUNCH_CHECK("tiny_forward");
+  }
+  ProfileScope ps(h, 1);
+  kk::tiny_back<<<dim3(a.tiles * a.tiles, 2), kk::TINY_THREADS, 0, h->stream>>>(a);
+  LAUNCH_CHECK("tiny_back");
+  return KK_OK;
+}
+
+// Whether the direction leaves f~_k in its partial rows for the next launch (combine_args).
+bool leaves_combine(kk_handle h, const double* K0) { return h->tiny_step && K0 == nullptr; }
+
+// Direction k: v_k and f~_k. in_rows: f~_{k-1} was left in its partial rows.
+kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows) {
   kk_status st;
   const int n2 = 2 * h->natoms;
   const int* stop = &h->kst->stop;
@@ -1541,13 +1614,14 @@ kk_status enqueue_direction(kk_handle h, int k, const double* K0) {
   const double* vk = h->V + (size_t)k * n2;
   double* ftk = h->Ft + (size_t)k * n2;
   if (fused) {
-    const bool split = h->precision != KK_FP64;
-    kk::orth_potentials<<<(h->natoms + kk::FUSED_ATOMS - 1) / kk::FUSED_ATOMS, kk::FUSED_THREADS, 0,
-                          h->stream>>>(src, h->V, n2, h->kst, k, h->gamma, h->natoms, h->W, h->offsets, h->np,
-                                       h->u, split ? h->cvec : nullptr, split ? h->pmax : nullptr);
-    LAUNCH_CHECK("orth_potentials");
-    if ((st = response_any(h, 1, vk, h->q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk)))
+    if ((st = launch_orth_potentials(h, k, src, in_rows))) return st;
+    if (h->tiny_step) {
+      if ((st = transforms_tiny(h, stop))) return st;
+      if (K0 == nullptr) return KK_OK;  // the combine waits for the next launch
+      if ((st = launch_combine(h, 1, h->q1, stop, nullptr, nullptr, h->kc / kk::TINY_TILE))) return st;
+    } else if ((st = response_any(h, 1, vk, h->q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk))) {
       return st;
+    }
   } else {
     // one block just large enough for 8 entries per thread
     const int orth_threads = std::max(64, std::min(1024, ((n2 + 7) / 8 + 63) / 64 * 64));
@@ -1562,10 +1636,13 @@ kk_status enqueue_direction(kk_handle h, int k, const double* K0) {
   return KK_OK;
 }
 
-// The solve on the directions so far; a residual <= tol (> 0) ends the expansion.
-kk_status enqueue_solve(kk_handle h, double* Kdelta, double tol, kk::SolveReport* report = nullptr,
-                        unsigned long long seq = 0) {
-  kk::krylov_solve<<<1, 1024, 0, h->stream>>>(h->V, h->Ft, h->ftilde, 2 * h->natoms, h->kst, Kdelta, tol, report, seq);
+// The solve on the directions 0..k; a residual <= tol (> 0) ends the expansion. in_rows: f~_k is
+// still in its partial rows.
+kk_status enqueue_solve(kk_handle h, int k, bool in_rows, double* Kdelta, double tol,
+                        kk::SolveReport* report = nullptr, unsigned long long seq = 0) {
+  kk::krylov_solve<<<1, kk::COMBINE_BLOCK, 0, h->stream>>>(h->V, h->Ft, h->ftilde, 2 * h->natoms, h->kst, Kdelta, tol,
+                                                           report, seq,
+                                                           in_rows ? combine_args(h, k) : kk::CombineArgs{});
   LAUNCH_CHECK("krylov_solve");
   return KK_OK;
 }
@@ -1573,11 +1650,13 @@ kk_status enqueue_solve(kk_handle h, double* Kdelta, double tol, kk::SolveReport
 kk_status enqueue_krylov(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta) {
   kk_status st;
   if ((st = enqueue_start(h, delta, K0))) return st;
+  const bool rows = leaves_combine(h, K0);
   for (int k = 0; k < m; ++k) {
-    if ((st = enqueue_direction(h, k, K0))) return st;
-    if (tol > 0.0 && k + 1 < m && (st = enqueue_solve(h, Kdelta, tol))) return st;
+    // (a solve between directions has formed f~_{k-1} already)
+    if ((st = enqueue_direction(h, k, K0, rows && k > 0 && tol == 0.0))) return st;
+    if (tol > 0.0 && k + 1 < m && (st = enqueue_solve(h, k, rows, Kdelta, tol))) return st;
   }
-  return enqueue_solve(h, Kdelta, 0.0);
+  return enqueue_solve(h, m - 1, rows, Kdelta, 0.0);
 }
 
 // An adaptive update whose caller waits for it anyway (info given): directions are enqueued only
@@ -1599,9 +1678,9 @@ kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double t
   kk_status st;
   if ((st = enqueue_start(h, delta, K0))) return st;
   for (int k = 0; k < m; ++k) {
-    if ((st = enqueue_direction(h, k, K0))) return st;
+    if ((st = enqueue_direction(h, k, K0, false))) return st;
     const unsigned long long seq = ++h->report_seq;
-    if ((st = enqueue_solve(h, Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
+    if ((st = enqueue_solve(h, k, leaves_combine(h, K0), Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
     if (k + 1 == m || k + 1 < h->rank_hint) continue;
     // the word of this solve, or the stream's end (an error included, which the sync reports)
     for (int spin = 1;; ++spin) {

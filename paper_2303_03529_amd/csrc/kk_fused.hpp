@@ -17,6 +17,7 @@
 
 #include "kk_kernels.hpp"
 #include "kk_gemm_mixed.hpp"
+#include "kk_tiny.hpp"
 
 namespace kk {
 
@@ -130,46 +131,64 @@ __device__ __forceinline__ void orth_wave0(double* sv, const double* vl, int sta
 // on every orbital of the block's atoms (Sec. III.A). With cvec given (split forms) the
 // potentials are centred by c = cvec . v (the response to a common shift is zero) and
 // pmax[2 blockIdx.x + s] receives the block's largest |u^s - c|.
-// The block first issues all its global loads (the stop flag, src, the centring vector and
+// The block first issues its global loads (the stop flag, src, the centring vector and
 // the first rows of V, up to FUSED_LDS_ROWS doubles, for LDS; its atoms' rows of gamma and
 // orbital ranges into registers) and tests the flag afterwards. Wave 0 then
 // runs the 2 rank projections out of LDS (rows past the staged ones from global memory),
 // and every wave forms its atoms' potentials from the new direction in LDS.
-// Grid: ceil(N / FUSED_ATOMS) blocks of FUSED_THREADS; 2N <= FUSED_MAX_N2.
+// COMBINE: src is still in the Mulliken partial rows of the previous direction; every block forms
+// it by combine_block (block 0 stores it), which spares the launch between.
+// NMAX: atoms the code is unrolled for (64, 128, 256 or 512), so that a small system does not
+// step through the loads and terms of a large one.
+// Grid: ceil(N / FUSED_ATOMS) blocks of FUSED_THREADS (COMBINE: COMBINE_BLOCK); N <= NMAX.
 constexpr int FUSED_LDS_ROWS = 8192;  // doubles of V staged in LDS (64 KB)
-__global__ void __launch_bounds__(FUSED_THREADS)
+template <int NMAX, bool COMBINE>
+__global__ void __launch_bounds__(COMBINE ? COMBINE_BLOCK : FUSED_THREADS)
     orth_potentials(const double* __restrict__ src, double* __restrict__ V, int n2, KrylovState* st, int rank,
                     const double* __restrict__ gamma, int natoms, double W, const int* __restrict__ offsets, int np,
-                    double* __restrict__ u, const double* __restrict__ cvec, double* __restrict__ pmax) {
-  __shared__ double sv[FUSED_MAX_N2];
+                    double* __restrict__ u, const double* __restrict__ cvec, double* __restrict__ pmax,
+                    const CombineArgs comb) {
+  constexpr int T = COMBINE ? COMBINE_BLOCK : FUSED_THREADS, N2MAX = 2 * NMAX;
+  static_assert(N2MAX <= FUSED_MAX_N2 && N2MAX % WAVE == 0, "atoms");
+  __shared__ double sv[N2MAX];
   __shared__ double vl[FUSED_LDS_ROWS];
-  __shared__ double mred[2][FUSED_THREADS / WAVE];
-  __shared__ double cvl[FUSED_MAX_N2];
+  __shared__ double mred[2][T / WAVE];
+  __shared__ double cvl[N2MAX];
   __shared__ double cshared;
   __shared__ int accepted;
   // the stop flag is read with the other loads and tested once they are issued (all of
   // them are in bounds either way), so that it costs no round trip of its own
   const int stopped = st->stop;
-  constexpr int NW = FUSED_THREADS / WAVE, APW = FUSED_ATOMS / NW, GPER = FUSED_MAX_N2 / 2 / WAVE;
+  constexpr int NW = T / WAVE, APW = (FUSED_ATOMS + NW - 1) / NW, GPER = (NMAX + WAVE - 1) / WAVE;
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
   const int a0 = blockIdx.x * FUSED_ATOMS, a1 = min(natoms, a0 + FUSED_ATOMS);
   const int staged = min(rank, FUSED_LDS_ROWS / n2);
-  // every global load of the block first, into registers (a load and its LDS store per
+  // global loads of the block first, into registers (a load and its LDS store per
   // loop step would wait for each load in turn)
-  constexpr int SPT = FUSED_MAX_N2 / FUSED_THREADS, VPT = FUSED_LDS_ROWS / FUSED_THREADS;
+  constexpr int SPT = (N2MAX + T - 1) / T, VPT = 8;  // rows of V: VPT loads at a time
   const int nv = staged * n2;
   double sr[SPT], vr[VPT], cr[SPT];
 #pragma unroll
   for (int k = 0; k < SPT; ++k) {
-    const int i = threadIdx.x + k * FUSED_THREADS;
-    sr[k] = i < n2 ? src[i] : 0.0;
+    const int i = threadIdx.x + k * T;
+    sr[k] = (!COMBINE && i < n2) ? src[i] : 0.0;
     cr[k] = (cvec != nullptr && i < n2) ? cvec[i] : 0.0;
   }
+  auto load_rows = [&](int base) __attribute__((always_inline)) {
 #pragma unroll
-  for (int k = 0; k < VPT; ++k) {
-    const int i = threadIdx.x + k * FUSED_THREADS;
-    vr[k] = i < nv ? V[i] : 0.0;
-  }
+    for (int k = 0; k < VPT; ++k) {
+      const int i = base + threadIdx.x + k * T;
+      vr[k] = i < nv ? V[i] : 0.0;
+    }
+  };
+  auto store_rows = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+      const int i = base + threadIdx.x + k * T;
+      if (i < nv) vl[i] = vr[k];
+    }
+  };
+  load_rows(0);
   double g[APW][GPER];
   int ob[APW], oe[APW];
 #pragma unroll
@@ -186,19 +205,20 @@ __global__ void __launch_bounds__(FUSED_THREADS)
   if (stopped) return;  // the same value in every thread: before the first barrier
 #pragma unroll
   for (int k = 0; k < SPT; ++k) {
-    const int i = threadIdx.x + k * FUSED_THREADS;
+    const int i = threadIdx.x + k * T;
     if (i < n2) {
-      sv[i] = sr[k];
+      if constexpr (!COMBINE) sv[i] = sr[k];
       cvl[i] = cr[k];
     }
   }
-#pragma unroll
-  for (int k = 0; k < VPT; ++k) {
-    const int i = threadIdx.x + k * FUSED_THREADS;
-    if (i < nv) vl[i] = vr[k];
+  store_rows(0);
+  for (int base = VPT * T; base < nv; base += VPT * T) {
+    load_rows(base);
+    store_rows(base);
   }
+  if constexpr (COMBINE) combine_block(comb, sv, blockIdx.x == 0);
   __syncthreads();
-  if (wave == 0) orth_wave0<FUSED_MAX_N2 / WAVE>(sv, vl, staged, V, n2, rank, st, cvl, &accepted, &cshared);
+  if (wave == 0) orth_wave0<N2MAX / WAVE>(sv, vl, staged, V, n2, rank, st, cvl, &accepted, &cshared);
   __syncthreads();
   if (!accepted) return;
   const double c = cvec != nullptr ? cshared : 0.0;
@@ -319,6 +339,40 @@ __global__ void split_operands_fused(const double* __restrict__ CT0, const doubl
     split_group8<BF16, NP>(v, w, scale, bg, uct_h + off, uct_l + off, re);
   }
 }
+
+// The solve of a single system. comb.natoms > 0: f~ of the last direction is still in its Mulliken
+// partial rows and is formed first (unless the expansion ended before that direction).
+__global__ void __launch_bounds__(COMBINE_BLOCK) krylov_solve(const double* __restrict__ V, const double* Ft,
+                                                              const double* __restrict__ ftilde, int n2,
+                                                              KrylovState* st, double* __restrict__ x, double stop_tol,
+                                                              SolveReport* report, unsigned long long seq,
+                                                              const CombineArgs comb) {
+  __shared__ double fl[2 * COMBINE_BLOCK_ATOMS];
+  if (comb.natoms > 0 && st->stop == 0) combine_block(comb, fl, true);  // ends with a barrier
+  solve_dev(V, Ft, ftilde, n2, st, x, stop_tol, report, seq);
+}
+
+struct SolveArgs {
+  static constexpr int COUNT = 10;
+  const double *V, *Ft, *ftilde;
+  int n2;
+  KrylovState* st;
+  double* out;
+  double tol;
+  SolveReport* report;
+  unsigned long long seq;
+  CombineArgs comb;
+  static SolveArgs from(void** kp) {
+    return {kernel_arg<const double*>(kp, 0), kernel_arg<const double*>(kp, 1), kernel_arg<const double*>(kp, 2),
+            kernel_arg<int>(kp, 3),           kernel_arg<KrylovState*>(kp, 4),  kernel_arg<double*>(kp, 5),
+            kernel_arg<double>(kp, 6),        kernel_arg<SolveReport*>(kp, 7),  kernel_arg<unsigned long long>(kp, 8),
+            kernel_arg<CombineArgs>(kp, 9)};
+  }
+  void pointers(void** o) {
+    o[0] = &V; o[1] = &Ft; o[2] = &ftilde; o[3] = &n2; o[4] = &st; o[5] = &out; o[6] = &tol;
+    o[7] = &report; o[8] = &seq; o[9] = &comb;
+  }
+};
 
 // The combine of the fused small-system step: the same results as combine (dmu from
 // w . diag X of both spins, per-atom sums of the Mulliken partial rows, dmu t_s, the (q, m)

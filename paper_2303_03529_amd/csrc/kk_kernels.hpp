@@ -692,7 +692,7 @@ __global__ void __launch_bounds__(1024) krylov_orthonormalize(const double* __re
 // projected residual ||F~ c - f~|| / ||f~|| formed explicitly. On a non-positive
 // pivot x = 0 and status = -5. With stop_tol > 0 a residual <= stop_tol ends the
 // expansion (used by the adaptive-rank call after each direction). One block.
-__device__ __forceinline__ void solve_dev(const double* __restrict__ V, const double* __restrict__ Ft,
+__device__ __forceinline__ void solve_dev(const double* __restrict__ V, const double* Ft,
                                           const double* __restrict__ ftilde, int n2, KrylovState* st,
                                           double* __restrict__ x, double stop_tol, SolveReport* report = nullptr,
                                           unsigned long long seq = 0) {
@@ -839,15 +839,7 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
   }
 }
 
-__global__ void __launch_bounds__(1024) krylov_solve(const double* __restrict__ V,
-                                                     const double* __restrict__ Ft,
-                                                     const double* __restrict__ ftilde, int n2,
-                                                     KrylovState* st, double* __restrict__ x,
-                                                     double stop_tol, SolveReport* report, unsigned long long seq) {
-  solve_dev(V, Ft, ftilde, n2, st, x, stop_tol, report, seq);
-}
-
-// Host-side copies of the argument lists of precondition and krylov_solve (declaration
+// Host-side copies of the argument lists of precondition and krylov_solve (SolveArgs; declaration
 // order), read from and written back to a kernel node of a captured graph so that a replay
 // can take other input and output pointers.
 template <class T>
@@ -871,26 +863,6 @@ struct PreconditionArgs {
   }
   void pointers(void** out) {
     out[0] = &K0; out[1] = &x; out[2] = &sub; out[3] = &y; out[4] = &n2; out[5] = &stop; out[6] = &reset;
-  }
-};
-
-struct SolveArgs {
-  static constexpr int COUNT = 9;
-  const double *V, *Ft, *ftilde;
-  int n2;
-  KrylovState* st;
-  double* out;
-  double tol;
-  SolveReport* report;
-  unsigned long long seq;
-  static SolveArgs from(void** kp) {
-    return {kernel_arg<const double*>(kp, 0), kernel_arg<const double*>(kp, 1), kernel_arg<const double*>(kp, 2),
-            kernel_arg<int>(kp, 3),           kernel_arg<KrylovState*>(kp, 4),  kernel_arg<double*>(kp, 5),
-            kernel_arg<double>(kp, 6),        kernel_arg<SolveReport*>(kp, 7),  kernel_arg<unsigned long long>(kp, 8)};
-  }
-  void pointers(void** o) {
-    o[0] = &V; o[1] = &Ft; o[2] = &ftilde; o[3] = &n2; o[4] = &st; o[5] = &out; o[6] = &tol;
-    o[7] = &report; o[8] = &seq;
   }
 };
 
