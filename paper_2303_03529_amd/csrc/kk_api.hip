@@ -1587,13 +1587,27 @@ kk_status transforms_tiny(kk_handle h, const int* stop) {
     it.eps = h->eps[s]; it.f = h->f[s]; it.fc = h->fc[s]; it.w = h->w[s];
     it.Y = h->Y + s * np2; it.xdiag = h->xdiag + s * np; it.part = h->part + (size_t)s * a.tiles * np;
   }
+  static_assert(KSTEP % (4 * kk::TINY_WAVES) == 0, "every wave takes the same steps");
+  const int steps = h->kc / (4 * kk::TINY_WAVES);
   {
     ProfileScope ps(h, 0);
-    kk::tiny_forward<<<dim3(a.tiles * (a.tiles + 1) / 2, 2), kk::TINY_THREADS, 0, h->stream>>>(a);
+    const dim3 grid(a.tiles * (a.tiles + 1) / 2, 2);
+    switch (kk::tiny_batch(kk::TINY_FORWARD_U, steps)) {
+      case 6: kk::tiny_forward<6><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+      case 5: kk::tiny_forward<5><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+      case 4: kk::tiny_forward<4><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+      default: kk::tiny_forward<3><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+    }
     LAUNCH_CHECK("tiny_forward");
   }
   ProfileScope ps(h, 1);
-  kk::tiny_back<<<dim3(a.tiles * a.tiles, 2), kk::TINY_THREADS, 0, h->stream>>>(a);
+  const dim3 grid(a.tiles * a.tiles, 2);
+  switch (kk::tiny_batch(kk::TINY_BACK_U, steps)) {
+    case 8: kk::tiny_back<8><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+    case 6: kk::tiny_back<6><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+    case 5: kk::tiny_back<5><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+    default: kk::tiny_back<3><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+  }
   LAUNCH_CHECK("tiny_back");
   return KK_OK;
 }

@@ -22,7 +22,24 @@
 namespace kk {
 
 constexpr int TINY_TILE = 32, TINY_WAVES = 8, TINY_THREADS = TINY_WAVES * WAVE;
-constexpr int TINY_BATCH = 4;  // contraction steps (4 rows each) in flight per wave
+// Contraction steps (4 rows each) that a wave has in flight, the kernels' U: of these the one that
+// leaves the fewest of the wave's `steps` over, then the largest. A load past the end is one of
+// the last step again, and costs as much: 8 atoms (3 steps) 80 us an update with U = 3 or 4 and 92 us with 6,
+// 37 atoms (11 steps) 190 us with 6, 200 us with 4 and 214 us with 5. Sixteen waves with half the steps
+// each were 1-17 % slower.
+constexpr int TINY_FORWARD_U[] = {6, 5, 4, 3}, TINY_BACK_U[] = {8, 6, 5, 3};
+template <int N>
+inline int tiny_batch(const int (&candidates)[N], int steps) {
+  int best = candidates[0], waste = 1 << 30;
+  for (int u : candidates) {
+    const int w = (steps + u - 1) / u * u - steps;
+    if (w < waste) {
+      waste = w;
+      best = u;
+    }
+  }
+  return best;
+}
 
 struct TinyArgs {
   struct Item {
@@ -37,8 +54,9 @@ struct TinyArgs {
 
 __device__ __forceinline__ d2 tiny_load(const double* p) { return *reinterpret_cast<const d2*>(p); }
 
+template <int U>
 __global__ __launch_bounds__(TINY_THREADS) void tiny_forward(const TinyArgs a) {
-  constexpr int T = TINY_TILE, U = TINY_BATCH;
+  constexpr int T = TINY_TILE;
   __shared__ double red[TINY_WAVES][T * T];
   __shared__ double yt[T][T + 1];
   const int stopped = *a.stop;
@@ -50,28 +68,38 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_forward(const TinyArgs a) {
   }
   const int m0 = I * T, n0 = (I + rem) * T, n = a.n;
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, lr = lane >> 4, lc = lane & 15;
-  const int steps = a.kc / (4 * TINY_WAVES);  // of this wave: rows 4 (wave + TINY_WAVES i) + lr
+  const int total = a.kc / 4;  // steps of the contraction; this wave's are wave, wave + TINY_WAVES, ...
   d4 acc[2][2] = {};
-  const size_t row0 = (size_t)(4 * wave + lr);
+  const size_t row0 = (size_t)lr;
   const double *cm = it.C + row0 * n + m0 + 2 * lc, *gm = it.G + row0 * n + m0 + 2 * lc;
   const double *cn = it.C + row0 * n + n0 + 2 * lc, *gn = it.G + row0 * n + n0 + 2 * lc;
   const double* up = it.u + row0;
-  const size_t stride = (size_t)4 * TINY_WAVES * n;
-  for (int s0 = 0; s0 < steps; s0 += U) {
+  const size_t stride = (size_t)4 * n;
+  // the spectrum at this thread's elements of the reduced tile, loaded ahead of the contraction
+  constexpr int EPT = T * T / TINY_THREADS;
+  double em[EPT], fm[EPT], fcm[EPT], en[EPT], fn[EPT], fcn[EPT];
+#pragma unroll
+  for (int h = 0; h < EPT; ++h) {
+    const int e = threadIdx.x + h * TINY_THREADS, q = e / WAVE, l = e & (WAVE - 1);
+    const int m = m0 + 2 * ((l >> 4) + 4 * (q & 3)) + (q >> 3), c = n0 + 2 * (l & 15) + ((q >> 2) & 1);
+    em[h] = it.eps[m]; fm[h] = it.f[m]; fcm[h] = it.fc[m];
+    en[h] = it.eps[c]; fn[h] = it.f[c]; fcn[h] = it.fc[c];
+  }
+  for (int s0 = wave; s0 < total; s0 += U * TINY_WAVES) {
     d2 vcm[U], vgm[U], vcn[U], vgn[U];
     double vu[U];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const size_t s = min(s0 + q, steps - 1);
+      const size_t s = min(s0 + q * TINY_WAVES, total - 1);
       vcm[q] = tiny_load(cm + s * stride);
       vgn[q] = tiny_load(gn + s * stride);
       vgm[q] = tiny_load(gm + s * stride);
       vcn[q] = tiny_load(cn + s * stride);
-      vu[q] = up[s * (4 * TINY_WAVES)];
+      vu[q] = up[s * 4];
     }
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const double u = s0 + q < steps ? vu[q] : 0.0;
+      const double u = s0 + q * TINY_WAVES < total ? vu[q] : 0.0;
       const d2 a0 = u * vcm[q], a1 = u * vgm[q];
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -107,7 +135,7 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_forward(const TinyArgs a) {
       it.xdiag[m] = x;
       y = -it.w[m] * x;
     } else {
-      y = fermi_divided_difference(it.eps[m], it.f[m], it.fc[m], it.eps[c], it.f[c], it.fc[c], a.beta) * x;
+      y = fermi_divided_difference(em[h], fm[h], fcm[h], en[h], fn[h], fcn[h], a.beta) * x;
     }
     yt[tm][tn] = y;
     if (m0 == n0) yt[tn][tm] = y;
@@ -121,16 +149,17 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_forward(const TinyArgs a) {
   }
 }
 
+template <int U>
 __global__ __launch_bounds__(TINY_THREADS) void tiny_back(const TinyArgs a) {
-  constexpr int T = TINY_TILE, U = TINY_BATCH;
+  constexpr int T = TINY_TILE;
   __shared__ double rs[TINY_WAVES][T];
   const int stopped = *a.stop;
   const TinyArgs::Item& it = a.item[blockIdx.y];
   const int tm = blockIdx.x / a.tiles, tn = blockIdx.x - tm * a.tiles;
   const int m0 = tm * T, n0 = tn * T, n = a.n;
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, lr = lane >> 4, lc = lane & 15;
-  const int steps = a.kc / (4 * TINY_WAVES);
-  const size_t row0 = (size_t)(4 * wave + lr), stride = (size_t)4 * TINY_WAVES * n;
+  const int total = a.kc / 4;
+  const size_t row0 = (size_t)lr, stride = (size_t)4 * n;
   const double *cp = it.CT + row0 * n + m0 + 2 * lc, *yp = it.Y + row0 * n + n0 + 2 * lc;
   d2 g[2][4];  // G at the accumulator's elements, loaded ahead of the contraction
 #pragma unroll
@@ -138,17 +167,17 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_back(const TinyArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) g[i][r] = tiny_load(it.G + (size_t)(m0 + 2 * (lr + 4 * r) + i) * n + n0 + 2 * lc);
   d4 acc[2][2] = {};
-  for (int s0 = 0; s0 < steps; s0 += 2 * U) {
-    d2 vc[2 * U], vy[2 * U];
+  for (int s0 = wave; s0 < total; s0 += U * TINY_WAVES) {
+    d2 vc[U], vy[U];
 #pragma unroll
-    for (int q = 0; q < 2 * U; ++q) {
-      const size_t s = min(s0 + q, steps - 1);
+    for (int q = 0; q < U; ++q) {
+      const size_t s = min(s0 + q * TINY_WAVES, total - 1);
       vc[q] = tiny_load(cp + s * stride);
       vy[q] = tiny_load(yp + s * stride);
     }
 #pragma unroll
-    for (int q = 0; q < 2 * U; ++q) {
-      const d2 c = s0 + q < steps ? vc[q] : d2{0.0, 0.0};
+    for (int q = 0; q < U; ++q) {
+      const d2 c = s0 + q * TINY_WAVES < total ? vc[q] : d2{0.0, 0.0};
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
