@@ -36,6 +36,84 @@ namespace kk {
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
+// Cross-lane moves of doubles that stay in the VALU: DPP within rows of 16 lanes, permlane swaps
+// between rows. The general shuffle goes through the LDS crossbar, two trips of about a hundred
+// cycles for a double, and competes with a kernel's LDS reads; the reductions that end almost every
+// kernel here are chains of them.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+// v of lane ^ B in x or y: x holds the lower lanes' (rows', halves') values in both places, y the
+// upper ones'.
+template <int B>
+__device__ __forceinline__ void swap_u32(unsigned v, unsigned& x, unsigned& y) {
+  static_assert(B == 16 || B == 32, "rows or halves");
+  if constexpr (B == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    x = r[0];
+    y = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    x = r[0];
+    y = r[1];
+  }
+}
+template <int B>
+__device__ __forceinline__ void swap_f64(double v, double& x, double& y) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  unsigned xl, yl, xh, yh;
+  swap_u32<B>((unsigned)b, xl, yl);
+  swap_u32<B>((unsigned)(b >> 32), xh, yh);
+  x = __builtin_bit_cast(double, ((unsigned long long)xh << 32) | xl);
+  y = __builtin_bit_cast(double, ((unsigned long long)yh << 32) | yl);
+}
+// v of lane ^ B
+template <int B>
+__device__ __forceinline__ double lane_xor(double v) {
+  if constexpr (B == 1) {
+    return dpp_f64<0xB1>(v);  // quad_perm [1, 0, 3, 2]
+  } else if constexpr (B == 2) {
+    return dpp_f64<0x4E>(v);  // quad_perm [2, 3, 0, 1]
+  } else if constexpr (B == 4) {  // row_shl:4 for the lower quad of each eight, row_shr:4 for the upper
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    auto move = [](int w) {
+      const int r = __builtin_amdgcn_update_dpp(0, w, 0x104, 0xf, 0x5, false);
+      return (unsigned)__builtin_amdgcn_update_dpp(r, w, 0x114, 0xf, 0xa, false);
+    };
+    return __builtin_bit_cast(double, ((unsigned long long)move((int)(unsigned)(b >> 32)) << 32) | move((int)(unsigned)b));
+  } else if constexpr (B == 8) {
+    return dpp_f64<0x128>(v);  // row_ror:8
+  } else {
+    double x, y;
+    swap_f64<B>(v, x, y);
+    return (threadIdx.x & B) ? x : y;
+  }
+}
+// v + (v of lane ^ B)
+template <int B>
+__device__ __forceinline__ double add_xor(double v) {
+  if constexpr (B < 16) {
+    return v + lane_xor<B>(v);
+  } else {
+    double x, y;
+    swap_f64<B>(v, x, y);
+    return x + y;
+  }
+}
+// Sum over the row of 16 lanes by exchanges with lane ^ 1, 2, 4, 8 in turn (after the first two steps
+// a quad holds one value, so a mirrored half row is the exchange with lane ^ 4).
+__device__ __forceinline__ double row16_sum(double v) {
+  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0x141>(v);  // row_half_mirror
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  return v;
+}
+
 constexpr int PAD = 128;    // every padded dimension is a multiple of this
 constexpr int MAX_GEMM_BATCH = 16;
 
@@ -388,10 +466,7 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
         double s = 0.0;
 #pragma unroll
         for (int j = 0; j < WTN; ++j) s += acc[i][j][r] * it.g[(size_t)m * n + nw + j * 16];
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
-        s += __shfl_xor(s, 4);
-        s += __shfl_xor(s, 8);
+        s = row16_sum(s);
         if (lc == 0) it.part[(size_t)p * n + m] = s;
       }
   }

@@ -20,6 +20,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kk_gemm.hpp"
 #include "kk_kernels.hpp"
 
@@ -384,11 +386,7 @@ __device__ __forceinline__ void mixed_epilogue(const MixedItem& it, const int n,
 #pragma unroll
         for (int j = 0; j < WTN; ++j) s += (double)acc[i][j][r] * it.g[(size_t)m * n + nw + j * 32];
         s *= inv;
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
-        s += __shfl_xor(s, 4);
-        s += __shfl_xor(s, 8);
-        s += __shfl_xor(s, 16);
+        s = add_xor<16>(row16_sum(s));
         if (l32 == 0) it.part[(size_t)p * n + m] = s;
       }
   } else {  // EPI_MULLIKEN, 4-wave direct-to-LDS tiles (64 x 64)
@@ -414,21 +412,25 @@ __device__ __forceinline__ void mixed_epilogue(const MixedItem& it, const int n,
         for (int j = 0; j < WTN; ++j) s += (double)acc[i][j][r] * it.g[(size_t)m * n + nw + j * 32];
         v[i * 16 + r] = s * inv;
       }
-#pragma unroll
-    for (int b = 4; b >= 0; --b) {
-      const int h = Q >> (5 - b);  // sums kept after this step (0: a plain pair sum)
-      if (h == 0) {
-        v[0] += __shfl_xor(v[0], 1 << b);
+    auto step = [&](auto bit) __attribute__((always_inline)) {
+      constexpr int b = decltype(bit)::value, h = Q >> (5 - b);  // h: sums kept after this step (0: a plain pair sum)
+      if constexpr (h == 0) {
+        v[0] = add_xor<(1 << b)>(v[0]);
       } else {
         const bool upper = (l32 >> b) & 1;
 #pragma unroll
         for (int k = 0; k < h; ++k) {
           const double keep = upper ? v[k + h] : v[k];
           const double send = upper ? v[k] : v[k + h];
-          v[k] = keep + __shfl_xor(send, 1 << b);
+          v[k] = keep + lane_xor<(1 << b)>(send);
         }
       }
-    }
+    };
+    step(std::integral_constant<int, 4>{});
+    step(std::integral_constant<int, 3>{});
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 0>{});
     // lane bits 4..0 (Q = 32) or 4..1 (Q = 16) are the bits of the sum's index q = 16 i + r
     const int q = Q == 32 ? l32 : (l32 >> 1);
     const int m = mw + (q >> 4) * 32 + 8 * ((q & 15) >> 2) + (q & 3);
@@ -925,7 +927,7 @@ __global__ void __launch_bounds__(ROW_STATS_THREADS)
     mx = fmax(mx, fmax(fabs(v[0]), fabs(v[1])));
     s2 += v[0] * v[0] + v[1] * v[1];
   }
-  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+  mx = wave_max(mx);
   if ((threadIdx.x & (WAVE - 1)) == 0) shm[threadIdx.x / WAVE] = mx;
   s2 = block_sum(s2, sh);  // its barriers also publish shm
   if (threadIdx.x == 0) {

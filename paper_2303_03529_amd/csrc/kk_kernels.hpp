@@ -15,26 +15,32 @@ constexpr int WAVE = 64;
 constexpr double BREAKDOWN_TOL = 1e-13;
 constexpr int MAX_RANK = 64;
 
+// Sum over the wave by exchanges with lane ^ 32, 16, 8, 4, 2, 1 in turn, the same bits in every lane.
+// (After the first three steps values repeat every 8 lanes, so a rotation by 4 is the exchange
+// with lane ^ 4.)
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = add_xor<32>(v);
+  v = add_xor<16>(v);
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  v += dpp_f64<0x124>(v);  // row_ror:4
+  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   return v;
 }
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, lane_xor<32>(v));
+  v = fmax(v, lane_xor<16>(v));
+  v = fmax(v, dpp_f64<0x128>(v));
+  v = fmax(v, dpp_f64<0x124>(v));
+  v = fmax(v, dpp_f64<0x4E>(v));
+  return fmax(v, dpp_f64<0xB1>(v));
+}
 
-// Wave-wide sum of a double in a fixed order, the same bits in every lane, for serial
+// Wave-wide sum of a double in another fixed order, the same bits in every lane, for serial
 // reduction chains (the orthonormalization, the m x m solve): within each row of 16 lanes by DPP moves
 // (rotate by 8 and 4, then exchange with lane ^ 2 and lane ^ 1: every step adds two values
 // that the partner lane adds in the other order, so all 16 lanes end with the same bits),
 // then the four row sums read from lanes 0, 16, 32 and 48 and added as (r0 + r1) + (r2 + r3).
-// The cross-lane moves stay in the VALU, where a shuffle through the LDS crossbar costs a
-// round trip per step.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
 __device__ __forceinline__ double lane_f64(double v, int lane) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
@@ -223,10 +229,8 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
     lo = fmin(lo, fmin(u, d));
     hi = fmax(hi, fmax(u, d));
   });
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = fmin(lo, __shfl_xor(lo, o));
-    hi = fmax(hi, __shfl_xor(hi, o));
-  }
+  lo = -wave_max(-lo);
+  hi = wave_max(hi);
   if (lane == 0) {
     smin[wave] = lo;
     smax[wave] = hi;
@@ -310,10 +314,8 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
       // keeps them reversed
       const bool nan = __any(in && !(e == e && mu == mu));
       double bl = in ? e : INFINITY, bh = in ? e : -INFINITY;
-      for (int o = 32; o > 0; o >>= 1) {
-        bl = fmin(bl, __shfl_xor(bl, o));
-        bh = fmax(bh, __shfl_xor(bh, o));
-      }
+      bl = -wave_max(-bl);
+      bh = wave_max(bh);
       if (lane == 0) {
         bmin[s][i / WIN] = nan ? -INFINITY : bl;
         bmax[s][i / WIN] = nan ? INFINITY : bh;
@@ -327,7 +329,7 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
   // Window tables
   static_assert(WIN == WAVE, "a wave's levels are a window block");
   const int nblk = a.np / WIN;
-  for (int o = 32; o > 0; o >>= 1) ref = fmax(ref, __shfl_xor(ref, o));
+  ref = wave_max(ref);
   if (lane == 0) smax[wave] = ref;
   __syncthreads();
   for (int q = 0; q < NW; ++q) ref = fmax(ref, smax[q]);

@@ -190,10 +190,7 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_back(const TinyArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       double s = acc[i][0][r] * g[i][r][0] + acc[i][1][r] * g[i][r][1];
-      s += dpp_f64<0x128>(s);  // the sum over a row of 16 lanes, as in wave_sum_dpp
-      s += dpp_f64<0x124>(s);
-      s += dpp_f64<0x4E>(s);
-      s += dpp_f64<0xB1>(s);
+      s = row16_sum(s);
       if (lc == 0) rs[wave][2 * (lr + 4 * r) + i] = s;
     }
   __syncthreads();
