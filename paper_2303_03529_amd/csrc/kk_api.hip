@@ -2504,9 +2504,10 @@ namespace {
 // transforms, systems with np <= small_np_max use 64 x 64 tiles.
 
 struct TileClass {  // full-tile list of one tile class, shared by both transforms
-  int4* tiles = nullptr;  // kk::TileQueues: the XCDs' queues one after another
+  int4* tiles = nullptr;  // kk::TileQueues: the XCDs' queues one after another; once: by decreasing cost
   int* off = nullptr;     // XCDS + 1 queue starts
   int n = 0;
+  bool once = false;      // the tiles all run at once: one workgroup each, without the queues
 };
 
 }  // namespace
@@ -2588,6 +2589,7 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
   for (int i = 0; i < b->ns; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->np_of[x] > b->np_of[y]; });
   std::vector<int4> queues[2][kk::XCDS];
+  std::vector<int4> plain[2];
   double load[2][kk::XCDS] = {};
   for (int i : order) {
     const int np = b->np_of[i];
@@ -2605,6 +2607,7 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
           q = (int)(std::min_element(load[c], load[c] + kk::XCDS) - load[c]);
         }
         queues[c][q].push_back(make_int4(item, t.x, t.y, 0));
+        plain[c].push_back(queues[c][q].back());
         load[c][q] += b->sys[i]->kc;
       }
     }
@@ -2625,6 +2628,10 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
   for (int c = 0; c < 2; ++c) {
     TileClass& tc = b->cls[c];
     tc.n = (int)lists[c].size();
+    const int per_cu = mixed ? (c ? SmallMx::MIN_BLOCKS : kk::MLargeCfg::MIN_BLOCKS)
+                             : (c ? SmallF64::MIN_BLOCKS : kk::BackCfg::MIN_BLOCKS);
+    tc.once = tc.n <= cu_count() * per_cu;
+    if (tc.once) lists[c] = plain[c];
     if (!tc.tiles) {  // capacity for every system in either class: the larger per-system count (small tiles)
       size_t cap = 0;
       for (int i = 0; i < b->ns; ++i) {
@@ -2650,9 +2657,13 @@ template <int EPI, class Cfg, class Item>
 kk_status launch_persistent(kk_batch b, const Item* items, const TileClass& c) {
   if (c.n == 0) return KK_OK;
   if (b->queues_used >= BATCH_QUEUE_LAUNCHES) return fail(KK_EINVAL, "internal: too many transform launches");
-  const int grid = std::min(c.n, cu_count() * b->grid_mult);
   const kk::TileQueues q{c.tiles, c.off, b->d_queue + kk::XCDS * b->queues_used++};
-  kk::b_gemm<EPI, Cfg><<<grid, Cfg::THREADS, 0, b->stream>>>(items, q);
+  if (c.once) {
+    kk::b_gemm<EPI, Cfg, false><<<c.n, Cfg::THREADS, 0, b->stream>>>(items, q);
+  } else {
+    const int grid = std::min(c.n, cu_count() * b->grid_mult);
+    kk::b_gemm<EPI, Cfg, true><<<grid, Cfg::THREADS, 0, b->stream>>>(items, q);
+  }
   LAUNCH_CHECK("b_gemm");
   return KK_OK;
 }

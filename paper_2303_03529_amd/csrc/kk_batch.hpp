@@ -194,75 +194,111 @@ constexpr int XCDS = 8;
 struct TileQueues {
   const int4* tiles;
   const int* off;  // XCDS + 1
-  int* next;       // XCDS counters, zero at the launch
+  int* next;       // XCDS counters, zero at the launch: tiles taken after the workgroups' first ones
 };
 
-// Takes the workgroup's next tile; false once every queue is empty. ahead: the position thread 0
-// has reserved in queue (blockIdx + turn) mod 8, taken while the previous tile ran.
-__device__ __forceinline__ bool queue_take(const TileQueues& q, int& turn, int& ahead, int4& tile) {
+// Takes the workgroup's next tile; false once there is none. A workgroup's first tile is its own
+// place in its XCD's queue, without the counters, and one look at all counters finds a queue
+// that is not empty: a counter's round trip is a microsecond and more, and walking the eight of
+// them to the end of a launch cost the 64 x 64 class of 16 small clusters 46 us for 16.
+struct QueueState {
+  bool first = true;
+};
+__device__ __forceinline__ bool queue_take(const TileQueues& q, QueueState& st, int4& tile) {
   __shared__ int4 taken;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < WAVE) {
+    const int lane = threadIdx.x, grid = gridDim.x, own = blockIdx.x % XCDS;
+    const int x = lane % XCDS, off = q.off[x], len = q.off[x + 1] - off;
+    const int ahead = (grid - x + XCDS - 1) / XCDS;  // first tiles of queue x's workgroups
     int4 got = make_int4(-1, 0, 0, 0);
-    while (turn < XCDS) {
-      const int x = (blockIdx.x + turn) % XCDS, at = q.off[x] + ahead;
-      if (at < q.off[x + 1]) {
-        got = q.tiles[at];
-        ahead = atomicAdd(&q.next[x], 1);
-        break;
+    if (st.first && (int)(blockIdx.x / XCDS) < __shfl(len, own)) {
+      got = q.tiles[__shfl(off, own) + blockIdx.x / XCDS];
+    } else {
+      for (;;) {
+        const int used = __hip_atomic_load(&q.next[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned full = (unsigned)__ballot(ahead + used < len) & ((1u << XCDS) - 1);
+        if (full == 0) break;  // every counter has reached its queue's end, and counters only grow
+        // the own queue, or the next one after it that has tiles left
+        const unsigned turned = ((full >> own) | (full << (XCDS - own))) & ((1u << XCDS) - 1);
+        const int from = (own + __builtin_ctz(turned)) % XCDS;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&q.next[from], 1);
+        at = __shfl(at, 0) + __shfl(ahead, from);
+        if (at < __shfl(len, from)) {
+          got = q.tiles[__shfl(off, from) + at];
+          break;
+        }
       }
-      if (++turn < XCDS) ahead = atomicAdd(&q.next[(blockIdx.x + turn) % XCDS], 1);
     }
-    taken = got;
+    if (lane == 0) taken = got;
   }
+  st.first = false;
   __syncthreads();
-  tile = taken;
+  // uniform for the compiler too: the tile's pointers stay scalar
+  tile = make_int4(__builtin_amdgcn_readfirstlane(taken.x), __builtin_amdgcn_readfirstlane(taken.y),
+                   __builtin_amdgcn_readfirstlane(taken.z), 0);
   __syncthreads();  // taken is free for the next call
   return tile.x >= 0;
 }
 
-// Persistent transforms over the tile queues; a tile of a system whose Krylov expansion has
-// stopped, or that its window leaves out, is skipped (uniformly for the workgroup).
+// Transforms over the tile queues (QUEUED), or one tile to each workgroup; a tile of a system whose
+// Krylov expansion has stopped, or that its window leaves out, is skipped (uniformly for the workgroup).
+// A launch whose tiles all run at once has neither queues nor windows, which could only add to its
+// latency: 10 clusters of 30-70 atoms, FP16 x 3, 1.28 ms an update against 1.49 with the queues and 1.35
+// with a stride loop; 16 of 20-60 atoms FP64, 2.10 against 2.15 and 2.14.
 // Held to MIN_BLOCKS workgroups per CU: the two-half forward form with the Fermi
 // epilogue, which this kernel ran before the full-tile forward, took ~164 registers per
 // lane and one workgroup per CU when left to itself (13 % slower); the full-tile
 // product and the back-transform fit without spilling.
-template <int EPI, class Cfg>
+template <int EPI, class Cfg, bool QUEUED>
 __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(Cfg::WAVES_PER_EU)))
 void b_gemm(const BatchItemF64* __restrict__ items, const TileQueues q) {
-  int turn = 0, ahead = 0;
-  int4 tl;
-  if (threadIdx.x == 0) ahead = atomicAdd(&q.next[blockIdx.x % XCDS], 1);
-  while (queue_take(q, turn, ahead, tl)) {
+  if constexpr (!QUEUED) {
+    const int4 tl = q.tiles[blockIdx.x];
     const BatchItemF64& it = items[tl.x];
-    if (*it.stop) continue;
-    int2 rows = make_int2(0, it.k);
-    if constexpr (EPI == EPI_MULLIKEN)
-      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, Cfg::BK, 0);
-    else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
-      continue;
-    const HalfRows src{it.g, it.n, rows.x, rows.y - rows.x, false};
-    f64_tile<EPI, Cfg>(it.g, src, it.n, make_int2(tl.y, tl.z), it.beta);
+    if (*it.stop) return;
+    f64_tile<EPI, Cfg>(it.g, HalfRows{it.g, it.n, 0, it.k, false}, it.n, make_int2(tl.y, tl.z), it.beta);
+  } else {
+    QueueState take;
+    int4 tl;
+    while (queue_take(q, take, tl)) {
+      const BatchItemF64& it = items[tl.x];
+      if (*it.stop) continue;
+      int2 rows = make_int2(0, it.k);
+      if constexpr (EPI == EPI_MULLIKEN)
+        rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, Cfg::BK, 0);
+      else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
+        continue;
+      const HalfRows src{it.g, it.n, rows.x, rows.y - rows.x, false};
+      f64_tile<EPI, Cfg>(it.g, src, it.n, make_int2(tl.y, tl.z), it.beta);
+    }
   }
 }
 
 // Held to MIN_BLOCKS workgroups per CU as well (the two-half forward form with a staged
 // mirror epilogue, which this kernel ran before the full-tile forward, took ~190 registers
 // and one workgroup per CU when left to itself, 4 % slower).
-template <int EPI, class Cfg>
+template <int EPI, class Cfg, bool QUEUED>
 __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu((Cfg::MIN_BLOCKS * Cfg::THREADS / 64 + 3) / 4)))
 void b_gemm(const BatchItemMixed* __restrict__ items, const TileQueues q) {
-  int turn = 0, ahead = 0;
-  int4 tl;
-  if (threadIdx.x == 0) ahead = atomicAdd(&q.next[blockIdx.x % XCDS], 1);
-  while (queue_take(q, turn, ahead, tl)) {
+  if constexpr (!QUEUED) {
+    const int4 tl = q.tiles[blockIdx.x];
     const BatchItemMixed& it = items[tl.x];
-    if (*it.stop) continue;
-    int2 rows = make_int2(0, it.k);
-    if constexpr (EPI == EPI_MULLIKEN)
-      rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, WIN_ROWS_MIXED<Cfg>, Cfg::BK);
-    else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
-      continue;
-    mixed_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, make_int2(tl.y, tl.z));
+    if (*it.stop) return;
+    mixed_tile<EPI, Cfg>(it.g, it.n, 0, it.k, make_int2(tl.y, tl.z));
+  } else {
+    QueueState take;
+    int4 tl;
+    while (queue_take(q, take, tl)) {
+      const BatchItemMixed& it = items[tl.x];
+      if (*it.stop) continue;
+      int2 rows = make_int2(0, it.k);
+      if constexpr (EPI == EPI_MULLIKEN)
+        rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, WIN_ROWS_MIXED<Cfg>, Cfg::BK);
+      else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
+        continue;
+      mixed_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, make_int2(tl.y, tl.z));
+    }
   }
 }
 

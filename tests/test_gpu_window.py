@@ -143,3 +143,31 @@ def test_batch(precision, small_np_max):
             b.close()
     err = [rel(p, q) for p, q in zip(*got)]
     assert max(err) < TOL[precision], err
+
+
+@pytest.mark.parametrize("precision", PRECISIONS[:2], ids=IDS[:2])
+@pytest.mark.parametrize("small_np_max", [0, 1 << 30])
+@pytest.mark.parametrize("copies", [1, 6])
+def test_batch_tiles_at_once_and_from_queues(copies, small_np_max, precision):
+    """Launches of either tile class that hold at most one tile for each co-resident workgroup (one
+    system of 640 and one of 1024 padded levels) and that take their tiles from the queues (six of
+    each), each system against its own handle."""
+    ys = [make(n, 400 + n + 7 * i) for i in range(copies) for n in (113, 66)]
+    rng = np.random.default_rng(copies)
+    deltas = [t(0.01 * rng.standard_normal(2 * (len(y["offsets"]) - 1))) for y in ys]
+    names = ("offsets", "S", "Z", "Q_up", "Q_dn", "eps_up", "eps_dn", "gamma", "W", "kT", "n_electrons")
+    b = krylov.Batch().prepare([dict(zip(names, arguments(y, False))) for y in ys], precision)
+    try:
+        b.set_tuning(small_np_max, 2)
+        got = [[x.cpu().numpy() for x in b.krylov_kernel_apply(deltas, 4)[0]] for _ in range(2)]
+    finally:
+        b.close()
+    for i, (y, delta) in enumerate(zip(ys, deltas)):
+        h = krylov.Handle()
+        try:
+            h.prepare(*arguments(y, False), precision)
+            want = h.krylov_kernel_apply(delta, 4)[0].cpu().numpy()
+        finally:
+            h.close()
+        assert rel(got[0][i], want) < TOL[precision], i
+        assert np.array_equal(got[0][i], got[1][i]), i
