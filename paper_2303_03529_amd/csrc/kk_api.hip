@@ -729,6 +729,9 @@ kk_status ensure_workspace(kk_handle h, int chunk) {
   return KK_OK;
 }
 
+// Mulliken partial rows per spin that a direction of an update leaves.
+int partial_rows(kk_handle h) { return h->tiny_step ? h->kc / kk::TINY_TILE : h->nparts; }
+
 int max_chunk(kk_handle h) {
   // FP64: one Y per spin and chunk; split path: four (BF16: six) 16-bit matrices per spin and
   // one FP32 per spin and chunk
@@ -742,9 +745,11 @@ int max_chunk(kk_handle h) {
 
 // The last step of a response: q1 (and with K0 = -I the preconditioned derivative ft) from
 // the Mulliken partial rows and diag X (combine; combine_small for the fused small step).
+// With q1 null the rows wait for the next launch (combine_args).
 kk_status launch_combine(kk_handle h, int batch, double* q1, const int* stop, const double* vsub, double* ft,
                          int nparts = 0) {
   const int N = h->natoms;
+  if (q1 == nullptr) return KK_OK;
   if (nparts == 0) nparts = h->nparts;
   dim3 grid((N + kk::COMBINE_ATOMS - 1) / kk::COMBINE_ATOMS, batch);
   if (2 * N <= kk::FUSED_MAX_N2)
@@ -1540,18 +1545,18 @@ kk_status enqueue_start(kk_handle h, const double* delta, const double* K0) {
   return KK_OK;
 }
 
-// What the next launch needs to form f~_k from the partial rows of direction k (tiny handles).
-kk::CombineArgs combine_args(kk_handle h, int k) {
+// What the next launch needs to form f~_k from the partial rows of direction k.
+kk::CombineArgs combine_args(kk_handle h, int k, const double* K0) {
   const size_t n2 = 2 * (size_t)h->natoms;
   kk::CombineArgs c{};
   c.xdiag = h->xdiag; c.part = h->part; c.w_up = h->w[0]; c.w_dn = h->w[1]; c.wsum = h->wsum; c.t = h->t;
-  c.v = h->V + k * n2; c.offsets = h->offsets; c.q1 = h->q1; c.ft = h->Ft + k * n2;
-  c.nparts = h->kc / kk::TINY_TILE; c.nb = h->nb; c.np = h->np; c.natoms = h->natoms;
+  c.v = h->V + k * n2; c.K0 = K0; c.offsets = h->offsets; c.q1 = h->q1; c.ft = h->Ft + k * n2;
+  c.nparts = partial_rows(h); c.split = h->precision != KK_FP64; c.nb = h->nb; c.np = h->np; c.natoms = h->natoms;
   return c;
 }
 
 // orth_potentials of direction k on the code for the system's size.
-template <int NMAX, bool COMBINE>
+template <int NMAX, kk::Combine COMBINE>
 void run_orth_potentials(kk_handle h, int k, const double* src, const kk::CombineArgs& c) {
   const bool split = h->precision != KK_FP64;
   kk::orth_potentials<NMAX, COMBINE>
@@ -1559,18 +1564,27 @@ void run_orth_potentials(kk_handle h, int k, const double* src, const kk::Combin
          h->stream>>>(src, h->V, 2 * h->natoms, h->kst, k, h->gamma, h->natoms, h->W, h->offsets, h->np, h->u,
                       split ? h->cvec : nullptr, split ? h->pmax : nullptr, c);
 }
-kk_status launch_orth_potentials(kk_handle h, int k, const double* src, bool combine) {
+kk_status launch_orth_potentials(kk_handle h, int k, const double* src, const double* K0, bool combine) {
   const int N = h->natoms;
-  if (combine)
-    run_orth_potentials<kk::COMBINE_BLOCK_ATOMS, true>(h, k, src, combine_args(h, k - 1));
+  const kk::CombineArgs none{};
+  if (combine) {
+    constexpr int A = kk::COMBINE_BLOCK_ATOMS;
+    const kk::CombineArgs c = combine_args(h, k - 1, K0);
+    if (c.split)
+      K0 ? run_orth_potentials<A, kk::COMBINE_SPLIT_DENSE>(h, k, src, c)
+         : run_orth_potentials<A, kk::COMBINE_SPLIT>(h, k, src, c);
+    else
+      K0 ? run_orth_potentials<A, kk::COMBINE_FP64_DENSE>(h, k, src, c)
+         : run_orth_potentials<A, kk::COMBINE_FP64>(h, k, src, c);
+  }
   else if (N <= 64)
-    run_orth_potentials<64, false>(h, k, src, kk::CombineArgs{});
+    run_orth_potentials<64, kk::COMBINE_NONE>(h, k, src, none);
   else if (N <= 128)
-    run_orth_potentials<128, false>(h, k, src, kk::CombineArgs{});
+    run_orth_potentials<128, kk::COMBINE_NONE>(h, k, src, none);
   else if (N <= 256)
-    run_orth_potentials<256, false>(h, k, src, kk::CombineArgs{});
+    run_orth_potentials<256, kk::COMBINE_NONE>(h, k, src, none);
   else
-    run_orth_potentials<512, false>(h, k, src, kk::CombineArgs{});
+    run_orth_potentials<512, kk::COMBINE_NONE>(h, k, src, none);
   LAUNCH_CHECK("orth_potentials");
   return KK_OK;
 }
@@ -1612,8 +1626,17 @@ kk_status transforms_tiny(kk_handle h, const int* stop) {
   return KK_OK;
 }
 
-// Whether the direction leaves f~_k in its partial rows for the next launch (combine_args).
-bool leaves_combine(kk_handle h, const double* K0) { return h->tiny_step && K0 == nullptr; }
+// Whether a direction leaves f~_k in its partial rows for the next launch (combine_args), sparing
+// the combine's and, with a dense K0, precondition's launch (4-5 us each): while the partial rows, which
+// every block of that launch reads, are few. Rows x Nb at most 8192 in the split forms and with a
+// dense K0 3072 in FP64 (elsewhere the launches / left to the next one, m = 6): FP16 x 3 8 atoms 157 / 146 us,
+// 16 atoms 177 / 167, 24 atoms 178 / 175, but 30 atoms 197 / 204, 37 atoms 205 / 217; dense K0 in FP64 8 atoms 126 /
+// 108 us, 16 atoms 144 / 128, 30 atoms 184 / 178, 37 atoms level, 50 atoms 258 / 272.
+constexpr int FOLD_MAX_SPLIT = 8192, FOLD_MAX_DENSE = 3072;
+bool leaves_combine(kk_handle h, const double* K0) {
+  if (h->precision != KK_FP64) return h->natoms <= kk::COMBINE_BLOCK_ATOMS && partial_rows(h) * h->nb <= FOLD_MAX_SPLIT;
+  return h->tiny_step && (K0 == nullptr || partial_rows(h) * h->nb <= FOLD_MAX_DENSE);
+}
 
 // Direction k: v_k and f~_k. in_rows: f~_{k-1} was left in its partial rows.
 kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows) {
@@ -1622,20 +1645,21 @@ kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows) 
   const int* stop = &h->kst->stop;
   const int gv_threads = 256, gv_blocks = (n2 * kk::WAVE + gv_threads - 1) / gv_threads;
   // Small systems: one launch orthonormalizes and builds the potentials (kk_fused.hpp), and
-  // with K0 = -I the combine also preconditions.
-  const bool fused = n2 <= kk::FUSED_MAX_N2;
+  // with K0 = -I the combine also preconditions; the smallest leave both to the next launch.
+  const bool fused = n2 <= kk::FUSED_MAX_N2, rows = leaves_combine(h, K0);
   const double* src = (k == 0) ? h->ftilde : h->Ft + (size_t)(k - 1) * n2;
   const double* vk = h->V + (size_t)k * n2;
   double* ftk = h->Ft + (size_t)k * n2;
   if (fused) {
-    if ((st = launch_orth_potentials(h, k, src, in_rows))) return st;
+    if ((st = launch_orth_potentials(h, k, src, K0, in_rows))) return st;
+    double* q1 = rows ? nullptr : h->q1;
     if (h->tiny_step) {
       if ((st = transforms_tiny(h, stop))) return st;
-      if (K0 == nullptr) return KK_OK;  // the combine waits for the next launch
-      if ((st = launch_combine(h, 1, h->q1, stop, nullptr, nullptr, h->kc / kk::TINY_TILE))) return st;
-    } else if ((st = response_any(h, 1, vk, h->q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk))) {
+      if ((st = launch_combine(h, 1, q1, stop, K0 ? nullptr : vk, K0 ? nullptr : ftk, partial_rows(h)))) return st;
+    } else if ((st = response_any(h, 1, vk, q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk))) {
       return st;
     }
+    if (rows) return KK_OK;
   } else {
     // one block just large enough for 8 entries per thread
     const int orth_threads = std::max(64, std::min(1024, ((n2 + 7) / 8 + 63) / 64 * 64));
@@ -1650,13 +1674,13 @@ kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows) 
   return KK_OK;
 }
 
-// The solve on the directions 0..k; a residual <= tol (> 0) ends the expansion. in_rows: f~_k is
-// still in its partial rows.
-kk_status enqueue_solve(kk_handle h, int k, bool in_rows, double* Kdelta, double tol,
+// The solve on the directions 0..k; a residual <= tol (> 0) ends the expansion. It forms
+// f~_k first where that is still in its partial rows.
+kk_status enqueue_solve(kk_handle h, int k, const double* K0, double* Kdelta, double tol,
                         kk::SolveReport* report = nullptr, unsigned long long seq = 0) {
   kk::krylov_solve<<<1, kk::COMBINE_BLOCK, 0, h->stream>>>(h->V, h->Ft, h->ftilde, 2 * h->natoms, h->kst, Kdelta, tol,
                                                            report, seq,
-                                                           in_rows ? combine_args(h, k) : kk::CombineArgs{});
+                                                           leaves_combine(h, K0) ? combine_args(h, k, K0) : kk::CombineArgs{});
   LAUNCH_CHECK("krylov_solve");
   return KK_OK;
 }
@@ -1668,9 +1692,9 @@ kk_status enqueue_krylov(kk_handle h, const double* delta, int m, double tol, co
   for (int k = 0; k < m; ++k) {
     // (a solve between directions has formed f~_{k-1} already)
     if ((st = enqueue_direction(h, k, K0, rows && k > 0 && tol == 0.0))) return st;
-    if (tol > 0.0 && k + 1 < m && (st = enqueue_solve(h, k, rows, Kdelta, tol))) return st;
+    if (tol > 0.0 && k + 1 < m && (st = enqueue_solve(h, k, K0, Kdelta, tol))) return st;
   }
-  return enqueue_solve(h, m - 1, rows, Kdelta, 0.0);
+  return enqueue_solve(h, m - 1, K0, Kdelta, 0.0);
 }
 
 // An adaptive update whose caller waits for it anyway (info given): directions are enqueued only
@@ -1694,7 +1718,7 @@ kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double t
   for (int k = 0; k < m; ++k) {
     if ((st = enqueue_direction(h, k, K0, false))) return st;
     const unsigned long long seq = ++h->report_seq;
-    if ((st = enqueue_solve(h, k, leaves_combine(h, K0), Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
+    if ((st = enqueue_solve(h, k, K0, Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
     if (k + 1 == m || k + 1 < h->rank_hint) continue;
     // the word of this solve, or the stream's end (an error included, which the sync reports)
     for (int spin = 1;; ++spin) {

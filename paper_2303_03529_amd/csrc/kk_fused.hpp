@@ -136,13 +136,14 @@ __device__ __forceinline__ void orth_wave0(double* sv, const double* vl, int sta
 // orbital ranges into registers) and tests the flag afterwards. Wave 0 then
 // runs the 2 rank projections out of LDS (rows past the staged ones from global memory),
 // and every wave forms its atoms' potentials from the new direction in LDS.
-// COMBINE: src is still in the Mulliken partial rows of the previous direction; every block forms
-// it by combine_block (block 0 stores it), which spares the launch between.
+// COMBINE not COMBINE_NONE: src is still in the Mulliken partial rows of the previous direction; every
+// block forms it by combine_block (block 0 stores it), which spares the launch or two between.
 // NMAX: atoms the code is unrolled for (64, 128, 256 or 512), so that a small system does not
 // step through the loads and terms of a large one.
 // Grid: ceil(N / FUSED_ATOMS) blocks of FUSED_THREADS (COMBINE: COMBINE_BLOCK); N <= NMAX.
 constexpr int FUSED_LDS_ROWS = 8192;  // doubles of V staged in LDS (64 KB)
-template <int NMAX, bool COMBINE>
+enum Combine { COMBINE_NONE, COMBINE_FP64, COMBINE_FP64_DENSE, COMBINE_SPLIT, COMBINE_SPLIT_DENSE };
+template <int NMAX, Combine COMBINE>
 __global__ void __launch_bounds__(COMBINE ? COMBINE_BLOCK : FUSED_THREADS)
     orth_potentials(const double* __restrict__ src, double* __restrict__ V, int n2, KrylovState* st, int rank,
                     const double* __restrict__ gamma, int natoms, double W, const int* __restrict__ offsets, int np,
@@ -216,7 +217,9 @@ __global__ void __launch_bounds__(COMBINE ? COMBINE_BLOCK : FUSED_THREADS)
     load_rows(base);
     store_rows(base);
   }
-  if constexpr (COMBINE) combine_block(comb, sv, blockIdx.x == 0);
+  if constexpr (COMBINE != COMBINE_NONE)
+    combine_block<(COMBINE >= COMBINE_SPLIT), (COMBINE == COMBINE_FP64_DENSE || COMBINE == COMBINE_SPLIT_DENSE)>(
+        comb, sv, blockIdx.x == 0);
   __syncthreads();
   if (wave == 0) orth_wave0<N2MAX / WAVE>(sv, vl, staged, V, n2, rank, st, cvl, &accepted, &cshared);
   __syncthreads();
@@ -348,7 +351,12 @@ __global__ void __launch_bounds__(COMBINE_BLOCK) krylov_solve(const double* __re
                                                               SolveReport* report, unsigned long long seq,
                                                               const CombineArgs comb) {
   __shared__ double fl[2 * COMBINE_BLOCK_ATOMS];
-  if (comb.natoms > 0 && st->stop == 0) combine_block(comb, fl, true);  // ends with a barrier
+  if (comb.natoms > 0 && st->stop == 0) {  // ends with a barrier
+    if (comb.split)
+      comb.K0 != nullptr ? combine_block<true, true>(comb, fl, true) : combine_block<true, false>(comb, fl, true);
+    else
+      comb.K0 != nullptr ? combine_block<false, true>(comb, fl, true) : combine_block<false, false>(comb, fl, true);
+  }
   solve_dev(V, Ft, ftilde, n2, st, x, stop_tol, report, seq);
 }
 

@@ -202,27 +202,45 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_back(const TinyArgs a) {
   }
 }
 
-// What combine_small does, for every atom of the system in one block of COMBINE_BLOCK threads:
-// f~ = -(q1 - v) of the direction v into ft_lds (2 natoms doubles). The block that `write`s also stores it
-// and q1. Two rounds of loads (the orbital ranges and the terms of the shift, then the partial
-// rows, an atom a wave), whose latency is most of what this costs. natoms <= COMBINE_BLOCK_ATOMS.
+// What combine_small does, and with K0 (DENSE) precondition after it, for every atom of the
+// system in one block of COMBINE_BLOCK threads: f~ = K0 (q1 - v), or -(q1 - v), of the direction v into
+// ft_lds (2 natoms doubles). The block that `write`s also stores it and q1. Two rounds of loads (K0's
+// rows, the orbital ranges and the terms of the shift, then the partial rows, an atom a wave), whose
+// latency is most of what this costs. SPLIT: the sums in combine_small's order, to the same bits, which
+// the split products, and so their rounding, go on from. natoms <= COMBINE_BLOCK_ATOMS.
 struct CombineArgs {
-  const double *xdiag, *part, *w_up, *w_dn, *wsum, *t, *v;
+  const double *xdiag, *part, *w_up, *w_dn, *wsum, *t, *v, *K0;
   const int* offsets;
   double *q1, *ft;
-  int nparts, nb, np, natoms;
+  int nparts, nb, np, natoms, split;
 };
 constexpr int COMBINE_BLOCK = 1024, COMBINE_BLOCK_ATOMS = 64;
+template <bool SPLIT, bool DENSE>
 __device__ __forceinline__ void combine_block(const CombineArgs& c, double* ft_lds, bool write) {
-  constexpr int NW = COMBINE_BLOCK / WAVE, LOADS = 3;
-  __shared__ double psum[NW];
-  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, N = c.natoms;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < c.nb; i += COMBINE_BLOCK) s += c.w_up[i] * c.xdiag[i] + c.w_dn[i] * c.xdiag[c.np + i];
+  constexpr int NW = COMBINE_BLOCK / WAVE, LOADS = SPLIT ? 6 : 3, N2MAX = 2 * COMBINE_BLOCK_ATOMS;
+  constexpr int SUM_THREADS = SPLIT ? COMBINE_THREADS : COMBINE_BLOCK;
+  constexpr int ROWS = DENSE ? N2MAX / NW : 1, COLS = DENSE ? N2MAX / WAVE : 1;
+  __shared__ double psum[SUM_THREADS / WAVE], dl[DENSE ? N2MAX : 1];
+  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, N = c.natoms, n2 = 2 * N;
+  auto sum = [](double x) __attribute__((always_inline)) { return SPLIT ? wave_sum(x) : wave_sum_dpp(x); };
+  double kr[ROWS][COLS];
+  if constexpr (DENSE) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+      for (int k = 0; k < COLS; ++k) {
+        const int row = wave + r * NW, j = lane + k * WAVE;
+        kr[r][k] = row < n2 && j < n2 ? c.K0[(size_t)row * n2 + j] : 0.0;
+      }
+  }
   const double wsum = *c.wsum;
-  s = wave_sum_dpp(s);
-  if (lane == 0) psum[wave] = s;
-  double* const dn = ft_lds;  // the atoms' Mulliken sums of both spins first
+  if (threadIdx.x < SUM_THREADS) {
+    double s = 0.0;
+    for (int i = threadIdx.x; i < c.nb; i += SUM_THREADS) s += c.w_up[i] * c.xdiag[i] + c.w_dn[i] * c.xdiag[c.np + i];
+    s = sum(s);
+    if (lane == 0) psum[wave] = s;
+  }
+  double* const dn = DENSE ? dl : ft_lds;  // the atoms' Mulliken sums of both spins first
   for (int a = wave; a < N; a += NW) {
     const int i0 = c.offsets[a], norb = c.offsets[a + 1] - i0, tot = c.nparts * norb;
     const double *p0 = c.part + i0, *p1 = p0 + (size_t)c.nparts * c.np;
@@ -244,8 +262,8 @@ __device__ __forceinline__ void combine_block(const CombineArgs& c, double* ft_l
         a1 += v1[k];
       }
     }
-    a0 = wave_sum_dpp(a0);
-    a1 = wave_sum_dpp(a1);
+    a0 = sum(a0);
+    a1 = sum(a1);
     if (lane == 0) {
       dn[a] = a0;
       dn[N + a] = a1;
@@ -253,22 +271,47 @@ __device__ __forceinline__ void combine_block(const CombineArgs& c, double* ft_l
   }
   __syncthreads();
   double top = 0.0;
-  for (int q = 0; q < NW; ++q) top += psum[q];
+  if constexpr (SPLIT) {
+    top = wave_sum(lane < SUM_THREADS / WAVE ? psum[lane] : 0.0);
+  } else {
+    for (int q = 0; q < NW; ++q) top += psum[q];
+  }
   const double dmu = wsum > 0.0 ? top / wsum : 0.0;
   for (int a = threadIdx.x; a < N; a += COMBINE_BLOCK) {
     const double d0 = dn[a] + dmu * c.t[a], d1 = dn[N + a] + dmu * c.t[N + a];
     const double qa = d0 + d1, ma = d0 - d1;
-    const double fa = -(qa - c.v[a]), fm = -(ma - c.v[N + a]);
+    const double fa = DENSE ? qa - c.v[a] : -(qa - c.v[a]), fm = DENSE ? ma - c.v[N + a] : -(ma - c.v[N + a]);
     dn[a] = fa;
     dn[N + a] = fm;
     if (write) {
       c.q1[a] = qa;
       c.q1[N + a] = ma;
-      c.ft[a] = fa;
-      c.ft[N + a] = fm;
+      if constexpr (!DENSE) {
+        c.ft[a] = fa;
+        c.ft[N + a] = fm;
+      }
     }
   }
   __syncthreads();
+  if constexpr (DENSE) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const int row = wave + r * NW;  // wave-uniform
+      if (row >= n2) break;
+      double f = 0.0;
+#pragma unroll
+      for (int k = 0; k < COLS; ++k) {
+        const int j = lane + k * WAVE;
+        if (j < n2) f += kr[r][k] * dl[j];
+      }
+      f = wave_sum(f);
+      if (lane == 0) {
+        ft_lds[row] = f;
+        if (write) c.ft[row] = f;
+      }
+    }
+    __syncthreads();
+  }
 }
 
 }  // namespace kk
