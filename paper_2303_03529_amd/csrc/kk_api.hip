@@ -967,20 +967,22 @@ kk_status launch_mixed(kk_handle h, bool forward, kk::MixedArgs& a, const _Float
 // transforms on FP16 x 3 MFMA products (Y kept as an FP16 split).
 kk_status response_chunk_mixed(kk_handle h, int batch, const double* v, double* q1, const int* stop,
                                bool identity = false, bool prologue_done = false, const double* vsub = nullptr,
-                               double* ft = nullptr) {
+                               double* ft = nullptr, const kk::ResidualTest& test = {}) {
   const int N = h->natoms, np = h->np;
   const size_t np2 = (size_t)np * np;
   const int blocks = (int)std::max<size_t>(1, std::min<size_t>((np2 / 8 + 255) / 256, 16384 / (2 * batch)));
   if (prologue_done) {  // one direction after orth_potentials: scales from its block maxima, then the split
     const int nblk = (N + kk::FUSED_ATOMS - 1) / kk::FUSED_ATOMS;
+    const bool tested = test.rank > 0;
+    auto launch = [&](auto* kernel) {
+      kernel<<<dim3(blocks + tested, 2), 256, tested ? sizeof(double) * kk::solve_lds(test.rank) : 0, h->stream>>>(
+          h->CT[0], h->CT[1], np, h->u, h->pmax, nblk, h->mconst, h->beta, h->msc, h->uct_h, h->uct_l,
+          h->bf16 ? h->uct_r : nullptr, stop, test);
+    };
     if (h->bf16)
-      kk::split_operands_fused<true, 3><<<dim3(blocks, 2), 256, 0, h->stream>>>(
-          h->CT[0], h->CT[1], np, h->u, h->pmax, nblk, h->mconst, h->beta, h->msc, h->uct_h, h->uct_l, h->uct_r,
-          stop);
+      launch(tested ? kk::split_operands_fused<true, 3, true> : kk::split_operands_fused<true, 3, false>);
     else
-      kk::split_operands_fused<false, 2><<<dim3(blocks, 2), 256, 0, h->stream>>>(
-          h->CT[0], h->CT[1], np, h->u, h->pmax, nblk, h->mconst, h->beta, h->msc, h->uct_h, h->uct_l, nullptr,
-          stop);
+      launch(tested ? kk::split_operands_fused<false, 2, true> : kk::split_operands_fused<false, 2, false>);
     LAUNCH_CHECK("split_operands_fused");
   } else {
     {
@@ -1082,9 +1084,10 @@ kk_status response_chunk_mixed(kk_handle h, int batch, const double* v, double* 
 
 kk_status response_any(kk_handle h, int batch, const double* v, double* q1, const int* stop,
                        bool identity = false, bool prologue_done = false, const double* vsub = nullptr,
-                       double* ft = nullptr) {
-  return h->precision == KK_FP64 ? response_chunk(h, batch, v, q1, stop, identity, prologue_done, vsub, ft)
-                                 : response_chunk_mixed(h, batch, v, q1, stop, identity, prologue_done, vsub, ft);
+                       double* ft = nullptr, const kk::ResidualTest& test = {}) {
+  return h->precision == KK_FP64
+             ? response_chunk(h, batch, v, q1, stop, identity, prologue_done, vsub, ft)
+             : response_chunk_mixed(h, batch, v, q1, stop, identity, prologue_done, vsub, ft, test);
 }
 
 kk_status check_handle(kk_handle h) {
@@ -1591,7 +1594,7 @@ kk_status launch_orth_potentials(kk_handle h, int k, const double* src, const do
 static_assert(2 * 512 == kk::FUSED_MAX_N2, "the largest unrolling");
 
 // Both transforms of one direction of a tiny handle, whose potentials are in h->u.
-kk_status transforms_tiny(kk_handle h, const int* stop) {
+kk_status transforms_tiny(kk_handle h, const int* stop, const kk::ResidualTest& test) {
   const size_t np = h->np, np2 = np * np;
   kk::TinyArgs a{};
   a.n = h->np; a.kc = h->kc; a.tiles = h->kc / kk::TINY_TILE; a.beta = h->beta; a.stop = stop;
@@ -1605,12 +1608,15 @@ kk_status transforms_tiny(kk_handle h, const int* stop) {
   const int steps = h->kc / (4 * kk::TINY_WAVES);
   {
     ProfileScope ps(h, 0);
-    const dim3 grid(a.tiles * (a.tiles + 1) / 2, 2);
+    const dim3 grid(a.tiles * (a.tiles + 1) / 2 + (test.rank > 0), 2);
+    auto launch = [&](auto* plain, auto* tested) {
+      (test.rank > 0 ? tested : plain)<<<grid, kk::TINY_THREADS, 0, h->stream>>>(a, test);
+    };
     switch (kk::tiny_batch(kk::TINY_FORWARD_U, steps)) {
-      case 6: kk::tiny_forward<6><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
-      case 5: kk::tiny_forward<5><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
-      case 4: kk::tiny_forward<4><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
-      default: kk::tiny_forward<3><<<grid, kk::TINY_THREADS, 0, h->stream>>>(a); break;
+      case 6: launch(kk::tiny_forward<6, false>, kk::tiny_forward<6, true>); break;
+      case 5: launch(kk::tiny_forward<5, false>, kk::tiny_forward<5, true>); break;
+      case 4: launch(kk::tiny_forward<4, false>, kk::tiny_forward<4, true>); break;
+      default: launch(kk::tiny_forward<3, false>, kk::tiny_forward<3, true>); break;
     }
     LAUNCH_CHECK("tiny_forward");
   }
@@ -1638,8 +1644,17 @@ bool leaves_combine(kk_handle h, const double* K0) {
   return h->tiny_step && (K0 == nullptr || partial_rows(h) * h->nb <= FOLD_MAX_DENSE);
 }
 
-// Direction k: v_k and f~_k. in_rows: f~_{k-1} was left in its partial rows.
-kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows) {
+// Whether the residual of `rank` directions is tested in a launch of the next (residual_test): in the
+// forward transform of tiny handles, in the operand split of the split forms. FP64 above the tiny
+// handles has no launch beside which the test would cost nothing.
+bool tests_in_launch(kk_handle h, int rank) {
+  return rank <= kk::RESIDUAL_TEST_MAX_RANK &&
+         (h->tiny_step || (h->precision != KK_FP64 && 2 * h->natoms <= kk::FUSED_MAX_N2));
+}
+
+// Direction k: v_k and f~_k. in_rows: f~_{k-1} was left in its partial rows. test.rank > 0: with
+// the test of the residual of k directions (tests_in_launch).
+kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows, const kk::ResidualTest& test = {}) {
   kk_status st;
   const int n2 = 2 * h->natoms;
   const int* stop = &h->kst->stop;
@@ -1654,9 +1669,9 @@ kk_status enqueue_direction(kk_handle h, int k, const double* K0, bool in_rows) 
     if ((st = launch_orth_potentials(h, k, src, K0, in_rows))) return st;
     double* q1 = rows ? nullptr : h->q1;
     if (h->tiny_step) {
-      if ((st = transforms_tiny(h, stop))) return st;
+      if ((st = transforms_tiny(h, stop, test))) return st;
       if ((st = launch_combine(h, 1, q1, stop, K0 ? nullptr : vk, K0 ? nullptr : ftk, partial_rows(h)))) return st;
-    } else if ((st = response_any(h, 1, vk, q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk))) {
+    } else if ((st = response_any(h, 1, vk, q1, stop, false, true, K0 ? nullptr : vk, K0 ? nullptr : ftk, test))) {
       return st;
     }
     if (rows) return KK_OK;
@@ -1701,8 +1716,9 @@ kk_status enqueue_krylov(kk_handle h, const double* delta, int m, double tol, co
 // as far as the expansion goes, where a graph of all m_max pays 2-4 us for every launch
 // after its end (six a direction). The first rank_hint directions, the rank of the last such
 // update, go out at once; after that the host waits for each solve's word before the next
-// direction, about as long as a direction enqueued in vain takes. Same launches up to the end, same
-// results. Synchronizes the stream; the final state is in h->report.
+// direction, about as long as a direction enqueued in vain takes. Between the directions that go out
+// at once, where the host doesn't wait, the solve is no launch of its own if tests_in_launch.
+// Same results. Synchronizes the stream; the final state is in h->report.
 kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double tol, const double* K0, double* Kdelta) {
   if (!h->report) {
     void* p = nullptr;
@@ -1715,11 +1731,18 @@ kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double t
   }
   kk_status st;
   if ((st = enqueue_start(h, delta, K0))) return st;
+  const int ahead = std::min(h->rank_hint, m);
+  kk::ResidualTest test{};
   for (int k = 0; k < m; ++k) {
-    if ((st = enqueue_direction(h, k, K0, false))) return st;
+    if ((st = enqueue_direction(h, k, K0, test.rank > 0 && leaves_combine(h, K0), test))) return st;
+    test.rank = 0;
+    if (k + 1 < ahead && tests_in_launch(h, k + 1)) {
+      test = {h->Ft, h->ftilde, h->kst, tol, 2 * h->natoms, k + 1};
+      continue;
+    }
     const unsigned long long seq = ++h->report_seq;
     if ((st = enqueue_solve(h, k, K0, Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
-    if (k + 1 == m || k + 1 < h->rank_hint) continue;
+    if (k + 1 == m || k + 1 < ahead) continue;
     // the word of this solve, or the stream's end (an error included, which the sync reports)
     for (int spin = 1;; ++spin) {
       if (__atomic_load_n(&h->report->word, __ATOMIC_RELAXED) >= 2 * seq) break;

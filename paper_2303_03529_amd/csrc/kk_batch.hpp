@@ -60,7 +60,7 @@ __global__ void b_reset(SysDesc* d, int* queue, int nqueue) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nqueue; i += gridDim.x * blockDim.x) queue[i] = 0;
   if (threadIdx.x == 0) {
     KrylovState* st = d[blockIdx.x].kst;
-    st->rank = 0; st->stop = 0; st->status = 0; st->pad = 0;
+    st->rank = 0; st->stop = 0; st->status = 0; st->done = 0;
     st->min_pivot = 0.0; st->max_pivot = 0.0; st->ls_residual = 1.0;
   }
 }

@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(COMBINE ? COMBINE_BLOCK : FUSED_THREADS)
   __shared__ int accepted;
   // the stop flag is read with the other loads and tested once they are issued (all of
   // them are in bounds either way), so that it costs no round trip of its own
-  const int stopped = st->stop;
+  const int done = st->done, stopped = st->stop | done;
   constexpr int NW = T / WAVE, APW = (FUSED_ATOMS + NW - 1) / NW, GPER = (NMAX + WAVE - 1) / WAVE;
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
   const int a0 = blockIdx.x * FUSED_ATOMS, a1 = min(natoms, a0 + FUSED_ATOMS);
@@ -203,7 +203,10 @@ __global__ void __launch_bounds__(COMBINE ? COMBINE_BLOCK : FUSED_THREADS)
     ob[t] = a < a1 ? offsets[a] : 0;
     oe[t] = a < a1 ? offsets[a + 1] : 0;
   }
-  if (stopped) return;  // the same value in every thread: before the first barrier
+  if (stopped) {  // in every thread alike: before the first barrier
+    if (done > 0 && blockIdx.x == 0 && threadIdx.x == 0) settle(st, done);
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < SPT; ++k) {
     const int i = threadIdx.x + k * T;
@@ -290,19 +293,31 @@ __device__ __forceinline__ void split_group8(const d2 (&v)[4], const d2 (&w)[4],
 // (U~ C)^T split at s_C s_u, grid-stride over 8-column groups. Every thread forms the
 // scales itself (a few cached loads), and its first group's operand and potentials are
 // loaded together with them, so that the block waits for memory once before it computes.
-// Grid (blocks, 2 items).
-template <bool BF16, int NP>
+// Grid (blocks, 2 items). TEST: the first block of the grid, one more than `blocks`, runs test
+// (solve_lds(test.rank) doubles of dynamic LDS).
+template <bool BF16, int NP, bool TEST>
 __global__ void split_operands_fused(const double* __restrict__ CT0, const double* __restrict__ CT1, int np,
                                      const double* __restrict__ u, const double* __restrict__ pmax, int nblk,
                                      const double* __restrict__ mconst, double beta, double* __restrict__ msc,
                                      _Float16* __restrict__ uct_h, _Float16* __restrict__ uct_l,
-                                     _Float16* __restrict__ uct_r, const int* __restrict__ stop) {
+                                     _Float16* __restrict__ uct_r, const int* __restrict__ stop,
+                                     const ResidualTest test) {
   const int z = blockIdx.y;
+  int bx = blockIdx.x, blocks = gridDim.x;
+  if constexpr (TEST) {
+    extern __shared__ double test_lds[];
+    if (bx == 0) {
+      if (z == 0) residual_test(test, test_lds);
+      return;
+    }
+    --bx;
+    --blocks;
+  }
   const double* src = z ? CT1 : CT0;
   const double* uz = u + (size_t)z * np;
   const size_t off = (size_t)z * np * np;
   const unsigned per_row = (unsigned)np / 8u, total = per_row * (unsigned)np;
-  const unsigned g0 = (unsigned)blockIdx.x * blockDim.x + threadIdx.x, gs = (unsigned)gridDim.x * blockDim.x;
+  const unsigned g0 = (unsigned)bx * blockDim.x + threadIdx.x, gs = (unsigned)blocks * blockDim.x;
   d2 v[4], w[4];
   size_t base = 0;
   if (g0 < total) {
@@ -321,7 +336,7 @@ __global__ void split_operands_fused(const double* __restrict__ CT0, const doubl
   if (stopped) return;
   const double s_u = pow2_scale(umax, 0);
   const double scale = sC * s_u;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (bx == 0 && threadIdx.x == 0) {
     const double sY = pow2_scale(0.25 * beta * umax * mconst[z * 4 + 2] * mconst[z * 4 + 3], 14);
     msc[z * 8 + 0] = 1.0 / (sC * sG * s_u);
     msc[z * 8 + 1] = sY;
@@ -351,7 +366,11 @@ __global__ void __launch_bounds__(COMBINE_BLOCK) krylov_solve(const double* __re
                                                               SolveReport* report, unsigned long long seq,
                                                               const CombineArgs comb) {
   __shared__ double fl[2 * COMBINE_BLOCK_ATOMS];
-  if (comb.natoms > 0 && st->stop == 0) {  // ends with a barrier
+  const int done = st->done;
+  if (done > 0) {
+    if (threadIdx.x == 0) settle(st, done);
+    __syncthreads();
+  } else if (comb.natoms > 0 && st->stop == 0) {  // ends with a barrier
     if (comb.split)
       comb.K0 != nullptr ? combine_block<true, true>(comb, fl, true) : combine_block<true, false>(comb, fl, true);
     else

@@ -580,7 +580,7 @@ struct KrylovState {
   int rank;       // accepted directions
   int stop;       // 1 after a breakdown, a zero starting vector or reaching the residual target
   int status;     // 0 ok, 1 breakdown, -5 singular Gram matrix
-  int pad;
+  int done;       // directions whose residual_test ended the expansion; 0: none did
   double min_pivot, max_pivot;
   double ls_residual;  // ||F~ c - f~|| / ||f~|| of the last solve
 };
@@ -600,7 +600,7 @@ __global__ void precondition(const double* __restrict__ K0, const double* __rest
                              const double* __restrict__ sub, double* __restrict__ y, int n2,
                              const int* __restrict__ stop, KrylovState* reset = nullptr) {
   if (reset != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
-    reset->rank = 0; reset->stop = 0; reset->status = 0; reset->pad = 0;
+    reset->rank = 0; reset->stop = 0; reset->status = 0; reset->done = 0;
     reset->min_pivot = 0.0; reset->max_pivot = 0.0; reset->ls_residual = 1.0;
   }
   if (stop != nullptr && *stop != 0) return;
@@ -690,19 +690,20 @@ __global__ void __launch_bounds__(1024) krylov_orthonormalize(const double* __re
   orth_dev(src, V, n2, st);
 }
 
-// O = F~^T F~, rhs = F~^T f~, Cholesky O = L L^T, c = O^-1 rhs, x = V c, and the
-// projected residual ||F~ c - f~|| / ||f~|| formed explicitly. On a non-positive
-// pivot x = 0 and status = -5. With stop_tol > 0 a residual <= stop_tol ends the
-// expansion (used by the adaptive-rank call after each direction). One block.
-__device__ __forceinline__ void solve_dev(const double* __restrict__ V, const double* Ft,
-                                          const double* __restrict__ ftilde, int n2, KrylovState* st,
-                                          double* __restrict__ x, double stop_tol, SolveReport* report = nullptr,
-                                          unsigned long long seq = 0) {
-  __shared__ double sr[2][16];
-  __shared__ double O[MAX_RANK][MAX_RANK + 1];
-  __shared__ double c[MAX_RANK];
-  __shared__ int ok;
-  const int r = st->rank;
+// O = F~^T F~, rhs = F~^T f~ of the first r directions, Cholesky O = L L^T, c = O^-1 rhs, with x given
+// x = V c (0 on a non-positive pivot), and the projected residual ||F~ c - f~|| / ||f~|| formed
+// explicitly, returned to thread 0. One block of at most 16 waves; lds: solve_lds(r) doubles. Ends
+// without a barrier.
+struct Solution {
+  double residual, min_pivot, max_pivot;
+  bool ok;  // every pivot positive
+};
+constexpr int solve_lds(int r) { return r * (r + 1) + r + 2 * 16 + 3; }
+__device__ __forceinline__ Solution least_squares(const double* __restrict__ V, const double* Ft,
+                                                  const double* __restrict__ ftilde, int n2, int r,
+                                                  double* __restrict__ x, double* lds) {
+  const int ldo = r + 1;
+  double *const O = lds, *const c = O + r * ldo, *const sr = c + r, *const fin = sr + 2 * 16;
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
   // The r (r + 1) / 2 entries of O and the r of the right-hand side, one wave each (fixed
   // lane order and reduction tree, so the result is deterministic); 4 loads per lane in flight.
@@ -733,7 +734,7 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
       }
       const double d = wave_sum_dpp((d4[0] + d4[1]) + (d4[2] + d4[3]));
       if (lane == 0) {
-        if (b >= 0) { O[a][b] = d; O[b][a] = d; }
+        if (b >= 0) { O[a * ldo + b] = d; O[b * ldo + a] = d; }
         else c[a] = d;
       }
     }
@@ -746,7 +747,7 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
     int good = 1;
     double pmin = 0.0, pmax = 0.0;
     for (int j = 0; j < r; ++j) {
-      const double dj = O[j][j];
+      const double dj = O[j * ldo + j];
       if (!(dj > 0.0)) {  // the same value in every lane
         good = 0;
         break;
@@ -755,38 +756,37 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
       pmax = (j == 0) ? dj : fmax(pmax, dj);
       const double ljj = sqrt(dj);
       const bool below = lane > j && lane < r;
-      const double lij = below ? O[lane][j] / ljj : 0.0;
-      if (lane == j) O[j][j] = ljj;
-      if (below) O[lane][j] = lij;
+      const double lij = below ? O[lane * ldo + j] / ljj : 0.0;
+      if (lane == j) O[j * ldo + j] = ljj;
+      if (below) O[lane * ldo + j] = lij;
       for (int k = j + 1; k < r; ++k) {
         const double lkj = lane_f64(lij, k);
-        if (below && k <= lane) O[lane][k] -= lij * lkj;
+        if (below && k <= lane) O[lane * ldo + k] -= lij * lkj;
       }
       __builtin_amdgcn_wave_barrier();
     }
     if (good) {
       double ci = lane < r ? c[lane] : 0.0;
       for (int j = 0; j < r; ++j) {  // L y = rhs
-        const double yj = lane_f64(ci / O[j][j], j);
+        const double yj = lane_f64(ci / O[j * ldo + j], j);
         if (lane == j) ci = yj;
-        else if (lane > j && lane < r) ci -= O[lane][j] * yj;
+        else if (lane > j && lane < r) ci -= O[lane * ldo + j] * yj;
       }
       for (int j = r - 1; j >= 0; --j) {  // L^T c = y
-        const double xj = lane_f64(ci / O[j][j], j);
+        const double xj = lane_f64(ci / O[j * ldo + j], j);
         if (lane == j) ci = xj;
-        else if (lane < j) ci -= O[j][lane] * xj;
+        else if (lane < j) ci -= O[j * ldo + lane] * xj;
       }
       if (lane < r) c[lane] = ci;
     }
     if (lane == 0) {
-      ok = good;
-      if (!good) st->status = -5;
-      st->min_pivot = pmin;
-      st->max_pivot = pmax;
+      fin[0] = good;
+      fin[1] = pmin;
+      fin[2] = pmax;
     }
   }
   __syncthreads();
-  const int okv = ok;
+  const bool okv = fin[0] != 0.0;
   double rr = 0.0, ff = 0.0;
   for (int i = threadIdx.x; i < n2; i += blockDim.x) {
     double s = 0.0, fi = 0.0;
@@ -796,7 +796,7 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
         double vv[4], fv[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          vv[q] = V[(size_t)(k + q) * n2 + i];
+          vv[q] = x != nullptr ? V[(size_t)(k + q) * n2 + i] : 0.0;
           fv[q] = Ft[(size_t)(k + q) * n2 + i];
         }
 #pragma unroll
@@ -806,11 +806,11 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
         }
       }
       for (; k < r; ++k) {
-        s += c[k] * V[(size_t)k * n2 + i];
+        s += c[k] * (x != nullptr ? V[(size_t)k * n2 + i] : 0.0);
         fi += c[k] * Ft[(size_t)k * n2 + i];
       }
     }
-    x[i] = s;
+    if (x != nullptr) x[i] = s;
     const double fti = ftilde[i];
     const double e = fi - fti;
     rr += e * e;
@@ -819,26 +819,65 @@ __device__ __forceinline__ void solve_dev(const double* __restrict__ V, const do
   rr = wave_sum_dpp(rr);
   ff = wave_sum_dpp(ff);
   if (lane == 0) {
-    sr[0][wave] = rr;
-    sr[1][wave] = ff;
+    sr[wave] = rr;
+    sr[16 + wave] = ff;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    rr = 0.0;
-    ff = 0.0;
+  rr = 0.0;
+  ff = 0.0;
+  if (threadIdx.x == 0)
     for (int q = 0; q < nw; ++q) {
-      rr += sr[0][q];
-      ff += sr[1][q];
+      rr += sr[q];
+      ff += sr[16 + q];
     }
-    const double res = ff > 0.0 ? sqrt(rr / ff) : 0.0;
-    st->ls_residual = res;
+  return {ff > 0.0 ? sqrt(rr / ff) : 0.0, fin[1], fin[2], okv};
+}
+
+// The solve on the accepted directions. On a non-positive pivot x = 0 and status = -5. With
+// stop_tol > 0 a residual <= stop_tol ends the expansion (used by the adaptive-rank call after
+// each direction). One block.
+__device__ __forceinline__ void solve_dev(const double* __restrict__ V, const double* Ft,
+                                          const double* __restrict__ ftilde, int n2, KrylovState* st,
+                                          double* __restrict__ x, double stop_tol, SolveReport* report = nullptr,
+                                          unsigned long long seq = 0) {
+  __shared__ double lds[solve_lds(MAX_RANK)];
+  const Solution sol = least_squares(V, Ft, ftilde, n2, st->rank, x, lds);
+  if (threadIdx.x == 0) {
+    if (!sol.ok) st->status = -5;
+    st->min_pivot = sol.min_pivot;
+    st->max_pivot = sol.max_pivot;
+    st->ls_residual = sol.residual;
     int stop = st->stop;
-    if (stop_tol > 0.0 && okv && res <= stop_tol) st->stop = stop = 1;
+    if (stop_tol > 0.0 && sol.ok && sol.residual <= stop_tol) st->stop = stop = 1;
     if (report != nullptr) {
       __hip_atomic_store(&report->word, 2 * seq + (stop != 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       report->st = *st;
     }
   }
+}
+
+// An adaptive update's test between two directions as one block of a launch of the second of them
+// (rank > 0; tol > 0): whether the residual of the first `rank` directions is <= tol. The word goes
+// into st->done, which nothing in that launch reads; the next orth_potentials or solve ends
+// the expansion at that rank (settle). As a launch of its own, 9 us a direction at 16 and
+// 10 us at 128 atoms, it stood in the chain between two directions.
+struct ResidualTest {
+  const double *Ft, *ftilde;
+  KrylovState* st;
+  double tol;
+  int n2, rank;
+};
+constexpr int RESIDUAL_TEST_MAX_RANK = 16;
+__device__ __forceinline__ void residual_test(const ResidualTest& t, double* lds) {
+  if (t.st->rank < t.rank || t.st->done != 0) return;  // the expansion had ended before
+  const Solution sol = least_squares(nullptr, t.Ft, t.ftilde, t.n2, t.rank, nullptr, lds);
+  if (threadIdx.x == 0 && sol.ok && sol.residual <= t.tol) t.st->done = t.rank;
+}
+// The end of the expansion that a residual_test found, whatever the directions after it did. One thread.
+__device__ __forceinline__ void settle(KrylovState* st, int done) {
+  st->stop = 1;
+  st->rank = done;
+  st->status = 0;
 }
 
 // Host-side copies of the argument lists of precondition and krylov_solve (SolveArgs; declaration

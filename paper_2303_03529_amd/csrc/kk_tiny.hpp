@@ -54,14 +54,20 @@ struct TinyArgs {
 
 __device__ __forceinline__ d2 tiny_load(const double* p) { return *reinterpret_cast<const d2*>(p); }
 
-template <int U>
-__global__ __launch_bounds__(TINY_THREADS) void tiny_forward(const TinyArgs a) {
+// Grid (tile pairs, 2 spins); TEST: one block more in each spin, the first of which runs test.
+template <int U, bool TEST>
+__global__ __launch_bounds__(TINY_THREADS) void tiny_forward(const TinyArgs a, const ResidualTest test) {
   constexpr int T = TINY_TILE;
   __shared__ double red[TINY_WAVES][T * T];
   __shared__ double yt[T][T + 1];
+  static_assert(TINY_WAVES * T * T >= solve_lds(RESIDUAL_TEST_MAX_RANK), "the test's LDS");
+  if (TEST && blockIdx.x == 0) {
+    if (blockIdx.y == 0) residual_test(test, &red[0][0]);
+    return;
+  }
   const int stopped = *a.stop;
   const TinyArgs::Item& it = a.item[blockIdx.y];
-  int I = 0, rem = blockIdx.x;
+  int I = 0, rem = TEST ? blockIdx.x - 1 : blockIdx.x;
   while (rem >= a.tiles - I) {
     rem -= a.tiles - I;
     ++I;

@@ -1,6 +1,6 @@
 """The short launch chains of small systems: f~ formed by the launch that orthonormalizes the next
-direction (tiny FP64 handles; the smallest split ones and those with a dense K0), and the two-launch
-FP64 transforms.
+direction (tiny FP64 handles; the smallest split ones and those with a dense K0), the two-launch
+FP64 transforms, and the adaptive update's residual tests inside another launch.
 
 The update against the same Krylov expansion in numpy, its responses from the handle's own
 density_response_batch, which has none of these. FP64 within 1e-9: the two orders of the sums differ by
@@ -72,3 +72,29 @@ def test_update(atoms, dense, precision):
     print(atoms, dense, precision, rel(got[0], want), flush=True)
     assert np.array_equal(got[0], got[1])
     assert rel(got[0], want) < TOL[precision]
+
+
+@pytest.mark.parametrize("precision", PRECISIONS, ids=IDS)
+@pytest.mark.parametrize("atoms", [12, 64, 100])
+def test_adaptive_ranks(atoms, precision):
+    """A handle's later adaptive updates enqueue as many directions at once as its last one took:
+    more, fewer and as many as the next needs, each with the rank and the result of a fresh handle."""
+    y, delta, _ = case(atoms, False)
+    h = prepared(y, precision)
+    try:
+        _, residuals = reference(h, delta, 6, None)
+        cuts = [0.5 * (residuals[r - 1] + residuals[r - 2]) for r in (5, 5, 2, 4, 3, 3)]
+        got = [h.krylov_kernel_apply_adaptive(t(delta), 8, cut) for cut in cuts]
+        short = h.krylov_kernel_apply_adaptive(t(delta), 2, cuts[0])  # m_max below the last rank
+    finally:
+        h.close()
+    assert [g[1].rank_used for g in got] == [5, 5, 2, 4, 3, 3] and short[1].rank_used == 2
+    for (x, info), cut, m_max in zip(got + [short], cuts + cuts[:1], [8] * 6 + [2]):
+        h = prepared(y, precision)
+        try:
+            want, fresh = h.krylov_kernel_apply_adaptive(t(delta), m_max, cut)
+        finally:
+            h.close()
+        assert info.rank_used == fresh.rank_used and info.status == fresh.status == 0
+        assert abs(info.ls_residual - fresh.ls_residual) <= TOL[precision]
+        assert rel(x.cpu().numpy(), want.cpu().numpy()) < TOL[precision]
