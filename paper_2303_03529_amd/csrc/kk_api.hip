@@ -1096,6 +1096,14 @@ kk_status check_handle(kk_handle h) {
   return KK_OK;
 }
 
+// The spectrum's arrays and scalars.
+kk::SpectrumArgs spectrum_args(kk_handle h) {
+  kk::SpectrumArgs a{};
+  for (int s = 0; s < 2; ++s) { a.eps[s] = h->eps[s]; a.f[s] = h->f[s]; a.fc[s] = h->fc[s]; a.w[s] = h->w[s]; }
+  a.mu = h->mu; a.wsum = h->wsum; a.nb = h->nb; a.np = h->np; a.n_e = h->n_e; a.beta = h->beta;
+  return a;
+}
+
 // The forward transform's tile list and tile sides, whose active part the window tables hold.
 struct ForwardTiles {
   const int2* tiles;
@@ -1123,6 +1131,26 @@ static_assert(kk::FwdCfg::BM == kk::BackCfg::BM && kk::FwdCfg::BN == kk::BackCfg
 // handles are of the first kind.
 bool use_window(kk_handle h, const ForwardTiles& ft, int cus) {
   return h->kch == 1 && 2 * (h->np / ft.bm) * (h->np / ft.bn) > cus;
+}
+
+// The window tables of the prepared spectrum, with the active tiles of the forward transform if
+// with_tiles. Handles whose transforms do not go by them have none until a reverse pass wants them.
+kk_status window_tables(kk_handle h, bool with_tiles) {
+  const ForwardTiles ft = forward_tiles(h);
+  kk::SpectrumArgs a = spectrum_args(h);
+  for (int s = 0; s < 2; ++s) {
+    a.act[s] = const_cast<unsigned char*>(h->win.act[s]);
+    a.range[s] = const_cast<int2*>(h->win.range[s]);
+    a.tiles[s] = const_cast<int2*>(h->win.tiles[s]);
+  }
+  a.count = const_cast<int*>(h->win.count);
+  a.tiles_in = ft.tiles; a.ntiles = with_tiles ? ft.n : 0;
+  a.bm = ft.bm / kk::WIN; a.bn = ft.bn / kk::WIN;
+  a.exact_cut = h->precision == KK_MIXED_F16;
+  a.cut = a.exact_cut ? kk::WIN_CUT_F16 : kk::WIN_CUT;
+  kk::window_tables<<<2, kk::SPECTRUM_MAX_THREADS, 0, h->stream>>>(a);
+  LAUNCH_CHECK("window_tables");
+  return KK_OK;
 }
 
 // Every device buffer of a prepared handle for its (natoms, np, precision),
@@ -1386,23 +1414,19 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
   kk::setup_copies<<<dim3(pg.x, pg.y, kk::SETUP_COPIES_Z), pb, 0, h->stream>>>(sc);
   LAUNCH_CHECK("setup_copies");
   // chemical potential, occupations and their weights, with the levels in padded arrays
-  kk::SpectrumArgs sp{};
+  kk::SpectrumArgs sp = spectrum_args(h);
   sp.e[0] = eps_up; sp.e[1] = eps_dn;
-  for (int s = 0; s < 2; ++s) { sp.eps[s] = h->eps[s]; sp.f[s] = h->f[s]; sp.fc[s] = h->fc[s]; sp.w[s] = h->w[s]; }
-  sp.mu = h->mu; sp.wsum = h->wsum; sp.nb = nb; sp.np = np; sp.n_e = n_electrons; sp.beta = h->beta;
-  const ForwardTiles ft = forward_tiles(h);
-  for (int s = 0; s < 2; ++s) {
-    sp.act[s] = const_cast<unsigned char*>(h->win.act[s]);
-    sp.range[s] = const_cast<int2*>(h->win.range[s]);
-    sp.tiles[s] = const_cast<int2*>(h->win.tiles[s]);
-  }
-  sp.count = const_cast<int*>(h->win.count);
-  sp.tiles_in = ft.tiles; sp.ntiles = split_large ? 0 : ft.n;  // a batch has tile lists of its own
-  sp.bm = ft.bm / kk::WIN; sp.bn = ft.bn / kk::WIN;
-  sp.exact_cut = precision == KK_MIXED_F16;
-  sp.cut = sp.exact_cut ? kk::WIN_CUT_F16 : kk::WIN_CUT;
-  kk::spectrum<<<1, kk::SPECTRUM_THREADS, 0, h->stream>>>(sp);
+  if (nb <= 256)
+    kk::spectrum<256, 1><<<1, 256, 0, h->stream>>>(sp);
+  else if (nb <= 512)
+    kk::spectrum<512, 1><<<1, 512, 0, h->stream>>>(sp);
+  else if (nb <= 2048)
+    kk::spectrum<1024, 2><<<1, 1024, 0, h->stream>>>(sp);
+  else
+    kk::spectrum<1024, 9><<<1, 1024, 0, h->stream>>>(sp);
   LAUNCH_CHECK("spectrum");
+  // (a batch, split_large, has tile lists of its own)
+  if ((h->windowed || split_large) && (st = window_tables(h, !split_large))) return st;
   kk::GemmArgs a{};
   a.n = np; a.k_half = h->kc; a.two_halves = 0; a.ntiles = h->n_store; a.tiles = h->tiles_store;
   a.stop = nullptr; a.nitems = 2;
@@ -2394,6 +2418,7 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double* delta, int m, const d
   const int npairs = want_H ? h->an0 + h->an1 : 0;
 
   if (want_H) {
+    if (!h->windowed && h->precision != KK_MIXED_F16 && (st = window_tables(h, true))) return st;
     if ((st = zero(h, h->aD, 2 * np2))) return st;
     if ((st = zero(h, h->agdiag, 2 * (size_t)np))) return st;
     if (npairs > 0 && (st = zero(h, h->apk, npairs))) return st;

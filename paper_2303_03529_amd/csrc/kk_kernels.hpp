@@ -18,15 +18,14 @@ constexpr int MAX_RANK = 64;
 // Sum over the wave by exchanges with lane ^ 32, 16, 8, 4, 2, 1 in turn, the same bits in every lane.
 // (After the first three steps values repeat every 8 lanes, so a rotation by 4 is the exchange
 // with lane ^ 4.)
-__device__ __forceinline__ double wave_sum(double v) {
-  v = add_xor<32>(v);
-  v = add_xor<16>(v);
+__device__ __forceinline__ double row_sum(double v) {  // of a row of 16 lanes
   v += dpp_f64<0x128>(v);  // row_ror:8
   v += dpp_f64<0x124>(v);  // row_ror:4
   v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   return v;
 }
+__device__ __forceinline__ double wave_sum(double v) { return row_sum(add_xor<16>(add_xor<32>(v))); }
 __device__ __forceinline__ double wave_max(double v) {
   v = fmax(v, lane_xor<32>(v));
   v = fmax(v, lane_xor<16>(v));
@@ -134,8 +133,12 @@ __global__ void transpose_sq(const TransposeArgs a, int np) {
   for (int q = 0; q < 4; ++q) dst[(size_t)(by + ty + 8 * q) * np + bx + tx] = t[tx][ty + 8 * q];
 }
 
+// From 40 kT below mu on it rounds to one, and a wave of such levels (most of them, in order) is
+// spared the exponential and the division.
 __device__ __forceinline__ double occ(double e, double mu, double beta) {
-  return 1.0 / (1.0 + exp(beta * (e - mu)));
+  const double x = beta * (e - mu);
+  if (x < -40.0) return 1.0;
+  return 1.0 / (1.0 + exp(x));
 }
 
 // Sec. II.C: the spectrum of a prepared expansion point in one launch of one block. One
@@ -152,7 +155,13 @@ __device__ __forceinline__ double occ(double e, double mu, double beta) {
 // Newton iteration that does not settle. The count is monotone and its slope changes by at most a
 // factor e per kT, so farther out its sign is that of the midpoint's side: mu has the same bits
 // either way. Against 57 counts, and with the occupations and the sum as launches of their own:
-// 16 atoms 65 + 14 -> 30 us, 128 atoms 89 + 14 -> 37 us, 1024 atoms 393 + 20 -> 123 us.
+// 16 atoms 65 + 14 -> 30 us, 128 atoms 89 + 14 -> 37 us, 1024 atoms 393 + 20 -> 123 us. Of what was left
+// much was instructions that every wave repeats, so the sums take one barrier and half the final
+// exchanges, the known halvings are one wave's, and the block has 256 or 512 threads where those
+// hold the levels; the window tables are a launch of their own where they are used: with
+// tables 31 us at 16 and 43 us at 128 atoms, now 14.5 and 28 us (tables 10 us at 200 atoms). The counts
+// with both midpoints that can follow, two halvings a reduction, cost more exponentials
+// than the reductions they spared (8.0 against 5.3 us at 16 atoms).
 struct SpectrumArgs {
   const double* e[2];                    // levels of each spin, nb
   double *eps[2], *f[2], *fc[2], *w[2];  // np each
@@ -181,32 +190,35 @@ constexpr double SPECTRUM_NOISE = 2e-14;
 //   both pieces of Y, so leaving the block out changes no bit of the products.
 constexpr double WIN_CUT = 0x1p-60, WIN_CUT_F16 = 0x1p-42;
 constexpr int WIN_MAX_BLOCKS = 1024;  // Nb <= 65536
-constexpr int SPECTRUM_THREADS = 1024, SPECTRUM_PER = 9;  // levels per thread and spin kept in registers
+constexpr int SPECTRUM_MAX_THREADS = 1024;
 
-// Sums of a pair over the block, the same bits in every thread, with one barrier: buf alternates
+// Sums of N values over the block, the same bits in every thread, with one barrier: buf alternates
 // between calls, so a wave still reading one call's partial sums never sees the next call's.
-__device__ __forceinline__ d2 block_sum_pair(double a, double b, double (*sh)[SPECTRUM_THREADS / WAVE][2], int& buf) {
-  constexpr int NW = SPECTRUM_THREADS / WAVE;
+// EXACT: to block_sum's bits (those of a block of 1024 threads too, if only the first T hold levels).
+template <int NW, int N, bool EXACT>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*sh)[NW][2], int& buf) {
+  static_assert(N <= 2, "sh");
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-  a = wave_sum_dpp(a);
-  b = wave_sum_dpp(b);
-  if (lane == 0) {
-    sh[buf][wave][0] = a;
-    sh[buf][wave][1] = b;
-  }
+#pragma unroll
+  for (int q = 0; q < N; ++q) v[q] = EXACT ? wave_sum(v[q]) : wave_sum_dpp(v[q]);
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < N; ++q) sh[buf][wave][q] = v[q];
   __syncthreads();
-  const double x = lane < NW ? sh[buf][lane][0] : 0.0, y = lane < NW ? sh[buf][lane][1] : 0.0;
+  // (block_sum's first two exchanges here would add zeros: the waves' sums fill one row)
+  static_assert(NW <= 16, "a row");
+#pragma unroll
+  for (int q = 0; q < N; ++q) v[q] = row_sum((lane & 15) < NW ? sh[buf][lane & 15][q] : 0.0);
   buf ^= 1;
-  return d2{wave_sum_dpp(x), wave_sum_dpp(y)};
 }
 
-__global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs a) {
-  constexpr int T = SPECTRUM_THREADS, PER = SPECTRUM_PER, NW = T / WAVE;
-  __shared__ double sh[17], pair[2][NW][2];
+// T: threads, 256 or 512 where they hold a level of each spin each (fewer waves repeat what every
+// wave computes alike), else 1024. PER: levels per thread and spin kept in registers.
+template <int T, int PER>
+__global__ void __launch_bounds__(T) spectrum(const SpectrumArgs a) {
+  constexpr int NW = T / WAVE;
+  __shared__ double sums[2][NW][2], ends[3];
   __shared__ double smin[NW], smax[NW];
-  __shared__ double bmin[2][WIN_MAX_BLOCKS], bmax[2][WIN_MAX_BLOCKS];  // levels of each window block
-  __shared__ double bf[WIN_MAX_BLOCKS], bfc[WIN_MAX_BLOCKS];           // largest f and 1 - f of one spin's
-  __shared__ int blo[WIN_MAX_BLOCKS], bhi[WIN_MAX_BLOCKS], wcount[NW];
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE, nb = a.nb;
   const double beta = a.beta, n_e = a.n_e, kT = 1.0 / beta;
   int buf = 0;
@@ -240,7 +252,6 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
     lo = fmin(lo, smin[q]);
     hi = fmax(hi, smax[q]);
   }
-  const double e_min = lo, e_max = hi;
   lo -= 40.0 * kT;
   hi += 40.0 * kT;
 
@@ -249,13 +260,13 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
   {
     double l = lo, h = hi, step = hi - lo;
     for (int it = 0; it < 24; ++it) {
-      double c = 0.0, d = 0.0;
+      double s[2] = {0.0, 0.0};
       levels(nb, [&](int, double u, double v) {
         const double fu = occ(u, root, beta), fv = occ(v, root, beta);
-        c += fu + fv;
-        d += fu * (1.0 - fu) + fv * (1.0 - fv);
+        s[0] += fu + fv;
+        s[1] += fu * (1.0 - fu) + fv * (1.0 - fv);
       });
-      const d2 s = block_sum_pair(c, d, pair, buf);
+      block_sums<NW, 2, false>(s, sums, buf);
       const double resid = s[0] - n_e, slope = beta * s[1];
       const double near = SPECTRUM_NOISE * n_e / slope + 1e-14 * fabs(root);
       if (fabs(resid) <= 0.05 * SPECTRUM_NOISE * n_e) {
@@ -270,34 +281,72 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
       root = next;
     }
   }
-  for (int iter = 0; iter < 400; ++iter) {
+  const auto ended = [&](double mid) __attribute__((always_inline)) { return hi - lo <= 1e-15 * fmax(1.0, fabs(mid)); };
+  bool end = false;
+  // the halvings of a certain outcome, up to the first that is to be counted, by one wave
+  if (margin < 1e300) {
+    if (wave == 0) {
+      if (margin > 1e-15 * fmax(1.0, fmax(fabs(lo), fabs(hi)))) {
+        // half the bracket stays above the margin, so the width at which the bisection ends is
+        // not reached. Four halvings to a branch, by the halves of lo and hi (0.5 (lo + hi) to the bit).
+        double hl = 0.5 * lo, hh = 0.5 * hi;
+        bool on = true;
+        for (int iter = 0; iter < 400 && on; iter += 4)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double mid = hl + hh, d = mid - root, half = 0.5 * mid;
+            on = on && fabs(d) > margin;
+            hl = on && d < 0.0 ? half : hl;
+            hh = on && !(d < 0.0) ? half : hh;
+          }
+        lo = 2.0 * hl;
+        hi = 2.0 * hh;
+      } else {
+        for (int iter = 0; iter < 400; ++iter) {
+          const double mid = 0.5 * (lo + hi);
+          if (!(fabs(mid - root) > margin)) break;
+          if (mid < root) lo = mid; else hi = mid;
+          if ((end = ended(mid))) break;
+        }
+      }
+      if (lane == 0) {
+        ends[0] = lo;
+        ends[1] = hi;
+        ends[2] = end;
+      }
+    }
+    __syncthreads();
+    lo = ends[0];
+    hi = ends[1];
+    end = ends[2] != 0.0;
+  }
+  for (int iter = 0; iter < 400 && !end; ++iter) {
     const double mid = 0.5 * (lo + hi);
     bool below = mid < root;
     if (!(fabs(mid - root) > margin)) {
-      double c = 0.0;
-      levels(nb, [&](int, double u, double v) { c += occ(u, mid, beta) + occ(v, mid, beta); });
-      c = block_sum(c, sh);
-      below = c < n_e;
+      double c[1] = {0.0};
+      levels(nb, [&](int, double u, double v) { c[0] += occ(u, mid, beta) + occ(v, mid, beta); });
+      block_sums<NW, 1, true>(c, sums, buf);
+      below = c[0] < n_e;
     }
     if (below) lo = mid; else hi = mid;
-    if (hi - lo <= 1e-15 * fmax(1.0, fabs(mid))) break;
+    end = ended(mid);
   }
   double mu = 0.5 * (lo + hi);
   for (int it = 0; it < 3; ++it) {
-    double c = 0.0, d = 0.0;
+    double s[2] = {0.0, 0.0};
     levels(nb, [&](int, double u, double v) {
       const double fu = occ(u, mu, beta), fd = occ(v, mu, beta);
-      c += fu + fd;
-      d += fu * occ(-u, -mu, beta) + fd * occ(-v, -mu, beta);
+      s[0] += fu + fd;
+      s[1] += fu * occ(-u, -mu, beta) + fd * occ(-v, -mu, beta);
     });
-    c = block_sum(c, sh);
-    d = block_sum(d, sh) * beta;
-    const double resid = c - n_e;
+    block_sums<NW, 2, true>(s, sums, buf);
+    const double d = s[1] * beta, resid = s[0] - n_e;
     if (d <= 0.0 || fabs(resid) <= 1e-13 * n_e) break;
     mu -= resid / d;
   }
   if (tid == 0) *a.mu = mu;
-  double ws = 0.0, ref = 0.0;
+  double ws[1] = {0.0};
   levels(a.np, [&](int i, double u, double v) {  // whole waves: np and the strides are multiples of 64
     double w[2];
 #pragma unroll
@@ -309,86 +358,112 @@ __global__ void __launch_bounds__(SPECTRUM_THREADS) spectrum(const SpectrumArgs 
       a.f[s][i] = f;
       a.fc[s][i] = fc;
       a.w[s][i] = w[s];
-      ref = fmax(ref, f * fc);
-      // the block's lowest and highest level; a NaN makes them unbounded, an all-padding block
-      // keeps them reversed
-      const bool nan = __any(in && !(e == e && mu == mu));
-      double bl = in ? e : INFINITY, bh = in ? e : -INFINITY;
-      bl = -wave_max(-bl);
-      bh = wave_max(bh);
-      if (lane == 0) {
-        bmin[s][i / WIN] = nan ? -INFINITY : bl;
-        bmax[s][i / WIN] = nan ? INFINITY : bh;
-      }
     }
-    ws += w[0] + w[1];
+    ws[0] += w[0] + w[1];
   });
-  ws = block_sum(ws, sh);
-  if (tid == 0) *a.wsum = ws;
+  block_sums<NW, 1, true>(ws, sums, buf);
+  if (tid == 0) *a.wsum = ws[0];
+}
 
-  // Window tables
+// The window tables of a spectrum, one block for each spin.
+__global__ void __launch_bounds__(SPECTRUM_MAX_THREADS) window_tables(const SpectrumArgs a) {
+  constexpr int T = SPECTRUM_MAX_THREADS, NW = T / WAVE;
+  __shared__ double smin[NW], smax[NW], sref[NW];
+  __shared__ double bmin[WIN_MAX_BLOCKS], bmax[WIN_MAX_BLOCKS];  // levels of each window block
+  __shared__ double bf[WIN_MAX_BLOCKS], bfc[WIN_MAX_BLOCKS];     // its largest f and 1 - f
+  __shared__ int blo[WIN_MAX_BLOCKS], bhi[WIN_MAX_BLOCKS], wcount[NW];
   static_assert(WIN == WAVE, "a wave's levels are a window block");
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE, nb = a.nb, s = blockIdx.x;
   const int nblk = a.np / WIN;
+  const double beta = a.beta, mu = *a.mu;
+  double e_min = 1e300, e_max = -1e300, ref = 0.0;  // of both spins
+  for (int i = tid; i < a.np; i += T) {             // whole waves: np and the strides are multiples of 64
+    const bool in = i < nb;
+    const double e = a.eps[s][i], other = a.eps[1 - s][i];
+    if (in) {
+      e_min = fmin(e_min, fmin(e, other));
+      e_max = fmax(e_max, fmax(e, other));
+      ref = fmax(ref, fmax(a.f[s][i] * a.fc[s][i], a.f[1 - s][i] * a.fc[1 - s][i]));
+    }
+    // the block's lowest and highest level; a NaN makes them unbounded, an all-padding block keeps
+    // them reversed
+    const bool nan = __any(in && !(e == e && mu == mu));
+    double bl = in ? e : INFINITY, bh = in ? e : -INFINITY;
+    bl = -wave_max(-bl);
+    bh = wave_max(bh);
+    if (lane == 0) {
+      bmin[i / WIN] = nan ? -INFINITY : bl;
+      bmax[i / WIN] = nan ? INFINITY : bh;
+    }
+  }
+  e_min = -wave_max(-e_min);
+  e_max = wave_max(e_max);
   ref = wave_max(ref);
-  if (lane == 0) smax[wave] = ref;
+  if (lane == 0) {
+    smin[wave] = e_min;
+    smax[wave] = e_max;
+    sref[wave] = ref;
+  }
   __syncthreads();
-  for (int q = 0; q < NW; ++q) ref = fmax(ref, smax[q]);
+  for (int q = 0; q < NW; ++q) {
+    e_min = fmin(e_min, smin[q]);
+    e_max = fmax(e_max, smax[q]);
+    ref = fmax(ref, sref[q]);
+  }
   const double wide = beta * (e_max - e_min);
   ref = fmax(ref, occ(e_min, mu, beta) * occ(-e_max, -mu, beta) * (wide > 0.0 ? -expm1(-wide) / wide : 1.0));
   const double cut = a.exact_cut ? a.cut : a.cut * ref;
-  for (int s = 0; s < 2; ++s) {
-    for (int b = tid; b < nblk; b += T) {  // f falls with the level, so the block's ends bound it
-      const bool any = bmin[s][b] <= bmax[s][b];
-      bf[b] = any ? (isinf(bmin[s][b]) ? 1.0 : occ(bmin[s][b], mu, beta)) : 0.0;
-      bfc[b] = any ? (isinf(bmax[s][b]) ? 1.0 : occ(-bmax[s][b], -mu, beta)) : 0.0;
-      blo[b] = INT_MAX;
-      bhi[b] = 0;
-    }
-    __syncthreads();
-    for (int p = tid; p < nblk * nblk; p += T) {
-      const int I = p / nblk, J = p - I * nblk;
-      const double imin = bmin[s][I], imax = bmax[s][I], jmin = bmin[s][J], jmax = bmax[s][J];
-      double bound = 0.0;
-      if (!(imin > jmax)) bound = bf[I] * bfc[J];
-      if (!(jmin > imax)) bound = fmax(bound, bf[J] * bfc[I]);
-      const double z = beta * fmax(jmin - imax, imin - jmax);
-      if (z > 1.0) bound /= z;
-      const bool on = imin <= imax && jmin <= jmax && !(bound < cut);
-      if (on) {
-        atomicMin(&blo[J], I);
-        atomicMax(&bhi[J], I + 1);
-      }
-      a.act[s][p] = on || I == J;
-    }
-    __syncthreads();
-    for (int b = tid; b < nblk; b += T) a.range[s][b] = bhi[b] > 0 ? make_int2(blo[b] * WIN, bhi[b] * WIN) : make_int2(0, 0);
-    int on_before = 0, off_before = 0;
-    for (int base = 0; base < a.ntiles; base += T) {
-      const int t = base + tid;
-      bool on = false;
-      int2 tile = make_int2(0, 0);
-      if (t < a.ntiles) {
-        tile = a.tiles_in[t];
-        for (int i = 0; i < a.bm; ++i)
-          for (int j = 0; j < a.bn; ++j) on |= a.act[s][(size_t)(tile.x * a.bm + i) * nblk + tile.y * a.bn + j] != 0;
-      }
-      const unsigned long long ball = __ballot(on);
-      if (lane == 0) wcount[wave] = __popcll(ball);
-      __syncthreads();
-      int before = 0, total = 0;
-      for (int q = 0; q < NW; ++q) {
-        if (q < wave) before += wcount[q];
-        total += wcount[q];
-      }
-      before += __popcll(ball & ((1ull << lane) - 1));
-      if (t < a.ntiles)
-        a.tiles[s][on ? on_before + before : a.ntiles - 1 - (off_before + tid - before)] = tile;
-      on_before += total;
-      off_before += min(T, a.ntiles - base) - total;
-      __syncthreads();
-    }
-    if (tid == 0) a.count[s] = on_before;
+  for (int b = tid; b < nblk; b += T) {  // f falls with the level, so the block's ends bound it
+    const bool any = bmin[b] <= bmax[b];
+    bf[b] = any ? (isinf(bmin[b]) ? 1.0 : occ(bmin[b], mu, beta)) : 0.0;
+    bfc[b] = any ? (isinf(bmax[b]) ? 1.0 : occ(-bmax[b], -mu, beta)) : 0.0;
+    blo[b] = INT_MAX;
+    bhi[b] = 0;
   }
+  __syncthreads();
+  for (int p = tid; p < nblk * nblk; p += T) {
+    const int I = p / nblk, J = p - I * nblk;
+    const double imin = bmin[I], imax = bmax[I], jmin = bmin[J], jmax = bmax[J];
+    double bound = 0.0;
+    if (!(imin > jmax)) bound = bf[I] * bfc[J];
+    if (!(jmin > imax)) bound = fmax(bound, bf[J] * bfc[I]);
+    const double z = beta * fmax(jmin - imax, imin - jmax);
+    if (z > 1.0) bound /= z;
+    const bool on = imin <= imax && jmin <= jmax && !(bound < cut);
+    if (on) {
+      atomicMin(&blo[J], I);
+      atomicMax(&bhi[J], I + 1);
+    }
+    a.act[s][p] = on || I == J;
+  }
+  __syncthreads();
+  for (int b = tid; b < nblk; b += T) a.range[s][b] = bhi[b] > 0 ? make_int2(blo[b] * WIN, bhi[b] * WIN) : make_int2(0, 0);
+  int on_before = 0, off_before = 0;
+  for (int base = 0; base < a.ntiles; base += T) {
+    const int t = base + tid;
+    bool on = false;
+    int2 tile = make_int2(0, 0);
+    if (t < a.ntiles) {
+      tile = a.tiles_in[t];
+      for (int i = 0; i < a.bm; ++i)
+        for (int j = 0; j < a.bn; ++j) on |= a.act[s][(size_t)(tile.x * a.bm + i) * nblk + tile.y * a.bn + j] != 0;
+    }
+    const unsigned long long ball = __ballot(on);
+    if (lane == 0) wcount[wave] = __popcll(ball);
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int q = 0; q < NW; ++q) {
+      if (q < wave) before += wcount[q];
+      total += wcount[q];
+    }
+    before += __popcll(ball & ((1ull << lane) - 1));
+    if (t < a.ntiles)
+      a.tiles[s][on ? on_before + before : a.ntiles - 1 - (off_before + tid - before)] = tile;
+    on_before += total;
+    off_before += min(T, a.ntiles - base) - total;
+    __syncthreads();
+  }
+  if (tid == 0) a.count[s] = on_before;
 }
 
 // out[s*natoms + I] = sum_{i in I} sum_k X_s[i][k] * Y_s[i][k] * wk_s[k], one block of

@@ -57,3 +57,21 @@ def test_insulator(gap):
     _, mu, q = charges(e, e, 6.0, 6)
     assert -1.0 + 30 * KT < mu < gap - 30 * KT
     assert np.allclose(q, [2, 2, 2, 0, 0, 0] + [0] * 6, rtol=0.0, atol=1e-12)
+
+
+@pytest.mark.parametrize("nb", [255, 256, 257, 511, 512, 513, 1024])
+def test_block_sizes(nb):
+    """Both sides of where the block grows from 256 to 512 and 1024 threads; a metal, with the levels
+    in any order, and an insulator."""
+    rng = np.random.default_rng(nb)
+    e_up, e_dn = (rng.uniform(-30.0, 25.0, nb) for _ in range(2))
+    off, mu, q = charges(e_up, e_dn, 1.7 * nb, 50)
+    ref = solve_mu([np.sort(e_up), np.sort(e_dn)], 1.7 * nb, KT)
+    f = [np.add.reduceat(fermi(e, ref, KT), off[:-1]) for e in (e_up, e_dn)]
+    assert abs(mu - ref) <= 1e-13 * 55.0, (mu, ref)
+    assert np.allclose(q, np.concatenate([f[0] + f[1], f[0] - f[1]]), rtol=0.0, atol=1e-12 * nb / 50)
+    n_full = nb // 3
+    e = np.concatenate([rng.uniform(-9.0, -1.0, n_full), rng.uniform(40.0, 50.0, nb - n_full)])
+    _, mu, q = charges(e, e, 2.0 * n_full, nb)
+    assert -1.0 + 30 * KT < mu < 40.0 - 30 * KT
+    assert np.allclose(q, np.where(np.arange(2 * nb) < n_full, 2.0, 0.0), rtol=0.0, atol=1e-12)
