@@ -626,13 +626,15 @@ kk_status launch_sym_mixed(kk_handle h, const kk::MixedArgs& sa, int nch, size_t
 }
 
 // One product launch, by its window tables where it has them (gemm_f64's and gemm_mixed's
-// WINDOWED; the tiny classes have too few tiles to, use_window).
+// WINDOWED; the tiny classes have too few tiles to, use_window), with workgroups for the pieces of the
+// last round's tiles (Tail: of fewer tiles than CUs).
 template <int EPI, class Cfg>
 void run_gemm_f64(kk_handle h, const kk::GemmArgs& a) {
   const int grid = a.ntiles * a.nitems;
   if constexpr (!std::is_same<Cfg, TinyF64>::value)
     if (a.win.count != nullptr) {
-      kk::gemm_f64<EPI, Cfg, true><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+      const int pieces = kk::f64_tail<EPI, Cfg>() ? (kk::Tail<Cfg>::PIECES - 1) * a.cus : 0;
+      kk::gemm_f64<EPI, Cfg, true><<<grid + pieces, Cfg::THREADS, 0, h->stream>>>(a);
       return;
     }
   kk::gemm_f64<EPI, Cfg><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
@@ -642,7 +644,8 @@ void run_gemm_mixed(kk_handle h, const kk::MixedArgs& a) {
   const int grid = a.ntiles * a.nitems;
   if constexpr (!std::is_same<Cfg, MTinyCfg>::value && !std::is_same<Cfg, MTinyBf6>::value)
     if (a.win.count != nullptr) {
-      kk::gemm_mixed<EPI, Cfg, true><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
+      const int pieces = kk::mixed_tail<EPI, Cfg>() ? (kk::Tail<Cfg>::PIECES - 1) * a.cus : 0;
+      kk::gemm_mixed<EPI, Cfg, true><<<grid + pieces, Cfg::THREADS, 0, h->stream>>>(a);
       return;
     }
   kk::gemm_mixed<EPI, Cfg><<<grid, Cfg::THREADS, 0, h->stream>>>(a);
@@ -834,8 +837,10 @@ kk_status transforms_f64(kk_handle h, int batch, const int* stop) {
   fa.nitems = 2 * batch; fa.tiles = small ? (full ? h->stiles_full : h->stiles_upper) : (full ? h->tiles_full : h->tiles_upper);
   fa.stop = stop; fa.beta = h->beta;
   if (h->windowed) fa.win = h->win;
+  fa.cus = cu_count();
   kk::GemmArgs ba{};
   ba.win = fa.win;
+  ba.cus = fa.cus;
   ba.n = np; ba.k_half = h->kc; ba.two_halves = 0; ba.ntiles = small ? h->n_sfull : h->n_full;
   ba.nitems = 2 * batch; ba.tiles = small ? h->stiles_full : h->tiles_full; ba.stop = stop; ba.beta = h->beta;
   for (int b = 0; b < batch; ++b)
@@ -1018,6 +1023,7 @@ kk_status response_chunk_mixed(kk_handle h, int batch, const double* v, double* 
   fa.n = np; fa.k = kch > 1 ? h->kck : h->kc; fa.ntiles = h->n_mfull; fa.nitems = 2 * batch * kch;
   fa.tiles = h->mtiles_full; fa.stop = stop; fa.beta = h->beta;
   if (h->windowed) fa.win = h->win;
+  fa.cus = cu_count();
   if (h->sk) {
     fa.sk_grid = h->sk_grid;
     fa.sk_slots = h->kch;
@@ -2270,6 +2276,7 @@ kk_status adjoint_back(kk_handle h, const F64Plan& plan, int slot, double* g) {
   ba.n = (int)np; ba.k_half = plan.chunks > 1 ? plan.ck : h->kc; ba.ntiles = plan.tiles((int)np);
   ba.nitems = 2 * plan.chunks; ba.tiles = h->atiles; ba.beta = h->beta;
   if (plan.chunks == 1) ba.win = adjoint_window(h);
+  ba.cus = cu_count();
   for (int s = 0; s < 2; ++s)
     for (int j = 0; j < plan.chunks; ++j) {
       const size_t k0 = (size_t)j * plan.ck;

@@ -31,6 +31,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace kk {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -163,16 +165,16 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
   return (x < r) ? x * (q + 1) + slot : r * (q + 1) + (x - r) * q + slot;
 }
 
-// Forward launch: the tile and item of block b, or false past the active tiles, whose XCD ranges
-// are taken over the active ones alone. Items are (direction, spin).
-__device__ __forceinline__ bool window_tile(const Window& w, int nitems, int& z, int2& tile) {
-  const int n0 = w.count[0], per = n0 + w.count[1], total = per * (nitems / 2);
-  if ((int)blockIdx.x >= total) return false;
-  const int logical = xcd_remap(blockIdx.x, total);
+// Forward launch: its active tiles, and the item and tile of the `logical` one of them. Items are
+// (direction, spin).
+__device__ __forceinline__ int window_total(const Window& w, int nitems) {
+  return (w.count[0] + w.count[1]) * (nitems / 2);
+}
+__device__ __forceinline__ void window_tile(const Window& w, int logical, int& z, int2& tile) {
+  const int n0 = w.count[0], per = n0 + w.count[1];
   const int set = logical / per, r = logical - set * per, s = r >= n0;
   z = 2 * set + s;
   tile = w.tiles[s][s ? r - n0 : r];
-  return true;
 }
 // The rest of the forward launch's blocks, one per inactive tile.
 __device__ __forceinline__ void window_rest(const Window& w, int ntiles, int nitems, int& z, int2& tile) {
@@ -208,6 +210,7 @@ struct GemmArgs {
   int two_halves; // 1: K runs over both halves (a0,b0) then (a1,b1)
   int ntiles;     // tiles per item
   int nitems;     // batch items
+  int cus;        // CUs of the chip (windowed launches: Tail)
   const int2* tiles;  // tile coordinates (tm, tn), in launch order
   const int* stop;    // if non-null and *stop != 0 the launch does nothing
   double beta;        // 1 / kT (EPI_FERMI)
@@ -230,8 +233,11 @@ __device__ __forceinline__ double fermi_divided_difference(double em, double fm,
   return -beta * flo * fchi * phi;
 }
 
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINB_>
+// ONE_ROW: the Mulliken sums of a tile's waves along n are added up into one partial row.
+template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINB_, bool ONE_ROW_ = false>
 struct TileCfg {
+  static constexpr bool ONE_ROW = ONE_ROW_;
+  static constexpr int PART_ROWS = ONE_ROW ? 1 : WAVES_N_;  // Mulliken partial rows of a tile
   static constexpr int BM = BM_, BN = BN_, BK = BK_;
   static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
   static constexpr int THREADS = 64 * WAVES_M * WAVES_N;
@@ -295,9 +301,42 @@ struct PairRows {
   __device__ __forceinline__ const double* scale(int) const { return nullptr; }
 };
 
+// LDS of f64_tile: two stages of each operand, those of LdsCfg, where a kernel runs tiles of two
+// configurations. Two objects (one, whose accesses the compiler orders, is 1.2 % slower on 128 x 128
+// tiles at 150 atoms), or one (OneLds) for the 64 x 64 tiles of single systems (171 atoms, a
+// transform 303 -> 297 us). Functions rather than references to the arrays: with those the
+// batches' queued tiles took a register more per lane and 1.2 % longer.
+template <class Cfg>
+struct OneLds : Cfg {};
+template <class Cfg, class LdsCfg>
+__device__ __forceinline__ double (&tile_a())[2][Cfg::BK][Cfg::BM] {
+  if constexpr (std::is_same<Cfg, LdsCfg>::value) {
+    __shared__ double As[2][Cfg::BK][Cfg::BM];
+    return As;
+  } else if constexpr (std::is_same<OneLds<Cfg>, LdsCfg>::value) {
+    __shared__ double As[2 * Cfg::BK * (Cfg::BM + Cfg::BN)];
+    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BM]>(&As[0]);
+  } else {
+    static_assert(Cfg::BK * Cfg::BM <= LdsCfg::BK * LdsCfg::BM, "LDS");
+    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BM]>(&tile_a<LdsCfg, LdsCfg>());
+  }
+}
+template <class Cfg, class LdsCfg>
+__device__ __forceinline__ double (&tile_b())[2][Cfg::BK][Cfg::BN] {
+  if constexpr (std::is_same<Cfg, LdsCfg>::value) {
+    __shared__ double Bs[2][Cfg::BK][Cfg::BN];
+    return Bs;
+  } else if constexpr (std::is_same<OneLds<Cfg>, LdsCfg>::value) {
+    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BN]>(&tile_a<Cfg, LdsCfg>()[0][0][0] + 2 * Cfg::BK * Cfg::BM);
+  } else {
+    static_assert(Cfg::BK * Cfg::BN <= LdsCfg::BK * LdsCfg::BN, "LDS");
+    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BN]>(&tile_b<LdsCfg, LdsCfg>());
+  }
+}
+
 // One output tile: both operands n x n (row stride n), contracted over src's rows. Ends with a
 // barrier, so a workgroup may run several tiles in sequence.
-template <int EPI, class Cfg, class Rows>
+template <int EPI, class Cfg, class LdsCfg = Cfg, class Rows>
 __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, const int n, const int2 tile,
                                          const double beta_arg) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
@@ -306,9 +345,6 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
   constexpr int APR = BM / 2;  // double2 pieces per A row
   constexpr int BPR = BN / 2;
   const int m0 = tile.x * BM, n0 = tile.y * BN;
-
-  __shared__ double As[2][BK][BM];
-  __shared__ double Bs[2][BK][BN];
 
   const int tid = threadIdx.x;
   const int nk = src.stages(BK);
@@ -376,12 +412,12 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
       const int idx = tid + p * Cfg::THREADS;
       d2 v = ra[p];
       if constexpr (SCALED) v *= Ss[kt % 3][idx / APR];
-      *reinterpret_cast<d2*>(&As[buf][idx / APR][(idx % APR) * 2]) = v;
+      *reinterpret_cast<d2*>(&tile_a<Cfg, LdsCfg>()[buf][idx / APR][(idx % APR) * 2]) = v;
     }
 #pragma unroll
     for (int p = 0; p < BP; ++p) {
       const int idx = tid + p * Cfg::THREADS;
-      *reinterpret_cast<d2*>(&Bs[buf][idx / BPR][(idx % BPR) * 2]) = rb[p];
+      *reinterpret_cast<d2*>(&tile_b<Cfg, LdsCfg>()[buf][idx / BPR][(idx % BPR) * 2]) = rb[p];
     }
   };
 
@@ -401,9 +437,9 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
     for (int kk = 0; kk < BK / 4; ++kk) {
       double a[WTM], b[WTN];
 #pragma unroll
-      for (int i = 0; i < WTM; ++i) a[i] = As[buf][kk * 4 + lr][wm * (BM / Cfg::WAVES_M) + i * 16 + lc];
+      for (int i = 0; i < WTM; ++i) a[i] = tile_a<Cfg, LdsCfg>()[buf][kk * 4 + lr][wm * (BM / Cfg::WAVES_M) + i * 16 + lc];
 #pragma unroll
-      for (int j = 0; j < WTN; ++j) b[j] = Bs[buf][kk * 4 + lr][wn * (BN / Cfg::WAVES_N) + j * 16 + lc];
+      for (int j = 0; j < WTN; ++j) b[j] = tile_b<Cfg, LdsCfg>()[buf][kk * 4 + lr][wn * (BN / Cfg::WAVES_N) + j * 16 + lc];
 #pragma unroll
       for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -457,7 +493,7 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
         }
       }
   } else {  // EPI_MULLIKEN
-    const int p = tile.y * Cfg::WAVES_N + wn;
+    const int p = Cfg::ONE_ROW ? tile.y : tile.y * Cfg::WAVES_N + wn;
 #pragma unroll
     for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -467,9 +503,63 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
 #pragma unroll
         for (int j = 0; j < WTN; ++j) s += acc[i][j][r] * it.g[(size_t)m * n + nw + j * 16];
         s = row16_sum(s);
-        if (lc == 0) it.part[(size_t)p * n + m] = s;
+        if constexpr (Cfg::ONE_ROW) {
+          if (lc == 0) tile_a<Cfg, LdsCfg>()[0][wn][m - m0] = s;  // (the last stage's reads ended with a barrier)
+        } else {
+          if (lc == 0) it.part[(size_t)p * n + m] = s;
+        }
       }
+    if constexpr (Cfg::ONE_ROW) {
+      __syncthreads();
+      if (tid < BM) {
+        double s = tile_a<Cfg, LdsCfg>()[0][0][tid];
+#pragma unroll
+        for (int w = 1; w < Cfg::WAVES_N; ++w) s += tile_a<Cfg, LdsCfg>()[0][w][tid];
+        it.part[(size_t)p * n + m0 + tid] = s;
+      }
+      __syncthreads();
+    }
   }
+}
+
+// The last, partly empty round of a windowed launch. Its tiles past the last multiple of the chip's
+// CUs are cut into PIECES tiles of a quarter or half the size, where that ends the round sooner:
+// the active tiles are known on the device only, so the choice is made there. tail_begin: the
+// first tile that is cut (total: none), where the pieces of the rest take fewer turns of all CUs
+// than a whole tile. Most of the CUs were left waiting for a few whole tiles. m = 4: FP64 (quarters)
+// 250 atoms, 572 and 648 tiles on 256 CUs, 7.29 -> 5.68 ms, 265 atoms 7.63 -> 7.12, 350 atoms 15.7 -> 14.6,
+// 300 atoms (no cut: 200 tiles past the last multiple of 256) level; FP16 x 3 (halves) 265 atoms
+// 1.97 -> 1.87 ms, 171 atoms 0.795 -> 0.777, 432 atoms 5.60 -> 5.44; BF16 265 atoms 3.23 -> 3.02.
+template <class Cfg>
+struct Tail {
+  static constexpr int PIECES = 1;
+};
+template <int EPI, class Cfg>
+constexpr bool f64_tail() {
+  return Tail<Cfg>::PIECES > 1 && (EPI == EPI_XSTORE || EPI == EPI_MULLIKEN);
+}
+__device__ __forceinline__ int tail_begin(int total, int cus, int pieces) {
+  const int rest = total % cus;
+  return (rest * pieces + cus - 1) / cus < pieces ? total - rest : total;
+}
+
+// Where workgroup b of a windowed launch works: `logical` tile of the launch's `total`, and with piece >= 0
+// which piece of it. false: nowhere.
+template <class Cfg>
+__device__ __forceinline__ bool tail_place(int b, int total, int cus, int& logical, int& piece) {
+  constexpr int S = Tail<Cfg>::PIECES;
+  const int whole = S > 1 ? tail_begin(total, cus, S) : total;
+  piece = -1;
+  if (b < whole) {
+    logical = xcd_remap(b, whole);
+    return true;
+  }
+  const int pieces = (total - whole) * S, q = b - whole;  // whole is a multiple of 8 here, so q keeps b's XCD
+  if (q >= pieces) return false;
+  const int at = xcd_remap(q, pieces);
+  logical = whole + at / S;
+  piece = at % S;
+  return true;
 }
 
 // WINDOWED: the launch goes by args.win. (A choice at run time cost the smallest systems, whose
@@ -478,11 +568,16 @@ template <int EPI, class Cfg, bool WINDOWED = false>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const GemmArgs args) {
   static_assert(Cfg::BN % WIN == 0 && Cfg::BM % WIN == 0, "tiles are whole window blocks");
   if (args.stop != nullptr && *args.stop != 0) return;
-  int z;
-  int2 tile, rows = make_int2(0, args.k_half);
-  if constexpr (WINDOWED && (EPI == EPI_FERMI || EPI == EPI_XSTORE)) {
-    if (!window_tile(args.win, args.nitems, z, tile)) {
+  constexpr bool ACTIVE = WINDOWED && (EPI == EPI_FERMI || EPI == EPI_XSTORE);  // only the active tiles
+  constexpr bool TAIL = WINDOWED && f64_tail<EPI, Cfg>();
+  const int total = ACTIVE ? window_total(args.win, args.nitems) : args.ntiles * args.nitems;
+  int z, logical, piece = -1;
+  if constexpr (TAIL) {
+    if (!tail_place<Cfg>(blockIdx.x, total, args.cus, logical, piece)) return;
+  } else {
+    if (ACTIVE && (int)blockIdx.x >= total) {
       if constexpr (EPI == EPI_FERMI) {  // no pass follows that would write the inactive tiles' zeros
+        int2 tile;
         window_rest(args.win, args.ntiles, args.nitems, z, tile);
         static_assert(Cfg::BM == Cfg::BN, "a tile and its mirror");
         double* const out = args.item[z].out;
@@ -494,17 +589,34 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const 
       }
       return;
     }
+    logical = xcd_remap(blockIdx.x, total);
+  }
+  int2 tile, rows = make_int2(0, args.k_half);
+  if constexpr (ACTIVE) {
+    window_tile(args.win, logical, z, tile);
   } else {
-    const int total = args.ntiles * args.nitems;
-    const int logical = xcd_remap(blockIdx.x, total);
     z = logical / args.ntiles;
     tile = args.tiles[logical - z * args.ntiles];
-    if constexpr (WINDOWED && EPI == EPI_MULLIKEN) {
-      rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k_half, Cfg::BK, 0);
+  }
+  if constexpr (TAIL) {
+    if (piece >= 0) {
+      using Sub = typename Tail<Cfg>::Cfg;
+      constexpr int SM = Cfg::BM / Sub::BM, SN = Cfg::BN / Sub::BN;
+      static_assert(SM * SN == Tail<Cfg>::PIECES && Sub::THREADS == Cfg::THREADS &&
+                    SN * Sub::PART_ROWS == Cfg::PART_ROWS, "the pieces of a tile");
+      const int2 part = make_int2(tile.x * SM + piece % SM, tile.y * SN + piece / SM);
+      if constexpr (EPI == EPI_MULLIKEN)
+        rows = window_rows(args.win.range[z & 1], part.y * (Sub::BN / WIN), Sub::BN / WIN, args.k_half, Sub::BK, 0);
+      const HalfRows src{args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0};
+      f64_tile<EPI, Sub, Cfg>(args.item[z], src, args.n, part, args.beta);
+      return;
     }
   }
+  if constexpr (WINDOWED && EPI == EPI_MULLIKEN)
+    rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k_half, Cfg::BK, 0);
   const HalfRows src{args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0};
-  f64_tile<EPI, Cfg>(args.item[z], src, args.n, tile, args.beta);
+  using Lds = typename std::conditional<(Cfg::MIN_BLOCKS > 2), OneLds<Cfg>, Cfg>::type;
+  f64_tile<EPI, Cfg, Lds>(args.item[z], src, args.n, tile, args.beta);
 }
 
 // The commutator sums of the reverse pass: out + (2 c + s) np2 (+)= chunk c of spin s's
@@ -633,5 +745,10 @@ using Cfg128x128w8n = TileCfg<128, 128, 16, 2, 4, 2>;
 using FwdCfg = KK_FWD_CFG;
 using BackCfg = KK_BACK_CFG;
 using StoreCfg = KK_STORE_CFG;
+template <>
+struct Tail<Cfg128x128w8> {
+  static constexpr int PIECES = 4;
+  using Cfg = TileCfg<64, 64, 16, 4, 2, 2, true>;
+};
 
 }  // namespace kk

@@ -89,6 +89,7 @@ struct MixedArgs {
   // (Mulliken partials) or not read (the symmetrizing pass, which finds the segment count of
   // each sk_side x sk_side tile from its table position, tile_table_pos).
   int sk_grid, sk_slots, sk_side;
+  int cus;  // CUs of the chip (windowed launches: Tail)
   size_t sk_stride;
   Window win;  // all null: every tile, every row
   MixedItem item[MAX_GEMM_BATCH];
@@ -464,8 +465,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 // before its products. Two fragment register sets alternate. The barrier before
 // a stage waits for every wave's DMA of that stage and also for
 // this wave's reads of the previous stage (lgkmcnt 0), so its slot can be refilled.
-// Leaves the FP32 sums in acc; ends with a barrier.
-template <class Cfg>
+// Leaves the FP32 sums in acc; ends with a barrier. LdsCfg: the configuration whose LDS it uses.
+template <class Cfg, class LdsCfg>
 __device__ __forceinline__ void mixed_mainloop_dl(const MixedItem& it, const int n, const int k_lo, const int kc,
                                                   const int m0, const int n0, f16x (&acc)[Cfg::WTM][Cfg::WTN]) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = 32, NS = Cfg::NS, PW = Cfg::PER_WAVE;
@@ -474,7 +475,8 @@ __device__ __forceinline__ void mixed_mainloop_dl(const MixedItem& it, const int
   // enter_stage(s) refills the slot of stage s - 1, whose last fragment reads (its second
   // half, read before its first half's products) every wave has finished by then
   static_assert(NS >= 2, "ring depth");
-  unsigned char* const ring = mixed_smem<Cfg>();
+  static_assert(Cfg::SMEM_BYTES <= LdsCfg::SMEM_BYTES, "LDS");
+  unsigned char* const ring = mixed_smem<LdsCfg>();
 
   const int tid = threadIdx.x;
   const int nk = kc / BK;
@@ -663,34 +665,67 @@ constexpr int WIN_ROWS_MIXED = (Cfg::FLUSH > 0 ? Cfg::FLUSH : 1) * Cfg::BK;
 
 // One output tile over the kc (>= 1 stage) columns of the operands from k_lo (see f64_tile); ends
 // with a barrier.
-template <int EPI, class Cfg>
+template <int EPI, class Cfg, class LdsCfg = Cfg>
 __device__ __forceinline__ void mixed_tile(const MixedItem& it, const int n, const int k_lo, const int kc,
                                            const int2 tile) {
   static_assert(EPI == EPI_STORE || EPI == EPI_MULLIKEN, "split-precision epilogues");
   const int m0 = tile.x * Cfg::BM, n0 = tile.y * Cfg::BN;
   f16x acc[Cfg::WTM][Cfg::WTN];
   if constexpr (Cfg::DL)
-    mixed_mainloop_dl<Cfg>(it, n, k_lo, kc, m0, n0, acc);
+    mixed_mainloop_dl<Cfg, LdsCfg>(it, n, k_lo, kc, m0, n0, acc);
   else
     mixed_mainloop_lds<Cfg>(it, n, k_lo, kc, m0, n0, acc);
   mixed_epilogue<EPI, Cfg>(it, n, tile, acc);
 }
 
+template <int EPI, class Cfg>
+constexpr bool mixed_tail() {
+  if constexpr (Tail<Cfg>::PIECES > 1)
+    return EPI == EPI_STORE || Tail<Cfg>::Cfg::WAVES_N == Cfg::WAVES_N;
+  return false;
+}
+
+// The pieces of a Tail do the same products in the same order, so the FP32 sums keep their bits; the
+// Mulliken sums only where the pieces' waves cover the same columns.
 template <int EPI, class Cfg, bool WINDOWED = false>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_mixed(const MixedArgs args) {
   if (args.stop != nullptr && *args.stop != 0) return;
-  int z;
+  constexpr bool ACTIVE = WINDOWED && EPI == EPI_STORE;  // only the active tiles
+  constexpr bool TAIL = WINDOWED && mixed_tail<EPI, Cfg>();
+  int z, piece = -1;
   int2 tile, rows = make_int2(0, args.k);
-  if constexpr (WINDOWED && EPI == EPI_STORE) {
-    if (!window_tile(args.win, args.nitems, z, tile)) return;  // the symmetrizing pass writes the zeros
+  if constexpr (ACTIVE) {
+    const int total = window_total(args.win, args.nitems);
+    int logical = 0;
+    if constexpr (TAIL) {
+      if (!tail_place<Cfg>(blockIdx.x, total, args.cus, logical, piece)) return;
+    } else {
+      if ((int)blockIdx.x >= total) return;  // the symmetrizing pass writes the zeros
+      logical = xcd_remap(blockIdx.x, total);
+    }
+    window_tile(args.win, logical, z, tile);
   } else {
     const int total = args.ntiles * args.nitems;
-    const int logical = xcd_remap(blockIdx.x, total);
+    int logical = 0;
+    if constexpr (TAIL) {
+      if (!tail_place<Cfg>(blockIdx.x, total, args.cus, logical, piece)) return;
+    } else {
+      logical = xcd_remap(blockIdx.x, total);
+    }
     z = logical / args.ntiles;
     tile = args.tiles[logical - z * args.ntiles];
-    if constexpr (WINDOWED && EPI == EPI_MULLIKEN) {
+    if constexpr (WINDOWED && EPI == EPI_MULLIKEN)
       rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k, WIN_ROWS_MIXED<Cfg>,
                          Cfg::BK);
+  }
+  if constexpr (TAIL) {
+    if (piece >= 0) {
+      using Sub = typename Tail<Cfg>::Cfg;
+      static_assert(Sub::BM * Tail<Cfg>::PIECES == Cfg::BM && Sub::BN == Cfg::BN && Sub::THREADS == Cfg::THREADS &&
+                    Sub::FLUSH == Cfg::FLUSH, "the pieces of a tile");
+      const int2 part = make_int2(tile.x * Tail<Cfg>::PIECES + piece, tile.y);
+      mixed_tile<EPI, Sub, Cfg>(args.item[z], args.n, rows.x, rows.y - rows.x, part);
+      return;
     }
   }
   mixed_tile<EPI, Cfg>(args.item[z], args.n, rows.x, rows.y - rows.x, tile);
@@ -826,6 +861,22 @@ struct WithProducts<MixedCfg<BM, BN, BK, WM, WN, MB, FL, B0, P0>, BF16, PROD> {
 // updates/s (one process), results 3-6e-8 apart (the summation order).
 using MSmallBf6 = WithProducts<MSmallCfg, true, PROD_ALL6>::type;
 using MLargeBf6 = MixedDlCfg<256, 128, 4, 2, 2, 8, true, PROD_ALL6>;
+// Halves of a tile for the last round (Tail), along m, in as many waves.
+template <>
+struct Tail<MDl256x128w16> {
+  static constexpr int PIECES = 2;
+  using Cfg = MixedDlCfg<128, 128, 4, 4, 3, 8>;
+};
+template <>
+struct Tail<MDl128x128n3> {
+  static constexpr int PIECES = 2;
+  using Cfg = MixedDlCfg<64, 128, 2, 4, 3, 8>;
+};
+template <>
+struct Tail<MLargeBf6> {
+  static constexpr int PIECES = 2;
+  using Cfg = MixedDlCfg<128, 128, 4, 2, 2, 8, true, PROD_ALL6>;
+};
 static_assert(MLargeBf6::BM == MLargeCfg::BM && MLargeBf6::BN == MLargeCfg::BN &&
                   MLargeBf6::WAVES_N == MLargeCfg::WAVES_N,
               "the BF16 large products share the large shape's tile table and partial rows");

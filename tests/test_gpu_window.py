@@ -171,3 +171,18 @@ def test_batch_tiles_at_once_and_from_queues(copies, small_np_max, precision):
             h.close()
         assert rel(got[0][i], want) < TOL[precision], i
         assert np.array_equal(got[0][i], got[1][i]), i
+
+
+@pytest.mark.parametrize("precision", PRECISIONS, ids=IDS)
+@pytest.mark.parametrize("atoms", [171, 250, 320])
+def test_last_round_in_pieces(atoms, precision):
+    """Sizes whose shuffled levels leave a last round of few tiles, run in quarters (FP64 at 250 and
+    320 atoms: 136 and 34 tiles past the last multiple of 256) or halves (FP16 x 3 at 171 atoms: 82;
+    FP16 x 3 and BF16 at 320: 40), against the ascending order with its other tile count."""
+    y = make(atoms, 600 + atoms)
+    rng = np.random.default_rng(atoms)
+    v, delta = rng.standard_normal((1, 2 * atoms)), 0.01 * rng.standard_normal(2 * atoms)
+    a, b = (results(y, shuffled, precision, v, delta, 3) for shuffled in (False, True))
+    err = [rel(p, q) for p, q in zip(a, b)]
+    print(atoms, precision, err, flush=True)
+    assert max(err) < TOL[precision], err
