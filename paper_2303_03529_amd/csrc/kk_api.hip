@@ -469,9 +469,34 @@ struct F64Plan {
 // 1680 -> 2977, 37 atoms 1816 -> 2747, 56 atoms 1734 -> 2100; from a padded size of 640
 // the rule stops splitting these tiles (70 and 85 atoms: level).
 constexpr int KTINY_MAX_NP = 512;
-F64Plan plan_f64(int np, int kc, int cus, bool may_split) {
+// Turns of the chip's CUs, in 128 x 128 tiles, that the unsplit 64 x 64 tiles of a windowed launch
+// take, the last in quarters (Tail), and that a K-split of 128 x 128 ones takes.
+double small_turns(int nb, int cus) {
+  constexpr int S = kk::Tail<SmallF64>::PIECES;
+  const int side = (nb + SmallF64::BM - 1) / SmallF64::BM, w = 2 * side * side;
+  const int whole = kk::tail_begin<SmallF64>(w, cus);
+  return ((whole + cus - 1) / cus + (double)((S * (w - whole) + cus - 1) / cus) / S) / 4.0;
+}
+double ksplit_turns(int np, int chunks, int cus) {
+  const int w = 2 * (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN) * chunks;
+  return (double)((w + cus - 1) / cus) / chunks;
+}
+// From a padded size of WINDOWED_MIN_NP a handle that would be K-split has unsplit 64 x 64 tiles and the
+// window tables instead where those take fewer turns: no partial products to write and add, and
+// no work on the padding. m = 4, K-split / unsplit: 90 atoms (turns 0.5 / 0.375) 591 / 540 us, 99
+// atoms (0.5 / 0.44) 625 / 596, 120 atoms (0.67 / 0.625) 957 / 850; but 113 atoms (0.5 / 0.5) 711 / 746,
+// 128 atoms (0.67 / 0.75) 957 / 997. Smaller, a lone workgroup's unsplit contraction is too long: 85
+// atoms (0.33 / 0.31) 423 / 465.
+constexpr int WINDOWED_MIN_NP = 896;
+// nb > 0: a handle whose transforms may go by window tables.
+F64Plan plan_f64(int np, int kc, int cus, bool may_split, int nb = 0) {
   F64Plan p;
   p.ck = kc;
+  if (may_split && nb > 0 && np >= WINDOWED_MIN_NP && np < LARGE_FILL_MIN_NP) {
+    int ck;
+    const int c = choose_ksplit(np, kc, (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN), cus, false, &ck);
+    if (small_turns(nb, cus) < ksplit_turns(np, c, cus)) may_split = false;
+  }
   if (may_split) {
     p.chunks = choose_ksplit(np, kc, (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN), cus, false, &p.ck);
     if (np <= KTINY_MAX_NP) {
@@ -1365,7 +1390,7 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
     h->ktiny = h->small_f64 = h->tiny_f64 = false;
     h->mx_tiny = mixed && !mx_large && !split_large && np <= MTINY_MAX_NP;
     if (!mixed) {
-      const F64Plan p = plan_f64(np, h->kc, cu_count(), !split_large);
+      const F64Plan p = plan_f64(np, h->kc, cu_count(), !split_large, split_large ? 0 : nb);
       h->kch = p.chunks;
       h->kck = p.ck;
       h->small_f64 = p.cls != 0;

@@ -236,6 +236,7 @@ __device__ __forceinline__ double fermi_divided_difference(double em, double fm,
 // ONE_ROW: the Mulliken sums of a tile's waves along n are added up into one partial row.
 template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINB_, bool ONE_ROW_ = false>
 struct TileCfg {
+  using Tile = TileCfg;  // the configuration itself (OneLds)
   static constexpr bool ONE_ROW = ONE_ROW_;
   static constexpr int PART_ROWS = ONE_ROW ? 1 : WAVES_N_;  // Mulliken partial rows of a tile
   static constexpr int BM = BM_, BN = BN_, BK = BK_;
@@ -307,7 +308,9 @@ struct PairRows {
 // transform 303 -> 297 us). Functions rather than references to the arrays: with those the
 // batches' queued tiles took a register more per lane and 1.2 % longer.
 template <class Cfg>
-struct OneLds : Cfg {};
+struct OneLds : Cfg {
+  using Tile = Cfg;
+};
 template <class Cfg, class LdsCfg>
 __device__ __forceinline__ double (&tile_a())[2][Cfg::BK][Cfg::BM] {
   if constexpr (std::is_same<Cfg, LdsCfg>::value) {
@@ -318,7 +321,7 @@ __device__ __forceinline__ double (&tile_a())[2][Cfg::BK][Cfg::BM] {
     return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BM]>(&As[0]);
   } else {
     static_assert(Cfg::BK * Cfg::BM <= LdsCfg::BK * LdsCfg::BM, "LDS");
-    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BM]>(&tile_a<LdsCfg, LdsCfg>());
+    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BM]>(&tile_a<typename LdsCfg::Tile, LdsCfg>());
   }
 }
 template <class Cfg, class LdsCfg>
@@ -330,7 +333,7 @@ __device__ __forceinline__ double (&tile_b())[2][Cfg::BK][Cfg::BN] {
     return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BN]>(&tile_a<Cfg, LdsCfg>()[0][0][0] + 2 * Cfg::BK * Cfg::BM);
   } else {
     static_assert(Cfg::BK * Cfg::BN <= LdsCfg::BK * LdsCfg::BN, "LDS");
-    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BN]>(&tile_b<LdsCfg, LdsCfg>());
+    return *reinterpret_cast<double (*)[2][Cfg::BK][Cfg::BN]>(&tile_b<typename LdsCfg::Tile, LdsCfg>());
   }
 }
 
@@ -525,22 +528,28 @@ __device__ __forceinline__ void f64_tile(const GemmItem& it, const Rows& src, co
 // The last, partly empty round of a windowed launch. Its tiles past the last multiple of the chip's
 // CUs are cut into PIECES tiles of a quarter or half the size, where that ends the round sooner:
 // the active tiles are known on the device only, so the choice is made there. tail_begin: the
-// first tile that is cut (total: none), where the pieces of the rest take fewer turns of all CUs
-// than a whole tile. Most of the CUs were left waiting for a few whole tiles. m = 4: FP64 (quarters)
+// first tile that is cut (total: none), where the pieces of the rest take less than a whole tile's
+// time. Most of the CUs were left waiting for a few whole tiles. m = 4: FP64 (quarters)
 // 250 atoms, 572 and 648 tiles on 256 CUs, 7.29 -> 5.68 ms, 265 atoms 7.63 -> 7.12, 350 atoms 15.7 -> 14.6,
 // 300 atoms (no cut: 200 tiles past the last multiple of 256) level; FP16 x 3 (halves) 265 atoms
 // 1.97 -> 1.87 ms, 171 atoms 0.795 -> 0.777, 432 atoms 5.60 -> 5.44; BF16 265 atoms 3.23 -> 3.02.
+// The 64 x 64 FP64 tiles, three workgroups per CU, gain while their quarters fit beside the whole
+// tiles: 160 atoms 1.90 -> 1.79 ms, 171 atoms 2.46 -> 2.30, 178 atoms 2.55 -> 2.45; after more rounds a
+// quarter takes a slot that a whole tile would have filled (182 atoms, 72 tiles after five
+// rounds, back-transform 315 us whole, 347 us cut).
 template <class Cfg>
 struct Tail {
-  static constexpr int PIECES = 1;
+  // REST: most tiles that are cut, in sixteenths of the CUs; REST_LONG: after more than four rounds
+  static constexpr int PIECES = 1, REST = 0, REST_LONG = 0;
 };
 template <int EPI, class Cfg>
 constexpr bool f64_tail() {
   return Tail<Cfg>::PIECES > 1 && (EPI == EPI_XSTORE || EPI == EPI_MULLIKEN);
 }
-__device__ __forceinline__ int tail_begin(int total, int cus, int pieces) {
-  const int rest = total % cus;
-  return (rest * pieces + cus - 1) / cus < pieces ? total - rest : total;
+template <class Cfg>
+__host__ __device__ inline int tail_begin(int total, int cus) {
+  const int rest = total % cus, most = total - rest <= 4 * cus ? Tail<Cfg>::REST : Tail<Cfg>::REST_LONG;
+  return 16 * rest <= most * cus ? total - rest : total;
 }
 
 // Where workgroup b of a windowed launch works: `logical` tile of the launch's `total`, and with piece >= 0
@@ -548,7 +557,7 @@ __device__ __forceinline__ int tail_begin(int total, int cus, int pieces) {
 template <class Cfg>
 __device__ __forceinline__ bool tail_place(int b, int total, int cus, int& logical, int& piece) {
   constexpr int S = Tail<Cfg>::PIECES;
-  const int whole = S > 1 ? tail_begin(total, cus, S) : total;
+  const int whole = S > 1 ? tail_begin<Cfg>(total, cus) : total;
   piece = -1;
   if (b < whole) {
     logical = xcd_remap(b, whole);
@@ -598,6 +607,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const 
     z = logical / args.ntiles;
     tile = args.tiles[logical - z * args.ntiles];
   }
+  using Lds = typename std::conditional<(Cfg::MIN_BLOCKS > 2), OneLds<Cfg>, Cfg>::type;
   if constexpr (TAIL) {
     if (piece >= 0) {
       using Sub = typename Tail<Cfg>::Cfg;
@@ -606,16 +616,16 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_f64(const 
                     SN * Sub::PART_ROWS == Cfg::PART_ROWS, "the pieces of a tile");
       const int2 part = make_int2(tile.x * SM + piece % SM, tile.y * SN + piece / SM);
       if constexpr (EPI == EPI_MULLIKEN)
-        rows = window_rows(args.win.range[z & 1], part.y * (Sub::BN / WIN), Sub::BN / WIN, args.k_half, Sub::BK, 0);
+        rows = window_rows(args.win.range[z & 1], part.y * Sub::BN / WIN, (Sub::BN + WIN - 1) / WIN, args.k_half,
+                           Sub::BK, 0);
       const HalfRows src{args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0};
-      f64_tile<EPI, Sub, Cfg>(args.item[z], src, args.n, part, args.beta);
+      f64_tile<EPI, Sub, Lds>(args.item[z], src, args.n, part, args.beta);
       return;
     }
   }
   if constexpr (WINDOWED && EPI == EPI_MULLIKEN)
     rows = window_rows(args.win.range[z & 1], tile.y * (Cfg::BN / WIN), Cfg::BN / WIN, args.k_half, Cfg::BK, 0);
   const HalfRows src{args.item[z], args.n, rows.x, rows.y - rows.x, args.two_halves != 0};
-  using Lds = typename std::conditional<(Cfg::MIN_BLOCKS > 2), OneLds<Cfg>, Cfg>::type;
   f64_tile<EPI, Cfg, Lds>(args.item[z], src, args.n, tile, args.beta);
 }
 
@@ -746,8 +756,13 @@ using FwdCfg = KK_FWD_CFG;
 using BackCfg = KK_BACK_CFG;
 using StoreCfg = KK_STORE_CFG;
 template <>
+struct Tail<Cfg64x64> {
+  static constexpr int PIECES = 4, REST = 9, REST_LONG = 1;
+  using Cfg = TileCfg<32, 32, 16, 2, 2, 3, true>;
+};
+template <>
 struct Tail<Cfg128x128w8> {
-  static constexpr int PIECES = 4;
+  static constexpr int PIECES = 4, REST = 12, REST_LONG = 12;
   using Cfg = TileCfg<64, 64, 16, 4, 2, 2, true>;
 };
 

@@ -864,17 +864,17 @@ using MLargeBf6 = MixedDlCfg<256, 128, 4, 2, 2, 8, true, PROD_ALL6>;
 // Halves of a tile for the last round (Tail), along m, in as many waves.
 template <>
 struct Tail<MDl256x128w16> {
-  static constexpr int PIECES = 2;
+  static constexpr int PIECES = 2, REST = 8, REST_LONG = 8;
   using Cfg = MixedDlCfg<128, 128, 4, 4, 3, 8>;
 };
 template <>
 struct Tail<MDl128x128n3> {
-  static constexpr int PIECES = 2;
+  static constexpr int PIECES = 2, REST = 8, REST_LONG = 8;
   using Cfg = MixedDlCfg<64, 128, 2, 4, 3, 8>;
 };
 template <>
 struct Tail<MLargeBf6> {
-  static constexpr int PIECES = 2;
+  static constexpr int PIECES = 2, REST = 8, REST_LONG = 8;
   using Cfg = MixedDlCfg<128, 128, 4, 2, 2, 8, true, PROD_ALL6>;
 };
 static_assert(MLargeBf6::BM == MLargeCfg::BM && MLargeBf6::BN == MLargeCfg::BN &&

@@ -186,3 +186,17 @@ def test_last_round_in_pieces(atoms, precision):
     err = [rel(p, q) for p, q in zip(a, b)]
     print(atoms, precision, err, flush=True)
     assert max(err) < TOL[precision], err
+
+
+@pytest.mark.parametrize("atoms", [86, 99, 114, 118, 160])
+def test_small_tiles_with_windows(atoms):
+    """FP64 on unsplit 64 x 64 tiles by window tables: both ends of the two ranges that are not K-split
+    (padded sizes 896 and 1152), a last round in quarters (99 atoms shuffled: 136 tiles past 256; 160
+    atoms: 128 past 1024) and one that is not cut (118 atoms ascending)."""
+    y = make(atoms, 700 + atoms)
+    rng = np.random.default_rng(atoms)
+    v, delta = rng.standard_normal((3, 2 * atoms)), 0.01 * rng.standard_normal(2 * atoms)
+    a, b = (results(y, shuffled, krylov.KK_FP64, v, delta, 4) for shuffled in (False, True))
+    err = [rel(p, q) for p, q in zip(a, b)]
+    print(atoms, err, flush=True)
+    assert max(err) < TOL[krylov.KK_FP64], err
