@@ -334,10 +334,44 @@ def time_updates(h, delta, out, m, steps, warmup, prof_steps):
     return elapsed, kern
 
 
-def roofline_of(kern, nb, precision, peak):
-    """Roofline object of the dominant transform step (algorithmic flops 2 spins x 2 Nb^3)."""
-    flops_launch = 2 * 2.0 * nb ** 3
+def executed_fractions(levels, mu, kT, precision):
+    """The parts of the whole forward and back products that the library computes: it leaves out the
+    64 x 64 blocks of levels in which every divided difference is negligible (the rule of its
+    window_tables: the forward by tiles with no other block, the back-transform by the rows outside
+    the blocks of its 128 columns)."""
+    import numpy as np
+    bm, cut_bits = (128, 60) if precision == "fp64" else (256, 42 if precision == "mixed" else 60)
+    occ = lambda e: 1.0 / (1.0 + np.exp(np.clip((e - mu) / kT, -700.0, 700.0)))  # noqa: E731
+    e = np.asarray(levels)
+    f, fc = occ(e), occ(2.0 * mu - e)
+    width = (e.max() - e.min()) / kT
+    ref = max((f * fc).max(), f.max() * fc.max() * -np.expm1(-width) / width)
+    cut = 2.0 ** -cut_bits * (1.0 if precision == "mixed" else ref)
+    fwd = back = 0.0
+    nb = e.shape[1]
+    for x in e:
+        edges = np.arange(0, nb, 64)
+        lo, hi = np.minimum.reduceat(x, edges), np.maximum.reduceat(x, edges)
+        bound = np.where(lo[:, None] <= hi[None, :], occ(lo)[:, None] * occ(2.0 * mu - hi)[None, :], 0.0)
+        bound = np.maximum(bound, bound.T)
+        z = np.maximum(lo[None, :] - hi[:, None], lo[:, None] - hi[None, :]) / kT
+        on = bound / np.maximum(z, 1.0) >= cut
+        size = np.diff(np.append(edges, nb))
+        for i in range(0, len(edges), bm // 64):
+            for j in range(0, len(edges), 2):
+                if on[i:i + bm // 64, j:j + 2].any() or (i <= j + 1 and j < i + bm // 64):
+                    fwd += size[i:i + bm // 64].sum() * size[j:j + 2].sum()
+        for j in range(0, len(edges), 2):
+            rows = np.flatnonzero(on[:, j:j + 2].any(1))
+            if len(rows):
+                back += size[rows[0]:rows[-1] + 1].sum() * size[j:j + 2].sum()
+    return {"forward_fermi": fwd / (len(e) * nb * nb), "back_mulliken": back / (len(e) * nb * nb)}
+
+
+def roofline_of(kern, nb, precision, peak, executed):
+    """Roofline object of the dominant transform step: the executed part of 2 spins x 2 Nb^3."""
     dom = max(kern, key=lambda k: kern[k][0] * kern[k][1])
+    flops_launch = 2 * 2.0 * nb ** 3 * executed.get(dom, 1.0)
     avg_ms = kern[dom][0]
     achieved = flops_launch / (avg_ms * 1e-3) / 1e12
     traffic = None
@@ -351,6 +385,7 @@ def roofline_of(kern, nb, precision, peak):
         "bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak, 2),
         "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": traffic,
         "kernel": dom, "avg_launch_ms": round(avg_ms, 4), "flops_per_launch": flops_launch,
+        "executed_fraction": {k: round(v, 4) for k, v in executed.items()},
         "other_kernel_avg_ms": {k: round(v[0], 4) for k, v in kern.items() if k != dom},
     }
 
@@ -400,6 +435,8 @@ def main():
         ref64 = ref64.cpu().numpy()
         h64.close()
         del h64
+    levels = np.stack([e["eps_up"].cpu().numpy(), e["eps_dn"].cpu().numpy()])
+    executed = {f: executed_fractions(levels, handles[f].mu, sysd["kT"], f) for f in forms}
     del e
     torch.cuda.empty_cache()
     delta = torch.as_tensor(sysd["delta"], dtype=torch.float64, device=dev)
@@ -414,7 +451,7 @@ def main():
             torch.mul(a, 1.0, out=b)
         torch.cuda.synchronize()
         del a, b
-    update_flops = 8.0 * m * nb ** 3
+    update_flops = {f: 4.0 * m * nb ** 3 * sum(executed[f].values()) for f in forms}
     prof_steps = max(1, min(args.steps, args.prof_steps))
     lines = {}
     results = {}
@@ -426,8 +463,8 @@ def main():
         if f == "fp64":
             ref64 = results[f]
         peak = FP64_MFMA_PEAK_TFLOPS if f == "fp64" else FP16_MFMA_PEAK_TFLOPS
-        rf = roofline_of(kern, nb, f, peak)
-        tflops = update_flops / (elapsed / args.steps) / 1e12
+        rf = roofline_of(kern, nb, f, peak, executed[f])
+        tflops = update_flops[f] / (elapsed / args.steps) / 1e12
         lines[f] = dict(value=args.steps / elapsed, elapsed=elapsed, roofline=rf, tflops=tflops)
         print(f"# {f}: {args.steps / elapsed:.4f} updates/s, dominant {rf['kernel']} {rf['avg_launch_ms']} ms",
               file=sys.stderr, flush=True)
