@@ -187,7 +187,7 @@ __device__ __forceinline__ bool window_tile_active(const Item& it, int tm, int t
 // what has been taken. A workgroup takes tiles from its own queue until that is empty, then from
 // the others', so the launch ends level whatever the systems' stop flags and windows leave out,
 // and a workgroup that starts late finds all queues empty and ends. Against a fixed stride over one
-// list (tile t to workgroup t mod grid): 24 clusters of 16-250 atoms, FP64, m = 6, 54.6 -> 49.8 ms
+// list (tile t to workgroup t mod grid): 24 clusters of 16-250 atoms, FP64, m = 6, 54.9 -> 48.8 ms
 // an update; 64 clusters FP16 x 3 49.8 -> 45.3 ms, FP64 5.33 -> 5.94 updates/s (the windows alone,
 // whose gaps a stride cannot close, gave the 24 clusters 0.8 %).
 constexpr int XCDS = 8;
