@@ -251,8 +251,13 @@ kk_status kk_xlbomd_update(kk_handle h, const double *n_hist, int k_max, const d
  * gamma_bar and W_bar are formed: one transposed response per direction (m
  * responses, like the forward), in the handle's precision, no workspace beyond
  * O(N m). With the H gradients the reverse sweep runs its transforms in FP64
- * on any handle (about 2.5x the forward's FP64 work; 12 padded Nb^2 FP64
- * matrices of workspace, allocated on first use and kept by the handle): the
+ * on any handle (about 2.5x the forward's FP64 work). Its workspace is allocated
+ * on first use and kept by the handle: 8 padded Nb^2 FP64 matrices for each
+ * direction of a group, as many directions as 2 GiB hold (at least one), and
+ * up to 34 more for the pieces of contractions that are cut to fill the chip
+ * (small systems; 4 to 8 from some 250 atoms on). Where the device has no room for
+ * that the groups get smaller and the contractions are left uncut, down to 12
+ * matrices in all; KK_ENOMEM only if these don't fit. The H gradients need FP64: the
  * expansion-point derivative divides commutators of products by level gaps,
  * which turns the ~1e-7 error of split-precision products into ~1e-4. On a
  * KK_MIXED_F16 handle the forward expansion (when recomputed) is split

@@ -276,6 +276,8 @@ struct kk_handle_s {
   double *aVbar = nullptr, *aFbar = nullptr, *abbar = nullptr, *aKd = nullptr;
   int2* atiles = nullptr;
   int adj_group = 0, adj_chunks = 1;
+  int adj_fit = 0;        // directions that still fit when a larger group did not (0: none failed)
+  bool adj_lean = false;  // not even one direction fit beside the partial products of a K-split
   std::vector<void*> pair_owned;
   int2* apairs = nullptr;
   double* apk = nullptr;
@@ -291,6 +293,8 @@ struct kk_handle_s {
   }
   void free_adjoint() {
     free_adjoint_h();
+    adj_fit = 0;
+    adj_lean = false;
     for (void* p : adj_owned) (void)hipFree(p);
     for (void* p : pair_owned) (void)hipFree(p);
     adj_owned.clear();
@@ -2170,13 +2174,17 @@ namespace {
 
 // The reverse pass's FP64 products run by the plan of an FP64 handle of the same size, whatever
 // the handle's own precision.
-F64Plan adjoint_plan(kk_handle h) { return plan_f64(h->np, h->kc, cu_count(), true); }
+F64Plan adjoint_plan(kk_handle h) { return plan_f64(h->np, h->kc, cu_count(), !h->adj_lean); }
 
-// Directions whose X and Y the reverse pass holds at a time: 8 padded matrices each, within the
-// workspace budget.
+// Directions whose X and Y the reverse pass holds at a time: 8 padded matrices each, which the handle
+// keeps, so no more of them than gain anything. Groups of 1 / 2 / 4 / all directions, dL/dH alone:
+// 128 atoms m = 8 5313 / 5086 / 4981 / 4936 us, 250 atoms 34.3 / 34.0 / 33.2 / 32.9 ms, 432 atoms m = 6 121.9 /
+// 122.5 / 121.5 / 120.6 ms, 686 atoms m = 4 312.6 / 309.8 / 307.9 / 308.0 ms. 2 GiB hold all eight at 200 atoms,
+// six at 250, two at 432 and one from 686 on.
+constexpr size_t ADJOINT_BUDGET = size_t(2) << 30;
 int adjoint_group(kk_handle h, int m) {
   const size_t per = (size_t)8 * h->np * h->np * sizeof(double);
-  return (int)std::max<size_t>(1, std::min<size_t>(m, WORKSPACE_BUDGET / per));
+  return (int)std::max<size_t>(1, std::min<size_t>(m, ADJOINT_BUDGET / per));
 }
 
 // Chunks of the commutator sums' contraction (gemm_pairs): the fewest of the candidates whose
@@ -2190,25 +2198,13 @@ int adjoint_chunks(int tiles, int cus) {
   return 1;
 }
 
-// Reverse-pass workspace: the Krylov vectors always; the padded matrices of the expansion-point
-// part only once a call asks for dL/dH (for a rank m, and again when a later rank wants larger
-// groups).
-kk_status ensure_adjoint(kk_handle h, bool want_H, int m) {
-  const size_t np = h->np, np2 = np * np, n2 = 2 * (size_t)h->natoms;
+// The matrices of the expansion-point part for groups of `group` directions.
+kk_status alloc_adjoint_h(kk_handle h, size_t group) {
+  const size_t np = h->np, np2 = np * np;
   kk_status st;
-  if (!h->ag) {
-    Slab slab;
-    for (double** q : {&h->alam, &h->abbar, &h->aKd, &h->ay}) slab.add(q, n2);
-    for (double** q : {&h->ag, &h->aVbar, &h->aFbar}) slab.add(q, kk::MAX_RANK * n2);
-    if ((st = slab.commit(h->adj_owned))) return st;
-  }
-  const size_t group = adjoint_group(h, m);
-  if (!want_H || (int)group <= h->adj_group) return KK_OK;
-  HIP_OR_FAIL(hipStreamSynchronize(h->stream));
-  h->free_adjoint_h();
   const F64Plan plan = adjoint_plan(h);
   const std::vector<int2> tiles = tile_order((int)np, plan.side(), plan.side(), false);
-  h->adj_chunks = adjoint_chunks((int)tiles.size(), cu_count());
+  h->adj_chunks = h->adj_lean ? 1 : adjoint_chunks((int)tiles.size(), cu_count());
   Slab slab;
   slab.add(&h->aX, group * 4 * np2);
   slab.add(&h->aY, group * 4 * np2);
@@ -2223,12 +2219,45 @@ kk_status ensure_adjoint(kk_handle h, bool want_H, int m) {
   slab.add(&h->agtot, 1);
   slab.add(&h->atiles, tiles.size());
   if ((st = slab.commit(h->adjh_owned))) return st;
-  h->adj_group = (int)group;
   HIP_OR_FAIL(hipMemcpyAsync(h->atiles, tiles.data(), sizeof(int2) * tiles.size(), hipMemcpyHostToDevice, h->stream));
   // rows of the potentials past nb are never written; they scale zero rows and must be finite
   if ((st = zero(h, h->au, (group + 1) * 2 * np))) return st;
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));  // the host table must outlive its copy
+  h->adj_group = (int)group;
   return KK_OK;
+}
+
+// Reverse-pass workspace: the Krylov vectors always; the padded matrices of the expansion-point
+// part only once a call asks for dL/dH (for a rank m, and again when a later rank wants larger
+// groups). Where the device has no room for them the groups are halved, down to one direction, and
+// then the contractions are left uncut (12 padded matrices in all); what fits is kept.
+kk_status ensure_adjoint(kk_handle h, bool want_H, int m) {
+  const size_t n2 = 2 * (size_t)h->natoms;
+  kk_status st;
+  if (!h->ag) {
+    Slab slab;
+    for (double** q : {&h->alam, &h->abbar, &h->aKd, &h->ay}) slab.add(q, n2);
+    for (double** q : {&h->ag, &h->aVbar, &h->aFbar}) slab.add(q, kk::MAX_RANK * n2);
+    if ((st = slab.commit(h->adj_owned))) return st;
+  }
+  int group = adjoint_group(h, m);
+  if (h->adj_fit > 0) group = std::min(group, h->adj_fit);
+  if (!want_H || group <= h->adj_group) return KK_OK;
+  HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+  h->free_adjoint_h();
+  while ((st = alloc_adjoint_h(h, group)) == KK_ENOMEM) {
+    if (group > 1) {
+      group = (group + 1) / 2;
+    } else if (!h->adj_lean) {
+      h->adj_lean = true;
+    } else {  // a later call starts over
+      h->adj_fit = 0;
+      h->adj_lean = false;
+      return st;
+    }
+    h->adj_fit = group;
+  }
+  return st;
 }
 
 // (The reverse pass of 128 atoms, m = 8, with the transforms of two spins cut along K like the
