@@ -768,17 +768,19 @@ __global__ void __launch_bounds__(1024) krylov_orthonormalize(const double* __re
 // O = F~^T F~, rhs = F~^T f~ of the first r directions, Cholesky O = L L^T, c = O^-1 rhs, with x given
 // x = V c (0 on a non-positive pivot), and the projected residual ||F~ c - f~|| / ||f~|| formed
 // explicitly, returned to thread 0. One block of at most 16 waves; lds: solve_lds(r) doubles. Ends
-// without a barrier.
+// without a barrier. Every result has the same bits whatever the number of waves and whether x is
+// given: an adaptive update ends at a rank that its inputs alone decide, wherever its tests ran.
 struct Solution {
   double residual, min_pivot, max_pivot;
   bool ok;  // every pivot positive
 };
-constexpr int solve_lds(int r) { return r * (r + 1) + r + 2 * 16 + 3; }
+constexpr int SOLVE_ROWS = 8 * 1024 / WAVE;  // n2 <= 8 * 1024
+constexpr int solve_lds(int r) { return r * (r + 1) + r + 2 * SOLVE_ROWS + 3; }
 __device__ __forceinline__ Solution least_squares(const double* __restrict__ V, const double* Ft,
                                                   const double* __restrict__ ftilde, int n2, int r,
                                                   double* __restrict__ x, double* lds) {
   const int ldo = r + 1;
-  double *const O = lds, *const c = O + r * ldo, *const sr = c + r, *const fin = sr + 2 * 16;
+  double *const O = lds, *const c = O + r * ldo, *const sr = c + r, *const fin = sr + 2 * SOLVE_ROWS;
   const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
   // The r (r + 1) / 2 entries of O and the r of the right-hand side, one wave each (fixed
   // lane order and reduction tree, so the result is deterministic); 4 loads per lane in flight.
@@ -862,48 +864,50 @@ __device__ __forceinline__ Solution least_squares(const double* __restrict__ V, 
   }
   __syncthreads();
   const bool okv = fin[0] != 0.0;
-  double rr = 0.0, ff = 0.0;
-  for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-    double s = 0.0, fi = 0.0;
-    if (okv) {
-      int k = 0;
-      for (; k + 4 <= r; k += 4) {
-        double vv[4], fv[4];
+  // The residual's sums of a row of WAVE entries each, added up in the rows' order
+  for (int base = wave * WAVE; base < n2; base += blockDim.x) {
+    const int i = base + lane;
+    double rr = 0.0, ff = 0.0;
+    if (i < n2) {
+      double s = 0.0, fi = 0.0;
+      if (okv) {
+        int k = 0;
+        for (; k + 4 <= r; k += 4) {
+          double vv[4], fv[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          vv[q] = x != nullptr ? V[(size_t)(k + q) * n2 + i] : 0.0;
-          fv[q] = Ft[(size_t)(k + q) * n2 + i];
+          for (int q = 0; q < 4; ++q) {
+            vv[q] = x != nullptr ? V[(size_t)(k + q) * n2 + i] : 0.0;
+            fv[q] = Ft[(size_t)(k + q) * n2 + i];
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            s += c[k + q] * vv[q];
+            fi += c[k + q] * fv[q];
+          }
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          s += c[k + q] * vv[q];
-          fi += c[k + q] * fv[q];
+        for (; k < r; ++k) {
+          s += c[k] * (x != nullptr ? V[(size_t)k * n2 + i] : 0.0);
+          fi += c[k] * Ft[(size_t)k * n2 + i];
         }
       }
-      for (; k < r; ++k) {
-        s += c[k] * (x != nullptr ? V[(size_t)k * n2 + i] : 0.0);
-        fi += c[k] * Ft[(size_t)k * n2 + i];
-      }
+      if (x != nullptr) x[i] = s;
+      const double fti = ftilde[i], e = fi - fti;
+      rr = e * e;
+      ff = fti * fti;
     }
-    if (x != nullptr) x[i] = s;
-    const double fti = ftilde[i];
-    const double e = fi - fti;
-    rr += e * e;
-    ff += fti * fti;
-  }
-  rr = wave_sum_dpp(rr);
-  ff = wave_sum_dpp(ff);
-  if (lane == 0) {
-    sr[wave] = rr;
-    sr[16 + wave] = ff;
+    rr = wave_sum_dpp(rr);
+    ff = wave_sum_dpp(ff);
+    if (lane == 0) {
+      sr[base / WAVE] = rr;
+      sr[SOLVE_ROWS + base / WAVE] = ff;
+    }
   }
   __syncthreads();
-  rr = 0.0;
-  ff = 0.0;
+  double rr = 0.0, ff = 0.0;
   if (threadIdx.x == 0)
-    for (int q = 0; q < nw; ++q) {
+    for (int q = 0; q < (n2 + WAVE - 1) / WAVE; ++q) {
       rr += sr[q];
-      ff += sr[16 + q];
+      ff += sr[SOLVE_ROWS + q];
     }
   return {ff > 0.0 ? sqrt(rr / ff) : 0.0, fin[1], fin[2], okv};
 }
