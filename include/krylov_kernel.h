@@ -272,12 +272,12 @@ kk_status krylov_kernel_adjoint(kk_handle h, const double *delta, int m, const d
 /*
  * Batched form: many independent systems (e.g. uneven Fe clusters) updated
  * together. Every step of the Krylov loop is one launch for all systems (the
- * two transforms are persistent kernels over a global tile list sorted by
- * cost); the whole rank-m update is captured once into a hipGraph on the
+ * two transforms two, one for each tile shape, a workgroup to a tile, the costliest
+ * tiles first); the whole rank-m update is captured once into a hipGraph on the
  * batch's private stream and replayed, ordered after the caller's stream by
  * events. The first update autotunes the tile shape per system size (64 x 64
- * tiles below a threshold, the single-system shape above) and the number of
- * persistent workgroups per CU by timing every candidate on the batch itself.
+ * tiles below a threshold, the single-system shape above) by timing every
+ * candidate threshold on the batch itself.
  */
 typedef struct kk_batch_s *kk_batch;
 
@@ -313,16 +313,17 @@ kk_status krylov_kernel_apply_batch(kk_batch b, const double *const *delta, int 
                                     kk_info *info);
 
 /* Tuning chosen by the autotuner (or set by kk_batch_set_tuning): the largest
- * padded size that uses 64 x 64 tiles (0 = none), persistent workgroups per
- * CU, and the fastest update's time in milliseconds (0 when set by hand). */
+ * padded size that uses 64 x 64 tiles (0 = none), the workgroups per CU that were
+ * set (2 if none were), and the fastest update's time in milliseconds (0 when set by hand). */
 kk_status kk_batch_tuning(kk_batch b, int *small_np_max, int *workgroups_per_cu, double *update_ms);
 
 /*
  * kk_batch_set_tuning -- fix the tuning instead of letting the first update
  * autotune: systems whose padded size is <= small_np_max (>= 0; 0 = none,
  * a value above every system's = all) take the 64 x 64 tile class, the rest
- * the large one; workgroups_per_cu (1..8) persistent workgroups per CU. Valid
- * after kk_batch_prepare (which resets it); drops any captured graph, so the
+ * the large one. workgroups_per_cu (1..8) is checked and reported but no longer
+ * changes anything: the hardware hands the tiles out. Valid after
+ * kk_batch_prepare (which resets it); drops any captured graph, so the
  * next update captures anew. For reproducible timings and for tests that must
  * reach each tile class. Synchronizes the batch's stream.
  */

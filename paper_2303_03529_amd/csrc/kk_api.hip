@@ -1260,11 +1260,9 @@ kk_status allocate_prepared(kk_handle h) {
   unsigned char* act[2];
   int2 *range[2], *tiles[2];
   slab.add(&count, 2);
-  for (int s = 0; s < 2; ++s) {
-    slab.add(&act[s], (size_t)h->win.nblk * h->win.nblk);
-    slab.add(&range[s], h->win.nblk);
-    slab.add(&tiles[s], ft.n);
-  }
+  for (int s = 0; s < 2; ++s) slab.add(&act[s], (size_t)h->win.nblk * h->win.nblk);
+  for (int s = 0; s < 2; ++s) slab.add(&range[s], h->win.nblk);  // (read_window copies the four tables at once)
+  for (int s = 0; s < 2; ++s) slab.add(&tiles[s], ft.n);
   kk_status st = slab.commit(h->owned);
   ++h->alloc_gen;
   if (st) return st;
@@ -2636,11 +2634,16 @@ namespace {
 // Tile configurations a batch chooses between: large systems use the default
 // transforms, systems with np <= small_np_max use 64 x 64 tiles.
 
-struct TileClass {  // full-tile list of one tile class, shared by both transforms
-  int4* tiles = nullptr;  // kk::TileQueues: the XCDs' queues one after another; once: by decreasing cost
-  int* off = nullptr;     // XCDS + 1 queue starts
-  int n = 0;
-  bool once = false;      // the tiles all run at once: one workgroup each, without the queues
+struct TileClass {  // tiles of one tile class in one transform
+  int4* tiles = nullptr;  // b_gemm's, one to a workgroup
+  int n = 0, cap = 0;
+};
+
+// What the host keeps of a system's Window: its tables of both spins, act then range.
+struct HostWindow {
+  std::vector<unsigned char> bytes;
+  const unsigned char* act[2];
+  const int2* range[2];
 };
 
 }  // namespace
@@ -2658,9 +2661,8 @@ struct kk_batch_s {
   void* d_items_back = nullptr;
   int* d_pair_off = nullptr;     // first symmetrizing block pair of each forward item
   int sym_pairs = 0;             // block pairs over all forward items
-  TileClass cls[2];              // 0: large tiles, 1: small tiles
-  int* d_queue = nullptr;        // queue counters: XCDS for each of an update's transform launches
-  int queues_used = 0;           // launches enqueued so far for the update at hand
+  TileClass fwd[2], back[2];     // 0: large tiles, 1: small tiles
+  std::vector<HostWindow> windows;
   const double** d_delta = nullptr;
   double** d_out = nullptr;
   kk::KrylovState* d_info = nullptr;
@@ -2670,7 +2672,8 @@ struct kk_batch_s {
   std::vector<kk::SysDesc> h_sys;   // host copy of the descriptors (nparts depends on the tile class)
   std::vector<int> parts_large, parts_small;
   // tuning state
-  int small_np_max = 0, grid_mult = 2;
+  int small_np_max = 0;
+  int workgroups_per_cu = 2;  // as set, for kk_batch_tuning
   bool tuned = false;
   double tuned_ms = 0.0;
   // graph
@@ -2692,10 +2695,11 @@ struct kk_batch_s {
     sys.clear();
     for (void* p : owned) (void)hipFree(p);
     owned.clear();
-    for (auto& c : cls) c = TileClass{};
+    for (auto& c : fwd) c = TileClass{};
+    for (auto& c : back) c = TileClass{};
+    windows.clear();
     d_sys = nullptr; d_items_fwd = d_items_back = nullptr; d_delta = nullptr; d_out = nullptr; d_info = nullptr;
     d_pair_off = nullptr;
-    d_queue = nullptr;
     sym_pairs = 0;
     prepared = false;
     tuned = false;
@@ -2712,91 +2716,119 @@ kk_status balloc(kk_batch b, T** p, size_t count) {
   return st;
 }
 
-// Build the tile queues of both classes for a threshold: the systems (2 items each) by decreasing
-// np, so that the costly tiles start first, each item cut into row groups of TILE_GROUP tile rows
-// walked column by column (tile_order), and every group given to the queue with the least work so far.
-// Both transforms walk the full tiles (the forward as the product A = C^T U~ G).
+// The window tables of a prepared system, read back.
+kk_status read_window(kk_handle h, HostWindow& w) {
+  const char* const base = reinterpret_cast<const char*>(h->win.act[0]);
+  const char* const end = reinterpret_cast<const char*>(h->win.range[1] + h->win.nblk);
+  w.bytes.resize(end - base);
+  HIP_OR_FAIL(hipMemcpyAsync(w.bytes.data(), base, w.bytes.size(), hipMemcpyDeviceToHost, h->stream));
+  for (int s = 0; s < 2; ++s) {
+    w.act[s] = w.bytes.data() + (reinterpret_cast<const char*>(h->win.act[s]) - base);
+    w.range[s] = reinterpret_cast<const int2*>(w.bytes.data() + (reinterpret_cast<const char*>(h->win.range[s]) - base));
+  }
+  return KK_OK;
+}
+
+// A tile of a transform and what it costs, in contraction rows; group: the tiles that share its panels.
+struct ListedTile {
+  int4 tile;
+  int cost, group;
+};
+// Rows that a tile's prologue and epilogue take the time of.
+constexpr int LIST_TILE_COST = 64;
+
+// The launch order of `all`, its XCDs (workgroup mod XCDS) in turn. In order, so that the costly tiles start
+// first, every group goes to the XCD with the least work, whose L2 then holds the group's panels, as far as
+// that stays within an even share. Item -1 where an XCD has no more.
+void deal_tiles(const std::vector<ListedTile>& all, std::vector<int4>& tiles) {
+  double total = 0.0, load[kk::XCDS] = {};
+  for (const ListedTile& t : all) total += t.cost;
+  std::vector<int4> lists[kk::XCDS];
+  int x = 0, group = -1;
+  for (const ListedTile& t : all) {
+    if (t.group != group || load[x] * kk::XCDS >= total) x = (int)(std::min_element(load, load + kk::XCDS) - load);
+    group = t.group;
+    load[x] += t.cost;
+    lists[x].push_back(t.tile);
+  }
+  tiles.clear();
+  for (size_t p = 0, left = all.size(); left > 0; ++p)
+    for (const std::vector<int4>& l : lists) {
+      tiles.push_back(p < l.size() ? l[p] : make_int4(-1, 0, 0, 0));
+      left -= p < l.size();
+    }
+}
+
+// Build the tile lists of both classes and transforms for a threshold: the systems (2 items each) by
+// decreasing np, each item in row groups of TILE_GROUP tile rows walked column by column (tile_order).
+// The forward (the product A = C^T U~ G) takes the tiles in which Y may be non-zero, the back-transform all, over
+// the rows where it may.
 kk_status build_tile_lists(kk_batch b, int small_np_max) {
+  static_assert(KSTEP % kk::LIST_STEP == 0 && kk::WIN % kk::LIST_STEP == 0 && 65536 / kk::LIST_STEP < 1 << 16, "list_rows");
   const bool mixed = b->precision == KK_MIXED_F16;
   std::vector<int> order(b->ns);
   for (int i = 0; i < b->ns; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->np_of[x] > b->np_of[y]; });
-  std::vector<int4> queues[2][kk::XCDS];
-  std::vector<int4> plain[2];
-  double load[2][kk::XCDS] = {};
+  std::vector<ListedTile> all[2][2];  // class, transform
+  int group = 0;
   for (int i : order) {
-    const int np = b->np_of[i];
+    const int np = b->np_of[i], k = b->sys[i]->kc;
     const int c = np <= small_np_max ? 1 : 0;
-    int bm, bn, sbm, sbn;
-    if (mixed) { bm = kk::MLargeCfg::BM; bn = kk::MLargeCfg::BN; sbm = SmallMx::BM; sbn = SmallMx::BN; }
-    else { bm = kk::BackCfg::BM; bn = kk::BackCfg::BN; sbm = SmallF64::BM; sbn = SmallF64::BN; }
-    const int tbm = c ? sbm : bm, tbn = c ? sbn : bn;
-    for (int s = 0; s < 2; ++s) {
-      const int item = 2 * i + s;
-      int group = -1, q = 0;
-      for (const int2& t : tile_order(np, tbm, tbn, false)) {
-        if (t.x / kk::TILE_GROUP != group) {
-          group = t.x / kk::TILE_GROUP;
-          q = (int)(std::min_element(load[c], load[c] + kk::XCDS) - load[c]);
-        }
-        queues[c][q].push_back(make_int4(item, t.x, t.y, 0));
-        plain[c].push_back(queues[c][q].back());
-        load[c][q] += b->sys[i]->kc;
-      }
+    int bm, bn, align, least;
+    if (mixed) {
+      bm = c ? SmallMx::BM : kk::MLargeCfg::BM; bn = c ? SmallMx::BN : kk::MLargeCfg::BN;
+      align = c ? kk::WIN_ROWS_MIXED<SmallMx> : kk::WIN_ROWS_MIXED<kk::MLargeCfg>;
+      least = c ? SmallMx::BK : kk::MLargeCfg::BK;
+    } else {
+      bm = c ? SmallF64::BM : kk::BackCfg::BM; bn = c ? SmallF64::BN : kk::BackCfg::BN;
+      align = kk::LIST_STEP;
+      least = 0;
     }
-  }
-  std::vector<int4> lists[2];
-  std::vector<int> offs[2];
-  for (int c = 0; c < 2; ++c) {
-    offs[c].push_back(0);
-    for (const std::vector<int4>& q : queues[c]) {
-      lists[c].insert(lists[c].end(), q.begin(), q.end());
-      offs[c].push_back((int)lists[c].size());
+    for (int s = 0; s < 2; ++s) {
+      const int item = 2 * i + s, nblk = np / kk::WIN;
+      const unsigned char* act = b->windows[i].act[s];
+      int row_group = -1;
+      for (const int2& t : tile_order(np, bm, bn, false)) {
+        if (t.x / kk::TILE_GROUP != row_group) ++group;
+        row_group = t.x / kk::TILE_GROUP;
+        const int whole = kk::list_rows(make_int2(0, k));
+        bool active = false;
+        for (int p = 0; p < bm / kk::WIN; ++p)
+          for (int q = 0; q < bn / kk::WIN; ++q)
+            active |= act[(size_t)(t.x * (bm / kk::WIN) + p) * nblk + t.y * (bn / kk::WIN) + q] != 0;
+        if (active) all[c][0].push_back({make_int4(item, t.x, t.y, whole), k + LIST_TILE_COST, group});
+        const int2 rows = kk::window_rows(b->windows[i].range[s], t.y * (bn / kk::WIN), bn / kk::WIN, k, align, least);
+        all[c][1].push_back({make_int4(item, t.x, t.y, kk::list_rows(rows)), rows.y - rows.x + LIST_TILE_COST, group});
+      }
     }
   }
   for (int i = 0; i < b->ns; ++i)
     b->h_sys[i].nparts = b->np_of[i] <= small_np_max ? b->parts_small[i] : b->parts_large[i];
   HIP_OR_FAIL(hipMemcpyAsync(b->d_sys, b->h_sys.data(), sizeof(kk::SysDesc) * b->ns, hipMemcpyHostToDevice,
                              b->stream));
-  for (int c = 0; c < 2; ++c) {
-    TileClass& tc = b->cls[c];
-    tc.n = (int)lists[c].size();
-    const int per_cu = mixed ? (c ? SmallMx::MIN_BLOCKS : kk::MLargeCfg::MIN_BLOCKS)
-                             : (c ? SmallF64::MIN_BLOCKS : kk::BackCfg::MIN_BLOCKS);
-    tc.once = tc.n <= cu_count() * per_cu;
-    if (tc.once) lists[c] = plain[c];
-    if (!tc.tiles) {  // capacity for every system in either class: the larger per-system count (small tiles)
-      size_t cap = 0;
-      for (int i = 0; i < b->ns; ++i) {
-        const int np = b->np_of[i];
-        const int sb = mixed ? SmallMx::BM : SmallF64::BM;
-        cap += 2 * (size_t)(np / sb) * (np / sb);
+  std::vector<int4> lists[2][2];
+  for (int c = 0; c < 2; ++c)
+    for (int d = 0; d < 2; ++d) {
+      TileClass& tc = d ? b->back[c] : b->fwd[c];
+      deal_tiles(all[c][d], lists[c][d]);
+      tc.n = (int)lists[c][d].size();
+      if (tc.n > tc.cap) {
+        kk_status st;
+        tc.cap = 0;
+        if ((st = balloc(b, &tc.tiles, tc.n))) return st;
+        tc.cap = tc.n;
       }
-      kk_status st;
-      if ((st = balloc(b, &tc.tiles, cap + 1))) return st;
-      if ((st = balloc(b, &tc.off, kk::XCDS + 1))) return st;
+      if (tc.n)
+        HIP_OR_FAIL(hipMemcpyAsync(tc.tiles, lists[c][d].data(), sizeof(int4) * tc.n, hipMemcpyHostToDevice, b->stream));
     }
-    HIP_OR_FAIL(hipMemcpyAsync(tc.off, offs[c].data(), sizeof(int) * offs[c].size(), hipMemcpyHostToDevice, b->stream));
-    if (tc.n)
-      HIP_OR_FAIL(hipMemcpyAsync(tc.tiles, lists[c].data(), sizeof(int4) * tc.n, hipMemcpyHostToDevice, b->stream));
-  }
   HIP_OR_FAIL(hipStreamSynchronize(b->stream));
   return KK_OK;
 }
 
-constexpr int BATCH_QUEUE_LAUNCHES = 4 * kk::MAX_RANK;  // per direction two transforms of two tile classes
-
 template <int EPI, class Cfg, class Item>
-kk_status launch_persistent(kk_batch b, const Item* items, const TileClass& c) {
+kk_status launch_tiles(kk_batch b, const Item* items, const TileClass& c) {
   if (c.n == 0) return KK_OK;
-  if (b->queues_used >= BATCH_QUEUE_LAUNCHES) return fail(KK_EINVAL, "internal: too many transform launches");
-  const kk::TileQueues q{c.tiles, c.off, b->d_queue + kk::XCDS * b->queues_used++};
-  if (c.once) {
-    kk::b_gemm<EPI, Cfg, false><<<c.n, Cfg::THREADS, 0, b->stream>>>(items, q);
-  } else {
-    const int grid = std::min(c.n, cu_count() * b->grid_mult);
-    kk::b_gemm<EPI, Cfg, true><<<grid, Cfg::THREADS, 0, b->stream>>>(items, q);
-  }
+  kk::b_gemm<EPI, Cfg><<<c.n, Cfg::THREADS, 0, b->stream>>>(items, c.tiles);
   LAUNCH_CHECK("b_gemm");
   return KK_OK;
 }
@@ -2805,8 +2837,7 @@ kk_status launch_persistent(kk_batch b, const Item* items, const TileClass& c) {
 kk_status enqueue_update(kk_batch b, int m) {
   const int ns = b->ns;
   const int bx_vec = (2 * b->maxN + 255) / 256;
-  b->queues_used = 0;
-  kk::b_reset<<<ns, 64, 0, b->stream>>>(b->d_sys, b->d_queue, kk::XCDS * BATCH_QUEUE_LAUNCHES);
+  kk::b_reset<<<ns, 64, 0, b->stream>>>(b->d_sys);
   LAUNCH_CHECK("b_reset");
   kk::b_init<<<dim3(bx_vec, ns), 256, 0, b->stream>>>(b->d_sys, b->d_delta);
   LAUNCH_CHECK("b_init");
@@ -2837,27 +2868,27 @@ kk_status enqueue_update(kk_batch b, int m) {
       auto* bi = static_cast<const kk::BatchItemMixed*>(b->d_items_back);
       // forward: full-tile products A = C^T U~ G (the back-transform's tile lists), then
       // one symmetrizing pass over all items
-      if ((st = launch_persistent<kk::EPI_STORE, kk::MLargeCfg>(b, fi, b->cls[0])))
+      if ((st = launch_tiles<kk::EPI_STORE, kk::MLargeCfg>(b, fi, b->fwd[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_STORE, SmallMx>(b, fi, b->cls[1]))) return st;
+      if ((st = launch_tiles<kk::EPI_STORE, SmallMx>(b, fi, b->fwd[1]))) return st;
       kk::b_symmetrize<<<b->sym_pairs, kk::BATCH_SYM_T_MIXED, 0, b->stream>>>(fi, b->d_pair_off, 2 * ns);
       LAUNCH_CHECK("b_symmetrize");
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, kk::MLargeCfg>(b, bi, b->cls[0])))
+      if ((st = launch_tiles<kk::EPI_MULLIKEN, kk::MLargeCfg>(b, bi, b->back[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, SmallMx>(b, bi, b->cls[1])))
+      if ((st = launch_tiles<kk::EPI_MULLIKEN, SmallMx>(b, bi, b->back[1])))
         return st;
     } else {
       auto* fi = static_cast<const kk::BatchItemF64*>(b->d_items_fwd);
       auto* bi = static_cast<const kk::BatchItemF64*>(b->d_items_back);
       // forward: full-tile products A = C^T U~ G into Y, then one in-place symmetrizing pass
-      if ((st = launch_persistent<kk::EPI_XSTORE, kk::BackCfg>(b, fi, b->cls[0])))
+      if ((st = launch_tiles<kk::EPI_XSTORE, kk::BackCfg>(b, fi, b->fwd[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_XSTORE, SmallF64>(b, fi, b->cls[1]))) return st;
+      if ((st = launch_tiles<kk::EPI_XSTORE, SmallF64>(b, fi, b->fwd[1]))) return st;
       kk::b_symmetrize_f64<<<b->sym_pairs, kk::BATCH_SYM_T_F64, 0, b->stream>>>(fi, b->d_pair_off, 2 * ns);
       LAUNCH_CHECK("b_symmetrize_f64");
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, kk::BackCfg>(b, bi, b->cls[0])))
+      if ((st = launch_tiles<kk::EPI_MULLIKEN, kk::BackCfg>(b, bi, b->back[0])))
         return st;
-      if ((st = launch_persistent<kk::EPI_MULLIKEN, SmallF64>(b, bi, b->cls[1])))
+      if ((st = launch_tiles<kk::EPI_MULLIKEN, SmallF64>(b, bi, b->back[1])))
         return st;
     }
     kk::b_combine<<<dim3((b->maxN + kk::COMBINE_ATOMS - 1) / kk::COMBINE_ATOMS, ns), kk::COMBINE_THREADS, 0,
@@ -2885,37 +2916,31 @@ kk_status upload_pointer_tables(kk_batch b, const double* const* delta, double* 
   return KK_OK;
 }
 
-// Autotuner: time one update for every (small-tile threshold, workgroups per CU)
-// candidate on the batch's own systems and keep the fastest.
+// Autotuner: time one update for every small-tile threshold on the batch's own systems and keep
+// the fastest.
 kk_status autotune(kk_batch b, int m) {
   const int thresholds[] = {0, 512, 1024, 1 << 30};
-  const int mults[] = {1, 2, 4};
   hipEvent_t e0, e1;
   HIP_OR_FAIL(hipEventCreate(&e0));
   HIP_OR_FAIL(hipEventCreate(&e1));
   double best = 1e300;
-  int best_t = 0, best_m = 2;
+  int best_t = 0;
   kk_status st = KK_OK;
   for (int th : thresholds) {
     if ((st = build_tile_lists(b, th))) break;
-    for (int gm : mults) {
-      b->grid_mult = gm;
-      if ((st = enqueue_update(b, m))) break;  // warm-up
-      (void)hipEventRecord(e0, b->stream);
-      if ((st = enqueue_update(b, m))) break;
-      (void)hipEventRecord(e1, b->stream);
-      if (hipEventSynchronize(e1) != hipSuccess) { st = fail(KK_EHIP, "autotune: event sync failed"); break; }
-      float ms = 0.f;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      if (ms < best) { best = ms; best_t = th; best_m = gm; }
-    }
-    if (st) break;
+    if ((st = enqueue_update(b, m))) break;  // warm-up
+    (void)hipEventRecord(e0, b->stream);
+    if ((st = enqueue_update(b, m))) break;
+    (void)hipEventRecord(e1, b->stream);
+    if (hipEventSynchronize(e1) != hipSuccess) { st = fail(KK_EHIP, "autotune: event sync failed"); break; }
+    float ms = 0.f;
+    (void)hipEventElapsedTime(&ms, e0, e1);
+    if (ms < best) { best = ms; best_t = th; }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st) return st;
   b->small_np_max = best_t;
-  b->grid_mult = best_m;
   b->tuned_ms = best;
   b->tuned = true;
   return build_tile_lists(b, best_t);
@@ -2971,6 +2996,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
   b->maxN = 0;
   b->max_np = 0;
   b->np_of.assign(n_systems, 0);
+  b->windows.resize(n_systems);
   kk_status st;
   for (int i = 0; i < n_systems; ++i) {
     kk_handle h = nullptr;
@@ -2984,6 +3010,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
       return fail(st, "kk_batch_prepare: %s", buf);
     }
     if ((st = ensure_workspace(h, 1))) return st;
+    if ((st = read_window(h, b->windows[i]))) return st;
     b->maxN = std::max(b->maxN, h->natoms);
     b->max_np = std::max(b->max_np, h->np);
     b->np_of[i] = h->np;
@@ -3020,7 +3047,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
       if (mixed) {
         kk::BatchItemMixed fi{}, bi{};
         fi.n = bi.n = h->np; fi.k = bi.k = h->kc; fi.beta = bi.beta = h->beta; fi.stop = bi.stop = &h->kst->stop;
-        fi.act = bi.act = h->win.act[s]; fi.range = bi.range = h->win.range[s]; fi.nblk = bi.nblk = h->win.nblk;
+        fi.act = bi.act = h->win.act[s]; fi.nblk = bi.nblk = h->win.nblk;
         kk::MixedItem& F = fi.g;
         F.a0h = h->uct_h + s * np2; F.a0l = h->uct_l + s * np2; F.b0h = h->GTh[s]; F.b0l = h->GTl[s];
         F.yh = h->yh + s * np2; F.yl = h->yl + s * np2; F.x32 = h->x32 + s * np2;
@@ -3034,7 +3061,7 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
       } else {
         kk::BatchItemF64 fi{}, bi{};
         fi.n = bi.n = h->np; fi.k = bi.k = h->kc; fi.beta = bi.beta = h->beta; fi.stop = bi.stop = &h->kst->stop;
-        fi.act = bi.act = h->win.act[s]; fi.range = bi.range = h->win.range[s]; fi.nblk = bi.nblk = h->win.nblk;
+        fi.act = bi.act = h->win.act[s]; fi.nblk = bi.nblk = h->win.nblk;
         kk::GemmItem& F = fi.g;
         F.a0 = h->C[s]; F.b0 = h->G[s]; F.a1 = h->G[s]; F.b1 = h->C[s];
         F.scale = h->u + s * np; F.out = h->Y + s * np2;
@@ -3085,7 +3112,6 @@ kk_status kk_batch_prepare(kk_batch b, int n_systems, const int* n_atoms, const 
   if ((st = balloc(b, &b->d_delta, n_systems))) return st;
   if ((st = balloc(b, &b->d_out, n_systems))) return st;
   if ((st = balloc(b, &b->d_info, n_systems))) return st;
-  if ((st = balloc(b, &b->d_queue, (size_t)kk::XCDS * BATCH_QUEUE_LAUNCHES))) return st;
   b->h_delta.assign(n_systems, nullptr);
   b->h_out.assign(n_systems, nullptr);
   if ((st = build_tile_lists(b, 0))) return st;
@@ -3169,7 +3195,7 @@ kk_status kk_batch_set_tuning(kk_batch b, int small_np_max, int workgroups_per_c
   kk_status st;
   if ((st = build_tile_lists(b, small_np_max))) return st;
   b->small_np_max = small_np_max;
-  b->grid_mult = workgroups_per_cu;
+  b->workgroups_per_cu = workgroups_per_cu;
   b->tuned_ms = 0.0;
   b->tuned = true;
   g_err.clear();
@@ -3180,7 +3206,7 @@ kk_status kk_batch_tuning(kk_batch b, int* small_np_max, int* workgroups_per_cu,
   if (!b) return fail(KK_EINVAL, "kk_batch_tuning: batch is NULL");
   if (!b->tuned) return fail(KK_ENOTPREPARED, "kk_batch_tuning: no update has run yet");
   if (small_np_max) *small_np_max = b->small_np_max;
-  if (workgroups_per_cu) *workgroups_per_cu = b->grid_mult;
+  if (workgroups_per_cu) *workgroups_per_cu = b->workgroups_per_cu;
   if (update_ms) *update_ms = b->tuned_ms;
   return KK_OK;
 }

@@ -3,8 +3,8 @@
 // Every system keeps its own prepared state (a full single-system handle);
 // the batch adds device descriptor tables so that each step of the Krylov
 // loop is ONE launch for all systems: small kernels take the system from
-// blockIdx.y, and the two dense transforms are persistent kernels that take
-// tiles (system, spin, tile row, tile column) from queues, dearest first.
+// blockIdx.y, and the two dense transforms take a list of tiles (system, spin,
+// tile row, tile column, contraction rows), one to a workgroup.
 // The whole update is captured once into a hipGraph and replayed.
 #pragma once
 
@@ -41,7 +41,6 @@ struct BatchItemF64 {
   const int* stop;
   double beta;
   const unsigned char* act;  // the item's spin of its system's Window
-  const int2* range;
   int nblk;
 };
 
@@ -51,13 +50,10 @@ struct BatchItemMixed {
   const int* stop;
   double beta;
   const unsigned char* act;  // the item's spin of its system's Window
-  const int2* range;
   int nblk;
 };
 
-// Also clears the update's tile queue counters.
-__global__ void b_reset(SysDesc* d, int* queue, int nqueue) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nqueue; i += gridDim.x * blockDim.x) queue[i] = 0;
+__global__ void b_reset(SysDesc* d) {
   if (threadIdx.x == 0) {
     KrylovState* st = d[blockIdx.x].kst;
     st->rank = 0; st->stop = 0; st->status = 0; st->done = 0;
@@ -171,135 +167,48 @@ __global__ void b_info(const SysDesc* __restrict__ d, int ns, KrylovState* __res
   if (i < ns) out[i] = *d[i].kst;
 }
 
-// Whether a BM x BN forward tile holds a block in which Y may be non-zero.
-template <class Cfg, class Item>
-__device__ __forceinline__ bool window_tile_active(const Item& it, int tm, int tn) {
-  bool any = false;
-  for (int i = 0; i < Cfg::BM / WIN; ++i)
-    for (int j = 0; j < Cfg::BN / WIN; ++j)
-      any |= window_active(it.act, it.nblk, tm * (Cfg::BM / WIN) + i, tn * (Cfg::BN / WIN) + j);
-  return any;
-}
-
-// Tile queues of a persistent transform: one per XCD, so that the workgroups of an XCD (blockIdx
-// mod 8) work on the same systems' panels in its L2. tiles[off[x]..off[x + 1]) is queue x, filled
-// by the host with whole row groups of systems, dearest first, to equal cost; next[x] counts
-// what has been taken. A workgroup takes tiles from its own queue until that is empty, then from
-// the others', so the launch ends level whatever the systems' stop flags and windows leave out,
-// and a workgroup that starts late finds all queues empty and ends. Against a fixed stride over one
-// list (tile t to workgroup t mod grid): 24 clusters of 16-250 atoms, FP64, m = 6, 54.9 -> 48.8 ms
-// an update; 64 clusters FP16 x 3 49.8 -> 45.3 ms, FP64 5.33 -> 5.94 updates/s (the windows alone,
-// whose gaps a stride cannot close, gave the 24 clusters 0.8 %).
-constexpr int XCDS = 8;
-struct TileQueues {
-  const int4* tiles;
-  const int* off;  // XCDS + 1
-  int* next;       // XCDS counters, zero at the launch: tiles taken after the workgroups' first ones
-};
-
-// Takes the workgroup's next tile; false once there is none. A workgroup's first tile is its own
-// place in its XCD's queue, without the counters, and one look at all counters finds a queue
-// that is not empty: a counter's round trip is a microsecond and more, and walking the eight of
-// them to the end of a launch cost the 64 x 64 class of 16 small clusters 46 us for 16.
-struct QueueState {
-  bool first = true;
-};
-__device__ __forceinline__ bool queue_take(const TileQueues& q, QueueState& st, int4& tile) {
-  __shared__ int4 taken;
-  if (threadIdx.x < WAVE) {
-    const int lane = threadIdx.x, grid = gridDim.x, own = blockIdx.x % XCDS;
-    const int x = lane % XCDS, off = q.off[x], len = q.off[x + 1] - off;
-    const int ahead = (grid - x + XCDS - 1) / XCDS;  // first tiles of queue x's workgroups
-    int4 got = make_int4(-1, 0, 0, 0);
-    if (st.first && (int)(blockIdx.x / XCDS) < __shfl(len, own)) {
-      got = q.tiles[__shfl(off, own) + blockIdx.x / XCDS];
-    } else {
-      for (;;) {
-        const int used = __hip_atomic_load(&q.next[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned full = (unsigned)__ballot(ahead + used < len) & ((1u << XCDS) - 1);
-        if (full == 0) break;  // every counter has reached its queue's end, and counters only grow
-        // the own queue, or the next one after it that has tiles left
-        const unsigned turned = ((full >> own) | (full << (XCDS - own))) & ((1u << XCDS) - 1);
-        const int from = (own + __builtin_ctz(turned)) % XCDS;
-        int at = 0;
-        if (lane == 0) at = atomicAdd(&q.next[from], 1);
-        at = __shfl(at, 0) + __shfl(ahead, from);
-        if (at < __shfl(len, from)) {
-          got = q.tiles[__shfl(off, from) + at];
-          break;
-        }
-      }
-    }
-    if (lane == 0) taken = got;
-  }
-  st.first = false;
-  __syncthreads();
-  // uniform for the compiler too: the tile's pointers stay scalar
-  tile = make_int4(__builtin_amdgcn_readfirstlane(taken.x), __builtin_amdgcn_readfirstlane(taken.y),
-                   __builtin_amdgcn_readfirstlane(taken.z), 0);
-  __syncthreads();  // taken is free for the next call
-  return tile.x >= 0;
-}
-
-// Transforms over the tile queues (QUEUED), or one tile to each workgroup; a tile of a system whose
-// Krylov expansion has stopped, or that its window leaves out, is skipped (uniformly for the workgroup).
-// A launch whose tiles all run at once has neither queues nor windows, which could only add to its
-// latency: 10 clusters of 30-70 atoms, FP16 x 3, 1.28 ms an update against 1.49 with the queues and 1.35
-// with a stride loop; 16 of 20-60 atoms FP64, 2.10 against 2.15 and 2.14.
+// Transforms of all systems, a workgroup to a tile: (item, tile row, tile column, contraction rows in steps
+// of LIST_STEP: first in the low, end in the high 16 bits), laid out by the host from the systems' sizes and
+// windows (deal_tiles); item -1: none. A tile of a system whose Krylov expansion has stopped is skipped.
+// The hardware hands the tiles out, which levels what stop flags and neighbours on a CU make of their
+// times at no cost to a tile. Against one list in strides of a fixed grid and against queues with counters in
+// memory (every tile waited 2-3 us for its counter, and a few bytes of LDS more took the split 64 x 64 class
+// from four workgroups a CU to three), m = 3, each at its best tuning, strides / queues / now: 24
+// clusters of 16-250 atoms FP64 27.2 / 23.9 / 24.0 ms, where no block is negligible 27.2 / 27.1 / 27.2; FP16 x 3 7.58 /
+// 6.91 / 6.38 and 7.79 / 8.11 / 7.49 ms; 64 of 30-50 atoms FP64 2.31 / 2.25 / 2.00 ms, FP16 x 3 1.56 / 1.47 / 1.40. Lists
+// that the host levels for a fixed grid were 1-2 % slower (FP64) or level.
 // Held to MIN_BLOCKS workgroups per CU: the two-half forward form with the Fermi
 // epilogue, which this kernel ran before the full-tile forward, took ~164 registers per
 // lane and one workgroup per CU when left to itself (13 % slower); the full-tile
 // product and the back-transform fit without spilling.
-template <int EPI, class Cfg, bool QUEUED>
+constexpr int XCDS = 8, LIST_STEP = 32;
+inline int list_rows(int2 rows) { return rows.x / LIST_STEP | (rows.y / LIST_STEP) << 16; }
+__device__ __forceinline__ int2 listed_rows(int w) {
+  return make_int2((w & 0xffff) * LIST_STEP, (int)((unsigned)w >> 16) * LIST_STEP);
+}
+template <int EPI, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu(Cfg::WAVES_PER_EU)))
-void b_gemm(const BatchItemF64* __restrict__ items, const TileQueues q) {
-  if constexpr (!QUEUED) {
-    const int4 tl = q.tiles[blockIdx.x];
-    const BatchItemF64& it = items[tl.x];
-    if (*it.stop) return;
-    f64_tile<EPI, Cfg>(it.g, HalfRows{it.g, it.n, 0, it.k, false}, it.n, make_int2(tl.y, tl.z), it.beta);
-  } else {
-    QueueState take;
-    int4 tl;
-    while (queue_take(q, take, tl)) {
-      const BatchItemF64& it = items[tl.x];
-      if (*it.stop) continue;
-      int2 rows = make_int2(0, it.k);
-      if constexpr (EPI == EPI_MULLIKEN)
-        rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, Cfg::BK, 0);
-      else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
-        continue;
-      const HalfRows src{it.g, it.n, rows.x, rows.y - rows.x, false};
-      f64_tile<EPI, Cfg>(it.g, src, it.n, make_int2(tl.y, tl.z), it.beta);
-    }
-  }
+void b_gemm(const BatchItemF64* __restrict__ items, const int4* __restrict__ tiles) {
+  const int4 tl = tiles[blockIdx.x];
+  if (tl.x < 0) return;
+  const BatchItemF64& it = items[tl.x];
+  if (*it.stop) return;
+  const int2 rows = listed_rows(tl.w);
+  f64_tile<EPI, Cfg>(it.g, HalfRows{it.g, it.n, rows.x, rows.y - rows.x, false}, it.n, make_int2(tl.y, tl.z), it.beta);
 }
 
 // Held to MIN_BLOCKS workgroups per CU as well (the two-half forward form with a staged
 // mirror epilogue, which this kernel ran before the full-tile forward, took ~190 registers
 // and one workgroup per CU when left to itself, 4 % slower).
-template <int EPI, class Cfg, bool QUEUED>
+template <int EPI, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS) __attribute__((amdgpu_waves_per_eu((Cfg::MIN_BLOCKS * Cfg::THREADS / 64 + 3) / 4)))
-void b_gemm(const BatchItemMixed* __restrict__ items, const TileQueues q) {
-  if constexpr (!QUEUED) {
-    const int4 tl = q.tiles[blockIdx.x];
-    const BatchItemMixed& it = items[tl.x];
-    if (*it.stop) return;
-    mixed_tile<EPI, Cfg>(it.g, it.n, 0, it.k, make_int2(tl.y, tl.z));
-  } else {
-    QueueState take;
-    int4 tl;
-    while (queue_take(q, take, tl)) {
-      const BatchItemMixed& it = items[tl.x];
-      if (*it.stop) continue;
-      int2 rows = make_int2(0, it.k);
-      if constexpr (EPI == EPI_MULLIKEN)
-        rows = window_rows(it.range, tl.z * (Cfg::BN / WIN), Cfg::BN / WIN, it.k, WIN_ROWS_MIXED<Cfg>, Cfg::BK);
-      else if (!window_tile_active<Cfg>(it, tl.y, tl.z))
-        continue;
-      mixed_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, make_int2(tl.y, tl.z));
-    }
-  }
+void b_gemm(const BatchItemMixed* __restrict__ items, const int4* __restrict__ tiles) {
+  const int4 tl = tiles[blockIdx.x];
+  if (tl.x < 0) return;
+  const BatchItemMixed& it = items[tl.x];
+  if (*it.stop) return;
+  const int2 rows = listed_rows(tl.w);
+  mixed_tile<EPI, Cfg>(it.g, it.n, rows.x, rows.y - rows.x, make_int2(tl.y, tl.z));
 }
 
 }  // namespace kk

@@ -187,17 +187,18 @@ __device__ __forceinline__ void window_rest(const Window& w, int ntiles, int nit
 // Back-transform: the rows [lo, hi) of a contraction over [0, k_len) that the columns of `blocks`
 // blocks from block c need, lo rounded down to a multiple of `align`; the first `least` rows where
 // none or fewer remain.
-__device__ __forceinline__ int2 window_rows(const int2* range, int c, int blocks, int k_len, int align, int least) {
+__host__ __device__ __forceinline__ int2 window_rows(const int2* range, int c, int blocks, int k_len, int align,
+                                                     int least) {
   int lo = 1 << 30, hi = 0;
   for (int q = 0; q < blocks; ++q) {
     const int2 r = range[c + q];
     if (r.y > r.x) {
-      lo = min(lo, r.x);
-      hi = max(hi, r.y);
+      lo = r.x < lo ? r.x : lo;
+      hi = r.y > hi ? r.y : hi;
     }
   }
   lo = lo / align * align;
-  hi = min(k_len, hi);
+  hi = k_len < hi ? k_len : hi;
   return hi > lo && hi - lo >= least ? make_int2(lo, hi) : make_int2(0, least);
 }
 __device__ __forceinline__ bool window_active(const unsigned char* act, int nblk, int I, int J) {
