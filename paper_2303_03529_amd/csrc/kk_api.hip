@@ -155,6 +155,10 @@ struct kk_handle_s {
   // the back-transform in kchb (= kch), nbase Mulliken partial rows per back chunk
   // (nparts = kchb nbase)
   int kch = 1, kchb = 1, kck = 0, nbase = 0;
+  // FP64 handles of both forms (plan_f64): kch = 1, and single directions in one_chunks chunks of one_ck rows with
+  // one_parts Mulliken partial rows where the prepared spectrum says so (one_split)
+  int one_chunks = 1, one_ck = 0, one_parts = 0;
+  bool one_split = false;
   // Stream-K products (split forms, small shape; choose_stream_k): kch = kchb = the slots
   // of partial results per item, sk_grid workgroups per product launch
   bool sk = false;
@@ -228,7 +232,7 @@ struct kk_handle_s {
 
   // Captured single-system update (krylov_run without profiling): captured on a private
   // stream (the caller's may be the null stream, which cannot capture) and replayed on the
-  // handle's stream while its key (K0, m, tol, allocation generation, W, beta) holds. The
+  // handle's stream while its key (K0, m, tol, allocation generation, W, beta, one_split) holds. The
   // caller's delta and K delta are arguments of two kinds of kernel node (the first
   // precondition reads delta, every krylov_solve writes K delta); a call with other
   // pointers rewrites those nodes' arguments in the executable graph.
@@ -250,6 +254,7 @@ struct kk_handle_s {
   double g_tol = -1.0;
   long g_gen = -1;
   double g_W = 0.0, g_beta = 0.0;
+  bool g_one_split = false;
   bool no_graph = false;  // set if a capture failed: the eager path from then on
 
   // adaptive updates that the host waits for (krylov_adaptive_sync)
@@ -460,6 +465,7 @@ constexpr int TINY_STEP_MAX_KC = KK_TINY_STEP_MAX_KC;
 // the chunks of their contraction, ck rows each.
 struct F64Plan {
   int cls = 0, chunks = 1, ck = 0;
+  int one_chunks = 1, one_ck = 0;  // the K-split that single directions may take in place of chunks = 1
   int side() const { return cls ? SmallF64::BM : kk::BackCfg::BM; }
   int tiles(int np) const { return (np / side()) * (np / side()); }
   // Mulliken partial rows per chunk
@@ -473,11 +479,10 @@ struct F64Plan {
 // 1680 -> 2977, 37 atoms 1816 -> 2747, 56 atoms 1734 -> 2100; from a padded size of 640
 // the rule stops splitting these tiles (70 and 85 atoms: level).
 constexpr int KTINY_MAX_NP = 512;
-// Turns of the chip's CUs, in 128 x 128 tiles, that the unsplit 64 x 64 tiles of a windowed launch
+// Turns of the chip's CUs, in 128 x 128 tiles, that w unsplit 64 x 64 tiles of a windowed launch
 // take, the last in quarters (Tail), and that a K-split of 128 x 128 ones takes.
-double small_turns(int nb, int cus) {
+double small_turns(int w, int cus) {
   constexpr int S = kk::Tail<SmallF64>::PIECES;
-  const int side = (nb + SmallF64::BM - 1) / SmallF64::BM, w = 2 * side * side;
   const int whole = kk::tail_begin<SmallF64>(w, cus);
   return ((whole + cus - 1) / cus + (double)((S * (w - whole) + cus - 1) / cus) / S) / 4.0;
 }
@@ -487,11 +492,23 @@ double ksplit_turns(int np, int chunks, int cus) {
 }
 // From a padded size of WINDOWED_MIN_NP a handle that would be K-split has unsplit 64 x 64 tiles and the
 // window tables instead where those take fewer turns: no partial products to write and add, and
-// no work on the padding. m = 4, K-split / unsplit: 90 atoms (turns 0.5 / 0.375) 591 / 540 us, 99
-// atoms (0.5 / 0.44) 625 / 596, 120 atoms (0.67 / 0.625) 957 / 850; but 113 atoms (0.5 / 0.5) 711 / 746,
-// 128 atoms (0.67 / 0.75) 957 / 997. Smaller, a lone workgroup's unsplit contraction is too long: 85
-// atoms (0.33 / 0.31) 423 / 465.
+// no work on the padding. K-split / unsplit, levels over 60 eV at kT = 0.25 and 1 eV (where no block is left
+// out), m = 4: 86 atoms (turns 0.5 / 0.375) 602 / 518 and 604 / 549 us, 99 atoms (0.5 / 0.44) 638 / 595 and 638 / 618; eight
+// responses 917 / 605 and 917 / 670, 980 / 725 and 981 / 836. A launch of one direction needs a lead of a tenth, by the tiles that
+// its spectrum leaves (small_turns of their count; one_split): 116 atoms (0.67 / 0.625 of all tiles, 0.56 of
+// those left at 0.25 eV) 890 / 829 and 889 / 967 us, 120 atoms 951 / 847 and 951 / 990; eight responses there 1615 / 1239
+// and 1614 / 1435 us. No gain at 113 atoms (0.5 / 0.5) 711 / 746, 128 atoms (0.67 / 0.75) 957 / 997. Smaller, a
+// lone workgroup's unsplit contraction is too long: 85 atoms (0.33 / 0.31) 423 / 465.
 constexpr int WINDOWED_MIN_NP = 896;
+constexpr double ONE_DIRECTION_LEAD = 0.9;
+// The forward tiles of both spins that hold a level each.
+int level_tiles(int nb) {
+  const int side = (nb + SmallF64::BM - 1) / SmallF64::BM;
+  return 2 * side * side;
+}
+bool one_direction_splits(int np, int chunks, int tiles, int cus) {
+  return small_turns(tiles, cus) >= ONE_DIRECTION_LEAD * ksplit_turns(np, chunks, cus);
+}
 // nb > 0: a handle whose transforms may go by window tables.
 F64Plan plan_f64(int np, int kc, int cus, bool may_split, int nb = 0) {
   F64Plan p;
@@ -499,7 +516,13 @@ F64Plan plan_f64(int np, int kc, int cus, bool may_split, int nb = 0) {
   if (may_split && nb > 0 && np >= WINDOWED_MIN_NP && np < LARGE_FILL_MIN_NP) {
     int ck;
     const int c = choose_ksplit(np, kc, (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN), cus, false, &ck);
-    if (small_turns(nb, cus) < ksplit_turns(np, c, cus)) may_split = false;
+    if (small_turns(level_tiles(nb), cus) < ksplit_turns(np, c, cus)) {
+      may_split = false;
+      if (c > 1 && one_direction_splits(np, c, level_tiles(nb), cus)) {
+        p.one_chunks = c;
+        p.one_ck = ck;
+      }
+    }
   }
   if (may_split) {
     p.chunks = choose_ksplit(np, kc, (np / kk::BackCfg::BM) * (np / kk::BackCfg::BN), cus, false, &p.ck);
@@ -740,7 +763,7 @@ kk_status ensure_workspace(kk_handle h, int chunk) {
   Slab slab;
   slab.add(&h->u, items * np);
   if (h->precision == KK_FP64) {
-    slab.add(&h->Y, items * kch * np * np);
+    slab.add(&h->Y, std::max(items * kch, (size_t)2 * h->one_chunks) * np * np);
   } else {
     for (_Float16** q : {&h->uct_h, &h->uct_l, &h->yh, &h->yl}) slab.add(q, items * np * np);
     if (h->bf16)
@@ -749,7 +772,7 @@ kk_status ensure_workspace(kk_handle h, int chunk) {
     slab.add(&h->msc, items * 8);
   }
   slab.add(&h->xdiag, items * np);
-  slab.add(&h->part, items * h->nparts * np);
+  slab.add(&h->part, std::max(items * h->nparts, (size_t)2 * h->one_parts) * np);
   kk_status st = slab.commit(h->ws_owned);
   ++h->alloc_gen;
   if (st) {
@@ -797,11 +820,11 @@ kk_status launch_combine(kk_handle h, int batch, double* q1, const int* stop, co
 }
 
 // K-split FP64 transforms (choose_ksplit) of `batch` directions whose potentials are in h->u:
-// the forward as kch full-tile partial products per item into Y (chunk j of item z at
+// the forward as kch full-tile partial products of ck rows per item into Y (chunk j of item z at
 // Y + (z kch + j) np^2), summed and symmetrized into the first; the back-transform as kch
-// partial Mulliken products per item, rows j nbase .. (j + 1) nbase - 1 of the item's partials.
-kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
-  const int np = h->np, kch = h->kch, ck = h->kck;
+// partial Mulliken products per item, rows j nbase .. (j + 1) nbase - 1 of the item's nparts.
+kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop, int kch, int ck, int nparts) {
+  const int np = h->np, nbase = nparts / kch;
   const size_t np2 = (size_t)np * np;
   const bool tiny = h->ktiny;  // chunks of 64 x 64 TinyF64 tiles, else of the 128 x 128 ones
   kk::GemmArgs fa{}, sa{}, ba{};
@@ -827,7 +850,7 @@ kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
       kk::GemmItem& bi = ba.item[z * kch + j];
       bi = kk::GemmItem{};
       bi.a0 = h->CT[s] + k0 * np; bi.b0 = Y0 + k0 * np; bi.g = h->G[s];
-      bi.part = h->part + ((size_t)z * h->nparts + (size_t)j * h->nbase) * np;
+      bi.part = h->part + ((size_t)z * nparts + (size_t)j * nbase) * np;
     }
   }
   if (fa.nitems > kk::MAX_GEMM_BATCH) return fail(KK_EINVAL, "internal: too many GEMM items");
@@ -854,7 +877,8 @@ kk_status ksplit_transforms_f64(kk_handle h, int batch, const int* stop) {
 
 // The two FP64 response transforms of `batch` directions whose potentials are in h->u.
 kk_status transforms_f64(kk_handle h, int batch, const int* stop) {
-  if (h->kch > 1) return ksplit_transforms_f64(h, batch, stop);
+  if (h->kch > 1) return ksplit_transforms_f64(h, batch, stop, h->kch, h->kck, h->nparts);
+  if (batch == 1 && h->one_split) return ksplit_transforms_f64(h, 1, stop, h->one_chunks, h->one_ck, h->one_parts);
   const int np = h->np;
   const bool small = h->small_f64;
   kk::GemmArgs fa{};
@@ -911,7 +935,7 @@ kk_status response_chunk(kk_handle h, int batch, const double* v, double* q1, co
   }
   kk_status st;
   if ((st = transforms_f64(h, batch, stop))) return st;
-  return launch_combine(h, batch, q1, stop, vsub, ft);
+  return launch_combine(h, batch, q1, stop, vsub, ft, batch == 1 && h->one_split ? h->one_parts : 0);
 }
 
 // Split-precision transform step: the forward (full-tile product into the FP32
@@ -1390,6 +1414,8 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
     h->sk = false;
     h->sk_grid = 0;
     h->ktiny = h->small_f64 = h->tiny_f64 = false;
+    h->one_chunks = 1;
+    h->one_ck = h->one_parts = 0;
     h->mx_tiny = mixed && !mx_large && !split_large && np <= MTINY_MAX_NP;
     if (!mixed) {
       const F64Plan p = plan_f64(np, h->kc, cu_count(), !split_large, split_large ? 0 : nb);
@@ -1398,6 +1424,11 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
       h->small_f64 = p.cls != 0;
       h->tiny_f64 = p.cls == 2;
       h->ktiny = h->tiny_f64 && p.chunks > 1;
+      if (p.one_chunks > 1) {
+        h->one_chunks = p.one_chunks;
+        h->one_ck = p.one_ck;
+        h->one_parts = p.one_chunks * (np / kk::BackCfg::BN) * kk::BackCfg::WAVES_N;
+      }
     } else if (!split_large && !mx_large) {
       const int tiles = h->mx_tiny ? (np / MTinyCfg::BM) * (np / MTinyCfg::BN)
                                    : (np / kk::MSmallCfg::BM) * (np / kk::MSmallCfg::BN);
@@ -1485,7 +1516,11 @@ kk_status prepare_impl(kk_handle h, int n_atoms, const int* atom_offsets, int n_
       h->C[0], h->C[1], np, h->G[0], h->G[1], np, h->w[0], h->w[1], np, h->offsets, n_atoms, h->t);
   LAUNCH_CHECK("atom_row_dots");
   if (mixed && (st = prepare_mixed(h))) return st;
+  int tiles[2] = {level_tiles(nb), 0};
+  if (h->one_chunks > 1 && h->windowed)
+    HIP_OR_FAIL(hipMemcpyAsync(tiles, h->win.count, sizeof tiles, hipMemcpyDeviceToHost, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+  h->one_split = h->one_chunks > 1 && one_direction_splits(np, h->one_chunks, tiles[0] + tiles[1], cu_count());
   h->prepared = true;
   ++h->prepare_gen;
   g_err.clear();
@@ -1822,9 +1857,9 @@ kk_status krylov_graph(kk_handle h, const double* delta, int m, double tol, cons
   hipStream_t user = h->stream;
   // The graph bakes in buffer pointers and two prepared scalars (W and beta = 1/kT); a
   // prepare of the same shape rewrites the buffers in place, so it keeps the graph unless
-  // one of those scalars changed.
+  // one of those scalars, or the form that its spectrum asks for, changed.
   if (!h->gexec || h->g_K0 != K0 || h->g_m != m || h->g_tol != tol || h->g_gen != h->alloc_gen ||
-      h->g_W != h->W || h->g_beta != h->beta) {
+      h->g_W != h->W || h->g_beta != h->beta || h->g_one_split != h->one_split) {
     // the last replay may still be running on the handle's stream: let it finish before its
     // exec goes
     HIP_OR_FAIL(hipStreamSynchronize(user));
@@ -1864,6 +1899,7 @@ kk_status krylov_graph(kk_handle h, const double* delta, int m, double tol, cons
     h->g_gen = h->alloc_gen;
     h->g_W = h->W;
     h->g_beta = h->beta;
+    h->g_one_split = h->one_split;
   }
   if (delta != h->g_delta || Kdelta != h->g_kd) {
     // an executable graph's node is not rewritten under a replay that may still run
@@ -2084,7 +2120,7 @@ ScratchLayout scratch_layout(kk_handle h, unsigned char* base) {
   };
   L.u = static_cast<double*>(take(items * np * sizeof(double)));
   if (h->precision == KK_FP64) {
-    L.Y = static_cast<double*>(take(items * kch * np2 * sizeof(double)));
+    L.Y = static_cast<double*>(take(items * std::max(kch, (size_t)h->one_chunks) * np2 * sizeof(double)));
   } else {
     L.uct_h = static_cast<_Float16*>(take(items * np2 * sizeof(_Float16)));
     L.uct_l = static_cast<_Float16*>(take(items * np2 * sizeof(_Float16)));
@@ -2098,7 +2134,7 @@ ScratchLayout scratch_layout(kk_handle h, unsigned char* base) {
     L.msc = static_cast<double*>(take(items * 8 * sizeof(double)));
   }
   L.xdiag = static_cast<double*>(take(items * np * sizeof(double)));
-  L.part = static_cast<double*>(take(items * (size_t)h->nparts * np * sizeof(double)));
+  L.part = static_cast<double*>(take(items * (size_t)std::max(h->nparts, h->one_parts) * np * sizeof(double)));
   return L;
 }
 
