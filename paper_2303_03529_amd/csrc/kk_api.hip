@@ -185,10 +185,10 @@ struct kk_handle_s {
   bool mx_large = false;  // split products on MLargeCfg (else MSmallCfg)
   bool mx_tiny = false;   // split products on MTinyCfg / MTinyBf6 (64 x 64 tiles)
   bool full_fwd = false;  // FP64 forward as full tiles + fermi_symmetrize_f64 (K-splits, 64 x 64 tiles, full_forward_pairs)
-  int2 *stiles_upper = nullptr, *stiles_full = nullptr;
+  int2* stiles_full = nullptr;
   kk::Window win{};       // window tables of the prepared spectrum (kk_gemm.hpp)
   bool windowed = false;  // the response transforms use them (use_window)
-  int n_supper = 0, n_sfull = 0;
+  int n_sfull = 0;
 
   // split-precision state (precision KK_MIXED_F16 or KK_MIXED_BF16; the BF16 form keeps a
   // third piece of every split operand, *r, for its refinement products)
@@ -717,13 +717,9 @@ kk_status launch_gemm(kk_handle h, int epi, kk::GemmArgs& a, int cls = 0) {
     else
       kk::gemm_f64<kk::EPI_STORE, kk::StoreCfg><<<grid, kk::StoreCfg::THREADS, 0, h->stream>>>(a);
   } else if (epi == kk::EPI_FERMI) {
+    if (small) return fail(KK_EINVAL, "internal: two-half forward on small tiles");
     ProfileScope ps(h, 0);
-    if (cls == 2)
-      run_gemm_f64<kk::EPI_FERMI, TinyF64>(h, a);
-    else if (cls == 1)
-      run_gemm_f64<kk::EPI_FERMI, SmallF64>(h, a);
-    else
-      run_gemm_f64<kk::EPI_FERMI, kk::FwdCfg>(h, a);
+    run_gemm_f64<kk::EPI_FERMI, kk::FwdCfg>(h, a);
   } else if (epi == kk::EPI_XSTORE) {  // forward: full-tile product into Y, then Y = F o X in place
     ProfileScope ps(h, 0);
     if (cls == 2)
@@ -886,8 +882,8 @@ kk_status transforms_f64(kk_handle h, int batch, const int* stop) {
   // Y = F o X in place; otherwise upper tiles over both K halves with the Fermi epilogue
   const bool full = h->full_fwd;
   fa.n = np; fa.k_half = h->kc; fa.two_halves = full ? 0 : 1;
-  fa.ntiles = small ? (full ? h->n_sfull : h->n_supper) : (full ? h->n_full : h->n_upper);
-  fa.nitems = 2 * batch; fa.tiles = small ? (full ? h->stiles_full : h->stiles_upper) : (full ? h->tiles_full : h->tiles_upper);
+  fa.ntiles = small ? h->n_sfull : full ? h->n_full : h->n_upper;
+  fa.nitems = 2 * batch; fa.tiles = small ? h->stiles_full : full ? h->tiles_full : h->tiles_upper;
   fa.stop = stop; fa.beta = h->beta;
   if (h->windowed) fa.win = h->win;
   fa.cus = cu_count();
@@ -1174,9 +1170,7 @@ ForwardTiles forward_tiles(kk_handle h) {
     if (h->mx_tiny) return {h->mtiles_full, h->n_mfull, MTinyCfg::BM, MTinyCfg::BN};
     return {h->mtiles_full, h->n_mfull, kk::MSmallCfg::BM, kk::MSmallCfg::BN};
   }
-  if (h->small_f64)
-    return {h->full_fwd ? h->stiles_full : h->stiles_upper, h->full_fwd ? h->n_sfull : h->n_supper, SmallF64::BM,
-            SmallF64::BN};
+  if (h->small_f64) return {h->stiles_full, h->n_sfull, SmallF64::BM, SmallF64::BN};
   return {h->full_fwd ? h->tiles_full : h->tiles_upper, h->full_fwd ? h->n_full : h->n_upper, kk::FwdCfg::BM,
           kk::FwdCfg::BN};
 }
@@ -1245,10 +1239,7 @@ kk_status allocate_prepared(kk_handle h) {
   h->store_cls = store_class(np, cu_count());
   const int sb = h->store_cls ? SmallF64::BM : kk::StoreCfg::BM;
   table(&h->tiles_store, &h->n_store, sb, sb, false);
-  if (h->small_f64) {
-    table(&h->stiles_upper, &h->n_supper, SmallF64::BM, SmallF64::BN, true);
-    table(&h->stiles_full, &h->n_sfull, SmallF64::BM, SmallF64::BN, false);
-  }
+  if (h->small_f64) table(&h->stiles_full, &h->n_sfull, SmallF64::BM, SmallF64::BN, false);
   static_assert(kk::FwdCfg::MIN_BLOCKS == kk::BackCfg::MIN_BLOCKS, "one slot count for both forward forms");
   h->full_fwd = h->kch > 1 || h->small_f64 || full_forward_pairs(h->n_upper, h->n_full, cu_count());
   if (h->precision != KK_FP64) {
