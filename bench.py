@@ -338,9 +338,14 @@ def executed_fractions(levels, mu, kT, precision):
     """The parts of the whole forward and back products that the library computes: it leaves out the
     64 x 64 blocks of levels in which every divided difference is negligible (the rule of its
     window_tables: the forward by tiles with no other block, the back-transform by the rows outside
-    the blocks of its 128 columns)."""
+    the blocks of its 128 columns). Not in the cells of up to 128 atoms, whose products are split along K
+    or run in one round of tiles; the split forms' tiles are 256 x 128 above Nb = 2304, else 128 x 128."""
     import numpy as np
-    bm, cut_bits = (128, 60) if precision == "fp64" else (256, 42 if precision == "mixed" else 60)
+    nb = np.shape(levels)[1]
+    if nb <= 1152:
+        return {"forward_fermi": 1.0, "back_mulliken": 1.0}
+    bm = 256 if precision != "fp64" and nb > 2304 else 128
+    cut_bits = 42 if precision == "mixed" else 60
     occ = lambda e: 1.0 / (1.0 + np.exp(np.clip((e - mu) / kT, -700.0, 700.0)))  # noqa: E731
     e = np.asarray(levels)
     f, fc = occ(e), occ(2.0 * mu - e)
@@ -348,7 +353,6 @@ def executed_fractions(levels, mu, kT, precision):
     ref = max((f * fc).max(), f.max() * fc.max() * -np.expm1(-width) / width)
     cut = 2.0 ** -cut_bits * (1.0 if precision == "mixed" else ref)
     fwd = back = 0.0
-    nb = e.shape[1]
     for x in e:
         edges = np.arange(0, nb, 64)
         lo, hi = np.minimum.reduceat(x, edges), np.maximum.reduceat(x, edges)
