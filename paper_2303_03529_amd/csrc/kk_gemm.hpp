@@ -138,16 +138,17 @@ struct GemmItem {
   double* xout;         // symmetrizing pass of the reverse pass: X (a0 then holds A, out receives Y)
 };
 
-// Where the divided differences F of a prepared spectrum are negligible (built by the spectrum
-// kernel from the levels alone; kk_kernels.hpp has the rule). Two levels that are both filled, or
+// Where the divided differences F of a prepared spectrum are negligible (built by window_tables
+// from the levels alone; kk_kernels.hpp has the rule). Two levels that are both filled, or
 // both empty, up to a few ten kT from mu do not respond, so blocks of Y = F o X between such
 // levels are zero: the forward transform leaves their tiles out, the symmetrizing pass writes
 // zeros there, and the back-transform contracts only over the rows that remain. In blocks of
 // WIN x WIN levels, per spin. With ascending levels the active blocks are all but two squares
 // on the diagonal; any other order is as correct, with less left out. On spectra 60 eV wide at
-// kT = 0.25 eV 86-89 % of the blocks remain (FP16 x 3, whose cut is higher: 77-80 %): FP64 1024
-// atoms m = 12 1092 -> 920 ms, eight responses at 250 atoms 11.8 -> 10.2 ms; FP16 x 3 at 432 atoms
-// m = 8 12.9 -> 11.7 ms (3.2 rounds of 256 x 128 tiles for 4).
+// kT = 0.25 eV, 1024 atoms, 84 % (forward, by tiles) and 83 % (back, by rows) of the products remain, in
+// FP16 x 3, whose cut is higher, 77 and 74 %; from kT = 1 eV on all of them (FP64 then 1 % slower at 265-350 atoms than
+// without the tables). m = 12 FP64 1024 atoms 1092 -> 920 ms, eight responses at 250 atoms 11.8 -> 10.2 ms;
+// FP16 x 3 at 432 atoms m = 8 12.9 -> 11.7 ms (3.2 rounds of 256 x 128 tiles for 4).
 constexpr int WIN = 64;
 struct Window {
   const unsigned char* act[2];  // nblk x nblk: 1 where Y may be non-zero (symmetric; the diagonal always)
@@ -307,7 +308,7 @@ struct PairRows {
 // configurations. Two objects (one, whose accesses the compiler orders, is 1.2 % slower on 128 x 128
 // tiles at 150 atoms), or one (OneLds) for the 64 x 64 tiles of single systems (171 atoms, a
 // transform 303 -> 297 us). Functions rather than references to the arrays: with those the
-// batches' queued tiles took a register more per lane and 1.2 % longer.
+// batches' tiles took a register more per lane and 1.2 % longer.
 template <class Cfg>
 struct OneLds : Cfg {
   using Tile = Cfg;
