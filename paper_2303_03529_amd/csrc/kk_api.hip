@@ -2829,20 +2829,26 @@ kk_status build_tile_lists(kk_batch b, int small_np_max) {
       }
     }
   }
+  // every buffer before the first change, so that a call that fails leaves the lists in use as they are
+  std::vector<int4> lists[2][2];
+  int4* grown[2][2] = {};
+  for (int c = 0; c < 2; ++c)
+    for (int d = 0; d < 2; ++d) {
+      const TileClass& tc = d ? b->back[c] : b->fwd[c];
+      deal_tiles(all[c][d], lists[c][d]);
+      kk_status st;
+      if ((int)lists[c][d].size() > tc.cap && (st = balloc(b, &grown[c][d], lists[c][d].size()))) return st;
+    }
   for (int i = 0; i < b->ns; ++i)
     b->h_sys[i].nparts = b->np_of[i] <= small_np_max ? b->parts_small[i] : b->parts_large[i];
   HIP_OR_FAIL(hipMemcpyAsync(b->d_sys, b->h_sys.data(), sizeof(kk::SysDesc) * b->ns, hipMemcpyHostToDevice,
                              b->stream));
-  std::vector<int4> lists[2][2];
   for (int c = 0; c < 2; ++c)
     for (int d = 0; d < 2; ++d) {
       TileClass& tc = d ? b->back[c] : b->fwd[c];
-      deal_tiles(all[c][d], lists[c][d]);
       tc.n = (int)lists[c][d].size();
-      if (tc.n > tc.cap) {
-        kk_status st;
-        tc.cap = 0;
-        if ((st = balloc(b, &tc.tiles, tc.n))) return st;
+      if (grown[c][d]) {
+        tc.tiles = grown[c][d];
         tc.cap = tc.n;
       }
       if (tc.n)
