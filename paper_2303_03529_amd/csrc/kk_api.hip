@@ -1826,13 +1826,17 @@ kk_status krylov_adaptive_sync(kk_handle h, const double* delta, int m, double t
     const unsigned long long seq = ++h->report_seq;
     if ((st = enqueue_solve(h, k, K0, Kdelta, k + 1 < m ? tol : 0.0, h->report, seq))) return st;
     if (k + 1 == m || k + 1 < ahead) continue;
-    // the word of this solve, or the stream's end (an error included, which the sync reports)
+    // the word of this solve; where the stream's query says anything but "not ready", its end or its error
     for (int spin = 1;; ++spin) {
       if (__atomic_load_n(&h->report->word, __ATOMIC_RELAXED) >= 2 * seq) break;
-      if (spin % 4096 == 0 && hipStreamQuery(h->stream) != hipErrorNotReady) break;
+      if (spin % 4096 == 0 && hipStreamQuery(h->stream) != hipErrorNotReady) {
+        HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+        break;
+      }
     }
     const unsigned long long word = __atomic_load_n(&h->report->word, __ATOMIC_RELAXED);
-    if (word < 2 * seq || (word & 1)) break;
+    if (word < 2 * seq) return fail(KK_EHIP, "internal: no word from solve %d", k);
+    if (word & 1) break;
   }
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   h->rank_hint = h->report->st.rank;
